@@ -21,38 +21,17 @@ __device__ __forceinline__ int lds_idx(int i) {
   return i + i / P;
 }
 
+// Node x of a tile in a lattice of n nodes.  small (the lattice is shorter
+// than the tile): x and n fit 32 bits.
 __device__ __forceinline__ int64_t wrap_near(int64_t x, int64_t n, bool small) {
-  if (small) return lbm::wrap_mod(x, n);
+  if (small) {
+    const int r = (int)x % (int)n;
+    return r < 0 ? r + (int)n : r;
+  }
   return x < 0 ? x + n : (x >= n ? x - n : x);
 }
 
-// Arrays of a lattice of length L are at fin + q*S (S >= L, the array
-// stride of the state the lattice lives in).
-template <int P>
-__device__ __forceinline__ void tile_load(const double* __restrict__ fin,
-                                          int64_t S, int64_t n, int64_t start,
-                                          bool inside, bool small, int lane,
-                                          double* lds, double (&f)[6][P]) {
-#pragma unroll
-  for (int q = 0; q < 6; ++q) {
-    const double* src = fin + (int64_t)q * S;
-#pragma unroll
-    for (int k = 0; k < P; ++k) {
-      const int i = k * 64 + lane;
-      const int64_t g = inside ? start + i : wrap_near(start + i, n, small);
-      lds[lds_idx<P>(i)] = src[g];
-    }
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int k = 0; k < P; ++k) f[q][k] = lds[lds_idx<P>(lane * P + k)];
-    __builtin_amdgcn_wave_barrier();
-  }
-}
-
-// tile_load in three parts, for a kernel that reloads the same segment of
-// successive states: the global indices of the coalesced order (computed
-// once), the global loads into registers in that order (which may be issued
-// a step ahead), and the pass through LDS into the register order.
+// The global indices of a segment in the coalesced order.
 template <int P>
 __device__ __forceinline__ void tile_index(int64_t n, int64_t start,
                                            bool inside, bool small, int lane,
@@ -64,6 +43,11 @@ __device__ __forceinline__ void tile_index(int64_t n, int64_t start,
   }
 }
 
+// A segment's load in parts, for a kernel that reloads the same segment of
+// successive states: the global loads into registers in the coalesced order
+// (which may be issued a step ahead), and the pass through LDS into the
+// register order (one node per lane: the orders are the same).  raw and f
+// may be one array.
 template <int P>
 __device__ __forceinline__ void tile_fetch(const double* __restrict__ fin,
                                            int64_t S, const int64_t (&gi)[P],
@@ -80,6 +64,10 @@ __device__ __forceinline__ void tile_transpose(int lane, double* lds,
                                                double (&f)[6][P]) {
 #pragma unroll
   for (int q = 0; q < 6; ++q) {
+    if constexpr (P == 1) {
+      f[q][0] = raw[q][0];
+      continue;
+    }
 #pragma unroll
     for (int k = 0; k < P; ++k) lds[lds_idx<P>(k * 64 + lane)] = raw[q][k];
     __builtin_amdgcn_wave_barrier();
@@ -87,6 +75,32 @@ __device__ __forceinline__ void tile_transpose(int lane, double* lds,
     for (int k = 0; k < P; ++k) f[q][k] = lds[lds_idx<P>(lane * P + k)];
     __builtin_amdgcn_wave_barrier();
   }
+}
+
+// Arrays of a lattice of length L are at fin + q*S (S >= L, the array
+// stride of the state the lattice lives in).  All 6 P global loads are issued
+// before the first pass through LDS, so a wavefront waits for memory once:
+// array by array it waited six times in a row, which was most of a launch's
+// fixed cost (at n = 8192, one-wavefront tiles: 4.1 -> 2.4 us per launch at
+// P = 1, 14 -> 5 us at P = 8; 2000 steps of it 1146 -> 918 us).
+template <int P>
+__device__ __forceinline__ void tile_load(const double* __restrict__ fin,
+                                          int64_t S, int64_t n, int64_t start,
+                                          bool inside, bool small, int lane,
+                                          double* lds, double (&f)[6][P]) {
+  if (inside) {  // uniform: one scalar base per array
+#pragma unroll
+    for (int q = 0; q < 6; ++q) {
+      const double* src = fin + ((int64_t)q * S + start);
+#pragma unroll
+      for (int k = 0; k < P; ++k) f[q][k] = src[k * 64 + lane];
+    }
+  } else {
+    int64_t gi[P];
+    tile_index<P>(n, start, false, small, lane, gi);
+    tile_fetch<P>(fin, S, gi, f);
+  }
+  tile_transpose<P>(lane, lds, f, f);
 }
 
 // Stores the nodes of this wavefront's segment whose tile index lies in
@@ -102,10 +116,14 @@ __device__ __forceinline__ void tile_store(double* __restrict__ fout,
   const int64_t lim = n - start;  // i < lim  <=>  start + i < n
 #pragma unroll
   for (int q = 0; q < 6; ++q) {
+    double* dst = fout + (int64_t)q * S + g0;
+    if constexpr (P == 1) {
+      if (lane >= lo && lane < hi && lane < lim) dst[0] = f[q][0];
+      continue;
+    }
 #pragma unroll
     for (int k = 0; k < P; ++k) lds[lds_idx<P>(lane * P + k)] = f[q][k];
     __builtin_amdgcn_wave_barrier();
-    double* dst = fout + (int64_t)q * S + g0;
 #pragma unroll
     for (int k = 0; k < P; ++k) {
       const int i = k * 64 + lane;
