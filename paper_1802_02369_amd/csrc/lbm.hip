@@ -50,6 +50,8 @@ int hip_check(hipError_t e, const char* what) {
   return set_err(LBM_EHIP, "%s: %s", what, hipGetErrorString(e));
 }
 
+constexpr double kLn2 = 0x1.62e42fefa39efp-1;  // ln 2
+
 static bool finite_pos(double x) { return std::isfinite(x) && x > 0.0; }
 static bool valid_rate(double s) { return std::isfinite(s) && s > 0.0 && s < 2.0; }
 
@@ -111,17 +113,19 @@ int make_consts(const lbm_params* p, Consts* c) {
   c->cp = cp;
   c->se_2 = p->s_e / 2.0;
   c->ise2 = 1.0 / (p->s_e * p->s_e);
-  c->se_3 = p->s_e / 3.0;
-  c->se_6 = p->s_e / 6.0;
   c->sp_2 = p->s_psi / 2.0;
-  c->sx_3 = p->s_eps / 3.0;
-  c->sx_6 = p->s_eps / 6.0;
+  c->sx_2 = p->s_eps / 2.0;
   c->hP = p->c0 * p->c0 / (g * l * l);
-  c->two_g = 2.0 / g;
+  c->hgam = g / kLn2;
+  c->hy0 = c->xs0 / kLn2;
+  c->tg = 2.0 / (3.0 * g);
+  c->tgy = c->tg * kLn2;
   c->hS = c->src_c * l * l / (3.0 * cp * c->T0);
   c->hC = cp * c->T0 / (p->prandtl * l * l);
   c->hSd = p->source_on ? -0.25 * c->ise2 * l * l / (3.0 * cp * c->T0) : 0.0;
-  c->xs0l = c->xs0 - c->gm1 * std::log(r0);
+  c->gcp2 = c->gcp / kLn2;
+  c->y0 = (c->xs0 - c->gm1 * std::log(r0)) / kLn2;
+  c->eps_y = c->eps_c * kLn2;
   c->eq_kind = p->eq_kind;
   c->flags = p->flags;
   if (p->eq_kind == 1) {
@@ -265,11 +269,8 @@ __global__ __launch_bounds__(kPlainBlock + 64) void k_step_plain(
   }
   __syncthreads();
   if (collide) {
-    const double add = lbm::source_g(c, rw, w, su[slot - 1], su[slot + 1],
-                                     sT[slot - 1], sT[slot + 1]);
-    g0 += add;
-    gp += add;
-    gm += add;
+    lbm::add_source(c, rw, w, su[slot - 1], su[slot + 1], sT[slot - 1],
+                    sT[slot + 1], g0, gp, gm);
     sfp[slot] = fp;
     sgp[slot] = gp;
     sfm[slot] = fm;
@@ -663,8 +664,8 @@ __global__ __launch_bounds__(kDiagBlock) void k_diag_partial(
     const double rho = lbm::density(c, f0, fp, fm);
     const double J = c.mJ * (fp - fm);
     const double zeta = c.mz * (g0 + (gp + gm));
-    double u, s_, X, T;
-    lbm::thermo(c, rho, J, zeta, u, s_, X, T);
+    double u, s_, Y, T;
+    lbm::thermo(c, rho, J, zeta, u, s_, Y, T);
     const double p = rho * c.r * T;
     const double b[8] = {rho, J, zeta, p / c.gm1 + 0.5 * J * u,
                          rho, T, nf, (rho > 0.0 && T > 0.0) ? 0.0 : 1.0};
@@ -713,8 +714,8 @@ __global__ __launch_bounds__(kDiagBlock) void k_batch_diag(
     const double rho = lbm::density(c, f0, fp, fm);
     const double J = c.mJ * (fp - fm);
     const double zeta = c.mz * (g0 + (gp + gm));
-    double u, s_, X, T;
-    lbm::thermo(c, rho, J, zeta, u, s_, X, T);
+    double u, s_, Y, T;
+    lbm::thermo(c, rho, J, zeta, u, s_, Y, T);
     const double p = rho * c.r * T;
     const double b[8] = {rho, J, zeta, p / c.gm1 + 0.5 * J * u,
                          rho, T, nf, (rho > 0.0 && T > 0.0) ? 0.0 : 1.0};
@@ -749,8 +750,8 @@ __device__ __forceinline__ bool node_fails(const Consts& c,
   const double rho = lbm::density(c, f0, fp, fm);
   const double J = c.mJ * (fp - fm);
   const double zeta = c.mz * (g0 + (gp + gm));
-  double u, s_, X, T;
-  lbm::thermo(c, rho, J, zeta, u, s_, X, T);
+  double u, s_, Y, T;
+  lbm::thermo(c, rho, J, zeta, u, s_, Y, T);
   return !(finite && rho > 0.0 && T > 0.0);
 }
 

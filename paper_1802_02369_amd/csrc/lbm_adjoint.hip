@@ -55,7 +55,7 @@ __device__ __forceinline__ int64_t wrap_in(int64_t x, int64_t n, bool small) {
 // Forward quantities of one node that the reverse sweep reuses.
 struct NodeFwd {
   double rho, J, zeta, e, psi, eps;
-  double u, s, X, T, w, ir;  // ir = 1/rho
+  double u, s, Y, T, w, ir;  // Y = log2(T/T0), ir = 1/rho
   double e_eq, psi_eq, eps_eq;
 };
 
@@ -70,13 +70,13 @@ __device__ __forceinline__ void node_forward(const Consts& c, double f0,
   q.zeta = c.mz * (g0 + sg);
   q.psi = c.mpsi * (gp - gm);
   q.eps = c.meps * (sg - 2.0 * g0);
-  lbm::thermo(c, q.rho, q.J, q.zeta, q.u, q.s, q.X, q.T, q.ir);
+  lbm::thermo(c, q.rho, q.J, q.zeta, q.u, q.s, q.Y, q.T, q.ir);
   q.w = lbm::recip(q.T);
   if (EQ == 0 || c.eq_kind == 0) {
     const double p = q.rho * c.r * q.T;
     q.e_eq = 3.0 * (q.J * q.u + p) - c.two_l2 * q.rho;
     q.psi_eq = q.zeta * q.u;
-    q.eps_eq = c.eps_c * q.rho * q.X + q.e_eq * q.s;
+    q.eps_eq = c.eps_y * q.rho * q.Y + q.e_eq * q.s;
   } else if (c.eq_kind == 2) {
     q.e_eq = 3.0 * (q.J * q.u + lbm::iso_pressure(c, q.rho)) - c.two_l2 * q.rho;
     q.psi_eq = 0.0;
@@ -102,8 +102,8 @@ __device__ __forceinline__ void equilibria_adjoint(const Consts& c,
   double sb = 0.0, Xb = 0.0;
   const double ir = q.ir;
   if (EQ == 0 || c.eq_kind == 0) {
-    // eps_eq = eps_c rho X + e_eq s
-    rb += c.eps_c * q.X * xb;
+    // eps_eq = eps_c rho X + e_eq s, X = Y ln 2
+    rb += c.eps_y * q.Y * xb;
     Xb += c.eps_c * q.rho * xb;
     eb += q.s * xb;
     sb += q.e_eq * xb;
@@ -280,44 +280,44 @@ __device__ __forceinline__ void shift_right(double (&a)[P], double in_left) {
 
 // One reverse step of a lane's P nodes in the forward step's own scaled
 // variables (collide_local: rh = f0 + f+ + f-, Jh = f+ - f-, zh = g0 + g+ +
-// g-, uh, sh, X, Th; the populations and their adjoints are the same in
+// g-, uh, sh, Y, Th; the populations and their adjoints are the same in
 // both).  The forward at a node, before streaming:
-//   d = jup - (f+ + f-), jup = Jh uh + hP rh Th (section 8; jup with the
-//     isentropic pressure for eq_kind 2), or d = eh - (f+ + f- - 2 f0)
-//     with linear eh (eq_kind 1);
-//   f0 -= s_e d, f+- += s_e d / 2 (s_e / 3, s_e / 6 for eq_kind 1);
-//   dpr = psih - (g+ - g-), dxr = epsh - (g+ + g- - 2 g0);
-//   g0 += -s_eps dxr / 3 + add, g+- += +-s_psi dpr / 2 + s_eps dxr / 6 + add,
+//   f0 -= s_e d, f+- += s_e d / 2; g0 += -s_eps dx + add,
+//   g+- += +-s_psi dp / 2 + s_eps dx / 2 + add, where for section 8
+//   d = rh y - (f+ + f-), y = uh^2 + hP Th, dp = zh uh - (g+ - g-),
+//   dx = rh v - (g+ + g-), v = y sh + tgy Y
+//   (eq_kind 2: Th in y is the isentropic one, the equilibria in dp and dx are
+//   0; eq_kind 1: d = (eh - (f+ + f- - 2 f0)) / 3 and so on, all linear);
 //   add = hS rh w (du^2 + hC dT^2 w), w = 1 / Th, du, dT across j-1, j+1.
 // Given a = fbar*(f), b = fbar*(g) at the node (after the transposed
 // streaming) the reverse is
-//   db = s_e (a+ + a-)/2 - s_e a0, dprb = s_psi (b+ - b-) / 2,
-//   dxrb = s_eps ((b+ + b-)/2 - b0) / 3, addb = b0 + b+ + b-,
-// the adjoints of the equilibria from (db, dprb, dxrb), of the source from
-// addb (its terms in the neighbours' uh, Th are gathered as A, B), of the
-// thermodynamic state (X = (gamma-1) ln rh + gamma sh + xs0, Th = e^X,
-// uh = Jh / rh, sh = zh / rh) and of the moments back to the populations,
-// plus the direct paths of the relaxation.  Rate partials: d db / s_e,
-// dpr (b+ - b-) / 2, dxr ((b+ + b-)/2 - b0) / 3, and the source's
-// d hS / d s_e, accumulated without their constant factors over the
-// owned nodes: acc = {sum d E1, sum F Q, sum dpr (b+ - b-), sum dxr E2}
-// (see rate_partials).  PRE: the thermodynamic state of f(t) is given in pre[k]
-// (kept by the forward step that recomputed the next state from f(t): the
-// same arithmetic on the same populations, so the same bits).
+//   db = s_e E1, E1 = (a+ + a-)/2 - a0, dpb = s_psi (b+ - b-) / 2,
+//   dxb = s_eps E2, E2 = (b+ + b-)/2 - b0, addb = b0 + b+ + b-,
+// the adjoints of rh, zh, uh, sh, Y, Th from (db, dpb, dxb), of the source
+// from addb (its terms in the neighbours' uh, Th are gathered as A, B), of
+// the thermodynamic state (X = Y ln 2 = (gamma-1) ln rh + gamma sh + xs0,
+// Th = e^X, uh = Jh / rh, sh = zh / rh) and of the moments back to the
+// populations, plus the direct paths of the relaxation.  Rate partials: d E1,
+// dp (b+ - b-) / 2, dx E2, and the source's d hS / d s_e, accumulated without
+// their constant factors over the owned nodes: acc = {sum d E1, sum F Q,
+// sum dp (b+ - b-), sum dx E2} (see rate_partials).  PRE: the thermodynamic
+// state of f(t) is given in pre[k] (kept by the forward step that recomputed
+// the next state from f(t): the same arithmetic on the same populations, so
+// the same bits).
 template <int P, int EQ, bool PRE = false>
 __device__ __forceinline__ void adjoint_step_local(
     const Consts& c, const double (&ft)[6][P], double (&fb)[6][P],
     const bool (&own)[P], double (&acc)[4], const lbm::NodeThermo* pre = nullptr) {
 #pragma clang fp contract(off)
   // A: scaled moments and thermodynamic state of every node of f(t)
-  double rh[P], uh[P], sh[P], X[P], Th[P], ir[P], lr[P], w[P];
+  double rh[P], uh[P], sh[P], Y[P], Th[P], ir[P], lr[P], w[P];
 #pragma unroll
   for (int k = 0; k < P; ++k) {
     rh[k] = (ft[0][k] + ft[1][k]) + ft[2][k];
     if constexpr (PRE) {
       uh[k] = pre[k].uh;
       sh[k] = pre[k].sh;
-      X[k] = pre[k].X;
+      Y[k] = pre[k].Y;
       Th[k] = pre[k].Th;
       lr[k] = pre[k].lr;
       ir[k] = pre[k].ir;
@@ -325,7 +325,7 @@ __device__ __forceinline__ void adjoint_step_local(
     } else {
       const double Jh = ft[1][k] - ft[2][k];
       const double zh = ft[3][k] + (ft[4][k] + ft[5][k]);
-      lbm::thermo_scaled(c, rh[k], Jh, zh, uh[k], sh[k], X[k], Th[k], lr[k], ir[k]);
+      lbm::thermo_scaled(c, rh[k], Jh, zh, uh[k], sh[k], Y[k], Th[k], lr[k], ir[k]);
     }
   }
   const double fpR = lbm::from_right(fb[1][0]), gpR = lbm::from_right(fb[4][0]);
@@ -365,60 +365,67 @@ __device__ __forceinline__ void adjoint_step_local(
     const double g0 = ft[3][k], gp = ft[4][k], gm = ft[5][k];
     const double a0 = fb[0][k], ap = fb[1][k], am = fb[2][k];
     const double b0 = fb[3][k], bp = fb[4][k], bm = fb[5][k];
-    const double r = rh[k], u = uh[k], sv = sh[k], x = X[k], T = Th[k];
-    const double Jh = fp - fm, sf = fp + fm, sg = gp + gm, zh = g0 + sg;
+    const double r = rh[k], u = uh[k], sv = sh[k], T = Th[k];
+    const double sf = fp + fm, sg = gp + gm;
     // adjoints of the relaxation's increments
     const double E1 = fma(0.5, ap + am, -a0);
     const double E2 = fma(0.5, bp + bm, -b0);
     const double bd = bp - bm;
-    const double dprb = c.sp_2 * bd;
-    const double dxrb = c.sx_3 * E2;
-    // the forward's equilibria, increments and the adjoints of the
-    // equilibria: rhb, Jhb, zhb, uhb, Thb, shb, Xb, lrb
-    double d, db, psih, epsh;
-    double rhb, Jhb, zhb = 0.0, uhb = 0.0, Thb = 0.0, shb = 0.0, Xb = 0.0, lrb = 0.0;
+    const double db = c.s_e * E1;
+    const double dpb = c.sp_2 * bd;
+    const double dxb = c.s_eps * E2;
+    // the forward's increments and the adjoints of the state: rhb, Jhb, zhb,
+    // uhb, Thb, shb, Xb, lrb; the direct paths of f+-, g+- (sfb, sgb) and of
+    // f0, g0 (f0b, g0b)
+    double d, dp, dx;
+    double rhb, Jhb = 0.0, zhb = 0.0, uhb = 0.0, Thb = 0.0, shb = 0.0, Xb = 0.0,
+                lrb = 0.0;
+    double sfb = -db, sgb = -dxb, f0b = a0, g0b = b0;
     if (EQ == 0 || c.eq_kind == 0) {
-      const double hPr = c.hP * r;
-      const double jup = fma(Jh, u, hPr * T);
-      const double eh = fma(-2.0, r, 3.0 * jup);
-      psih = zh * u;
-      const double tgr = c.two_g * r;
-      epsh = fma(eh, sv, tgr * x);
-      d = jup - sf;
-      db = c.s_e * E1;
-      // epsh = eh sh + (2/gamma) rh X, psih = zh uh, eh = 3 jup - 2 rh,
-      // jup = Jh uh + hP rh Th
-      const double ehb = sv * dxrb;
-      shb = eh * dxrb;
-      Xb = tgr * dxrb;
-      zhb = u * dprb;
-      const double jupb = fma(3.0, ehb, db);
-      rhb = fma(-2.0, ehb, (c.two_g * x) * dxrb);
-      rhb = fma(c.hP * T, jupb, rhb);
-      Jhb = u * jupb;
-      uhb = fma(Jh, jupb, zh * dprb);
-      Thb = hPr * jupb;
+      const double zh = g0 + sg;
+      const double y = fma(u, u, c.hP * T);
+      const double ty = c.tgy * Y[k];
+      const double v = fma(y, sv, ty);
+      d = fma(r, y, -sf);
+      dp = fma(zh, u, gm - gp);
+      dx = fma(r, v, -sg);
+      const double vb = r * dxb;
+      const double yb = fma(r, db, sv * vb);
+      rhb = fma(y, db, v * dxb);
+      zhb = u * dpb;
+      uhb = fma(u + u, yb, zh * dpb);
+      Thb = c.hP * yb;
+      shb = y * vb;
+      Xb = c.tg * vb;
     } else if (c.eq_kind == 2) {
-      const double pe = lbm::exp_fin(c.gm1 * lr[k]);
-      const double hPr = c.hP * r;
-      const double jup = fma(Jh, u, hPr * pe);
-      psih = 0.0;
-      epsh = 0.0;
-      d = jup - sf;
-      db = c.s_e * E1;
-      rhb = (c.hP * pe) * db;
-      lrb = (c.gm1 * (hPr * pe)) * db;
-      Jhb = u * db;
-      uhb = Jh * db;
+      const double pe = c.hP * lbm::exp2_fin(c.gm1 * lr[k]);
+      const double y = fma(u, u, pe);
+      d = fma(r, y, -sf);
+      dp = gm - gp;
+      dx = fma(2.0, g0, -sg) * (1.0 / 3.0);
+      const double yb = r * db;
+      rhb = y * db;
+      uhb = (u + u) * yb;
+      lrb = (c.gm1 * pe) * yb;
+      const double x3 = dxb * (1.0 / 3.0);
+      g0b = fma(2.0, x3, b0);
+      sgb = -x3;
     } else {
+      const double Jh = fp - fm, zh = g0 + sg;
       const double eh = fma(c.hlin[2], zh, fma(c.hlin[1], Jh, c.hlin[0] * r));
-      psih = fma(c.hlin[5], zh, fma(c.hlin[4], Jh, c.hlin[3] * r));
-      epsh = fma(c.hlin[8], zh, fma(c.hlin[7], Jh, c.hlin[6] * r));
-      d = eh - fma(-2.0, f0, sf);
-      db = c.se_3 * E1;
-      rhb = fma(c.hlin[6], dxrb, fma(c.hlin[3], dprb, c.hlin[0] * db));
-      Jhb = fma(c.hlin[7], dxrb, fma(c.hlin[4], dprb, c.hlin[1] * db));
-      zhb = fma(c.hlin[8], dxrb, fma(c.hlin[5], dprb, c.hlin[2] * db));
+      const double psih = fma(c.hlin[5], zh, fma(c.hlin[4], Jh, c.hlin[3] * r));
+      const double epsh = fma(c.hlin[8], zh, fma(c.hlin[7], Jh, c.hlin[6] * r));
+      d = (eh - fma(-2.0, f0, sf)) * (1.0 / 3.0);
+      dp = psih - (gp - gm);
+      dx = (epsh - fma(-2.0, g0, sg)) * (1.0 / 3.0);
+      const double d3 = db * (1.0 / 3.0), x3 = dxb * (1.0 / 3.0);
+      rhb = fma(c.hlin[6], x3, fma(c.hlin[3], dpb, c.hlin[0] * d3));
+      Jhb = fma(c.hlin[7], x3, fma(c.hlin[4], dpb, c.hlin[1] * d3));
+      zhb = fma(c.hlin[8], x3, fma(c.hlin[5], dpb, c.hlin[2] * d3));
+      f0b = fma(2.0, d3, a0);
+      sfb = -d3;
+      g0b = fma(2.0, x3, b0);
+      sgb = -x3;
     }
     // the source at this node (add = hS rh w Q, Q = du^2 + hC dT^2 w) and
     // the neighbours' terms in this node's uh and Th
@@ -434,8 +441,8 @@ __device__ __forceinline__ void adjoint_step_local(
     if (own[k]) {
       acc[0] = fma(d, E1, acc[0]);
       acc[1] = fma(F[k], Q, acc[1]);
-      acc[2] = fma(psih - (gp - gm), bd, acc[2]);
-      acc[3] = fma(epsh - fma(-2.0, g0, sg), E2, acc[3]);
+      acc[2] = fma(dp, bd, acc[2]);
+      acc[3] = fma(dx, E2, acc[3]);
     }
     // the thermodynamic state: Th = e^X, X = gm1 lr + gamma sh + xs0,
     // lr = ln rh, uh = Jh / rh, sh = zh / rh
@@ -447,30 +454,27 @@ __device__ __forceinline__ void adjoint_step_local(
     Jhb = fma(iv, uhb, Jhb);
     rhb = fma(iv, lrb - fma(u, uhb, sv * shb), rhb);
     // the moments and the relaxation's direct paths
-    const double dfm = (EQ == 0 || c.eq_kind != 1) ? a0 : fma(2.0, db, a0);
-    const double rd = rhb - db, zx = zhb - dxrb;
-    fb[0][k] = dfm + rhb;
+    const double rd = rhb + sfb, zx = zhb + sgb;
+    fb[0][k] = f0b + rhb;
     fb[1][k] = (ap + rd) + Jhb;
     fb[2][k] = (am + rd) - Jhb;
-    fb[3][k] = fma(2.0, dxrb, b0) + zhb;
-    fb[4][k] = (bp + zx) - dprb;
-    fb[5][k] = (bm + zx) + dprb;
+    fb[3][k] = g0b + zhb;
+    fb[4][k] = (bp + zx) - dpb;
+    fb[5][k] = (bm + zx) + dpb;
   }
 }
 
 // The three rate partials from the sums adjoint_step_local accumulates:
-// d/ds_e = sum d E1 (x 1/3 for the linear equilibria, whose increment is
-// s_e d / 3) + (d hS / d s_e) / hS sum F Q, d/ds_psi = sum dpr (b+ - b-) / 2,
-// d/ds_eps = sum dxr E2 / 3.
+// d/ds_e = sum d E1 + (d hS / d s_e) / hS sum F Q, d/ds_psi =
+// sum dp (b+ - b-) / 2, d/ds_eps = sum dx E2.
 __device__ __forceinline__ void rate_partials(const Consts& c,
                                               const double (&acc)[4],
                                               double& r0, double& r1,
                                               double& r2) {
 #pragma clang fp contract(off)
-  const double se = c.eq_kind == 1 ? acc[0] * (1.0 / 3.0) : acc[0];
-  r0 = c.hS != 0.0 ? fma(c.hSd / c.hS, acc[1], se) : se;
+  r0 = c.hS != 0.0 ? fma(c.hSd / c.hS, acc[1], acc[0]) : acc[0];
   r1 = 0.5 * acc[2];
-  r2 = acc[3] * (1.0 / 3.0);
+  r2 = acc[3];
 }
 
 // Mirror lanes of the reverse tile before a step: lanes 1 and 62 publish
@@ -699,7 +703,7 @@ __global__ __launch_bounds__(256) void k_equilibrium_adjoint(
     q.rho = rho[j];
     q.J = J[j];
     q.zeta = zeta[j];
-    lbm::thermo(c, q.rho, q.J, q.zeta, q.u, q.s, q.X, q.T, q.ir);
+    lbm::thermo(c, q.rho, q.J, q.zeta, q.u, q.s, q.Y, q.T, q.ir);
     if (c.eq_kind == 0) {
       const double p = q.rho * c.r * q.T;
       q.e_eq = 3.0 * (q.J * q.u + p) - c.two_l2 * q.rho;

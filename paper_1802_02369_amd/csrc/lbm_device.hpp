@@ -5,7 +5,8 @@
 // transcendental calls):
 //   X = ln(T/T0) = (gamma-1) ln(rho/rho0) + gamma (s - s0)/cp, T = T0 e^X,
 //   p = rho r T with r = cp (gamma-1)/gamma.  This is eq. gaz-parfait with
-//   T0 = p0 / (rho0 r), p0 = rho0 c0^2 / gamma: one log and one exp per node.
+//   T0 = p0 / (rho0 r), p0 = rho0 c0^2 / gamma: one log and one exp per node,
+//   both to base 2: Y = X / ln 2, T = T0 2^Y.
 //   eps_eq = (2 cp lambda^2 / gamma) rho X + e_eq s, because the bracket of
 //   eq. eq-energie-entropie-d1q3q3 equals e_eq of eq. energie-equilibre.
 //   Step (vii): dt S_j = (sigma_e/4) (rho_j/T_j) [(u_{j+1}-u_{j-1})^2
@@ -25,9 +26,12 @@ struct Consts {
   double mJ, me;      // rho0 lambda, rho0 lambda^2
   double mz, mpsi, meps;  // rho0 cp, rho0 cp lambda, rho0 cp lambda^2
   double gm1, gcp, xs0;   // gamma - 1, gamma / cp, -gamma s0 / cp
+  double gcp2, y0;        // Y = gm1 log2 rho + gcp2 s + y0: gcp / ln 2,
+                          // (xs0 - gm1 ln rho0) / ln 2
   double T0, r;
   double two_l2;      // 2 lambda^2
   double eps_c;       // 2 cp lambda^2 / gamma
+  double eps_y;       // eps_c ln 2
   double s_e, s_psi, s_eps;
   double src_c;       // sigma_e / 4, or 0 without the source
   double cPr;         // cp / Pr
@@ -37,13 +41,13 @@ struct Consts {
   // linear equilibria (section 7, and the thermal scheme of section 4):
   // e = l[0] rho + l[1] J + l[2] zeta, psi = l[3..5] . W, eps = l[6..8] . W
   double lin[9];
-  double xs0l;         // xs0 - (gamma - 1) ln rho0
   // The time step in scaled moments (see collide_local):
-  double se_2, se_3, se_6;  // s_e / 2, s_e / 3, s_e / 6
+  double se_2;              // s_e / 2
   double ise2;              // 1 / s_e^2 (d sigma_e / d s_e = -1 / s_e^2)
-  double sp_2, sx_3, sx_6;  // s_psi / 2, s_eps / 3, s_eps / 6
+  double sp_2, sx_2;        // s_psi / 2, s_eps / 2
   double hP;                // c0^2 / (gamma lambda^2) = p0 / (rho0 lambda^2)
-  double two_g;             // 2 / gamma
+  double hgam, hy0;         // gamma / ln 2, xs0 / ln 2
+  double tg, tgy;           // 2 / (3 gamma), tg ln 2
   double hS, hC;            // source: src_c lambda^2 / (3 cp T0), cp T0 / (Pr lambda^2)
   double hSd;               // d hS / d s_e = -lambda^2 / (12 cp T0 s_e^2), or 0
   double hlin[9];           // linear equilibria in scaled moments
@@ -91,102 +95,73 @@ __device__ __forceinline__ double recip(double x) {
   return fma(r, fma(e, e, e), r);
 }
 
-// ln 2 = kLn2Hi + kLn2Lo: kLn2Hi is ln 2 rounded to 42 significant bits, so
-// that n kLn2Hi is exact for |n| < 2^11; kLn2Lo is the rest rounded to double.
-constexpr double kLn2Hi = 0x1.62e42fefa3800p-1;
-constexpr double kLn2Lo = 0x1.ef35793c76730p-45;
-constexpr double kLog2e = 0x1.71547652b82fep+0;     // 1 / ln 2
-constexpr double kSqrtHalf = 0x1.6a09e667f3bcdp-1;  // sqrt(1/2)
-
-// Natural logarithm of a positive finite x.  Method: x = m 2^k with m in
-// [sqrt(1/2), sqrt(2)); ln m = 2 atanh(z) with z = (m-1)/(m+1), |z| < 0.172,
-// written z (2 + w Q(w)), w = z^2, where Q is a degree-6 Chebyshev fit of
-// (2 atanh(z) - 2z)/z^3 on [0, 0.02944] (relative error of the fit below
-// 5e-18; coefficients from csrc/gen_poly.py); ln x = k ln 2 + ln m with ln 2
-// in two parts (the additive reduction of Cody & Waite).  Error a few ulp.
-// x <= 0 gives NaN; so do NaN and +inf.
-//
-// ln_reduce splits x: the hardware mantissa mh in [1/2, 1) and a = 2 when
-// mh < sqrt(1/2), else 1, so that m = a mh exactly; m - 1 and m + 1 are
-// then single FMAs (a mh - 1 is exact).  ln_finish completes ln x from z.
-struct LnReduced {
-  double mh, a;
-  int k;
-};
-
-__device__ __forceinline__ LnReduced ln_reduce(double x) {
-  LnReduced r;
-  r.mh = __builtin_amdgcn_frexp_mant(x);
-  const bool lo = r.mh < kSqrtHalf;
-  r.a = lo ? 2.0 : 1.0;
-  r.k = __builtin_amdgcn_frexp_exp(x) - (lo ? 1 : 0);
-  return r;
+// 1/x as recip, from the reciprocal square root: its estimate y is NaN for a
+// negative x, so the logarithm below needs no test of its argument (two
+// instructions), for one multiplication more.  y^2 x = 1 + O(2^-23), then the
+// same third-order step.
+__device__ __forceinline__ double recip_pos(double x) {
+#pragma clang fp contract(off)
+  const double y = __builtin_amdgcn_rsq(x);
+  const double r = y * y;
+  const double e = fma(-x, r, 1.0);
+  return fma(r, fma(e, e, e), r);
 }
 
-__device__ __forceinline__ double ln_finish(double x, const LnReduced& rd,
-                                            double z) {
+// log2 x and 1/x of a positive finite x with one reciprocal.  Method: x = m 2^k
+// with m in [sqrt(1/2), sqrt(2)) up to the 20 fraction bits of the high word,
+// taken apart with 32-bit integer operations on that word (kk = k 2^20, which
+// an FMA with 2^-20 adds); R = 1/(x (m+1)) gives 1/x = R (m+1)
+// and 1/(m+1) = R x, each within about two ulp; log2 m = 2 atanh(z) / ln 2
+// with z = (m-1)/(m+1), |z| < 0.1716, written z (c0 + w Q(w)), w = z^2, where
+// Q is a degree-6 Chebyshev fit on [0, 0.02944] and c0 is 2/ln 2 rounded
+// (relative error of the whole below 2e-17; coefficients from
+// csrc/gen_poly.py).  Base 2 needs no product k ln 2 and gives the exponent
+// of exp2_fin without a reduction by ln 2.  Non-positive, NaN or infinite x
+// give NaN; subnormal x (whose inverse overflows) are not supported.
+__device__ __forceinline__ double log2_inv(double x, double& inv) {
 #pragma clang fp contract(off)
-  const double w = z * z;
-  double q = 0x1.2b584c80de001p-3;
-  q = fma(q, w, 0x1.39fe603f8739ep-3);
-  q = fma(q, w, 0x1.7462b4ac51915p-3);
-  q = fma(q, w, 0x1.c71c62e57c0cfp-3);
-  q = fma(q, w, 0x1.2492492df14bfp-2);
-  q = fma(q, w, 0x1.99999999952e2p-2);
-  q = fma(q, w, 0x1.5555555555558p-1);
-  const double lm = z * fma(w, q, 2.0);
-  const double kd = (double)rd.k;
-  const double r = fma(kd, kLn2Hi, fma(kd, kLn2Lo, lm));
-  // x <= 0: replace the high word by a quiet-NaN pattern (one select)
-  const uint64_t b = __builtin_bit_cast(uint64_t, r);
-  const uint32_t hi = x > 0.0 ? (uint32_t)(b >> 32) : 0x7ff80000u;
-  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | (b & 0xffffffffu));
-}
-
-__device__ __forceinline__ double ln_pos(double x) {
-#pragma clang fp contract(off)
-  const LnReduced rd = ln_reduce(x);
-  const double z = fma(rd.a, rd.mh, -1.0) * recip(fma(rd.a, rd.mh, 1.0));
-  return ln_finish(x, rd, z);
-}
-
-// ln x and 1/x of a positive finite x with one reciprocal: R = 1/(x (m+1))
-// gives 1/x = R (m+1) and 1/(m+1) = R x (each within about two ulp: the
-// rounding of x (m+1), of R and of the product).  Non-positive, NaN or
-// infinite x give a NaN logarithm, as ln_pos.
-__device__ __forceinline__ double ln_inv(double x, double& inv) {
-#pragma clang fp contract(off)
-  const LnReduced rd = ln_reduce(x);
-  const double d = fma(rd.a, rd.mh, 1.0);
-  const double R = recip(x * d);
+  const uint64_t b = __builtin_bit_cast(uint64_t, x);
+  const uint32_t hi = (uint32_t)(b >> 32);
+  const uint32_t kk = (hi - 0x3fe6a09eu) & 0xfff00000u;
+  const double m = __builtin_bit_cast(
+      double, ((uint64_t)(hi - kk) << 32) | (b & 0xffffffffu));
+  const double d = m + 1.0;
+  const double R = recip_pos(x * d);
   inv = R * d;
-  const double z = fma(rd.a, rd.mh, -1.0) * (R * x);
-  return ln_finish(x, rd, z);
+  const double z = (m - 1.0) * (R * x);
+  const double w = z * z;
+  double q = 0x1.afdd0afdc54ffp-3;
+  q = fma(q, w, 0x1.c4ff413719d10p-3);
+  q = fma(q, w, 0x1.0c9e91772d37ep-2);
+  q = fma(q, w, 0x1.484b091bae181p-2);
+  q = fma(q, w, 0x1.a61762b532fa8p-2);
+  q = fma(q, w, 0x1.2776c50ef68fbp-1);
+  q = fma(q, w, 0x1.ec709dc3a0401p-1);
+  const double lm = z * fma(q, w, 0x1.71547652b82fep+1);
+  return fma((double)(int32_t)kk, 0x1p-20, lm);
 }
 
-// e^x for the moderate arguments of the equation of state.  Method (Cody &
-// Waite): n = nearest integer to x / ln 2, r = x - n ln 2 with ln 2 in two
-// parts, |r| <= 0.3466; e^r = 1 + r (1 + r R(r)) where R is a degree-9
-// Chebyshev fit of (e^r - 1 - r)/r^2 (relative error of e^r below 2e-17;
-// coefficients from csrc/gen_poly.py); e^x = 2^n e^r.  Error a few ulp.
-// Overflow gives +inf and underflow 0 (the hardware saturates n); NaN stays
-// NaN.
-__device__ __forceinline__ double exp_fin(double x) {
+// 2^y for the moderate arguments of the equation of state: n = the nearest
+// integer to y, f = y - n exactly, 2^f = 1 + f R(f) with R a degree-10
+// Chebyshev fit on |f| <= 1/2 (relative error of 2^f below 2e-17; coefficients
+// from csrc/gen_poly.py).  Error below one ulp.  Overflow gives +inf and
+// underflow 0 (the hardware saturates n); NaN stays NaN, infinite y give NaN.
+__device__ __forceinline__ double exp2_fin(double y) {
 #pragma clang fp contract(off)
-  const double n = __builtin_rint(x * kLog2e);
-  const double r = fma(-n, kLn2Lo, fma(-n, kLn2Hi, x));
-  double q = 0x1.af38a71a18cb9p-26;
-  q = fma(q, r, 0x1.2891834686c7ep-22);
-  q = fma(q, r, 0x1.71de0daf7a6ccp-19);
-  q = fma(q, r, 0x1.a019b90eefe8ep-16);
-  q = fma(q, r, 0x1.a01a01a7c3d59p-13);
-  q = fma(q, r, 0x1.6c16c1788b646p-10);
-  q = fma(q, r, 0x1.11111111109b4p-7);
-  q = fma(q, r, 0x1.5555555553d64p-5);
-  q = fma(q, r, 0x1.5555555555556p-3);
-  q = fma(q, r, 0x1.0000000000001p-1);
-  q = fma(q, r, 1.0);
-  q = fma(q, r, 1.0);
+  const double n = __builtin_rint(y);
+  const double f = y - n;
+  double q = 0x1.e9d3fe4047b38p-32;
+  q = fma(q, f, 0x1.e6063f7a40c36p-28);
+  q = fma(q, f, 0x1.b524fae624087p-24);
+  q = fma(q, f, 0x1.62bfd4776f20bp-20);
+  q = fma(q, f, 0x1.ffcbfc670dce6p-17);
+  q = fma(q, f, 0x1.430913096fdb5p-13);
+  q = fma(q, f, 0x1.5d87fe78a5276p-10);
+  q = fma(q, f, 0x1.3b2ab6fba1ddap-7);
+  q = fma(q, f, 0x1.c6b08d704a0c2p-5);
+  q = fma(q, f, 0x1.ebfbdff82c598p-3);
+  q = fma(q, f, 0x1.62e42fefa39efp-1);
+  q = fma(q, f, 1.0);
   return __builtin_amdgcn_ldexp(q, (int)n);
 }
 
@@ -196,31 +171,33 @@ __device__ __forceinline__ double exp_fin(double x) {
 // these functions (one-step, any tile shape, batched), and those kernels
 // produce bitwise identical states.
 
-// Thermodynamics from conserved moments: u, s and X = ln(T/T0), T; ir
+// Thermodynamics from conserved moments: u, s, Y = log2(T/T0) and T; ir
 // returns 1/rho.
 __device__ __forceinline__ void thermo(const Consts& c, double rho, double J,
                                        double zeta, double& u, double& s,
-                                       double& X, double& T, double& ir) {
+                                       double& Y, double& T, double& ir) {
 #pragma clang fp contract(off)
-  const double lr = ln_inv(rho, ir);
+  const double lr = log2_inv(rho, ir);
   u = J * ir;
   s = zeta * ir;
-  X = fma(c.gm1, lr, fma(c.gcp, s, c.xs0l));
-  T = c.T0 * exp_fin(X);
+  Y = fma(c.gm1, lr, fma(c.gcp2, s, c.y0));
+  T = c.T0 * exp2_fin(Y);
 }
 
 __device__ __forceinline__ void thermo(const Consts& c, double rho, double J,
                                        double zeta, double& u, double& s,
-                                       double& X, double& T) {
+                                       double& Y, double& T) {
   double ir;
-  thermo(c, rho, J, zeta, u, s, X, T, ir);
+  thermo(c, rho, J, zeta, u, s, Y, T, ir);
 }
 
 // Isentropic pressure p0 (rho/rho0)^gamma = rho r T0 (rho/rho0)^(gamma-1)
 // of the fluid D1Q3 scheme (sections 2-3).
 __device__ __forceinline__ double iso_pressure(const Consts& c, double rho) {
 #pragma clang fp contract(off)
-  return ((rho * c.r) * c.T0) * exp_fin(c.gm1 * ln_pos(rho * c.irho0));
+  double unused;
+  return ((rho * c.r) * c.T0) *
+         exp2_fin(c.gm1 * log2_inv(rho * c.irho0, unused));
 }
 
 // Step (iv): equilibria of the non-conserved moments from rho, J, zeta and
@@ -228,14 +205,14 @@ __device__ __forceinline__ double iso_pressure(const Consts& c, double rho) {
 template <int EQ>
 __device__ __forceinline__ void equilibria(const Consts& c, double rho,
                                            double J, double zeta, double u,
-                                           double s, double X, double T,
+                                           double s, double Y, double T,
                                            double& e_eq, double& psi_eq,
                                            double& eps_eq) {
 #pragma clang fp contract(off)
   if (EQ == 0 || c.eq_kind == 0) {
     e_eq = fma(3.0, fma(J, u, (rho * c.r) * T), -(c.two_l2 * rho));
     psi_eq = zeta * u;
-    eps_eq = fma(e_eq, s, (c.eps_c * rho) * X);
+    eps_eq = fma(e_eq, s, (c.eps_y * rho) * Y);
   } else if (c.eq_kind == 2) {
     e_eq = fma(3.0, fma(J, u, iso_pressure(c, rho)), -(c.two_l2 * rho));
     psi_eq = 0.0;
@@ -251,39 +228,38 @@ __device__ __forceinline__ void equilibria(const Consts& c, double rho,
 // rho0, lambda, cp, T0 from the per-node arithmetic:
 //   rh = rho/rho0 = f0 + f+ + f-,  Jh = J/(rho0 lambda) = f+ - f-,
 //   zh = zeta/(rho0 cp) = g0 + g+ + g-,  uh = u/lambda,  sh = s/cp,
-//   Th = T/T0 = e^X,  X = (gamma-1) ln rh + gamma sh - gamma s0/cp,
+//   Th = T/T0 = 2^Y,  Y = [(gamma-1) ln rh + gamma sh - gamma s0/cp] / ln 2,
 // and the equilibria divided by the scale of their moment (rho0 lambda^2 for
 // e, rho0 cp lambda for psi, rho0 cp lambda^2 for eps):
-//   eh = 3 (Jh uh + hP rh Th) - 2 rh,  psih = zh uh,
-//   epsh = (2/gamma) rh X + eh sh,  hP = c0^2/(gamma lambda^2).
+//   eh = 3 rh y - 2 rh with y = uh^2 + hP Th, hP = c0^2/(gamma lambda^2),
+//   psih = zh uh,  epsh = (2/gamma) ln 2 rh Y + eh sh.
 // (With rho0 = 1, rh is the density summed in the order of eq. M-d1q3q3.)
-// lr returns ln rh.
-// ir returns 1/rh.
+// lr returns log2 rh, ir 1/rh.
 __device__ __forceinline__ void thermo_scaled(const Consts& c, double rh,
                                               double Jh, double zh, double& uh,
-                                              double& sh, double& X,
+                                              double& sh, double& Y,
                                               double& Th, double& lr,
                                               double& ir) {
 #pragma clang fp contract(off)
-  lr = ln_inv(rh, ir);
+  lr = log2_inv(rh, ir);
   uh = Jh * ir;
   sh = zh * ir;
-  X = fma(c.gm1, lr, fma(c.gamma, sh, c.xs0));
-  Th = exp_fin(X);
+  Y = fma(c.gm1, lr, fma(c.hgam, sh, c.hy0));
+  Th = exp2_fin(Y);
 }
 
 __device__ __forceinline__ void thermo_scaled(const Consts& c, double rh,
                                               double Jh, double zh, double& uh,
-                                              double& sh, double& X,
+                                              double& sh, double& Y,
                                               double& Th, double& lr) {
   double ir;
-  thermo_scaled(c, rh, Jh, zh, uh, sh, X, Th, lr, ir);
+  thermo_scaled(c, rh, Jh, zh, uh, sh, Y, Th, lr, ir);
 }
 
 // The thermodynamic state of a node's incoming populations, as the time
 // step computes it (kept by the reverse sweep for a state it recomputes).
 struct NodeThermo {
-  double uh, sh, X, Th, lr, ir, w;
+  double uh, sh, Y, Th, lr, ir, w;
 };
 
 // Steps (ii)-(vi) at one node, in place on the six populations: moments,
@@ -292,6 +268,23 @@ struct NodeThermo {
 // the equilibria of section 8 only (every lattice of the launch has
 // eq_kind 0); EQ = -1 selects them per lattice from c.eq_kind.  SAVE: also
 // writes the node's thermodynamic state into *save.
+//
+// (v) relaxation (eq. relaxation-d1q3q3) and (vi) f* = M^-1 m*, combined: only
+// e, psi, eps change, so f* = f + M^-1 (m* - m).  With the entries of M^-1
+// the changes are f0 -= s_e d, f+- += s_e d / 2 and g0 -= s_eps dx,
+// g+- += s_eps dx / 2 +- s_psi dp / 2, where
+//   d = (eh - (f+ + f- - 2 f0)) / 3,  dp = psih - (g+ - g-),
+//   dx = (epsh - (g+ + g- - 2 g0)) / 3.
+// For the equilibria of section 8 the sums of populations in eh and epsh
+// cancel (rh = f0 + f+ + f-, rh sh = zh = g0 + g+ + g-):
+//   d = rh y - (f+ + f-),  dx = rh (y sh + tgy Y) - (g+ + g-),
+// with tgy = (2/(3 gamma)) ln 2: three FMAs instead of eh, epsh and their
+// differences.  The kernels are bound by the issue of these instructions; with
+// the base-2 logarithm and exponential a node of a P = 8 tile takes 86 VALU
+// instructions (78 of them FP64, two of those reciprocal estimates at a
+// quarter of the rate) where ln, exp and separate equilibria took 98 (91):
+// 200 steps of 2^24 nodes 11.5 -> 10.1 ms, 4096 ragged lattices 12.5 -> 11.0
+// ms for 160 steps.
 template <int EQ, bool SAVE = false>
 __device__ __forceinline__ void collide_local(const Consts& c, double& f0,
                                               double& fp, double& fm,
@@ -303,57 +296,39 @@ __device__ __forceinline__ void collide_local(const Consts& c, double& f0,
   // (ii) the conserved moments, eq. M-d1q3q3, scaled
   const double rh = (f0 + fp) + fm;
   const double Jh = fp - fm;
+  const double sf = fp + fm;
   const double sg = gp + gm;
   const double zh = g0 + sg;
   // (iv) equilibria
-  double sh, X, lr, ir;
-  thermo_scaled(c, rh, Jh, zh, u, sh, X, T, lr, ir);
-  double jup, eh, psih, epsh;
+  double sh, Y, lr, ir;
+  thermo_scaled(c, rh, Jh, zh, u, sh, Y, T, lr, ir);
+  double d, dp, dx;
   if (EQ == 0 || c.eq_kind == 0) {
-    jup = fma(Jh, u, (c.hP * rh) * T);
-    eh = fma(-2.0, rh, 3.0 * jup);
-    psih = zh * u;
-    epsh = fma(eh, sh, (c.two_g * rh) * X);
+    const double y = fma(u, u, c.hP * T);
+    d = fma(rh, y, -sf);
+    dp = fma(zh, u, gm - gp);
+    dx = fma(rh, fma(y, sh, c.tgy * Y), -sg);
   } else if (c.eq_kind == 2) {
-    jup = fma(Jh, u, (c.hP * rh) * exp_fin(c.gm1 * lr));
-    eh = fma(-2.0, rh, 3.0 * jup);
-    psih = 0.0;
-    epsh = 0.0;
+    d = fma(rh, fma(u, u, c.hP * exp2_fin(c.gm1 * lr)), -sf);
+    dp = gm - gp;
+    dx = fma(2.0, g0, -sg) * (1.0 / 3.0);
   } else {
-    jup = 0.0;
-    eh = fma(c.hlin[2], zh, fma(c.hlin[1], Jh, c.hlin[0] * rh));
-    psih = fma(c.hlin[5], zh, fma(c.hlin[4], Jh, c.hlin[3] * rh));
-    epsh = fma(c.hlin[8], zh, fma(c.hlin[7], Jh, c.hlin[6] * rh));
+    const double eh = fma(c.hlin[2], zh, fma(c.hlin[1], Jh, c.hlin[0] * rh));
+    const double psih = fma(c.hlin[5], zh, fma(c.hlin[4], Jh, c.hlin[3] * rh));
+    const double epsh = fma(c.hlin[8], zh, fma(c.hlin[7], Jh, c.hlin[6] * rh));
+    d = (eh - fma(-2.0, f0, sf)) * (1.0 / 3.0);
+    dp = psih - (gp - gm);
+    dx = (epsh - fma(-2.0, g0, sg)) * (1.0 / 3.0);
   }
-  // (v) relaxation (eq. relaxation-d1q3q3) and (vi) f* = M^-1 m*, combined:
-  // only e, psi, eps change, so f* = f + M^-1 (m* - m).  The entries of M^-1
-  // turn the changes into
-  //   de = fb (e* - e) = (s_e/3) (eh - (f+ + f- - 2 f0)),
-  //   dp = gc (psi* - psi) = (s_psi/2) (psih - (g+ - g-)),
-  //   dx = gb (eps* - eps) = (s_eps/3) (epsh - (g+ + g- - 2 g0)),
-  // and f0 -= de, f+- += de/2; g0 -= dx, g+- += dx/2 +- dp.  When
-  // eh = 3 (Jh uh + hP rh Th) - 2 rh, de reduces to
-  // s_e (Jh uh + hP rh Th - (f+ + f-)) since rh = f0 + f+ + f-.  The rates
-  // enter through the FMAs of the updates.
-  if (EQ == 0 || c.eq_kind != 1) {
-    const double d = jup - (fp + fm);
-    f0 = fma(-c.s_e, d, f0);
-    fp = fma(c.se_2, d, fp);
-    fm = fma(c.se_2, d, fm);
-  } else {
-    const double d = eh - fma(-2.0, f0, fp + fm);
-    f0 = fma(-c.se_3, d, f0);
-    fp = fma(c.se_6, d, fp);
-    fm = fma(c.se_6, d, fm);
-  }
-  const double dpr = psih - (gp - gm);
-  const double dxr = epsh - fma(-2.0, g0, sg);
-  g0 = fma(-c.sx_3, dxr, g0);
-  gp = fma(c.sp_2, dpr, fma(c.sx_6, dxr, gp));
-  gm = fma(-c.sp_2, dpr, fma(c.sx_6, dxr, gm));
+  f0 = fma(-c.s_e, d, f0);
+  fp = fma(c.se_2, d, fp);
+  fm = fma(c.se_2, d, fm);
+  g0 = fma(-c.s_eps, dx, g0);
+  gp = fma(c.sp_2, dp, fma(c.sx_2, dx, gp));
+  gm = fma(-c.sp_2, dp, fma(c.sx_2, dx, gm));
   w = recip(T);
   rw = rh * w;
-  if constexpr (SAVE) *save = NodeThermo{u, sh, X, T, lr, ir, w};
+  if constexpr (SAVE) *save = NodeThermo{u, sh, Y, T, lr, ir, w};
 }
 
 // uh and Th of a node (the halo nodes of the one-step kernel), rounded as in
@@ -365,31 +340,36 @@ __device__ __forceinline__ void node_uT(const Consts& c, double f0, double fp,
   const double rh = (f0 + fp) + fm;
   const double Jh = fp - fm;
   const double zh = g0 + (gp + gm);
-  double sh, X, lr;
-  thermo_scaled(c, rh, Jh, zh, u, sh, X, T, lr);
+  double sh, Y, lr;
+  thermo_scaled(c, rh, Jh, zh, u, sh, Y, T, lr);
 }
 
-// Step (vii): the increment of zeta at node j, already divided into the
+// Step (vii): adds the increment of zeta at node j, already divided into the
 // M^-1 column of zeta (each of g0, g+, g- receives ga dt S_j), from scaled
 // quantities: ga dt S_j = hS rh wh [(uh_{j+1} - uh_{j-1})^2
-// + hC (Th_{j+1} - Th_{j-1})^2 wh] with wh = 1/Th_j.
-__device__ __forceinline__ double source_g(const Consts& c, double rw, double w,
+// + hC (Th_{j+1} - Th_{j-1})^2 wh] with wh = 1/Th_j, as an FMA each.
+__device__ __forceinline__ void add_source(const Consts& c, double rw, double w,
                                            double uL, double uR, double TL,
-                                           double TR) {
+                                           double TR, double& g0, double& gp,
+                                           double& gm) {
 #pragma clang fp contract(off)
   const double du = uR - uL;
   const double dT = TR - TL;
-  return (c.hS * rw) * fma(du, du, (c.hC * (dT * dT)) * w);
+  const double a = c.hS * rw;
+  const double q = fma(du, du, (c.hC * (dT * dT)) * w);
+  g0 = fma(a, q, g0);
+  gp = fma(a, q, gp);
+  gm = fma(a, q, gm);
 }
 
 // Equilibrium populations from (rho, J, zeta).
 __device__ __forceinline__ void equilibrium(const Consts& c, double rho,
                                             double J, double zeta, double f[6]) {
 #pragma clang fp contract(off)
-  double u, s, X, T;
-  thermo(c, rho, J, zeta, u, s, X, T);
+  double u, s, Y, T;
+  thermo(c, rho, J, zeta, u, s, Y, T);
   double e_eq, psi_eq, eps_eq;
-  equilibria<-1>(c, rho, J, zeta, u, s, X, T, e_eq, psi_eq, eps_eq);
+  equilibria<-1>(c, rho, J, zeta, u, s, Y, T, e_eq, psi_eq, eps_eq);
   const double fr = c.fa * rho, fe = c.fb * e_eq, fj = c.fc * J;
   f[0] = fr - fe;
   f[1] = fma(0.5, fe, fr) + fj;

@@ -147,12 +147,9 @@ __device__ __forceinline__ void tile_step(const lbm::Consts& c, double (&f)[6][P
     double u, T, rw, w;
     lbm::collide_local<EQ, SAVE>(c, f[0][0], f[1][0], f[2][0], f[3][0], f[4][0],
                                  f[5][0], u, T, rw, w, th);
-    const double add =
-        lbm::source_g(c, rw, w, lbm::from_left(u), lbm::from_right(u),
-                      lbm::from_left(T), lbm::from_right(T));
-    f[3][0] += add;
-    f[4][0] += add;
-    f[5][0] += add;
+    lbm::add_source(c, rw, w, lbm::from_left(u), lbm::from_right(u),
+                    lbm::from_left(T), lbm::from_right(T), f[3][0], f[4][0],
+                    f[5][0]);
     f[1][0] = lbm::from_left(f[1][0]);
     f[4][0] = lbm::from_left(f[4][0]);
     f[2][0] = lbm::from_right(f[2][0]);
@@ -188,10 +185,7 @@ __device__ __forceinline__ void tile_step(const lbm::Consts& c, double (&f)[6][P
       ur = uR;
       Tr = TR;
     }
-    const double add = lbm::source_g(c, rwm, wm, ul, ur, Tl, Tr);
-    f[3][k] += add;
-    f[4][k] += add;
-    f[5][k] += add;
+    lbm::add_source(c, rwm, wm, ul, ur, Tl, Tr, f[3][k], f[4][k], f[5][k]);
     ul = um;
     Tl = Tm;
     um = ur;
