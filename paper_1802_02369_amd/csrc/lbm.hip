@@ -302,74 +302,83 @@ __global__ __launch_bounds__(kPlainBlock + 64) void k_step_plain(
 
 // K time steps of one register-resident tile per workgroup (see the file
 // header).  The workgroup has WG wavefronts of 64 lanes, lane l of wavefront
-// w holding the P consecutive nodes starting at tile index w*62P + (l-1)P
-// (l = 0..63; wavefront 0 starts at tile index 0).  Neighbouring wavefronts
-// overlap by two lanes: lane 0 of wavefront w > 0 mirrors lane 62 of w-1,
-// lane 63 of w < WG-1 mirrors lane 1 of w+1.  A tile thus spans
-// tile_nodes = P(62 WG + 2) nodes; tile t stores nodes [t*OUT, t*OUT + OUT)
-// with OUT = tile_nodes - 4K and loads [t*OUT - 2K, t*OUT + OUT + 2K)
-// (periodic).
+// w holding the P consecutive nodes starting at tile index
+// P ((64 - 2M) w + l).  Neighbouring wavefronts overlap by 2M lanes: the first
+// M lanes of wavefront w > 0 mirror lanes 64-2M .. 63-M of w-1, the last M
+// lanes of w < WG-1 mirror lanes M .. 2M-1 of w+1.  A tile thus spans
+// tile_nodes = P((64 - 2M) WG + 2M) nodes; tile t stores nodes
+// [t*OUT, t*OUT + OUT) with OUT = tile_nodes - 4K and loads
+// [t*OUT - 2K, t*OUT + OUT + 2K) (periodic).
 //
 // Every step runs within the wavefront (lane neighbours through DPP).  The
 // outermost lanes have no neighbour there; as one step has radius 2, the
-// error this leaves at a mirror lane's outer end moves two nodes inwards per
-// step and reaches the wavefront's own lanes after P/2 steps.  So every P/2
-// steps the wavefronts copy their edge lanes 1 and 62 into the neighbours'
-// mirror lanes through LDS (one workgroup barrier per copy, double-buffered);
-// each wavefront stores only its own lanes.  The error at the tile's two
-// outer ends is what the halo of 2K nodes absorbs.
+// error this leaves at the mirror lanes' outer end moves two nodes inwards per
+// step and reaches the wavefront's own lanes after MP/2 steps.  So every MP/2
+// steps the wavefronts copy their edge lanes into the neighbours' mirror
+// lanes through LDS (one workgroup barrier per copy, double-buffered); each
+// wavefront stores only its own lanes.  The error at the tile's two outer
+// ends is what the halo of 2K nodes absorbs.  A copy costs about 0.3 us of
+// latency.  With M = 1 a P = 2 tile pays it at every step (n = 8192, 4
+// wavefronts, K = 40: 0.80 us per step, 0.54 with M = 4), so the wide shapes
+// of plan_steps take 8/P mirror lanes: a copy every four steps at every P.
+// One node per lane needs them to have several wavefronts at all.
 //
-// Refresh of the mirror lanes: lanes 1 and 62 publish their populations in
-// `edge` (one buffer of the double-buffered pair: a buffer is written again
-// only after the next refresh's barrier, which every reader of its previous
-// contents has passed), then lane 0 takes lane 62 of the wavefront to its
-// left and lane 63 lane 1 of the wavefront to its right.
-template <int P, int WG>
+// Refresh of the mirror lanes: the M lanes next to them on each side publish
+// their populations in `edge` (one buffer of the double-buffered pair: a
+// buffer is written again only after the next refresh's barrier, which every
+// reader of its previous contents has passed), then the mirror lanes take
+// those of the neighbouring wavefronts.
+template <int P, int WG, int M>
 __device__ __forceinline__ void mirror_refresh(double (&f)[6][P],
-                                               double (*edge)[2][6 * P],
+                                               double (*edge)[2][6 * P * M],
                                                int lane, int wave, int nw) {
-  if (lane == 1 || lane == 62) {
-    double* d = edge[wave][lane == 62];
+  const bool hi = lane >= 32;  // the right half of the wavefront
+  const int pub = hi ? lane - (64 - 2 * M) : lane - M;
+  if (pub >= 0 && pub < M) {
+    double* d = edge[wave][hi] + pub;
 #pragma unroll
     for (int q = 0; q < 6; ++q)
 #pragma unroll
-      for (int k = 0; k < P; ++k) d[q * P + k] = f[q][k];
+      for (int k = 0; k < P; ++k) d[(q * P + k) * M] = f[q][k];
   }
   __syncthreads();
-  const bool left = lane == 0 && wave > 0, right = lane == 63 && wave < nw - 1;
+  const bool left = lane < M && wave > 0, right = lane >= 64 - M && wave < nw - 1;
   if (left || right) {
-    const double* e = left ? edge[wave - 1][1] : edge[wave + 1][0];
+    const double* e = left ? edge[wave - 1][1] + lane
+                           : edge[wave + 1][0] + (lane - (64 - M));
 #pragma unroll
     for (int q = 0; q < 6; ++q)
 #pragma unroll
-      for (int k = 0; k < P; ++k) f[q][k] = e[q * P + k];
+      for (int k = 0; k < P; ++k) f[q][k] = e[(q * P + k) * M];
   }
 }
 
 // Active wavefronts of a tile that starts at lattice index `start` (halo H)
-// in a lattice of n nodes: the fewest of the WG whose span P(62 nw + 2)
-// still covers the nodes the tile stores plus both halos.  Only a lattice's
-// last tile, or a lattice shorter than one tile, needs fewer than WG.
-template <int P, int WG>
+// in a lattice of n nodes: the fewest of the WG whose span
+// P((64 - 2M) nw + 2M) still covers the nodes the tile stores plus both halos.
+// Only a lattice's last tile, or a lattice shorter than one tile, needs fewer
+// than WG.
+template <int P, int WG, int M>
 __device__ __forceinline__ int active_waves(int64_t n, int64_t start, int H) {
+  constexpr int WS = (64 - 2 * M) * P;
   const int64_t store = n - (start + H);  // nodes from the tile's first output
-  const int64_t need = store + 2 * H - 2 * P;  // span - 2P the tile needs
-  if (need >= (int64_t)62 * P * WG) return WG;
-  const int nw = (int)((need + 62 * P - 1) / (62 * P));
+  const int64_t need = store + 2 * H - 2 * M * P;  // beyond the mirror lanes
+  if (need >= (int64_t)WS * WG) return WG;
+  const int nw = ((int)need + WS - 1) / WS;
   return nw < 1 ? 1 : nw;
 }
 
 // Tile t of a lattice of n nodes (array stride S) starting at lattice index
 // `start` = t*OUT - H, OUT = tile_nodes - 2H: load, K <= H/2 steps, store of
 // the interior [H, span - H) (one step has radius 2, so K steps need
-// H >= 2K).  Only the first nw wavefronts work (span P(62 nw + 2)); the
+// H >= 2K).  Only the first nw wavefronts work (active_waves); the
 // others end at once, which a workgroup barrier allows (it waits for the
 // wavefronts that have not ended), and leave their SIMDs to other
 // workgroups.  With every_step (the recompute of a checkpoint segment for a
 // reverse sweep), the state after step s = 1..K is state i = first + s of
 // the segment, and the interior of those states whose i is a multiple of
 // `every` is stored, state i into fout + ((i-1)/every)*state_stride.
-template <int P, int WG, int EQ>
+template <int P, int WG, int M, int EQ>
 __device__ __forceinline__ void tile_run(const Consts& c,
                                          const double* __restrict__ fin,
                                          double* __restrict__ fout, int64_t S,
@@ -377,18 +386,19 @@ __device__ __forceinline__ void tile_run(const Consts& c,
                                          int K, bool every_step = false,
                                          int64_t state_stride = 0,
                                          int first = 0, int every = 1) {
-  // one node per lane leaves no room for mirror lanes: one wavefront
-  static_assert(P > 1 || WG == 1, "P = 1 tiles have one wavefront");
-  constexpr int WW = 64 * P;       // nodes of one wavefront
-  constexpr int WS = 62 * P;       // wavefront stride in the tile
-  __shared__ double stage[WG * (WW + 64)];
-  __shared__ double edge[2][WG][2][6 * P];
+  // mirror lanes must hold at least one step's two wrong nodes
+  static_assert(WG == 1 || (M * P >= 2 && 2 * M <= 32), "mirror lanes");
+  constexpr int WW = 64 * P;              // nodes of one wavefront
+  constexpr int WS = (64 - 2 * M) * P;    // wavefront stride in the tile
+  // one node per lane needs no staging: the register order is the coalesced
+  __shared__ double stage[P == 1 ? 1 : WG * (WW + 64)];
+  __shared__ double edge[2][WG][2][6 * P * M];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int nw = active_waves<P, WG>(n, start, H);
+  const int nw = active_waves<P, WG, M>(n, start, H);
   if (wave >= nw) return;  // uniform over the wavefront
-  const int W = lbm::tile_nodes(P, nw);
-  double* lds = stage + wave * (WW + 64);
+  const int W = lbm::tile_nodes(P, nw, M);
+  double* lds = stage + (P == 1 ? 0 : wave * (WW + 64));
   const int64_t wstart = start + wave * WS;
   const bool inside = start >= 0 && start + W <= n;
   const bool small = n < W;
@@ -396,16 +406,16 @@ __device__ __forceinline__ void tile_run(const Consts& c,
   tile_load<P>(fin, S, n, wstart, inside, small, lane, lds, f);
   // the tile's valid indices [H, W - H), in this wavefront's numbering and
   // restricted to its own lanes (the mirror lanes belong to the neighbours)
-  const int lo = max(H - wave * WS, wave > 0 ? P : 0);
-  const int hi = min(W - H - wave * WS, wave < nw - 1 ? WW - P : WW);
+  const int lo = max(H - wave * WS, wave > 0 ? M * P : 0);
+  const int hi = min(W - H - wave * WS, wave < nw - 1 ? WW - M * P : WW);
   int since = 0, buf = 0;
   for (int step = 0; step < K; ++step) {
     tile_step<P, EQ>(c, f);
     if (every_step && (first + step + 1) % every == 0)
       tile_store<P>(fout + (int64_t)((first + step) / every) * state_stride, S,
                     n, wstart, lo, hi, lane, lds, f);
-    if (WG > 1 && ++since == P / 2 && step + 1 < K) {
-      mirror_refresh<P, WG>(f, edge[buf], lane, wave, nw);
+    if (WG > 1 && ++since == M * P / 2 && step + 1 < K) {
+      mirror_refresh<P, WG, M>(f, edge[buf], lane, wave, nw);
       buf ^= 1;
       since = 0;
     }
@@ -422,17 +432,17 @@ __device__ __forceinline__ void tile_run(const Consts& c,
 // of a reverse sweep, need more registers at P >= 4 and take one.  P <= 2
 // needs few registers: four.
 constexpr int tile_waves_per_simd(int P, int WG, bool sec8_plain) {
-  return P <= 2 ? 4 : (!sec8_plain ? 1 : (P == 8 && WG <= 4 ? 3 : 2));
+  return P <= 2 ? 4 : WG > 8 ? 3 : !sec8_plain ? 1 : P == 8 && WG <= 4 ? 3 : 2;
 }
 
-template <int P, int WG, int EQ>
+template <int P, int WG, int M, int EQ>
 __global__ __launch_bounds__(64 * WG, tile_waves_per_simd(P, WG, EQ == 0)) void k_step_tile(
     Consts c, const double* __restrict__ fin, double* __restrict__ fout,
     int64_t n, int K, int64_t ntiles) {
   const int64_t tile = blockIdx.x;
   if (tile >= ntiles) return;  // uniform over the workgroup
-  const int OUT = lbm::tile_nodes(P, WG) - 4 * K;
-  tile_run<P, WG, EQ>(c, fin, fout, n, n, tile * OUT - 2 * K, 2 * K, K);
+  const int OUT = lbm::tile_nodes(P, WG, M) - 4 * K;
+  tile_run<P, WG, M, EQ>(c, fin, fout, n, n, tile * OUT - 2 * K, 2 * K, K);
 }
 
 // Batched form: workgroup b advances tile tiles[b].t of lattice tiles[b].inst,
@@ -441,7 +451,7 @@ __global__ __launch_bounds__(64 * WG, tile_waves_per_simd(P, WG, EQ == 0)) void 
 // OUT = W - 2H) is fixed by the tile table; a launch runs K <= H/2 steps.
 // EVERY: store the states of a checkpoint segment that the reverse sweep
 // loads (see tile_run: first, every).
-template <int P, int WG, int EQ, bool EVERY>
+template <int P, int WG, int M, int EQ, bool EVERY>
 __global__ __launch_bounds__(64 * WG, tile_waves_per_simd(P, WG, EQ == 0 && !EVERY)) void k_batch_tile(
     const Consts* __restrict__ cs, const int64_t* __restrict__ offs,
     const lbm::TileRef* __restrict__ tiles, const double* __restrict__ fin,
@@ -453,8 +463,8 @@ __global__ __launch_bounds__(64 * WG, tile_waves_per_simd(P, WG, EQ == 0 && !EVE
   const int64_t off = offs[tr.inst];
   const int64_t n = offs[tr.inst + 1] - off;
   const Consts c = cs[tr.inst];
-  const int OUT = lbm::tile_nodes(P, WG) - 2 * H;
-  tile_run<P, WG, EQ>(c, fin + off, fout + off, S, n, (int64_t)tr.t * OUT - H, H,
+  const int OUT = lbm::tile_nodes(P, WG, M) - 2 * H;
+  tile_run<P, WG, M, EQ>(c, fin + off, fout + off, S, n, (int64_t)tr.t * OUT - H, H,
                   K, EVERY, state_stride, first, every);
 }
 
@@ -870,49 +880,42 @@ int launch_step_plain(const Consts& c, const double* fin, double* fout,
   return hip_check(hipGetLastError(), "k_step_plain");
 }
 
-int64_t tile_out(int P, int K, int wg) { return tile_nodes(P, wg) - 4 * K; }
-
-template <int P, int WG>
+template <int P, int WG, int M>
 static void launch_tile_t(const Consts& c, const double* fin, double* fout,
                           int64_t n, int K, hipStream_t s) {
-  const int64_t ntiles = cdiv(n, tile_out(P, K, WG));
+  const int64_t ntiles = cdiv(n, tile_nodes(P, WG, M) - 4 * K);
   if (c.eq_kind == 0)
-    hipLaunchKernelGGL((k_step_tile<P, WG, 0>), dim3((unsigned)ntiles),
+    hipLaunchKernelGGL((k_step_tile<P, WG, M, 0>), dim3((unsigned)ntiles),
                        dim3(64 * WG), 0, s, c, fin, fout, n, K, ntiles);
   else
-    hipLaunchKernelGGL((k_step_tile<P, WG, -1>), dim3((unsigned)ntiles),
+    hipLaunchKernelGGL((k_step_tile<P, WG, M, -1>), dim3((unsigned)ntiles),
                        dim3(64 * WG), 0, s, c, fin, fout, n, K, ntiles);
 }
 
-template <int P>
-static int launch_tile_p(const Consts& c, const double* fin, double* fout,
-                         int64_t n, int K, int wg, hipStream_t s) {
-  switch (wg) {
-    case 1: launch_tile_t<P, 1>(c, fin, fout, n, K, s); break;
-    case 2: launch_tile_t<P, 2>(c, fin, fout, n, K, s); break;
-    case 4: launch_tile_t<P, 4>(c, fin, fout, n, K, s); break;
-    case 8: launch_tile_t<P, 8>(c, fin, fout, n, K, s); break;
-    default: return set_err(LBM_EINVAL, "waves_per_group must be 1, 2, 4 or 8");
-  }
-  return LBM_OK;
-}
+// The tile shapes (P, wavefronts, mirror lanes) of tuning records, and the
+// wide ones that plan_steps chooses from besides them.
+#define LBM_TILE_SHAPES(X)                                                    \
+  X(1, 1, 1) X(2, 1, 1) X(2, 2, 1) X(2, 4, 1) X(2, 8, 1) X(4, 1, 1)           \
+  X(4, 2, 1) X(4, 4, 1) X(4, 8, 1) X(8, 1, 1) X(8, 2, 1) X(8, 4, 1)           \
+  X(8, 8, 1)
+#define LBM_WIDE_SHAPES(X)                                                    \
+  X(1, 4, 8) X(1, 8, 8) X(1, 12, 8) X(2, 8, 4) X(2, 12, 4) X(4, 4, 2)         \
+  X(4, 8, 2) X(4, 12, 2)
 
 int launch_step_tile(const Consts& c, const double* fin, double* fout,
-                     int64_t n, int P, int K, int wpg, hipStream_t s) {
-  int rc;
-  switch (P) {
-    case 1:
-      if (wpg != 1) return set_err(LBM_EINVAL, "nodes_per_lane 1 needs one wavefront");
-      launch_tile_t<1, 1>(c, fin, fout, n, K, s);
-      rc = LBM_OK;
-      break;
-    case 2: rc = launch_tile_p<2>(c, fin, fout, n, K, wpg, s); break;
-    case 4: rc = launch_tile_p<4>(c, fin, fout, n, K, wpg, s); break;
-    case 8: rc = launch_tile_p<8>(c, fin, fout, n, K, wpg, s); break;
-    default: return set_err(LBM_EINVAL, "nodes_per_lane must be 1, 2, 4 or 8");
+                     int64_t n, const TileShape& t, int K, hipStream_t s) {
+  if (K < 1 || 4 * K >= tile_nodes(t.P, t.W, t.M))
+    return set_err(LBM_EINVAL, "bad tile geometry K=%d", K);
+#define LBM_STEP_CASE(PP, WW, MM)                                             \
+  if (t.P == PP && t.W == WW && t.M == MM) {                                  \
+    launch_tile_t<PP, WW, MM>(c, fin, fout, n, K, s);                         \
+    return hip_check(hipGetLastError(), "k_step_tile");                       \
   }
-  if (rc) return rc;
-  return hip_check(hipGetLastError(), "k_step_tile");
+  LBM_TILE_SHAPES(LBM_STEP_CASE)
+  LBM_WIDE_SHAPES(LBM_STEP_CASE)
+#undef LBM_STEP_CASE
+  return set_err(LBM_EINVAL, "unsupported tile shape P=%d waves=%d mirror=%d",
+                 t.P, t.W, t.M);
 }
 
 // reduction scratch of the diagnostics (8 final values, 8 per block), then
@@ -1007,7 +1010,7 @@ int launch_moments(const Consts& c, const double* f, double* m, int64_t n,
   return hip_check(hipGetLastError(), "k_moments");
 }
 
-template <int P, int WG>
+template <int P, int WG, int M>
 static void launch_batch_t(const Consts* cs, const int64_t* offs,
                            const TileRef* tiles, int64_t ntiles,
                            const double* fin, double* fout, int64_t S, int H,
@@ -1015,54 +1018,43 @@ static void launch_batch_t(const Consts* cs, const int64_t* offs,
                            int eq, hipStream_t s) {
   const dim3 grid((unsigned)ntiles), block(64 * WG);
   if (eq == 0 && state_stride == 0)
-    hipLaunchKernelGGL((k_batch_tile<P, WG, 0, false>), grid, block, 0, s, cs,
+    hipLaunchKernelGGL((k_batch_tile<P, WG, M, 0, false>), grid, block, 0, s, cs,
                        offs, tiles, fin, fout, S, H, K, ntiles, state_stride, first,
                        every);
   else if (eq == 0)
-    hipLaunchKernelGGL((k_batch_tile<P, WG, 0, true>), grid, block, 0, s, cs,
+    hipLaunchKernelGGL((k_batch_tile<P, WG, M, 0, true>), grid, block, 0, s, cs,
                        offs, tiles, fin, fout, S, H, K, ntiles, state_stride, first,
                        every);
   else if (state_stride == 0)
-    hipLaunchKernelGGL((k_batch_tile<P, WG, -1, false>), grid, block, 0, s, cs,
+    hipLaunchKernelGGL((k_batch_tile<P, WG, M, -1, false>), grid, block, 0, s, cs,
                        offs, tiles, fin, fout, S, H, K, ntiles, state_stride, first,
                        every);
   else
-    hipLaunchKernelGGL((k_batch_tile<P, WG, -1, true>), grid, block, 0, s, cs,
+    hipLaunchKernelGGL((k_batch_tile<P, WG, M, -1, true>), grid, block, 0, s, cs,
                        offs, tiles, fin, fout, S, H, K, ntiles, state_stride, first,
                        every);
 }
 
 int launch_batch_tile(const Consts* cs, const int64_t* offs,
                       const TileRef* tiles, int64_t ntiles, const double* fin,
-                      double* fout, int64_t S, int P, int H, int K, int wg,
+                      double* fout, int64_t S, const TileShape& t, int H, int K,
                       int eq, hipStream_t s, int64_t state_stride, int first,
                       int every) {
   if (ntiles <= 0) return LBM_OK;
-  if (K < 1 || 2 * K > H || 2 * H >= tile_nodes(P, wg))
+  if (K < 1 || 2 * K > H || 2 * H >= tile_nodes(t.P, t.W, t.M))
     return set_err(LBM_EINVAL, "bad batched tile geometry H=%d K=%d", H, K);
   if (first < 0 || every < 1)
     return set_err(LBM_EINVAL, "bad segment state numbering");
-#define LBM_BATCH_CASE(PP, WW)                                              \
-  if (P == PP && wg == WW) {                                                \
-    launch_batch_t<PP, WW>(cs, offs, tiles, ntiles, fin, fout, S, H, K,    \
-                           state_stride, first, every, eq, s);              \
-    return hip_check(hipGetLastError(), "k_batch_tile");                    \
+#define LBM_BATCH_CASE(PP, WW, MM)                                            \
+  if (t.P == PP && t.W == WW && t.M == MM) {                                  \
+    launch_batch_t<PP, WW, MM>(cs, offs, tiles, ntiles, fin, fout, S, H, K,   \
+                               state_stride, first, every, eq, s);            \
+    return hip_check(hipGetLastError(), "k_batch_tile");                      \
   }
-  LBM_BATCH_CASE(1, 1)
-  LBM_BATCH_CASE(2, 1)
-  LBM_BATCH_CASE(2, 2)
-  LBM_BATCH_CASE(2, 4)
-  LBM_BATCH_CASE(2, 8)
-  LBM_BATCH_CASE(4, 1)
-  LBM_BATCH_CASE(4, 2)
-  LBM_BATCH_CASE(4, 4)
-  LBM_BATCH_CASE(4, 8)
-  LBM_BATCH_CASE(8, 1)
-  LBM_BATCH_CASE(8, 2)
-  LBM_BATCH_CASE(8, 4)
-  LBM_BATCH_CASE(8, 8)
+  LBM_TILE_SHAPES(LBM_BATCH_CASE)
 #undef LBM_BATCH_CASE
-  return set_err(LBM_EINVAL, "unsupported tile shape P=%d waves=%d", P, wg);
+  return set_err(LBM_EINVAL, "unsupported tile shape P=%d waves=%d mirror=%d",
+                 t.P, t.W, t.M);
 }
 
 int launch_batch_equilibrium(const Consts* cs, const int64_t* offs,

@@ -988,8 +988,7 @@ int fwd_steps(lbm_batch* b, const Consts* cs, const int64_t* offs,
   const int H = 2 * t.steps_per_launch;
   for (int k : split_steps(steps, t.steps_per_launch)) {
     int rc = launch_batch_tile(cs, offs, tiles, ntiles, a, w, b->n_total,
-                               t.nodes_per_lane, H, k, t.waves_per_group,
-                               b->eq_class(), s);
+                               shape_of(t), H, k, b->eq_class(), s);
     if (rc) return rc;
     std::swap(a, w);
     ++launches;
@@ -1052,7 +1051,6 @@ int enqueue_adjoint(lbm_batch* b, void* ws, int64_t nsteps, int64_t C,
   double* cur = fbar;
   double* oth = at<double>(ws, L.pp);
   const lbm_tuning rt = rec_tuning(b->tune);
-  const int Prec = rt.nodes_per_lane, Wrec = rt.waves_per_group;
   const int Krec = b->tune.steps_per_launch;
   // stride of the stored segment states
   const int E = plan.plain ? 1 : plan.rev.E;
@@ -1077,7 +1075,7 @@ int enqueue_adjoint(lbm_batch* b, void* ws, int64_t nsteps, int64_t C,
       const int kk = (int)std::min<int64_t>(Kst, len - 1 - i0);
       const int r = launch_batch_tile(cs, offs, at<TileRef>(ws, L.rec_tiles),
                                       L.n_rec, state(k, i0), segbuf(k),
-                                      b->n_total, Prec, 2 * Krec, kk, Wrec,
+                                      b->n_total, shape_of(rt), 2 * Krec, kk,
                                       b->eq_class(), st, (int64_t)SD, (int)i0,
                                       E);
       if (r) return r;

@@ -81,6 +81,65 @@ lbm_tuning default_tuning(int64_t len, int64_t total, int eq) {
   return shapes[count - 1];
 }
 
+// The plan of nsteps steps of one lattice of n nodes when no tuning was set:
+// the shape and launch length with the least modelled time.  A step of a
+// tile takes base + node P m microseconds on a compute unit that holds m
+// wavefronts per SIMD (issue-bound in m, with the chain of one node's
+// arithmetic as the base), a launch adds `fixed` (dispatch, latency of load
+// and store) and its bytes at 11 TB/s (partly behind other tiles' arithmetic),
+// and the tiles run in rounds of as many workgroups as the 256 compute units
+// hold (`per_cu` each: registers).  So the best tiles just fill one or a few
+// rounds, with their K as large as that leaves room for (1e5 nodes: 251 tiles
+// of (1, 12) at K = 48 take 0.66 us per step, the narrow (2, 1) tiles of the
+// default tuning at K = 16 1.09; 4e5 nodes 1.50 against 2.73, 1e6 nodes 3.55
+// against 3.88, 8192 nodes 0.35 against 0.51).  The constants are fits to
+// sweeps of every shape over K at twelve sizes from 160 to 2^24 nodes, where
+// the modelled choice is within 1 % of the fastest measured one.  From some
+// millions of nodes on the widest tile wins by its small halo.
+StepPlan plan_steps(int64_t n, int64_t nsteps) {
+  struct Cost {
+    TileShape t;
+    int per_cu;
+    double base, node, fixed;
+  };
+  static const Cost costs[] = {
+      {{1, 4, 8}, 8, 0.098, 0.155, 3.2},  {{1, 8, 8}, 4, 0.098, 0.155, 3.2},
+      {{1, 12, 8}, 2, 0.098, 0.155, 3.2}, {{2, 8, 4}, 4, 0.115, 0.153, 3.6},
+      {{2, 12, 4}, 2, 0.115, 0.153, 3.6}, {{4, 4, 2}, 4, 0.21, 0.150, 4.4},
+      {{4, 8, 2}, 2, 0.21, 0.150, 4.4},   {{4, 12, 2}, 1, 0.21, 0.150, 4.4},
+      {{8, 4, 1}, 3, 0.375, 0.147, 6.2}};
+  StepPlan best{{8, 4, 1}, 40};
+  double least = INFINITY;
+  for (const Cost& c : costs) {
+    const int64_t nodes = tile_nodes(c.t.P, c.t.W, c.t.M);
+    const double per_wg = c.node * c.t.P * c.t.W / 4.0;
+    auto step = [&](int64_t g) { return g ? c.base + per_wg * (double)g : 0.0; };
+    const int64_t top = std::min<int64_t>(128, nodes * 9 / 40);
+    auto consider = [&](int64_t K) {
+      if (K < 1) return;
+      const StepSplit sp = split_steps(nsteps, (int)std::min(K, top));
+      const int64_t k = sp.base + (sp.extra ? 1 : 0);
+      const int64_t out = nodes - 4 * k;
+      const int64_t tiles = (n + out - 1) / out, g = (tiles + 255) / 256;
+      const double us =
+          (double)sp.count *
+          (c.fixed + 48.0 * ((double)tiles * (double)nodes + (double)n) / 11e6 +
+           (double)k * ((double)(g / c.per_cu) * step(c.per_cu) +
+                        step(g % c.per_cu)));
+      if (us < least) {
+        least = us;
+        best = StepPlan{c.t, (int)k};
+      }
+    };
+    // the longest launches whose tiles fit g per compute unit, and some
+    // lengths for the many rounds of large lattices
+    for (int64_t g = 1; g <= 4 * c.per_cu; ++g)
+      consider((nodes - (n + 256 * g - 1) / (256 * g)) / 4);
+    for (int64_t K : {16, 24, 32, 40}) consider(K);
+  }
+  return best;
+}
+
 bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
   const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
   return x < y + nb && y < x + na;
@@ -198,10 +257,16 @@ int step_run(lbm_handle* h, double* f, double* ws, int64_t nsteps) {
       ++launches;
     }
   } else {
+    if (h->plan_auto && h->plan_nsteps != nsteps) {
+      h->plan = plan_steps(n, nsteps);
+      h->plan_nsteps = nsteps;
+    }
+    const StepPlan plan = h->plan_auto
+                              ? h->plan
+                              : StepPlan{shape_of(h->tune), h->tune.steps_per_launch};
     // An even number of launches leaves the result in f without a copy.
-    for (int k : split_steps(nsteps, h->tune.steps_per_launch)) {
-      rc = launch_step_tile(h->c, a, b, n, h->tune.nodes_per_lane, k,
-                            h->tune.waves_per_group, h->stream);
+    for (int k : split_steps(nsteps, plan.K)) {
+      rc = launch_step_tile(h->c, a, b, n, plan.t, k, h->stream);
       done += k;
       if (!rc && check) rc = launch_check_state(h->c, b, n, done, rec, h->stream);
       if (rc) break;
@@ -396,6 +461,7 @@ int lbm_set_tuning(lbm_handle* h, const lbm_tuning* t) {
   if (rc) return rc;
   h->tune = *t;
   h->tune_default = false;
+  h->plan_auto = false;
   if (h->tune.kernel == LBM_KERNEL_AUTO) h->tune.kernel = LBM_KERNEL_BLOCKED;
   return LBM_OK;
 }

@@ -113,8 +113,7 @@ int enqueue_tiles(lbm_batch* b, const Layout& L, void* ws, double* f,
   int64_t done = 0, launches = 0;
   for (int k : split_steps(nsteps, t.steps_per_launch)) {
     int rc = launch_batch_tile(cs, offs, tiles, ntiles, a, w, b->n_total,
-                               t.nodes_per_lane, H, k, t.waves_per_group,
-                               b->eq_class(), s);
+                               shape_of(t), H, k, b->eq_class(), s);
     done += k;
     if (!rc && check)
       rc = launch_batch_check(cs, offs, tiles, ntiles, w, b->n_total, out,
@@ -456,7 +455,7 @@ int apply_groups(lbm_batch* b, const std::vector<lbm_tuning>& gshape,
 
 // Generation of the tile kernels, the last component of every tuning-cache
 // key: entries measured on kernels of another generation are not reused.
-constexpr const char* kKernelGeneration = "/k6";
+constexpr const char* kKernelGeneration = "/k7";
 
 // Times `run(t)` for each candidate on the state f, restoring f from
 // `backup` before each run and at the end; returns the fastest, and every
@@ -537,33 +536,39 @@ int lbm_autotune(lbm_handle* h, double* f, void* ws, size_t ws_bytes,
       gpu_arch_name() + "/single/n" + std::to_string(log2_class((double)h->n)) +
       (h->p.eq_kind == 0 ? "/eq8" : "/eqsel") + kKernelGeneration;
   lbm_tuning best{};
+  const lbm_tuning d = default_tuning(h->n, h->n, h->p.eq_kind == 0 ? 0 : -1);
   if (!tune_cache_get(cache_path, key, &best)) {
     std::vector<lbm_tuning> cands = tuning_candidates();
     cands.push_back(lbm_tuning{LBM_KERNEL_PLAIN, 0, 1, 1});
-    // the default shape (one wavefront, or one node per lane, on small
-    // lattices) is not among the throughput candidates
-    const lbm_tuning d = default_tuning(h->n, h->n, h->p.eq_kind == 0 ? 0 : -1);
+    // the default tuning stands for the library's own plan (plan_steps) here
     if (std::none_of(cands.begin(), cands.end(),
                      [&](const lbm_tuning& c) { return same_tuning(c, d); }))
       cands.push_back(d);
     double* backup = static_cast<double*>(ws) + 6 * h->n + diag_ws_doubles();
     const size_t step_ws = lbm_workspace_bytes(h, LBM_WS_STEP);
     const lbm_tuning prev = h->tune;
+    const bool prev_auto = h->plan_auto;
     int rc = autotune_impl(
         h->stream, f, backup, sbytes, probe_steps, cands,
-        [&](const lbm_tuning& t) { h->tune = t; return LBM_OK; },
+        [&](const lbm_tuning& t) {
+          h->tune = t;
+          h->plan_auto = same_tuning(t, d);
+          return LBM_OK;
+        },
         [&](const lbm_tuning&, int64_t k) {
           return lbm_step(h, f, ws, step_ws, k);
         },
         &best);
     if (rc) {
       h->tune = prev;  // a failed search leaves the tuning as it was
+      h->plan_auto = prev_auto;
       return rc;
     }
     tune_cache_put(cache_path, key, best);
   }
   h->tune = best;
   h->tune_default = false;
+  h->plan_auto = same_tuning(best, d);
   if (out) *out = best;
   return LBM_OK;
 }

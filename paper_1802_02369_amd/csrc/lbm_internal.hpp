@@ -17,7 +17,18 @@ int set_err(int code, const char* fmt, ...);
 int hip_check(hipError_t e, const char* what);
 int make_consts(const lbm_params* p, Consts* c);
 
-int64_t tile_out(int P, int K, int wg);
+// A register tile's shape: P nodes per lane, W wavefronts, M mirror lanes on
+// each side of a wavefront (see tile_run).
+struct TileShape {
+  int P, W, M;
+};
+
+// Nodes spanned by a register tile of wg wavefronts of P nodes per lane:
+// neighbouring wavefronts share 2M lanes.
+__host__ __device__ constexpr int tile_nodes(int P, int wg, int M = 1) {
+  return P * ((64 - 2 * M) * wg + 2 * M);
+}
+
 size_t diag_ws_doubles();
 
 // Failure detection (LBM_CHECK_FINITE).  The record is one 64-bit word in
@@ -70,7 +81,7 @@ int launch_equilibrium(const Consts& c, const double* rho, const double* J,
 int launch_step_plain(const Consts& c, const double* fin, double* fout,
                       int64_t n, hipStream_t s);
 int launch_step_tile(const Consts& c, const double* fin, double* fout,
-                     int64_t n, int P, int K, int wpg, hipStream_t s);
+                     int64_t n, const TileShape& t, int K, hipStream_t s);
 int launch_diagnostics(const Consts& c, const double* f, int64_t n,
                        double* scratch, hipStream_t s);
 int launch_moments(const Consts& c, const double* f, double* m, int64_t n,
@@ -83,7 +94,7 @@ int launch_moments(const Consts& c, const double* f, double* m, int64_t n,
 // (eq_kind 0), else -1.
 int launch_batch_tile(const Consts* cs, const int64_t* offs,
                       const TileRef* tiles, int64_t ntiles, const double* fin,
-                      double* fout, int64_t S, int P, int H, int K, int wg,
+                      double* fout, int64_t S, const TileShape& t, int H, int K,
                       int eq, hipStream_t s, int64_t state_stride = 0,
                       int first = 0, int every = 1);
 int launch_batch_equilibrium(const Consts* cs, const int64_t* offs,
@@ -127,6 +138,14 @@ StepSplit split_steps(int64_t nsteps, int K);
 // equilibrium class eq (0: every lattice has eq_kind 0, else -1).
 lbm_tuning default_tuning(int64_t len, int64_t total, int eq);
 
+// Shape and steps per launch of the next steps of a single lattice on the
+// library's own plan (see plan_steps).
+struct StepPlan {
+  TileShape t;
+  int K;
+};
+StepPlan plan_steps(int64_t n, int64_t nsteps);
+
 // Tile shapes the autotuner tries (P, K, waves per tile).
 std::vector<lbm_tuning> tuning_candidates();
 
@@ -167,10 +186,9 @@ inline bool same_tunings(const std::vector<lbm_tuning>& a,
   return true;
 }
 
-// Nodes spanned by a register tile of wg wavefronts of P nodes per lane:
-// neighbouring wavefronts share two lanes (one mirror lane each).
-__host__ __device__ constexpr int tile_nodes(int P, int wg) {
-  return P * (62 * wg + 2);
+// The tile shape of a tuning record.
+inline TileShape shape_of(const lbm_tuning& t) {
+  return TileShape{t.nodes_per_lane, t.waves_per_group, 1};
 }
 
 inline int64_t tile_width(const lbm_tuning& t) {
@@ -203,6 +221,12 @@ struct lbm_handle {
   hipStream_t stream;
   lbm_tuning tune;
   bool tune_default = true;  // tune is the default for n and the equilibria
+  // steps run on the library's own plan (plan_steps): until lbm_set_tuning,
+  // or when lbm_autotune measured nothing faster; the last plan and the step
+  // count it was made for
+  bool plan_auto = true;
+  lbm::StepPlan plan{};
+  int64_t plan_nsteps = -1;
   int32_t adj_kernel = LBM_KERNEL_AUTO;  // reverse-sweep kernel
   int32_t rec_stride = 0;  // stride of the stored segment states (0: auto)
   lbm_batch* one = nullptr;  // batch of this one lattice, for the adjoint
