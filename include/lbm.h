@@ -186,7 +186,12 @@ LBM_API size_t lbm_workspace_bytes(const lbm_handle* h, int kind);
  * that select the equilibria per lattice and need more registers at P = 8)
  * P = 4, K = 24, 4 wavefronts; narrower tiles for short lattices or few
  * tiles, down to P = 1, K = 13 for problems of at most 16384 nodes in all
- * (bound by the latency of each step rather than by throughput).
+ * (bound by the latency of each step rather than by throughput).  Until
+ * lbm_set_tuning (or when lbm_autotune finds nothing faster than the default)
+ * lbm_step does not keep to the default's shape: it picks tile shape and
+ * launch length, or one resident workgroup for a short lattice, by a cost
+ * model of n and nsteps, from the shapes above and wider ones with several
+ * mirror lanes (with LBM_CHECK_FINITE it keeps to the default's launches).
  * lbm_set_params re-derives the default unless lbm_set_tuning or
  * lbm_autotune chose the shape.  Every
  * kernel and tile shape rounds each node-update identically: results are
@@ -350,7 +355,11 @@ LBM_API int lbm_batch_init(lbm_batch** b, int64_t n_inst, const int64_t* offsets
 LBM_API void lbm_batch_destroy(lbm_batch* b);
 LBM_API int lbm_batch_set_stream(lbm_batch* b, void* stream);
 /* Tile shape of the batch (as lbm_set_tuning; the blocked kernel only).
- * Clears any shape groups. */
+ * Clears any shape groups.  Until it is called (or lbm_batch_set_groups, or
+ * when lbm_batch_autotune finds nothing faster than the default),
+ * lbm_batch_run picks by a cost model of the lattices' lengths which lattices
+ * run resident, at how many nodes per lane, and the tile shape of the others
+ * (not with LBM_CHECK_FINITE on some lattice). */
 LBM_API int lbm_batch_set_tuning(lbm_batch* b, const lbm_tuning* t);
 LBM_API int lbm_batch_get_tuning(const lbm_batch* b, lbm_tuning* t);
 
@@ -374,11 +383,14 @@ LBM_API int lbm_batch_set_groups(lbm_batch* b, int32_t n_groups,
  * group_of (capacity n_inst) receive the assignment unless NULL. */
 LBM_API int lbm_batch_get_groups(const lbm_batch* b, int32_t* n_groups,
                                  lbm_tuning* shapes, int32_t* group_of);
-/* Resident lattices of lbm_batch_run.  With mode 1 (the default) every
- * lattice of LBM_RESIDENT_MIN..LBM_RESIDENT_MAX nodes runs all nsteps steps
+/* Resident lattices of lbm_batch_run.  With mode 1 (the default) a lattice
+ * of LBM_RESIDENT_MIN..LBM_RESIDENT_MAX nodes may run all nsteps steps (with a
+ * set tuning or shape groups every such lattice does, else those for which
+ * the cost model finds it faster)
  * inside one launch (up to 65536 steps per launch): its state is loaded once
  * into registers (8 nodes per lane, one wavefront per 496 nodes, lattices
- * packed into workgroups of 12 wavefronts), advanced step after step with
+ * packed into workgroups of 12 wavefronts; on the library's own choice also
+ * 1, 2 or 4 nodes per lane), advanced step after step with
  * the periodic wrap and the neighbouring wavefronts' edge nodes exchanged
  * through LDS every 4 steps, and stored once (96 bytes of HBM per node for
  * the whole run).  That launch
@@ -393,7 +405,7 @@ LBM_API int lbm_batch_get_groups(const lbm_batch* b, int32_t* n_groups,
  * always use tiles.  LBM_EINVAL for another mode. */
 enum { LBM_RESIDENT_MIN = 16, LBM_RESIDENT_MAX = 5952 };
 LBM_API int lbm_batch_set_resident(lbm_batch* b, int mode);
-/* Number of lattices that run resident with the current mode. */
+/* Number of lattices that may run resident with the current mode. */
 LBM_API int64_t lbm_batch_resident_lattices(const lbm_batch* b);
 /* Total nodes n_total of the batch (0 on a bad handle). */
 LBM_API int64_t lbm_batch_total_nodes(const lbm_batch* b);

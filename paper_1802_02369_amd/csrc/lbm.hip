@@ -609,6 +609,132 @@ __global__ __launch_bounds__(64 * kResWaves, 3) void k_batch_resident(
                 lds, f);
 }
 
+// The same for 1, 2 or 4 nodes per lane (short lattices, or a chip that has
+// room: a step of P nodes per lane takes about 0.1 + 0.15 P us on a SIMD of its
+// own), with M = 8/P mirror lanes on each side of a wavefront, so that at every
+// P the copies hold 8 nodes and are refreshed every four steps.  Lane l of
+// wavefront lw holds positions WS lw + P (l - M) + k, WS = (64 - 2M) P; lanes
+// M .. 63-M own the positions below L.  Published before a refresh: the 8
+// nodes next to the mirror lanes at both ends of every wavefront, and the
+// lattice's last 8 nodes; what a position that is not owned takes from them
+// (its mirror, or its periodic image) is worked out once.  Positions from
+// L + 8 on are never refreshed: what they hold reaches 8 nodes in, to L.
+// `copies`: two buffers of 3 x 48 doubles per wavefront of the workgroup
+// (left edge, right edge, tail of a lattice by its first wavefront).
+constexpr int kCopyDoubles = 3 * 48;
+
+template <int P, int EQ>
+__device__ __forceinline__ void resident_run(
+    const Consts& c, const double* fin, double* fout, int64_t S, int L,
+    int lane, int wave, int lw, int nw, int W, int64_t T, double* stage,
+    double* copies) {
+  constexpr int M = 8 / P;
+  constexpr int WW = 64 * P;
+  constexpr int WS = (64 - 2 * M) * P;
+  const int w0 = wave - lw;
+  const int p0 = WS * lw + P * (lane - M);
+  // offsets into a buffer: left and right edge of wavefront w, tail
+  auto edge = [](int w, int side) { return (2 * w + side) * 48; };
+  const int tail = (2 * W + w0) * 48;
+  const bool hi = lane >= 32;
+  const int pl = hi ? lane - (64 - 2 * M) : lane - M;
+  const int pub = pl >= 0 && pl < M ? edge(wave, hi) + pl * P : -1;
+  const bool mid = lane >= M && lane < 64 - M;
+  int put[P], src[P];
+#pragma unroll
+  for (int k = 0; k < P; ++k) {
+    const int p = p0 + k;
+    put[k] = mid && p < L && p >= L - 8 ? tail + p - (L - 8) : -1;
+    if (mid && p < L)
+      src[k] = -1;  // owned
+    else if (p < 0)
+      src[k] = tail + p + 8;
+    else if (p >= L)
+      src[k] = p - L < 8 ? edge(w0, 0) + p - L : -1;
+    else if (lane < M)
+      src[k] = edge(wave - 1, 1) + lane * P + k;
+    else
+      src[k] = edge(wave + 1, 0) + (lane - (64 - M)) * P + k;
+  }
+  double f[6][P];
+  tile_load<P>(fin, S, L, WS * lw - 8, false, true, lane, stage, f);
+  // every wavefront has loaded before any stores (fout may be fin)
+  __syncthreads();
+  int since = 0;
+  double* buf = copies;
+  for (int64_t step = 0; step < T; ++step) {
+    tile_step<P, EQ>(c, f);
+    if (++since == 4 && step + 1 < T) {
+      if (pub >= 0) {
+#pragma unroll
+        for (int q = 0; q < 6; ++q)
+#pragma unroll
+          for (int k = 0; k < P; ++k) buf[pub + q * 8 + k] = f[q][k];
+      }
+#pragma unroll
+      for (int k = 0; k < P; ++k)
+        if (put[k] >= 0) {
+#pragma unroll
+          for (int q = 0; q < 6; ++q) buf[put[k] + q * 8] = f[q][k];
+        }
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < P; ++k)
+        if (src[k] >= 0) {
+#pragma unroll
+          for (int q = 0; q < 6; ++q) f[q][k] = buf[src[k] + q * 8];
+        }
+      buf = buf == copies ? copies + W * kCopyDoubles : copies;
+      since = 0;
+    }
+  }
+  tile_store<P>(fout, S, L, WS * lw - 8, 8, WW - 8, lane, stage, f);
+}
+
+// Dynamic LDS of a workgroup of W wavefronts: the copies and, for more than
+// one node per lane, the load and store staging.
+constexpr size_t resident_lds(int P, int W) {
+  return sizeof(double) * W * (2 * kCopyDoubles + (P == 1 ? 0 : 64 * P + 64));
+}
+
+// Lattices of a batch (items), W wavefronts per workgroup.
+template <int P, int EQ>
+__global__ __launch_bounds__(1024) void k_batch_resident_small(
+    const Consts* __restrict__ cs, const int64_t* __restrict__ offs,
+    const lbm::ResidentItem* __restrict__ items,
+    const int32_t* __restrict__ wg_first, const double* fin, double* fout,
+    int64_t S, int64_t T) {
+  extern __shared__ double sm[];
+  const int W = blockDim.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int item = -1;  // this wavefront's lattice (uniform over the wavefront)
+  for (int i = wg_first[blockIdx.x]; i < wg_first[blockIdx.x + 1]; ++i) {
+    const int w0 = items[i].wave0;
+    if (wave >= w0 && wave < w0 + items[i].nw) item = i;
+  }
+  if (item < 0) return;
+  const lbm::ResidentItem it = items[item];
+  const int64_t off = offs[it.inst];
+  const Consts c = cs[it.inst];
+  resident_run<P, EQ>(c, fin + off, fout + off, S,
+                      (int)(offs[it.inst + 1] - off), lane, wave,
+                      wave - it.wave0, it.nw, W, T,
+                      sm + W * 2 * kCopyDoubles + wave * (64 * P + 64), sm);
+}
+
+// One lattice of n nodes in one workgroup.
+template <int P, int EQ>
+__global__ __launch_bounds__(1024) void k_step_resident(Consts c, double* f,
+                                                        int n, int64_t T) {
+  extern __shared__ double sm[];
+  const int W = blockDim.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  resident_run<P, EQ>(c, f, f, n, n, lane, wave, wave, W, W, T,
+                      sm + W * 2 * kCopyDoubles + wave * (64 * P + 64), sm);
+}
+
 // One workgroup per lattice of a batch: moments m = M f (eq. M-d1q3q3).
 __global__ __launch_bounds__(256) void k_batch_moments(
     const Consts* __restrict__ cs, const int64_t* __restrict__ offs,
@@ -961,14 +1087,53 @@ int launch_batch_copy_tiles(const int64_t* offs, const TileRef* tiles,
 int launch_batch_resident(const Consts* cs, const int64_t* offs,
                           const ResidentItem* items, const int32_t* wg_first,
                           int64_t nwg, const double* fin, double* fout,
-                          int64_t S, int64_t T, int eq, hipStream_t s) {
+                          int64_t S, int64_t T, int P, int W, int eq,
+                          hipStream_t s) {
   if (nwg <= 0 || T <= 0) return LBM_OK;
   if (eq != 0)
     return set_err(LBM_EINVAL, "resident lattices need the section-8 equilibria");
-  hipLaunchKernelGGL((k_batch_resident<kResP, 0>), dim3((unsigned)nwg),
-                     dim3(64 * kResWaves), 0, s, cs, offs, items, wg_first, fin,
-                     fout, S, T);
+  if (W < 1 || W > resident_max_waves(P) || (P == kResP && W != kResWaves))
+    return set_err(LBM_EINVAL, "bad resident workgroup of %d wavefronts", W);
+  const dim3 grid((unsigned)nwg), block(64 * W);
+  if (P == 1)
+    hipLaunchKernelGGL((k_batch_resident_small<1, 0>), grid, block,
+                       resident_lds(1, W), s, cs, offs, items, wg_first, fin,
+                       fout, S, T);
+  else if (P == 2)
+    hipLaunchKernelGGL((k_batch_resident_small<2, 0>), grid, block,
+                       resident_lds(2, W), s, cs, offs, items, wg_first, fin,
+                       fout, S, T);
+  else if (P == 4)
+    hipLaunchKernelGGL((k_batch_resident_small<4, 0>), grid, block,
+                       resident_lds(4, W), s, cs, offs, items, wg_first, fin,
+                       fout, S, T);
+  else if (P == kResP)
+    hipLaunchKernelGGL((k_batch_resident<kResP, 0>), grid, block, 0, s, cs, offs,
+                       items, wg_first, fin, fout, S, T);
+  else
+    return set_err(LBM_EINVAL, "unsupported resident shape P=%d", P);
   return hip_check(hipGetLastError(), "k_batch_resident");
+}
+
+int launch_step_resident(const Consts& c, double* f, int64_t n, int64_t T,
+                         int P, hipStream_t s) {
+  const int64_t W = cdiv(n, resident_span(P));
+  if ((P != 1 && P != 2 && P != 4) || n < kResidentMin || W > resident_max_waves(P))
+    return set_err(LBM_EINVAL, "bad resident lattice of %lld nodes at P=%d",
+                   (long long)n, P);
+  const dim3 grid(1), block((unsigned)(64 * W));
+#define LBM_RES_CASE(PP)                                                      \
+  if (P == PP && c.eq_kind == 0)                                              \
+    hipLaunchKernelGGL((k_step_resident<PP, 0>), grid, block,                 \
+                       resident_lds(PP, (int)W), s, c, f, (int)n, T);              \
+  else if (P == PP)                                                           \
+    hipLaunchKernelGGL((k_step_resident<PP, -1>), grid, block,                \
+                       resident_lds(PP, (int)W), s, c, f, (int)n, T);
+  LBM_RES_CASE(1)
+  LBM_RES_CASE(2)
+  LBM_RES_CASE(4)
+#undef LBM_RES_CASE
+  return hip_check(hipGetLastError(), "k_step_resident");
 }
 
 int launch_batch_check_lattices(const Consts* cs, const int64_t* offs,
@@ -1052,6 +1217,22 @@ int launch_batch_tile(const Consts* cs, const int64_t* offs,
     return hip_check(hipGetLastError(), "k_batch_tile");                      \
   }
   LBM_TILE_SHAPES(LBM_BATCH_CASE)
+#undef LBM_BATCH_CASE
+  // the wide shapes of plan_batch, which stores no checkpoint segments
+#define LBM_BATCH_CASE(PP, WW, MM)                                            \
+  if (t.P == PP && t.W == WW && t.M == MM && state_stride == 0) {             \
+    const dim3 grid((unsigned)ntiles), block(64 * WW);                        \
+    if (eq == 0)                                                              \
+      hipLaunchKernelGGL((k_batch_tile<PP, WW, MM, 0, false>), grid, block,   \
+                         0, s, cs, offs, tiles, fin, fout, S, H, K, ntiles,   \
+                         state_stride, first, every);                         \
+    else                                                                      \
+      hipLaunchKernelGGL((k_batch_tile<PP, WW, MM, -1, false>), grid, block,  \
+                         0, s, cs, offs, tiles, fin, fout, S, H, K, ntiles,   \
+                         state_stride, first, every);                         \
+    return hip_check(hipGetLastError(), "k_batch_tile");                      \
+  }
+  LBM_WIDE_SHAPES(LBM_BATCH_CASE)
 #undef LBM_BATCH_CASE
   return set_err(LBM_EINVAL, "unsupported tile shape P=%d waves=%d mirror=%d",
                  t.P, t.W, t.M);

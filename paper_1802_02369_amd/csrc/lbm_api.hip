@@ -96,24 +96,48 @@ lbm_tuning default_tuning(int64_t len, int64_t total, int eq) {
 // sweeps of every shape over K at twelve sizes from 160 to 2^24 nodes, where
 // the modelled choice is within 1 % of the fastest measured one.  From some
 // millions of nodes on the widest tile wins by its small halo.
+namespace {
+
+struct TileCost {
+  TileShape t;
+  int per_cu;
+  double base, node, fixed;
+  // microseconds of a step of g workgroups on each compute unit
+  double step(double g) const {
+    return g > 0 ? base + node * t.P * t.W / 4.0 * g : 0.0;
+  }
+};
+
+const TileCost kTileCosts[] = {
+    {{1, 4, 8}, 8, 0.098, 0.155, 3.2},  {{1, 8, 8}, 4, 0.098, 0.155, 3.2},
+    {{1, 12, 8}, 2, 0.098, 0.155, 3.2}, {{2, 8, 4}, 4, 0.115, 0.153, 3.6},
+    {{2, 12, 4}, 2, 0.115, 0.153, 3.6}, {{4, 4, 2}, 4, 0.21, 0.150, 4.4},
+    {{4, 8, 2}, 2, 0.21, 0.150, 4.4},   {{4, 12, 2}, 1, 0.21, 0.150, 4.4},
+    {{8, 4, 1}, 3, 0.375, 0.147, 6.2}};
+
+}  // namespace
+
 StepPlan plan_steps(int64_t n, int64_t nsteps) {
-  struct Cost {
-    TileShape t;
-    int per_cu;
-    double base, node, fixed;
-  };
-  static const Cost costs[] = {
-      {{1, 4, 8}, 8, 0.098, 0.155, 3.2},  {{1, 8, 8}, 4, 0.098, 0.155, 3.2},
-      {{1, 12, 8}, 2, 0.098, 0.155, 3.2}, {{2, 8, 4}, 4, 0.115, 0.153, 3.6},
-      {{2, 12, 4}, 2, 0.115, 0.153, 3.6}, {{4, 4, 2}, 4, 0.21, 0.150, 4.4},
-      {{4, 8, 2}, 2, 0.21, 0.150, 4.4},   {{4, 12, 2}, 1, 0.21, 0.150, 4.4},
-      {{8, 4, 1}, 3, 0.375, 0.147, 6.2}};
-  StepPlan best{{8, 4, 1}, 40};
+  StepPlan best{{8, 4, 1}, 40, 0};
   double least = INFINITY;
-  for (const Cost& c : costs) {
+  // one step ends in the second state and is copied back
+  const double copy = nsteps == 1 ? 3.0 + 96.0 * (double)n / 5e6 : 0.0;
+  // A lattice that fits one workgroup needs neither halo nor launches
+  // (n = 160, one node per lane, 4 wavefronts: 0.25 us per step, 0.33 on
+  // tiles), but has one compute unit: from 5 wavefronts on, two on a SIMD,
+  // tiles over several units are faster again except for a few steps.
+  for (int P : {1, 2, 4}) {
+    const int64_t nw = resident_waves(n, P);
+    if (n < kResidentMin || nw > resident_max_waves(P)) continue;
+    const double us =
+        3.2 + (double)nsteps * (0.1 + 0.153 * P * (double)((nw + 3) / 4));
+    if (us < least) {
+      least = us;
+      best.resident = P;
+    }
+  }
+  for (const TileCost& c : kTileCosts) {
     const int64_t nodes = tile_nodes(c.t.P, c.t.W, c.t.M);
-    const double per_wg = c.node * c.t.P * c.t.W / 4.0;
-    auto step = [&](int64_t g) { return g ? c.base + per_wg * (double)g : 0.0; };
     const int64_t top = std::min<int64_t>(128, nodes * 9 / 40);
     auto consider = [&](int64_t K) {
       if (K < 1) return;
@@ -124,11 +148,12 @@ StepPlan plan_steps(int64_t n, int64_t nsteps) {
       const double us =
           (double)sp.count *
           (c.fixed + 48.0 * ((double)tiles * (double)nodes + (double)n) / 11e6 +
-           (double)k * ((double)(g / c.per_cu) * step(c.per_cu) +
-                        step(g % c.per_cu)));
+           (double)k * ((double)(g / c.per_cu) * c.step(c.per_cu) +
+                        c.step((double)(g % c.per_cu)))) +
+          copy;
       if (us < least) {
         least = us;
-        best = StepPlan{c.t, (int)k};
+        best = StepPlan{c.t, (int)k, 0};
       }
     };
     // the longest launches whose tiles fit g per compute unit, and some
@@ -136,6 +161,119 @@ StepPlan plan_steps(int64_t n, int64_t nsteps) {
     for (int64_t g = 1; g <= 4 * c.per_cu; ++g)
       consider((nodes - (n + 256 * g - 1) / (256 * g)) / 4);
     for (int64_t K : {16, 24, 32, 40}) consider(K);
+  }
+  return best;
+}
+
+// The plan of a batch, by the model of plan_steps over the lattices' lengths
+// (in bins).  Resident lattices at P nodes per lane take 0.06 + node P m per
+// step, m their wavefronts per SIMD of the longest lattice or, a third more
+// for uneven compute units, on average: no halo and no launches, but each is
+// bound to one compute unit, while tiles spread a lattice over several.  Where
+// both run they share the chip's SIMDs and the times add up (1.39: the
+// launches of the two streams do not overlap perfectly).  Large batches keep
+// four or eight nodes per lane, batches that leave the chip room take one or
+// two, or tiles alone: 64 lattices of 128 .. 2048 nodes ran 5.0 us per step
+// packed by twelve wavefronts of eight nodes per lane (a tenth of the chip),
+// 0.6 on (1, 8) tiles; 965 lattices of 247 .. 1108 nodes 5.2, 2.7 resident at
+// two nodes per lane; 4096 of 512 .. 16384 60 either way.  The constants
+// minimise the regret over sweeps of every choice on sixteen batches of 2e4 to
+// 2e7 nodes: 3 % on average, at most 8 %.
+BatchPlan plan_batch(const std::vector<int64_t>& offsets, bool resident) {
+  struct Bin {
+    int64_t len, count;
+  };
+  std::vector<Bin> bins;
+  {
+    std::vector<int64_t> lens;
+    for (size_t i = 0; i + 1 < offsets.size(); ++i)
+      lens.push_back((offsets[i + 1] - offsets[i] + 31) / 32 * 32);
+    std::sort(lens.begin(), lens.end());
+    for (int64_t l : lens) {
+      if (bins.empty() || bins.back().len != l) bins.push_back(Bin{l, 0});
+      ++bins.back().count;
+    }
+    // at most 64 bins: neighbours merge
+    while (bins.size() > 64) {
+      std::vector<Bin> half;
+      for (size_t i = 0; i < bins.size(); i += 2) {
+        Bin x = bins[i];
+        if (i + 1 < bins.size()) x = Bin{bins[i + 1].len, x.count + bins[i + 1].count};
+        half.push_back(x);
+      }
+      bins.swap(half);
+    }
+  }
+  // tiles of one candidate over the lattices longer than `above` nodes
+  auto tiles_us = [&](const TileCost& c, int K, int64_t above) {
+    const int64_t nodes = tile_nodes(c.t.P, c.t.W, c.t.M), out = nodes - 4 * K;
+    double tiles = 0, waves = 0, total = 0;
+    for (const Bin& b : bins) {
+      if (b.len <= above) continue;
+      const int64_t nt = (b.len + out - 1) / out;
+      const int64_t last = b.len - (nt - 1) * out + 4 * K - 2 * c.t.M * c.t.P;
+      const int64_t own = (64 - 2 * c.t.M) * c.t.P;
+      const int64_t nw = std::min<int64_t>(
+          c.t.W, std::max<int64_t>(1, (last + own - 1) / own));
+      tiles += (double)(nt * b.count);
+      waves += (double)(((nt - 1) * c.t.W + nw) * b.count);
+      total += (double)(b.len * b.count);
+    }
+    if (tiles == 0) return 0.0;
+    const double g = std::ceil(tiles / 256.0);
+    const double full = std::floor(g / c.per_cu), rest = g - full * c.per_cu;
+    // workgroups that need fewer wavefronts than W leave their SIMDs free
+    const double used =
+        std::min(1.0, std::max(1.3 * waves / (tiles * c.t.W), 1.0 / g));
+    const double step = full * (c.base + used * (c.step(c.per_cu) - c.base)) +
+                        (rest > 0 ? c.base + used * (c.step(rest) - c.base) : 0.0);
+    return step +
+           (0.75 * c.fixed + 48.0 * (tiles * (double)nodes + total) / 11e6) / (double)K;
+  };
+  BatchPlan best;
+  double least = INFINITY;
+  auto consider = [&](int P, int waves, int64_t above, double res_us,
+                      const TileCost& c, int K) {
+    double us = tiles_us(c, K, above);
+    us = us == 0 ? res_us : P == 0 ? us : us + 1.39 * (res_us - 0.1);
+    if (us < least) {
+      least = us;
+      best.P = P;
+      best.waves = waves;
+      best.t = c.t;
+      best.K = K;
+    }
+  };
+  for (int P : {0, 1, 2, 4, 8}) {
+    if (P > 0 && !resident) continue;
+    for (int waves : {4, 8, 12, 16}) {
+      if (P == 0 ? waves != 4 : waves > resident_max_waves(P)) continue;
+      double n_waves = 0, longest = 0;
+      const int64_t above = P == 0 ? 0 : waves * resident_span(P);
+      for (const Bin& b : bins) {
+        if (b.len > above || b.len < kResidentMin) continue;
+        const double nw = (double)resident_waves(b.len, P);
+        n_waves += nw * (double)b.count;
+        longest = std::max(longest, nw);
+      }
+      if (P > 0 && n_waves == 0) continue;
+      // wavefronts per SIMD: of the longest lattice, or on average; the
+      // workgroups of eight nodes per lane are filled before new ones open
+      double m = std::max(std::ceil(longest / 4.0), n_waves / 1024.0 * 1.33);
+      if (P == 8) m = std::max(m, std::min(3.0, n_waves / 4.0));
+      const double res_us =
+          P == 0 ? 0.0 : (P == 8 ? 0.375 + 0.184 * P * m : 0.06 + 0.163 * P * m);
+      for (const TileCost& c : kTileCosts) {
+        // beside resident lattices, the shapes of four or eight wavefronts
+        // with at least two nodes per lane that proved even-tempered there
+        const bool mixes = (c.t.P == 2 && c.t.W == 8) || (c.t.P == 4 && c.t.W == 4) ||
+                           c.t.P == 8;
+        if (P > 0 && !mixes) continue;
+        for (int K : {12, 16, 20, 28, 40, 60, 90})
+          if (tile_nodes(c.t.P, c.t.W, c.t.M) - 4 * K >= kPlanMinOut)
+            consider(P, waves, above, res_us, c, K);
+      }
+    }
   }
   return best;
 }
@@ -257,13 +395,23 @@ int step_run(lbm_handle* h, double* f, double* ws, int64_t nsteps) {
       ++launches;
     }
   } else {
-    if (h->plan_auto && h->plan_nsteps != nsteps) {
+    // with LBM_CHECK_FINITE the launches are the tuning's, so that the steps a
+    // failure is reported after do not depend on the plan
+    const bool planned = h->plan_auto && !check;
+    if (planned && h->plan_nsteps != nsteps) {
       h->plan = plan_steps(n, nsteps);
       h->plan_nsteps = nsteps;
     }
-    const StepPlan plan = h->plan_auto
-                              ? h->plan
-                              : StepPlan{shape_of(h->tune), h->tune.steps_per_launch};
+    const StepPlan plan =
+        planned ? h->plan
+                : StepPlan{shape_of(h->tune), h->tune.steps_per_launch, 0};
+    if (plan.resident) {
+      for (int64_t t = 0; t < nsteps && !rc; t += kResidentMaxSteps)
+        rc = launch_step_resident(h->c, a, n,
+                                  std::min<int64_t>(kResidentMaxSteps, nsteps - t),
+                                  plan.resident, h->stream);
+      return rc;
+    }
     // An even number of launches leaves the result in f without a copy.
     for (int k : split_steps(nsteps, plan.K)) {
       rc = launch_step_tile(h->c, a, b, n, plan.t, k, h->stream);

@@ -85,7 +85,8 @@ int check_batch_ws(const lbm_batch* b, const void* ws, size_t ws_bytes) {
   if (b->prep_ws != ws || !same_tuning(b->prep_tune, b->tune) ||
       !same_tunings(b->prep_group_tune, b->group_tune) ||
       b->prep_group_of != b->group_of ||
-      b->prep_resident_mode != b->resident_mode)
+      b->prep_resident_mode != b->resident_mode ||
+      b->prep_planned != b->planned())
     return set_err(LBM_EINVAL,
                    "workspace not prepared for this tuning: call "
                    "lbm_batch_prepare");
@@ -95,25 +96,25 @@ int check_batch_ws(const lbm_batch* b, const void* ws, size_t ws_bytes) {
 }
 
 // Launches of nsteps steps of the tiles [first, first + ntiles) of the table
-// with tuning t on stream s (ping-pong between f and the workspace state).
+// with shape t and K steps per launch on stream s (ping-pong between f and the workspace state).
 // An odd number of launches (nsteps = 1, or K = 1 and nsteps odd) leaves
 // the result in the workspace state: a copy of those tiles' nodes brings it
 // into f.
 int enqueue_tiles(lbm_batch* b, const Layout& L, void* ws, double* f,
-                  int64_t nsteps, const lbm_tuning& t, int64_t first,
+                  int64_t nsteps, const TileShape& t, int K, int64_t first,
                   int64_t ntiles, hipStream_t s) {
   const Consts* cs = at<Consts>(ws, L.consts);
   const int64_t* offs = at<int64_t>(ws, L.offs);
   const TileRef* tiles = at<TileRef>(ws, L.tiles) + first;
   double* a = f;
   double* w = at<double>(ws, L.state2);
-  const int H = 2 * t.steps_per_launch;
+  const int H = 2 * K;
   const bool check = b->check_finite();
-  const int out = (int)(tile_width(t) - 2 * H);
+  const int out = tile_nodes(t.P, t.W, t.M) - 2 * H;
   int64_t done = 0, launches = 0;
-  for (int k : split_steps(nsteps, t.steps_per_launch)) {
-    int rc = launch_batch_tile(cs, offs, tiles, ntiles, a, w, b->n_total,
-                               shape_of(t), H, k, b->eq_class(), s);
+  for (int k : split_steps(nsteps, K)) {
+    int rc = launch_batch_tile(cs, offs, tiles, ntiles, a, w, b->n_total, t, H,
+                               k, b->eq_class(), s);
     done += k;
     if (!rc && check)
       rc = launch_batch_check(cs, offs, tiles, ntiles, w, b->n_total, out,
@@ -143,12 +144,17 @@ int enqueue_batch(lbm_batch* b, double* f, void* ws, int64_t nsteps,
   // graph); no tile reads or writes their nodes.
   const int64_t nres = (int64_t)b->prep_res_items.size();
   const int64_t nwg = nres ? (int64_t)b->prep_res_first.size() - 1 : 0;
+  // without tiles the resident launch takes s itself
+  const bool fork = nres && b->prep_tiles > 0;
+  const hipStream_t rs = fork ? b->res_stream : s;
   if (nres) {
-    rc = hip_check(hipEventRecord(b->res_events[0], s), "hipEventRecord");
-    if (!rc)
-      rc = hip_check(hipStreamWaitEvent(b->res_stream, b->res_events[0], 0),
-                     "hipStreamWaitEvent");
-    if (rc) return rc;
+    if (fork) {
+      rc = hip_check(hipEventRecord(b->res_events[0], s), "hipEventRecord");
+      if (!rc)
+        rc = hip_check(hipStreamWaitEvent(rs, b->res_events[0], 0),
+                       "hipStreamWaitEvent");
+      if (rc) return rc;
+    }
     const Consts* cs = at<Consts>(ws, L.consts);
     const int64_t* offs = at<int64_t>(ws, L.offs);
     const ResidentItem* items = at<ResidentItem>(ws, L.res_items);
@@ -157,27 +163,29 @@ int enqueue_batch(lbm_batch* b, double* f, void* ws, int64_t nsteps,
     for (int64_t done = 0; done < nsteps && !rc;) {
       const int64_t T = std::min<int64_t>(kResidentMaxSteps, nsteps - done);
       rc = launch_batch_resident(cs, offs, items, at<int32_t>(ws, L.res_first),
-                                 nwg, f, f, b->n_total, T, b->eq_class(),
-                                 b->res_stream);
+                                 nwg, f, f, b->n_total, T, b->prep_res_P,
+                                 b->prep_res_wg, b->eq_class(), rs);
       done += T;
       if (!rc && b->check_finite())
         rc = launch_batch_check_lattices(cs, offs, items, nres, f, b->n_total,
                                          done, at<unsigned long long>(ws, L.rec),
-                                         b->res_stream);
+                                         rs);
     }
     // join even after a failure, so that a capture ends
-    const int r1 = hip_check(hipEventRecord(b->res_events[1], b->res_stream),
-                             "hipEventRecord");
-    if (!rc) rc = r1;
-    if (rc) {
-      (void)hipStreamWaitEvent(s, b->res_events[1], 0);
-      return rc;
+    if (fork) {
+      const int r1 = hip_check(hipEventRecord(b->res_events[1], rs),
+                               "hipEventRecord");
+      if (!rc) rc = r1;
+      if (rc) (void)hipStreamWaitEvent(s, b->res_events[1], 0);
     }
+    if (rc) return rc;
   }
   if (b->prep_tiles == 0) {
     // every lattice is resident
   } else if (b->prep_group_tune.empty()) {
-    rc = enqueue_tiles(b, L, ws, f, nsteps, b->tune, 0, b->prep_tiles, s);
+    const TileShape t = b->planned() ? b->plan().t : shape_of(b->tune);
+    const int K = b->planned() ? b->plan().K : b->tune.steps_per_launch;
+    rc = enqueue_tiles(b, L, ws, f, nsteps, t, K, 0, b->prep_tiles, s);
   } else {
     const size_t ng = b->prep_group_tune.size();
     rc = hip_check(hipEventRecord(b->gevents[0], s), "hipEventRecord");
@@ -187,8 +195,9 @@ int enqueue_batch(lbm_batch* b, double* f, void* ws, int64_t nsteps,
     for (size_t g = 0; g < ng && !rc; ++g) {
       const hipStream_t sg = g == 0 ? s : b->gstreams[g - 1];
       const int64_t first = b->prep_group_first[g];
-      rc = enqueue_tiles(b, L, ws, f, nsteps, b->prep_group_tune[g], first,
-                         b->prep_group_first[g + 1] - first, sg);
+      const lbm_tuning& t = b->prep_group_tune[g];
+      rc = enqueue_tiles(b, L, ws, f, nsteps, shape_of(t), t.steps_per_launch,
+                         first, b->prep_group_first[g + 1] - first, sg);
     }
     // join every side stream even after a failure, so that a capture ends
     for (size_t g = 1; g < ng; ++g) {
@@ -199,7 +208,7 @@ int enqueue_batch(lbm_batch* b, double* f, void* ws, int64_t nsteps,
       if (!rc) rc = r1 ? r1 : r2;
     }
   }
-  if (nres) {
+  if (fork) {
     const int r = hip_check(hipStreamWaitEvent(s, b->res_events[1], 0),
                             "hipStreamWaitEvent");
     if (!rc) rc = r;
@@ -383,6 +392,7 @@ std::vector<lbm_tuning> batch_candidates(const lbm_batch* b) {
   std::vector<lbm_tuning> v = tuning_candidates();
   const lbm_tuning d =
       default_tuning(b->n_total / b->n_inst, b->n_total, b->eq_class());
+  // (it stands for the library's own plan)
   if (std::none_of(v.begin(), v.end(),
                    [&](const lbm_tuning& c) { return same_tuning(c, d); }))
     v.push_back(d);
@@ -399,7 +409,8 @@ int64_t tune_tiles(const lbm_batch* b) {
     for (const lbm_tuning& t : cands) m = std::max(m, b->lattice_tiles(i, t));
     mx += m;
   }
-  return std::max(mx, std::max(b->run_tiles(), b->count_tiles(b->tune)));
+  return std::max(std::max(mx, b->plan_tiles),
+                  std::max(b->run_tiles(), b->count_tiles(b->tune)));
 }
 
 // Modelled time of a grouping: lattice i costs work_i(s) * c_s on shape s,
@@ -606,6 +617,10 @@ int lbm_batch_init(lbm_batch** b, int64_t n_inst, const int64_t* offsets,
       return set_err(rc, "lattice %lld: %s", (long long)i, g_err.c_str());
     }
   }
+  for (int64_t i = 0; i < n_inst; ++i) {
+    x->plan_tiles += (offsets[i + 1] - offsets[i] + kPlanMinOut - 1) / kPlanMinOut;
+    if (params[i].flags & LBM_CHECK_FINITE) x->any_check = true;
+  }
   x->stream = (hipStream_t)stream;
   x->tune = default_tuning(x->n_total / n_inst, x->n_total, x->eq_class());
   *b = x;
@@ -642,6 +657,7 @@ int lbm_batch_set_tuning(lbm_batch* b, const lbm_tuning* t) {
     return set_err(LBM_EINVAL, "batches run the blocked kernel only");
   b->tune = *t;
   b->tune.kernel = LBM_KERNEL_BLOCKED;
+  b->plan_auto = false;
   b->group_tune.clear();
   b->group_of.clear();
   return LBM_OK;
@@ -734,56 +750,92 @@ size_t lbm_batch_workspace_bytes(const lbm_batch* b, int kind) {
 
 int lbm_batch_prepare(lbm_batch* b, void* ws, size_t ws_bytes) {
   if (!b || !ws) return set_err(LBM_EINVAL, "NULL argument");
+  if (b->planned()) b->make_plan();
   const int64_t ntiles = b->run_tiles();
   const Layout L = layout(b, ntiles, false);
   if (ws_bytes < L.total)
     return set_err(LBM_EWORKSPACE, "workspace of %zu bytes, need %zu", ws_bytes,
                    L.total);
-  // one table per group (a single group: tune), concatenated
+  const bool planned = b->planned();
+  // one table per group (a single group: the plan or tune), concatenated
   const bool grouped = !b->group_tune.empty();
   const size_t ng = grouped ? b->group_tune.size() : 1;
   std::vector<TileRef> tiles;
-  tiles.reserve(ntiles);
   std::vector<int64_t> first(ng + 1, 0);
   for (size_t g = 0; g < ng; ++g) {
     first[g] = (int64_t)tiles.size();
     const lbm_tuning& t = grouped ? b->group_tune[g] : b->tune;
-    const int64_t out = tile_width(t) - 4 * (int64_t)t.steps_per_launch;
+    const int64_t out = planned ? plan_out(b->plan())
+                                : tile_width(t) - 4 * (int64_t)t.steps_per_launch;
     for (int64_t i = 0; i < b->n_inst; ++i) {
-      if ((grouped && b->group_of[i] != (int32_t)g) || b->resident(i)) continue;
+      if ((grouped && b->group_of[i] != (int32_t)g) || b->in_registers(i)) continue;
       const int64_t n = b->offsets[i + 1] - b->offsets[i];
       for (int64_t k = 0; k * out < n; ++k)
         tiles.push_back(TileRef{(int32_t)i, (int32_t)k});
     }
   }
   first[ng] = (int64_t)tiles.size();
-  // Resident lattices packed into workgroups of kResidentWaves wavefronts,
-  // longest first, each into the first workgroup with room for its
-  // ceil(L / 62P) wavefronts.
+  // Resident lattices packed into workgroups, longest first.  On a plan with
+  // fewer than eight nodes per lane the chip has room: each goes to the
+  // emptiest of as many workgroups as there are compute units (more when
+  // their wavefronts fill those); else into the first of the workgroups of
+  // kResidentWaves wavefronts with room for it.
+  const int res_P = planned ? b->plan().P : kResP;
+  int res_wg = kResidentWaves;  // else as wide as the longest lattice, at least 4
   std::vector<ResidentItem> items;
   std::vector<int32_t> res_first;
   {
     std::vector<int64_t> order;
     for (int64_t i = 0; i < b->n_inst; ++i)
-      if (b->resident(i)) order.push_back(i);
+      if (b->in_registers(i)) order.push_back(i);
     auto waves = [&](int64_t i) {
       const int64_t L = b->offsets[i + 1] - b->offsets[i];
-      return (int32_t)((L + 62 * kResP - 1) / (62 * kResP));
+      return (int32_t)(res_P == kResP ? (L + 62 * kResP - 1) / (62 * kResP)
+                                      : resident_waves(L, res_P));
     };
     std::stable_sort(order.begin(), order.end(),
                      [&](int64_t x, int64_t y) { return waves(x) > waves(y); });
-    std::vector<int32_t> used;                     // wavefronts used per workgroup
     std::vector<std::vector<ResidentItem>> bins;
-    for (int64_t i : order) {
-      const int32_t w = waves(i);
-      size_t g = 0;
-      while (g < used.size() && used[g] + w > kResidentWaves) ++g;
-      if (g == used.size()) {
-        used.push_back(0);
-        bins.emplace_back();
+    if (res_P != kResP && !order.empty()) {
+      int64_t total = 0;
+      for (int64_t i : order) total += waves(i);
+      res_wg = std::max<int>(4, waves(order[0]));
+      const size_t least =
+          std::min<size_t>(order.size(), 256 * (size_t)((total + 256 * res_wg - 1) /
+                                                        (256 * res_wg)));
+      std::multimap<int32_t, size_t> by_use;  // wavefronts used -> workgroup
+      for (size_t g = 0; g < least; ++g) by_use.emplace(0, g);
+      bins.resize(least);
+      for (int64_t i : order) {
+        const int32_t w = waves(i);
+        auto it = by_use.begin();
+        int32_t used = 0;
+        size_t g = bins.size();
+        if (it->first + w <= res_wg) {
+          used = it->first;
+          g = it->second;
+          by_use.erase(it);
+        } else {
+          bins.emplace_back();
+        }
+        bins[g].push_back(ResidentItem{(int32_t)i, used, w, 0});
+        by_use.emplace(used + w, g);
       }
-      bins[g].push_back(ResidentItem{(int32_t)i, used[g], w, 0});
-      used[g] += w;
+    } else {
+      std::vector<int32_t> used;  // wavefronts used per workgroup
+      size_t full = 0;            // the workgroups before it have no room left
+      for (int64_t i : order) {
+        const int32_t w = waves(i);
+        while (full < used.size() && used[full] == res_wg) ++full;
+        size_t g = full;
+        while (g < used.size() && used[g] + w > res_wg) ++g;
+        if (g == used.size()) {
+          used.push_back(0);
+          bins.emplace_back();
+        }
+        bins[g].push_back(ResidentItem{(int32_t)i, used[g], w, 0});
+        used[g] += w;
+      }
     }
     for (const auto& bin : bins) {
       res_first.push_back((int32_t)items.size());
@@ -840,6 +892,9 @@ int lbm_batch_prepare(lbm_batch* b, void* ws, size_t ws_bytes) {
   b->prep_group_of = b->group_of;
   b->prep_group_first = grouped ? first : std::vector<int64_t>();
   b->prep_resident_mode = b->resident_mode;
+  b->prep_planned = planned;
+  b->prep_res_P = res_P;
+  b->prep_res_wg = res_wg;
   b->prep_res_items = items;
   b->prep_res_first = items.empty() ? std::vector<int32_t>() : res_first;
   return LBM_OK;
@@ -875,7 +930,8 @@ int lbm_batch_run(lbm_batch* b, double* f, void* ws, size_t ws_bytes,
   if (!(b->exec && b->g_f == f && b->g_ws == ws && b->g_nsteps == nsteps &&
         same_tuning(b->g_tune, b->tune) &&
         same_tunings(b->g_group_tune, b->group_tune) &&
-        b->g_group_of == b->group_of && b->g_resident_mode == b->resident_mode)) {
+        b->g_group_of == b->group_of && b->g_resident_mode == b->resident_mode &&
+        b->g_planned == b->planned())) {
     drop_graph(b);
     if (!b->cap &&
         (rc = hip_check(hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking),
@@ -907,6 +963,7 @@ int lbm_batch_run(lbm_batch* b, double* f, void* ws, size_t ws_bytes,
     b->g_group_tune = b->group_tune;
     b->g_group_of = b->group_of;
     b->g_resident_mode = b->resident_mode;
+    b->g_planned = b->planned();
   }
   rc = hip_check(hipGraphLaunch(b->exec, b->stream), "hipGraphLaunch");
   return rc ? rc : batch_check_result(b, ws);
@@ -959,6 +1016,13 @@ int lbm_batch_autotune(lbm_batch* b, double* f, void* ws, size_t ws_bytes,
                           std::to_string(log2_class(mean_len)) +
                           (b->eq_class() == 0 ? "/eq8" : "/eqsel") +
                           (b->resident_mode ? "/res" : "") + kKernelGeneration;
+  // the default tuning stands for the library's own plan (plan_batch)
+  const lbm_tuning d =
+      default_tuning(b->n_total / b->n_inst, b->n_total, b->eq_class());
+  auto use = [&](const lbm_tuning& t) {
+    b->tune = t;
+    b->plan_auto = same_tuning(t, d);
+  };
   lbm_tuning best = b->tune;
   std::vector<lbm_tuning> gshape;
   std::vector<double> gcost;
@@ -968,11 +1032,13 @@ int lbm_batch_autotune(lbm_batch* b, double* f, void* ws, size_t ws_bytes,
     const size_t sbytes = sizeof(double) * 6 * (size_t)b->n_total;
     // a failed search leaves the tuning, the groups and the mode as they were
     const lbm_tuning prev = b->tune;
+    const bool prev_auto = b->plan_auto;
     const std::vector<lbm_tuning> prev_gt = b->group_tune;
     const std::vector<int32_t> prev_go = b->group_of;
     const int32_t prev_mode = b->resident_mode;
     auto fail = [&](int code) {
       b->tune = prev;
+      b->plan_auto = prev_auto;
       b->group_tune = prev_gt;
       b->group_of = prev_go;
       b->resident_mode = prev_mode;
@@ -987,7 +1053,7 @@ int lbm_batch_autotune(lbm_batch* b, double* f, void* ws, size_t ws_bytes,
     // to tune, and the run is timed as it is.
     auto search = [&](lbm_tuning* best_out, std::vector<lbm_tuning>* gs,
                       std::vector<double>* gc, float* ms) -> int {
-      b->tune = prev;
+      use(prev);
       b->group_tune.clear();
       b->group_of.clear();
       gs->clear();
@@ -1007,7 +1073,7 @@ int lbm_batch_autotune(lbm_batch* b, double* f, void* ws, size_t ws_bytes,
       int rc = autotune_impl(
           b->stream, f, backup, sbytes, probe_steps, cands,
           [&](const lbm_tuning& t) {
-            b->tune = t;
+            use(t);
             return lbm_batch_prepare(b, ws, ws_bytes);
           },
           run, best_out, &times);
@@ -1057,7 +1123,7 @@ int lbm_batch_autotune(lbm_batch* b, double* f, void* ws, size_t ws_bytes,
           sh.push_back(cands[c]);
           co.push_back(cost[c]);
         }
-        b->tune = *best_out;
+        use(*best_out);
         std::vector<float> gt;
         lbm_tuning unused = *best_out;
         rc = autotune_impl(
@@ -1096,7 +1162,7 @@ int lbm_batch_autotune(lbm_batch* b, double* f, void* ws, size_t ws_bytes,
                               const std::vector<lbm_tuning>& gs,
                               const std::vector<double>& gc, float* out_ms) {
         b->resident_mode = mode;
-        b->tune = t;
+        use(t);
         std::vector<float> tm;
         lbm_tuning unused = t;
         const int r = autotune_impl(
@@ -1125,7 +1191,7 @@ int lbm_batch_autotune(lbm_batch* b, double* f, void* ws, size_t ws_bytes,
     tune_cache_put(cache_path, key, best, &gshape, &gcost, resident);
   }
   b->resident_mode = resident;
-  b->tune = best;
+  use(best);
   int rc = gshape.empty() ? lbm_batch_set_groups(b, 0, nullptr, nullptr)
                           : apply_groups(b, gshape, gcost);
   if (!rc) rc = lbm_batch_prepare(b, ws, ws_bytes);

@@ -70,7 +70,17 @@ int launch_batch_copy_tiles(const int64_t* offs, const TileRef* tiles,
 int launch_batch_resident(const Consts* cs, const int64_t* offs,
                           const ResidentItem* items, const int32_t* wg_first,
                           int64_t nwg, const double* fin, double* fout,
-                          int64_t S, int64_t T, int eq, hipStream_t s);
+                          int64_t S, int64_t T, int P, int W, int eq,
+                          hipStream_t s);
+// Nodes a wavefront owns in a resident lattice of P nodes per lane (8/P
+// mirror lanes on each side).
+constexpr int64_t resident_span(int P) { return 64 * P - 16; }
+// Most wavefronts of a resident workgroup: at P = 4 twelve, whose LDS (58 KB)
+// is what 16 take at P = 2.
+constexpr int resident_max_waves(int P) { return P == 8 || P == 4 ? 12 : 16; }
+// All T steps of one lattice of n nodes in place in one workgroup.
+int launch_step_resident(const Consts& c, double* f, int64_t n, int64_t T,
+                         int P, hipStream_t s);
 int launch_batch_check_lattices(const Consts* cs, const int64_t* offs,
                                 const ResidentItem* items, int64_t nitems,
                                 const double* f, int64_t S, int64_t steps,
@@ -139,12 +149,20 @@ StepSplit split_steps(int64_t nsteps, int K);
 lbm_tuning default_tuning(int64_t len, int64_t total, int eq);
 
 // Shape and steps per launch of the next steps of a single lattice on the
-// library's own plan (see plan_steps).
+// library's own plan (see plan_steps); resident > 0: all the steps in one
+// workgroup's registers with that many nodes per lane instead.
 struct StepPlan {
   TileShape t;
   int K;
+  int resident;
 };
 StepPlan plan_steps(int64_t n, int64_t nsteps);
+struct BatchPlan;
+// The plan of a batch with these offsets (see BatchPlan), with resident
+// lattices or on tiles alone.
+BatchPlan plan_batch(const std::vector<int64_t>& offsets, bool resident);
+// Fewest nodes a tile of a batch's plan stores (bounds the table's size).
+constexpr int64_t kPlanMinOut = 48;
 
 // Tile shapes the autotuner tries (P, K, waves per tile).
 std::vector<lbm_tuning> tuning_candidates();
@@ -214,6 +232,24 @@ inline int64_t lattice_lane_nodes(int64_t L, const lbm_tuning& t) {
 }
 }  // namespace lbm
 
+namespace lbm {
+// How a batch runs on the library's own plan (see plan_batch): lattices of at
+// most `waves` wavefronts at P nodes per lane resident (P = 0: none), the
+// others on tiles of shape t with K steps per launch.
+struct BatchPlan {
+  int P = 0, waves = 0;
+  TileShape t{2, 1, 1};
+  int K = 16;
+};
+inline int64_t plan_out(const BatchPlan& p) {
+  return tile_nodes(p.t.P, p.t.W, p.t.M) - 4 * (int64_t)p.K;
+}
+// Wavefronts of a resident lattice of L nodes.
+inline int64_t resident_waves(int64_t L, int P) {
+  return (L + resident_span(P) - 1) / resident_span(P);
+}
+}  // namespace lbm
+
 struct lbm_handle {
   int64_t n;
   lbm_params p;
@@ -244,8 +280,18 @@ struct lbm_batch {
   hipStream_t rstream = nullptr;
   hipEvent_t revents[6] = {};
   lbm_tuning tune{};
+  // The run goes by the library's own plan until lbm_batch_set_tuning or
+  // lbm_batch_set_groups, or when lbm_batch_autotune measured nothing faster;
+  // the plans of the two resident modes (they depend on the lengths alone),
+  // made by lbm_batch_prepare; plan_tiles bounds the tiles of either.
+  bool plan_auto = true;
+  bool plan_made[2] = {false, false};
+  lbm::BatchPlan plans[2];
+  int64_t plan_tiles = 0;
+  bool any_check = false;  // some lattice asks for LBM_CHECK_FINITE
   // what lbm_batch_prepare uploaded
   const void* prep_ws = nullptr;
+  bool prep_planned = false;
   lbm_tuning prep_tune{};
   int64_t prep_tiles = 0;
   // Resident lattices (lbm_batch_set_resident): 1 (default) runs every
@@ -257,6 +303,7 @@ struct lbm_batch {
   int32_t prep_resident_mode = -1;
   hipStream_t res_stream = nullptr;  // side stream of the resident launch
   hipEvent_t res_events[2] = {};     // fork, join
+  int prep_res_P = 0, prep_res_wg = 0;
   std::vector<lbm::ResidentItem> prep_res_items;
   std::vector<int32_t> prep_res_first;
   // Shape groups of lbm_batch_run (lbm_batch_set_groups): lattice i runs with
@@ -280,6 +327,7 @@ struct lbm_batch {
   std::vector<lbm_tuning> g_group_tune;
   std::vector<int32_t> g_group_of;
   int32_t g_resident_mode = -1;
+  bool g_planned = false;
   // adjoint workspace uploaded by lbm_batch_forward_ckpt
   const void* adj_ws = nullptr;
   int64_t adj_nsteps = -1, adj_ckpt = -1;
@@ -299,25 +347,41 @@ struct lbm_batch {
   const double* ag_fbar = nullptr;
   const double* ag_rbar = nullptr;
 
-  // whether some lattice asks for LBM_CHECK_FINITE
-  bool check_finite() const {
-    for (const lbm_params& q : params)
-      if (q.flags & LBM_CHECK_FINITE) return true;
-    return false;
-  }
+  bool check_finite() const { return any_check; }
 
   // equilibrium class of the tile kernels: 0 if every lattice has eq_kind 0
   // (set by lbm_batch_init; the constants do not change afterwards)
   int32_t eq_cls = 0;
   int eq_class() const { return eq_cls; }
 
-  // whether lattice i runs resident with the current settings: only in
+  // whether lattice i may run resident with the current mode: only in
   // batches of section-8 lattices (the kernel that selects the equilibria
   // per lattice needs more registers than three wavefronts per SIMD leave)
   bool resident(int64_t i) const {
     const int64_t L = offsets[i + 1] - offsets[i];
     return resident_mode == 1 && eq_cls == 0 && L >= lbm::kResidentMin &&
            L <= lbm::kResidentMax;
+  }
+
+  // Whether the run goes by plan().  With LBM_CHECK_FINITE it does not, so
+  // that the steps a failure is reported after do not depend on the plan.
+  bool planned() const {
+    return plan_auto && group_tune.empty() && !check_finite();
+  }
+  int plan_mode() const { return eq_cls == 0 ? resident_mode : 0; }
+  void make_plan() {
+    const int m = plan_mode();
+    if (!plan_made[m]) plans[m] = lbm::plan_batch(offsets, m == 1);
+    plan_made[m] = true;
+  }
+  const lbm::BatchPlan& plan() const { return plans[plan_mode()]; }
+
+  // whether lattice i runs in the resident launch
+  bool in_registers(int64_t i) const {
+    if (!planned()) return resident(i);
+    const lbm::BatchPlan& p = plan();
+    return p.P > 0 && resident(i) &&
+           lbm::resident_waves(offsets[i + 1] - offsets[i], p.P) <= p.waves;
   }
 
   // tiles of lattice i for a tuning: ceil(L_i / OUT)
@@ -348,6 +412,7 @@ struct lbm_batch {
 
   // tiles of the run's table: the groups' shapes, else tune
   int64_t run_tiles() const {
+    if (planned()) return plan_tiles;
     if (group_tune.empty()) return count_tiles(tune);
     int64_t s = 0;
     for (int64_t i = 0; i < n_inst; ++i)

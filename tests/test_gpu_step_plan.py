@@ -75,3 +75,65 @@ def test_plan_ends_with_a_set_tuning():
     with pytest.raises(lbm.LBMError) as e:
         lbm.Lattice(n, p).step(f0.clone(), 90)
     assert e.value.code == lbm.LBM_ENONFINITE
+
+
+def batch_params(names, rates):
+    return [oracle_params(p, s_e=float(s)) for p, s in zip(names, rates)]
+
+
+def packed(states):
+    return np.concatenate(states, axis=1)
+
+
+# Batches that the plan treats differently: few short lattices (one node per
+# lane, up to 16 wavefronts each), a few dozen to 2000 nodes (resident and
+# tiled), lattices around the wavefront and workgroup limits of every P (48,
+# 112, 240 and 496 nodes per wavefront, up to 16 or 12 of them), many one-
+# wavefront lattices (more than the chip's SIMDs), long ones, and lattices too
+# short to run resident.
+BATCHES = {
+    "short": [16, 17, 40, 47, 48, 49, 95, 96, 97, 160, 191, 192, 193, 3, 15],
+    "mid": [128, 2000, 300, 1791, 1792, 1793, 767, 768, 769, 900, 512, 64, 2500],
+    "limits": [48, 49, 112, 113, 240, 241, 448, 449, 495, 496, 497, 960, 961,
+               1344, 1345, 1920, 1921, 2880, 2881, 3840, 3841, 5952, 5953, 7, 16],
+    "many": [20 + (37 * i) % 180 for i in range(3000)],
+    "long": [20000, 9000, 30011, 16, 100, 5000, 12000],
+    "one": [333],
+    "tiny": [3, 4, 5, 6, 15],
+}
+
+
+@pytest.mark.parametrize("which", list(BATCHES))
+@pytest.mark.parametrize("kinds", ["section8", "linear"])
+def test_batch_plan_bitwise_equals_set_tuning(which, kinds):
+    """Resident and tiled lattices of a batch on its plan, direct and through
+    a graph, equal the run with a set tuning and every lattice on tiles."""
+    from paper_1802_02369_amd import lbm
+    lens = BATCHES[which]
+    rng = np.random.default_rng(len(lens))
+    names = ("paper", "odd", "nosource") if kinds == "section8" else ("linear", "fluid", "odd")
+    params = batch_params([names[i % 3] for i in range(len(lens))],
+                          rng.uniform(1.1, 1.7, len(lens)))
+    states = [random_state(rng, L, p, amp=0.05, u=0.02, ds=0.05)
+              for L, p in zip(lens, params)]
+    offsets = np.concatenate([[0], np.cumsum(lens)])
+    ref = lbm.Batch(offsets, [gpu_params(p) for p in params])
+    ref.set_resident(0)
+    ref.set_tuning(2, 5, 1)
+    plan = lbm.Batch(offsets, [gpu_params(p) for p in params])
+    f0 = torch.from_numpy(packed(states)).to(dev())
+    for steps in (1, 4, 5, 37, 90):
+        want = f0.clone()
+        ref.run(want, steps, use_graph=False)
+        for mode in (1, 0):
+            plan.set_resident(mode)
+            for use_graph in (False, True):
+                got = f0.clone()
+                plan.run(got, steps, use_graph=use_graph)
+                assert torch.equal(got, want), (steps, mode, use_graph)
+    assert torch.isfinite(want).all()
+    if which != "many":
+        for i, (L, p, f) in enumerate(zip(lens, params, states)):
+            got = want[:, offsets[i]:offsets[i + 1]].cpu().numpy()
+            if L <= 1000:
+                assert max_err(got, oracle.run(f, 90, p)) < 1e-10, (i, L)
