@@ -735,13 +735,12 @@ __global__ __launch_bounds__(1024) void k_step_resident(Consts c, double* f,
                       sm + W * 2 * kCopyDoubles + wave * (64 * P + 64), sm);
 }
 
-// One workgroup per lattice of a batch: moments m = M f (eq. M-d1q3q3).
+// Moments m = M f (eq. M-d1q3q3) of a batch.
 __global__ __launch_bounds__(256) void k_batch_moments(
     const Consts* __restrict__ cs, const int64_t* __restrict__ offs,
-    const double* __restrict__ f, double* __restrict__ m, int64_t S) {
-  const int inst = blockIdx.x;
-  const Consts c = cs[inst];
-  for (int64_t j = offs[inst] + threadIdx.x; j < offs[inst + 1]; j += 256) {
+    int64_t n_inst, const double* __restrict__ f, double* __restrict__ m,
+    int64_t S) {
+  lbm::batch_nodes(cs, offs, n_inst, [&](const Consts& c, int64_t j) {
     const double f0 = f[j], fp = f[S + j], fm = f[2 * S + j];
     const double g0 = f[3 * S + j], gp = f[4 * S + j], gm = f[5 * S + j];
     const double sf = fp + fm, sg = gp + gm;
@@ -751,22 +750,21 @@ __global__ __launch_bounds__(256) void k_batch_moments(
     m[3 * S + j] = c.me * (sf - 2.0 * f0);
     m[4 * S + j] = c.mpsi * (gp - gm);
     m[5 * S + j] = c.meps * (sg - 2.0 * g0);
-  }
+  });
 }
 
-// One workgroup per lattice of a batch: equilibrium populations.
+// Equilibrium populations of a batch.
 __global__ __launch_bounds__(256) void k_batch_equilibrium(
     const Consts* __restrict__ cs, const int64_t* __restrict__ offs,
-    const double* __restrict__ rho, const double* __restrict__ J,
-    const double* __restrict__ zeta, double* __restrict__ f, int64_t S) {
-  const int inst = blockIdx.x;
-  const Consts c = cs[inst];
-  for (int64_t j = offs[inst] + threadIdx.x; j < offs[inst + 1]; j += 256) {
+    int64_t n_inst, const double* __restrict__ rho,
+    const double* __restrict__ J, const double* __restrict__ zeta,
+    double* __restrict__ f, int64_t S) {
+  lbm::batch_nodes(cs, offs, n_inst, [&](const Consts& c, int64_t j) {
     double v[6];
     lbm::equilibrium(c, rho[j], J[j], zeta[j], v);
 #pragma unroll
     for (int k = 0; k < 6; ++k) f[k * S + j] = v[k];
-  }
+  });
 }
 
 struct DiagAcc {
@@ -1242,15 +1240,15 @@ int launch_batch_equilibrium(const Consts* cs, const int64_t* offs,
                              int64_t n_inst, const double* rho, const double* J,
                              const double* zeta, double* f, int64_t S,
                              hipStream_t s) {
-  hipLaunchKernelGGL(k_batch_equilibrium, dim3((unsigned)n_inst), dim3(256), 0,
-                     s, cs, offs, rho, J, zeta, f, S);
+  hipLaunchKernelGGL(k_batch_equilibrium, dim3((unsigned)cdiv(S, kNodeBlock)),
+                     dim3(256), 0, s, cs, offs, n_inst, rho, J, zeta, f, S);
   return hip_check(hipGetLastError(), "k_batch_equilibrium");
 }
 
 int launch_batch_moments(const Consts* cs, const int64_t* offs, int64_t n_inst,
                          const double* f, double* m, int64_t S, hipStream_t s) {
-  hipLaunchKernelGGL(k_batch_moments, dim3((unsigned)n_inst), dim3(256), 0, s,
-                     cs, offs, f, m, S);
+  hipLaunchKernelGGL(k_batch_moments, dim3((unsigned)cdiv(S, kNodeBlock)),
+                     dim3(256), 0, s, cs, offs, n_inst, f, m, S);
   return hip_check(hipGetLastError(), "k_batch_moments");
 }
 

@@ -692,13 +692,11 @@ int launch_adjoint_tile(int P, int WG, int E, int eq, const Consts* cs,
 // fbar of the equilibrium initialisation -> adjoints of rho, J, zeta.
 __global__ __launch_bounds__(256) void k_equilibrium_adjoint(
     const Consts* __restrict__ cs, const int64_t* __restrict__ offs,
-    const double* __restrict__ rho, const double* __restrict__ J,
-    const double* __restrict__ zeta, const double* __restrict__ fb,
-    double* __restrict__ rho_b, double* __restrict__ J_b,
-    double* __restrict__ zeta_b, int64_t S) {
-  const int inst = blockIdx.x;
-  const Consts c = cs[inst];
-  for (int64_t j = offs[inst] + threadIdx.x; j < offs[inst + 1]; j += 256) {
+    int64_t n_inst, const double* __restrict__ rho,
+    const double* __restrict__ J, const double* __restrict__ zeta,
+    const double* __restrict__ fb, double* __restrict__ rho_b,
+    double* __restrict__ J_b, double* __restrict__ zeta_b, int64_t S) {
+  lbm::batch_nodes(cs, offs, n_inst, [&](const Consts& c, int64_t j) {
     NodeFwd q;
     q.rho = rho[j];
     q.J = J[j];
@@ -720,16 +718,15 @@ __global__ __launch_bounds__(256) void k_equilibrium_adjoint(
     rho_b[j] = rb;
     J_b[j] = Jb;
     zeta_b[j] = zb;
-  }
+  });
 }
 
 // fbar = M^T mbar (mbar in moment order rho, J, zeta, e, psi, eps).
 __global__ __launch_bounds__(256) void k_moments_adjoint(
     const Consts* __restrict__ cs, const int64_t* __restrict__ offs,
-    const double* __restrict__ mb, double* __restrict__ fb, int64_t S) {
-  const int inst = blockIdx.x;
-  const Consts c = cs[inst];
-  for (int64_t j = offs[inst] + threadIdx.x; j < offs[inst + 1]; j += 256) {
+    int64_t n_inst, const double* __restrict__ mb, double* __restrict__ fb,
+    int64_t S) {
+  lbm::batch_nodes(cs, offs, n_inst, [&](const Consts& c, int64_t j) {
     const double rb = mb[j], Jb = mb[S + j], zb = mb[2 * S + j];
     const double eb = mb[3 * S + j], pb = mb[4 * S + j], xb = mb[5 * S + j];
     fb[j] = c.rho0 * rb - 2.0 * c.me * eb;
@@ -738,24 +735,28 @@ __global__ __launch_bounds__(256) void k_moments_adjoint(
     fb[3 * S + j] = c.mz * zb - 2.0 * c.meps * xb;
     fb[4 * S + j] = c.mz * zb + c.mpsi * pb + c.meps * xb;
     fb[5 * S + j] = c.mz * zb - c.mpsi * pb + c.meps * xb;
-  }
+  });
 }
 
 // L_i = 1/2 sum_j (rho_j - target_j)^2 per lattice (target NULL: rho0) and
-// its gradient with respect to the state; fixed tree order.
+// its gradient with respect to the state.  Workgroup b takes the kAdjOut
+// nodes of tile tiles[b] and leaves their sum in parts[b]; k_loss_sum adds a
+// lattice's tiles.  Fixed order in both.
 __global__ __launch_bounds__(256) void k_loss(
     const Consts* __restrict__ cs, const int64_t* __restrict__ offs,
-    const double* __restrict__ f, const double* __restrict__ target,
-    double* __restrict__ loss, double* __restrict__ fb, int64_t S) {
-  __shared__ double red[256];
-  const int inst = blockIdx.x;
-  const Consts c = cs[inst];
+    const TileRef* __restrict__ tiles, const double* __restrict__ f,
+    const double* __restrict__ target, double* __restrict__ parts,
+    double* __restrict__ fb, int64_t S) {
+  __shared__ double red[4];
+  const TileRef tr = tiles[blockIdx.x];
+  const double rho0 = cs[tr.inst].rho0;
+  const int64_t j = offs[tr.inst] + (int64_t)tr.t * kAdjOut + threadIdx.x;
   double acc = 0.0;
-  for (int64_t j = offs[inst] + threadIdx.x; j < offs[inst + 1]; j += 256) {
-    const double rho = lbm::density(c, f[j], f[S + j], f[2 * S + j]);
-    const double d = rho - (target ? target[j] : c.rho0);
-    acc += 0.5 * d * d;
-    const double g = c.rho0 * d;
+  if ((int)threadIdx.x < kAdjOut && j < offs[tr.inst + 1]) {
+    const double rho = lbm::density(cs[tr.inst], f[j], f[S + j], f[2 * S + j]);
+    const double d = rho - (target ? target[j] : rho0);
+    acc = 0.5 * d * d;
+    const double g = rho0 * d;
     fb[j] = g;
     fb[S + j] = g;
     fb[2 * S + j] = g;
@@ -763,35 +764,41 @@ __global__ __launch_bounds__(256) void k_loss(
     fb[4 * S + j] = 0.0;
     fb[5 * S + j] = 0.0;
   }
-  red[threadIdx.x] = acc;
+  acc = wave_sum(acc);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
   __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
+  if (threadIdx.x == 0)
+    parts[blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
+}
+
+// out[N*inst + q] = sum of in[N*t + q] over the lattice's tiles t in
+// [first[inst], first[inst + 1]): one workgroup per lattice, each thread
+// every 256th tile in order, then the wavefronts' butterflies in order (one
+// thread per lattice took 75 us for the 683 tiles of 8192 nodes, 340 us for
+// 2^20 nodes; 4 and 6 us this way).
+template <int N>
+__global__ __launch_bounds__(256) void k_tile_sum(
+    const int64_t* __restrict__ first, const double* __restrict__ in,
+    double* __restrict__ out) {
+  __shared__ double red[N][4];
+  const int64_t i = blockIdx.x;
+  double a[N] = {};
+  for (int64_t t = first[i] + threadIdx.x; t < first[i + 1]; t += 256)
+#pragma unroll
+    for (int q = 0; q < N; ++q) a[q] += in[N * t + q];
+#pragma unroll
+  for (int q = 0; q < N; ++q) {
+    a[q] = wave_sum(a[q]);
+    if ((threadIdx.x & 63) == 0) red[q][threadIdx.x >> 6] = a[q];
   }
-  if (threadIdx.x == 0) loss[inst] = red[0];
+  __syncthreads();
+  const int q = threadIdx.x;
+  if (q < N) out[N * i + q] = ((red[q][0] + red[q][1]) + red[q][2]) + red[q][3];
 }
 
 __global__ void k_fill(double* __restrict__ p, int64_t n, double v) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = v;
-}
-
-// rbar[3*inst + q] = sum over the lattice's adjoint tiles, in tile order.
-__global__ void k_rbar_reduce(const int64_t* __restrict__ first,
-                              int64_t n_inst, const double* __restrict__ slots,
-                              double* __restrict__ rbar) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n_inst) return;
-  double a = 0.0, b = 0.0, c = 0.0;
-  for (int64_t t = first[i]; t < first[i + 1]; ++t) {
-    a += slots[3 * t];
-    b += slots[3 * t + 1];
-    c += slots[3 * t + 2];
-  }
-  rbar[3 * i] = a;
-  rbar[3 * i + 1] = b;
-  rbar[3 * i + 2] = c;
 }
 
 // ------------------------------------------------------------ host side --
@@ -1156,11 +1163,15 @@ int enqueue_adjoint(lbm_batch* b, void* ws, int64_t nsteps, int64_t C,
                                      hipMemcpyDeviceToDevice, s),
                       "hipMemcpyAsync")))
     return rc;
-  hipLaunchKernelGGL(k_rbar_reduce, dim3((unsigned)((b->n_inst + 255) / 256)),
-                     dim3(256), 0, s,
+  hipLaunchKernelGGL((k_tile_sum<3>), dim3((unsigned)b->n_inst), dim3(256), 0, s,
                      at<int64_t>(ws, b->adj_plain ? L.adj_first : L.rev_first),
-                     b->n_inst, (const double*)slots, rbar);
-  return hip_check(hipGetLastError(), "k_rbar_reduce");
+                     (const double*)slots, rbar);
+  return hip_check(hipGetLastError(), "k_tile_sum");
+}
+
+// Grid of the node-wise kernels (batch_nodes).
+dim3 node_grid(const lbm_batch* b) {
+  return dim3((unsigned)((b->n_total + kNodeBlock - 1) / kNodeBlock));
 }
 
 lbm_batch* single_batch(lbm_handle* h) {
@@ -1342,10 +1353,18 @@ int lbm_batch_loss(lbm_batch* b, const double* f, const double* target,
   if (b->adj_ws != ws || ws_bytes < adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b)).total)
     return set_err(LBM_EINVAL, "call lbm_batch_forward_ckpt with this workspace first");
   const AdjLayout L = adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b));
-  hipLaunchKernelGGL(k_loss, dim3((unsigned)b->n_inst), dim3(256), 0, b->stream,
-                     at<Consts>(ws, L.consts), at<int64_t>(ws, L.offs), f, target,
-                     loss, fbar, b->n_total);
-  return hip_check(hipGetLastError(), "k_loss");
+  // the tiles' sums take the rate slots, which a reverse sweep clears first
+  double* parts = at<double>(ws, L.rslots);
+  hipLaunchKernelGGL(k_loss, dim3((unsigned)L.n_adj), dim3(256), 0, b->stream,
+                     at<Consts>(ws, L.consts), at<int64_t>(ws, L.offs),
+                     at<TileRef>(ws, L.adj_tiles), f, target, parts, fbar,
+                     b->n_total);
+  int rc = hip_check(hipGetLastError(), "k_loss");
+  if (rc) return rc;
+  hipLaunchKernelGGL((k_tile_sum<1>), dim3((unsigned)b->n_inst), dim3(256), 0,
+                     b->stream, at<int64_t>(ws, L.adj_first),
+                     (const double*)parts, loss);
+  return hip_check(hipGetLastError(), "k_tile_sum");
 }
 
 int lbm_batch_equilibrium_adjoint(lbm_batch* b, const double* rho,
@@ -1358,10 +1377,9 @@ int lbm_batch_equilibrium_adjoint(lbm_batch* b, const double* rho,
   if (b->adj_ws != ws || ws_bytes < adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b)).total)
     return set_err(LBM_EINVAL, "call lbm_batch_forward_ckpt with this workspace first");
   const AdjLayout L = adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b));
-  hipLaunchKernelGGL(k_equilibrium_adjoint, dim3((unsigned)b->n_inst), dim3(256),
-                     0, b->stream, at<Consts>(ws, L.consts),
-                     at<int64_t>(ws, L.offs), rho, J, zeta, fbar, rho_bar,
-                     J_bar, zeta_bar, b->n_total);
+  hipLaunchKernelGGL(k_equilibrium_adjoint, node_grid(b), dim3(256), 0, b->stream,
+                     at<Consts>(ws, L.consts), at<int64_t>(ws, L.offs), b->n_inst,
+                     rho, J, zeta, fbar, rho_bar, J_bar, zeta_bar, b->n_total);
   return hip_check(hipGetLastError(), "k_equilibrium_adjoint");
 }
 
@@ -1371,8 +1389,8 @@ int lbm_batch_moments_adjoint(lbm_batch* b, const double* mbar, double* fbar,
   if (b->adj_ws != ws || ws_bytes < adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b)).total)
     return set_err(LBM_EINVAL, "call lbm_batch_forward_ckpt with this workspace first");
   const AdjLayout L = adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b));
-  hipLaunchKernelGGL(k_moments_adjoint, dim3((unsigned)b->n_inst), dim3(256), 0,
-                     b->stream, at<Consts>(ws, L.consts), at<int64_t>(ws, L.offs),
+  hipLaunchKernelGGL(k_moments_adjoint, node_grid(b), dim3(256), 0, b->stream,
+                     at<Consts>(ws, L.consts), at<int64_t>(ws, L.offs), b->n_inst,
                      mbar, fbar, b->n_total);
   return hip_check(hipGetLastError(), "k_moments_adjoint");
 }
