@@ -175,8 +175,9 @@ int make_consts(const lbm_params* p, Consts* c) {
 namespace {
 
 // nodes per block of the one-step kernel: 15 wavefronts and one more for the
-// halo (960 against 256 nodes per block: 60.7 -> 61.4 GLUPS at N = 2^24)
-constexpr int kPlainBlock = 960;
+// halo (960 against 256 nodes per block: 60.7 -> 61.4 GLUPS at N = 2^24), or 3
+// and one while blocks of 960 would not give every compute unit one
+constexpr int kPlainBlock = 960, kPlainSmall = 192;
 constexpr int kDiagBlock = 256;
 constexpr int kDiagMaxBlocks = 1024;
 
@@ -209,7 +210,7 @@ __global__ __launch_bounds__(256) void k_moments(Consts c,
 }
 
 // One time step, one node per thread.  Block b stores nodes
-// [b*B, b*B + B) (B = kPlainBlock), each thread its own node with aligned
+// [b*B, b*B + B), each thread its own node with aligned
 // stores: the streamed values f+(j) = f+*(j-1) and f-(j) = f-*(j+1) come
 // through LDS.  One more wavefront handles the four halo nodes: b*B - 1 and
 // b*B + B are collided too (their f+* and f-* stream into the block), and
@@ -217,26 +218,31 @@ __global__ __launch_bounds__(256) void k_moments(Consts c,
 // holds node b*B - 2 + s.  NT: non-temporal loads and stores, for states far
 // larger than the caches (measured on a 6-array copy: 6.1 against 5.6 TB/s;
 // with stores shifted by one node, as push streaming writes them, 5.5).
-template <int EQ, bool NT>
-__global__ __launch_bounds__(kPlainBlock + 64) void k_step_plain(
-    Consts c, const double* __restrict__ fin, double* __restrict__ fout,
-    int64_t n) {
-  constexpr int NS = kPlainBlock + 4;
+// HALO: the step is in place (fin = fout = f): the four halo nodes of every
+// block, which other blocks overwrite, come from `halo`, where k_save_halo put
+// them before; a block's own nodes are read and written by one thread each.
+// One step by itself thus costs its 96 bytes per node and a small launch
+// instead of a step into the second state and a copy of it back (n = 4194301:
+// 72 us instead of 82 + 85).
+template <int B, int EQ, bool NT, bool HALO>
+__global__ __launch_bounds__(B + 64) void k_step_plain(
+    Consts c, const double* fin, double* fout, const double* halo, int64_t n) {
+  constexpr int NS = B + 4;
   __shared__ double su[NS], sT[NS], sfp[NS], sgp[NS], sfm[NS], sgm[NS];
   const int tid = threadIdx.x;
-  const int64_t b0 = (int64_t)blockIdx.x * kPlainBlock;
+  const int64_t b0 = (int64_t)blockIdx.x * B;
   const int64_t rem = n - b0;
-  const int nloc = rem < kPlainBlock ? (int)rem : kPlainBlock;
+  const int nloc = rem < B ? (int)rem : B;
   // this thread's node and LDS slot; -1: no node
   int slot = -1;
   int64_t j = 0;
-  if (tid < kPlainBlock) {
+  if (tid < B) {
     if (tid < nloc) {
       slot = tid + 2;
       j = b0 + tid;
     }
-  } else if (tid < kPlainBlock + 4) {
-    const int h = tid - kPlainBlock;  // b0-2, b0-1, b0+nloc, b0+nloc+1
+  } else if (tid < B + 4) {
+    const int h = tid - B;  // b0-2, b0-1, b0+nloc, b0+nloc+1
     slot = h < 2 ? h : nloc + h;
     j = lbm::wrap_mod(b0 - 2 + slot, n);
   }
@@ -245,7 +251,15 @@ __global__ __launch_bounds__(kPlainBlock + 64) void k_step_plain(
   double f0 = 0, fp = 0, fm = 0, g0 = 0, gp = 0, gm = 0, u = 0, T = 0, rw = 0,
          w = 0;
   if (slot >= 0) {
-    if (NT) {
+    if (HALO && tid >= B) {
+      const double* h = halo + ((int64_t)blockIdx.x * 4 + (tid - B)) * 6;
+      f0 = h[0];
+      fp = h[1];
+      fm = h[2];
+      g0 = h[3];
+      gp = h[4];
+      gm = h[5];
+    } else if (NT) {
       f0 = __builtin_nontemporal_load(&fin[j]);
       fp = __builtin_nontemporal_load(&fin[n + j]);
       fm = __builtin_nontemporal_load(&fin[2 * n + j]);
@@ -298,6 +312,22 @@ __global__ __launch_bounds__(kPlainBlock + 64) void k_step_plain(
     fout[4 * n + j] = gp;
     fout[5 * n + j] = gm;
   }
+}
+
+// The halo nodes of every block of k_step_plain, [block][4][6].
+__global__ __launch_bounds__(256) void k_save_halo(const double* __restrict__ f,
+                                                   double* __restrict__ halo,
+                                                   int64_t n, int64_t blocks,
+                                                   int B) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= 4 * blocks) return;
+  const int64_t b0 = (i >> 2) * B;
+  const int h = (int)(i & 3);
+  const int64_t rem = n - b0;
+  const int nloc = rem < B ? (int)rem : B;
+  const int64_t j = lbm::wrap_mod(b0 - 2 + (h < 2 ? h : nloc + h), n);
+#pragma unroll
+  for (int q = 0; q < 6; ++q) halo[i * 6 + q] = f[q * n + j];
 }
 
 // K time steps of one register-resident tile per workgroup (see the file
@@ -987,20 +1017,46 @@ int launch_equilibrium(const Consts& c, const double* rho, const double* J,
   return hip_check(hipGetLastError(), "k_equilibrium");
 }
 
-int launch_step_plain(const Consts& c, const double* fin, double* fout,
-                      int64_t n, hipStream_t s) {
-  const dim3 grid((unsigned)cdiv(n, kPlainBlock)), block(kPlainBlock + 64);
+template <int B, int EQ>
+static void launch_plain_t(const Consts& c, const double* fin, double* fout,
+                           double* halo, int64_t n, hipStream_t s) {
+  const int64_t blocks = cdiv(n, B);
+  const dim3 grid((unsigned)blocks), block(B + 64);
   // non-temporal accesses once the two states (96 B per node) outgrow the
   // 256 MB of on-die cache
   const bool nt = 96 * n > (int64_t(256) << 20);
-  if (c.eq_kind == 0 && nt)
-    hipLaunchKernelGGL((k_step_plain<0, true>), grid, block, 0, s, c, fin, fout, n);
-  else if (c.eq_kind == 0)
-    hipLaunchKernelGGL((k_step_plain<0, false>), grid, block, 0, s, c, fin, fout, n);
+  if (fin == fout)
+    hipLaunchKernelGGL(k_save_halo, dim3((unsigned)cdiv(4 * blocks, 256)),
+                       dim3(256), 0, s, fin, halo, n, blocks, B);
+  if (fin == fout && nt)
+    hipLaunchKernelGGL((k_step_plain<B, EQ, true, true>), grid, block, 0, s, c,
+                       fin, fout, halo, n);
+  else if (fin == fout)
+    hipLaunchKernelGGL((k_step_plain<B, EQ, false, true>), grid, block, 0, s, c,
+                       fin, fout, halo, n);
   else if (nt)
-    hipLaunchKernelGGL((k_step_plain<-1, true>), grid, block, 0, s, c, fin, fout, n);
+    hipLaunchKernelGGL((k_step_plain<B, EQ, true, false>), grid, block, 0, s, c,
+                       fin, fout, halo, n);
   else
-    hipLaunchKernelGGL((k_step_plain<-1, false>), grid, block, 0, s, c, fin, fout, n);
+    hipLaunchKernelGGL((k_step_plain<B, EQ, false, false>), grid, block, 0, s, c,
+                       fin, fout, halo, n);
+}
+
+// One step from fin to fout, or in place (fin = fout) with `halo` for 24
+// doubles per block.
+int launch_step_plain(const Consts& c, const double* fin, double* fout,
+                      double* halo, int64_t n, hipStream_t s) {
+  if (n >= 256 * (int64_t)kPlainBlock) {
+    if (c.eq_kind == 0)
+      launch_plain_t<kPlainBlock, 0>(c, fin, fout, halo, n, s);
+    else
+      launch_plain_t<kPlainBlock, -1>(c, fin, fout, halo, n, s);
+  } else {
+    if (c.eq_kind == 0)
+      launch_plain_t<kPlainSmall, 0>(c, fin, fout, halo, n, s);
+    else
+      launch_plain_t<kPlainSmall, -1>(c, fin, fout, halo, n, s);
+  }
   return hip_check(hipGetLastError(), "k_step_plain");
 }
 

@@ -120,8 +120,6 @@ const TileCost kTileCosts[] = {
 StepPlan plan_steps(int64_t n, int64_t nsteps) {
   StepPlan best{{8, 4, 1}, 40, 0};
   double least = INFINITY;
-  // one step ends in the second state and is copied back
-  const double copy = nsteps == 1 ? 3.0 + 96.0 * (double)n / 5e6 : 0.0;
   // A lattice that fits one workgroup needs neither halo nor launches
   // (n = 160, one node per lane, 4 wavefronts: 0.25 us per step, 0.33 on
   // tiles), but has one compute unit: from 5 wavefronts on, two on a SIMD,
@@ -150,7 +148,7 @@ StepPlan plan_steps(int64_t n, int64_t nsteps) {
           (c.fixed + 48.0 * ((double)tiles * (double)nodes + (double)n) / 11e6 +
            (double)k * ((double)(g / c.per_cu) * c.step(c.per_cu) +
                         c.step((double)(g % c.per_cu)))) +
-          copy;
+          (sp.count & 1 ? 2.5 : 0.0);  // in place: one more small launch
       if (us < least) {
         least = us;
         best = StepPlan{c.t, (int)k, 0};
@@ -378,7 +376,6 @@ namespace {
 // record of LBM_CHECK_FINITE.
 int step_run(lbm_handle* h, double* f, double* ws, int64_t nsteps) {
   const int64_t n = h->n;
-  const size_t sbytes = (size_t)(6 * n) * sizeof(double);
   double* a = f;
   double* b = ws;
   // failure record of LBM_CHECK_FINITE, after the diagnostics scratch
@@ -386,13 +383,21 @@ int step_run(lbm_handle* h, double* f, double* ws, int64_t nsteps) {
   unsigned long long* rec = reinterpret_cast<unsigned long long*>(
       ws + 6 * n + check_record_double());
   int rc = check ? launch_check_reset(rec, h->stream) : LBM_OK;
-  int64_t launches = 0, done = 0;
+  int64_t done = 0;
+  // one step in place (its halo goes to the second state): what a run starts
+  // with when its launches would otherwise end in the second state
+  auto one_step = [&] {
+    if (!rc) rc = launch_step_plain(h->c, f, f, ws, n, h->stream);
+    ++done;
+    if (!rc && check) rc = launch_check_state(h->c, f, n, done, rec, h->stream);
+  };
   if (h->tune.kernel == LBM_KERNEL_PLAIN) {
-    for (int64_t t = 0; t < nsteps && !rc; ++t) {
-      rc = launch_step_plain(h->c, a, b, n, h->stream);
-      if (!rc && check) rc = launch_check_state(h->c, b, n, t + 1, rec, h->stream);
+    if (nsteps & 1) one_step();
+    while (done < nsteps && !rc) {
+      rc = launch_step_plain(h->c, a, b, nullptr, n, h->stream);
+      ++done;
+      if (!rc && check) rc = launch_check_state(h->c, b, n, done, rec, h->stream);
       std::swap(a, b);
-      ++launches;
     }
   } else {
     // with LBM_CHECK_FINITE the launches are the tuning's, so that the steps a
@@ -412,21 +417,26 @@ int step_run(lbm_handle* h, double* f, double* ws, int64_t nsteps) {
                                   plan.resident, h->stream);
       return rc;
     }
-    // An even number of launches leaves the result in f without a copy.
-    for (int k : split_steps(nsteps, plan.K)) {
+    // An even number of launches leaves the result in f; the number is odd
+    // for nsteps = 1, or K = 1 and nsteps odd.  Then the first step is taken
+    // in place, on short lattices the state copied back at the end: either is
+    // two launches, and from 65536 nodes on the copy's bytes count (a step and
+    // its moments at 6e4 nodes: 14.9 us with the copy, 15.3 in place; at 1e5
+    // 17.0 and 14.9, at 1e6 50.7 and 37.7).
+    const bool odd = split_steps(nsteps, plan.K).count & 1;
+    if (odd && n >= 65536) one_step();
+    for (int k : split_steps(nsteps - done, plan.K)) {
+      if (rc) break;
       rc = launch_step_tile(h->c, a, b, n, plan.t, k, h->stream);
       done += k;
       if (!rc && check) rc = launch_check_state(h->c, b, n, done, rec, h->stream);
-      if (rc) break;
       std::swap(a, b);
-      ++launches;
     }
+    if (!rc && a != f)
+      rc = hip_check(hipMemcpyAsync(f, a, 48 * (size_t)n, hipMemcpyDeviceToDevice,
+                                    h->stream),
+                     "hipMemcpyAsync");
   }
-  if (rc) return rc;
-  if (launches & 1)
-    rc = hip_check(hipMemcpyAsync(f, ws, sbytes, hipMemcpyDeviceToDevice,
-                                  h->stream),
-                   "hipMemcpyAsync");
   if (rc || !check) return rc;
   unsigned long long key = 0;
   if ((rc = read_check_record(rec, h->stream, &key))) return rc;

@@ -89,7 +89,7 @@ int launch_batch_check_lattices(const Consts* cs, const int64_t* offs,
 int launch_equilibrium(const Consts& c, const double* rho, const double* J,
                        const double* zeta, double* f, int64_t n, hipStream_t s);
 int launch_step_plain(const Consts& c, const double* fin, double* fout,
-                      int64_t n, hipStream_t s);
+                      double* halo, int64_t n, hipStream_t s);
 int launch_step_tile(const Consts& c, const double* fin, double* fout,
                      int64_t n, const TileShape& t, int K, hipStream_t s);
 int launch_diagnostics(const Consts& c, const double* f, int64_t n,

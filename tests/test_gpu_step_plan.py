@@ -137,3 +137,46 @@ def test_batch_plan_bitwise_equals_set_tuning(which, kinds):
             got = want[:, offsets[i]:offsets[i + 1]].cpu().numpy()
             if L <= 1000:
                 assert max_err(got, oracle.run(f, 90, p)) < 1e-10, (i, L)
+
+
+# around the one-step kernel's blocks of 960 nodes, and past the size from
+# which it uses non-temporal accesses (2.8e6 nodes)
+@pytest.mark.parametrize("n", [3, 4, 5, 15, 769, 958, 959, 960, 961, 962, 1919,
+                               1920, 1921, 2500, 100003, 2900001])
+@pytest.mark.parametrize("pname", ["paper", "linear"])
+def test_odd_step_counts_in_place(n, pname):
+    """Runs that would end in the second state take their first step in place:
+    one step on the plan or a set shape, odd counts at one step per launch and
+    of the one-step kernel; bitwise an even split of the same steps."""
+    from paper_1802_02369_amd import lbm
+    po = oracle_params(pname)
+    rng = np.random.default_rng(n)
+    f0 = torch.from_numpy(random_state(rng, n, po, amp=0.1, u=0.05, ds=0.1)).to(dev())
+    ref = lbm.Lattice(n, gpu_params(po))
+    ref.set_tuning(nodes_per_lane=2, steps_per_launch=5, waves_per_group=2)
+    four = f0.clone()
+    ref.step(four, 4)  # two launches of two
+    want3 = f0.clone()
+    ref.step(want3, 3)  # two launches
+    # step 4 alone after three others is the fourth step of four
+    for kw in ({}, {"nodes_per_lane": 2, "steps_per_launch": 1, "waves_per_group": 4},
+               {"kernel": lbm.KERNEL_PLAIN}):
+        lat = lbm.Lattice(n, gpu_params(po))
+        if kw:
+            lat.set_tuning(**kw)
+        f = f0.clone()
+        lat.step(f, 3)
+        assert torch.equal(f, want3), kw
+        lat.step(f, 1)
+        assert torch.equal(f, four), kw
+    p = gpu_params(po)
+    p.flags = lbm.LBM_CHECK_FINITE
+    lat = lbm.Lattice(n, p)
+    f = want3.clone()
+    lat.step(f, 1)
+    assert torch.equal(f, four)
+    f = want3.clone()
+    f[4, n // 2] = float("nan")
+    with pytest.raises(lbm.LBMError) as e:
+        lat.step(f, 1)
+    assert "after 1 time steps" in str(e.value)
