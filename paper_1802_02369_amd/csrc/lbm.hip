@@ -420,15 +420,14 @@ __device__ __forceinline__ void tile_run(const Consts& c,
   static_assert(WG == 1 || (M * P >= 2 && 2 * M <= 32), "mirror lanes");
   constexpr int WW = 64 * P;              // nodes of one wavefront
   constexpr int WS = (64 - 2 * M) * P;    // wavefront stride in the tile
-  // one node per lane needs no staging: the register order is the coalesced
-  __shared__ double stage[P == 1 ? 1 : WG * (WW + 64)];
+  __shared__ double stage[staged(P) ? WG * (WW + 64) : 1];
   __shared__ double edge[2][WG][2][6 * P * M];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nw = active_waves<P, WG, M>(n, start, H);
   if (wave >= nw) return;  // uniform over the wavefront
   const int W = lbm::tile_nodes(P, nw, M);
-  double* lds = stage + (P == 1 ? 0 : wave * (WW + 64));
+  double* lds = stage + (staged(P) ? wave * (WW + 64) : 0);
   const int64_t wstart = start + wave * WS;
   const bool inside = start >= 0 && start + W <= n;
   const bool small = n < W;
@@ -722,9 +721,14 @@ __device__ __forceinline__ void resident_run(
 }
 
 // Dynamic LDS of a workgroup of W wavefronts: the copies and, for more than
-// one node per lane, the load and store staging.
+// two nodes per lane, the load and store staging.
 constexpr size_t resident_lds(int P, int W) {
-  return sizeof(double) * W * (2 * kCopyDoubles + (P == 1 ? 0 : 64 * P + 64));
+  return sizeof(double) * W * (2 * kCopyDoubles + (staged(P) ? 64 * P + 64 : 0));
+}
+
+template <int P>
+__device__ __forceinline__ double* resident_stage(double* sm, int W, int wave) {
+  return staged(P) ? sm + W * 2 * kCopyDoubles + wave * (64 * P + 64) : sm;
 }
 
 // Lattices of a batch (items), W wavefronts per workgroup.
@@ -750,7 +754,7 @@ __global__ __launch_bounds__(1024) void k_batch_resident_small(
   resident_run<P, EQ>(c, fin + off, fout + off, S,
                       (int)(offs[it.inst + 1] - off), lane, wave,
                       wave - it.wave0, it.nw, W, T,
-                      sm + W * 2 * kCopyDoubles + wave * (64 * P + 64), sm);
+                      resident_stage<P>(sm, W, wave), sm);
 }
 
 // One lattice of n nodes in one workgroup.
@@ -762,7 +766,7 @@ __global__ __launch_bounds__(1024) void k_step_resident(Consts c, double* f,
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   resident_run<P, EQ>(c, f, f, n, n, lane, wave, wave, W, W, T,
-                      sm + W * 2 * kCopyDoubles + wave * (64 * P + 64), sm);
+                      resident_stage<P>(sm, W, wave), sm);
 }
 
 // Moments m = M f (eq. M-d1q3q3) of a batch.

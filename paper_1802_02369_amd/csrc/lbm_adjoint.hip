@@ -246,11 +246,10 @@ __global__ __launch_bounds__(kAdjBlock) void k_adjoint_step(
 // on each side, or 2K + 2 when only every second forward state is stored, K
 // the forward's steps per launch).  The tile has the forward kernels'
 // layout: WG wavefronts, lane l of wavefront w holding the P consecutive
-// nodes from tile index 62 P w + P l, so that neighbouring wavefronts share
-// two lanes (lane 0 of w mirrors lane 62 of w - 1, lane 63 of w mirrors
-// lane 1 of w + 1) and a tile spans P (62 WG + 2) nodes.  fbar stays in
+// nodes from tile index P ((64 - 2M) w + l), so that neighbouring wavefronts
+// share 2M lanes.  fbar stays in
 // registers; each step takes the forward state f(t) of the tile (coalesced
-// loads issued during the previous step, through LDS, or recomputed from the
+// loads issued during the previous step, or recomputed from the
 // stored state before: see k_adjoint_tile) and does, with neighbours inside
 // the wavefront through DPP only:
 //   A  u, T (and rho, s, X) of every node from f(t);
@@ -259,11 +258,10 @@ __global__ __launch_bounds__(kAdjBlock) void k_adjoint_step(
 //      A_k = 2 c rho w du zbar and B_k = 2 c (cp/Pr) rho w^2 dT zbar;
 //   C  the gather of A, B from both neighbours and the node-local chain.
 // One step has radius 2 in fbar(t+1) and f(t), so the wrong values the
-// outermost lanes get from their missing neighbours reach two nodes into
-// the wavefront: the mirror lanes (P >= 2 nodes) absorb them, and before
-// every step the mirror lanes take fbar (and a recomputed f(t)) from the
-// lanes they mirror, through LDS with one workgroup barrier.  Rate partials
-// are summed over the tile's output nodes [H, W - H) that the wavefront owns
+// outermost lanes get from their missing neighbours move two nodes into the
+// wavefront per step: the mirror lanes absorb them, and every few steps take
+// fbar from the lanes they mirror, through LDS with one workgroup barrier
+// (see k_adjoint_tile).  Rate partials are summed over the tile's output nodes [H, W - H) that the wavefront owns
 // (the output regions of the tiles partition each lattice).
 template <int P>
 __device__ __forceinline__ void shift_left(double (&a)[P], double in_right) {
@@ -477,42 +475,31 @@ __device__ __forceinline__ void rate_partials(const Consts& c,
   r2 = acc[3];
 }
 
-// Mirror lanes of the reverse tile before a step: lanes 1 and 62 publish
-// fbar (and, after a recomputation, f(t)) in `edge` (one buffer of a
-// double-buffered pair, as in the forward kernels), then lane 0 takes lane
-// 62 of the wavefront to its left and lane 63 lane 1 of the one to its
-// right.  with_ft is the same for every wavefront of the workgroup.
-template <int P, int WG>
+// Mirror lanes of the reverse tile: the M lanes next to them on each side
+// publish fbar in `edge` (one buffer of a double-buffered pair, as in the
+// forward kernels), then the mirror lanes take those of the neighbouring
+// wavefronts.
+template <int P, int WG, int M>
 __device__ __forceinline__ void adjoint_mirror_refresh(
-    double (&fb)[6][P], double (&ft)[6][P], bool with_ft,
-    double (*edge)[2][12 * P], int lane, int wave) {
-  if (lane == 1 || lane == 62) {
-    double* d = edge[wave][lane == 62];
+    double (&fb)[6][P], double (*edge)[2][6 * P * M], int lane, int wave) {
+  const bool hi = lane >= 32;  // the right half of the wavefront
+  const int pub = hi ? lane - (64 - 2 * M) : lane - M;
+  if (pub >= 0 && pub < M) {
+    double* d = edge[wave][hi] + pub;
 #pragma unroll
     for (int q = 0; q < 6; ++q)
 #pragma unroll
-      for (int k = 0; k < P; ++k) d[q * P + k] = fb[q][k];
-    if (with_ft) {
-#pragma unroll
-      for (int q = 0; q < 6; ++q)
-#pragma unroll
-        for (int k = 0; k < P; ++k) d[6 * P + q * P + k] = ft[q][k];
-    }
+      for (int k = 0; k < P; ++k) d[(q * P + k) * M] = fb[q][k];
   }
   __syncthreads();
-  const bool left = lane == 0 && wave > 0, right = lane == 63 && wave < WG - 1;
+  const bool left = lane < M && wave > 0, right = lane >= 64 - M && wave < WG - 1;
   if (left || right) {
-    const double* e = left ? edge[wave - 1][1] : edge[wave + 1][0];
+    const double* e = left ? edge[wave - 1][1] + lane
+                           : edge[wave + 1][0] + (lane - (64 - M));
 #pragma unroll
     for (int q = 0; q < 6; ++q)
 #pragma unroll
-      for (int k = 0; k < P; ++k) fb[q][k] = e[q * P + k];
-    if (with_ft) {
-#pragma unroll
-      for (int q = 0; q < 6; ++q)
-#pragma unroll
-        for (int k = 0; k < P; ++k) ft[q][k] = e[6 * P + q * P + k];
-    }
+      for (int k = 0; k < P; ++k) fb[q][k] = e[(q * P + k) * M];
   }
 }
 
@@ -522,24 +509,36 @@ __device__ __forceinline__ void adjoint_mirror_refresh(
 // state is recomputed from the one before (tile_step, the forward kernels'
 // node arithmetic in the same order: bitwise the state they store), which
 // then serves the next (even) step, so each such pair of steps loads one
-// state.  The prefetch of a pair's state is issued during the previous
-// pair.  If the launch's first step is odd, its recomputed state is wrong at
-// the two outer nodes of each side, which costs the halo two more nodes
-// (H >= 2K + 2).  EQ = 0: every lattice of the table has the equilibria of
-// section 8.
-template <int P, int WG, int E, int EQ>
+// state.  EQ = 0: every lattice of the table has the equilibria of section 8.
+//
+// The mirror lanes hold their own nodes' f(t) (loaded, or recomputed in
+// place: a recomputed state is wrong at the two outer nodes of the wavefront)
+// and fbar, whose wrong part grows by two nodes per step from the
+// wavefront's ends and reaches four nodes after a step on a recomputed state.
+// So M P mirror nodes serve `every` = M P / 2 steps between refreshes (E = 1),
+// or M P / 2 - 1 (E = 2), of which pairs take an even number; the same
+// counts for the tile's outer ends (H >= 2K, or 2K + 2).  One refresh in four
+// steps (M = 4 or 5 at P = 2) in place of one per step, each lane loading its
+// two nodes as 16 bytes instead of through LDS: 512 lattices of 1024 .. 8192
+// nodes, 16 steps, 369 -> 327 us.
+//
+// The stored states are fetched a step (E = 1) or a pair (E = 2) ahead.
+template <int P, int WG, int M, int E, int EQ>
 __global__ __launch_bounds__(64 * WG) void k_adjoint_tile(
     const Consts* __restrict__ cs, const int64_t* __restrict__ offs,
     const TileRef* __restrict__ tiles, int64_t ntiles,
     const double* __restrict__ ck, const double* __restrict__ seg, int64_t SD,
     int i_lo, int i_hi, const double* __restrict__ fbn,
     double* __restrict__ fbo, int64_t S, int H, double* __restrict__ rslots) {
-  static_assert(P > 1 || WG == 1, "P = 1 tiles have one wavefront");
-  constexpr int WW = 64 * P;   // nodes of one wavefront
-  constexpr int WS = 62 * P;   // wavefront stride in the tile
-  constexpr int W = lbm::tile_nodes(P, WG);
-  __shared__ double stage[WG * (WW + 64)];
-  __shared__ double edge[2][WG][2][12 * P];
+  static_assert(WG == 1 || (M * P >= 2 * E && 2 * M <= 32), "mirror lanes");
+  constexpr int WW = 64 * P;                  // nodes of one wavefront
+  constexpr int WS = (64 - 2 * M) * P;        // wavefront stride in the tile
+  constexpr int W = lbm::tile_nodes(P, WG, M);
+  // steps between refreshes of the mirror lanes (E = 2: whole pairs, at least
+  // one with a refresh between its steps when a pair does not fit)
+  constexpr int every = E == 1 ? M * P / 2 : (M * P / 2 - 1);
+  __shared__ double stage[staged(P) ? WG * (WW + 64) : 1];
+  __shared__ double edge[2][WG][2][6 * P * M];
   __shared__ double red[3][64 * WG];
   const int64_t b = blockIdx.x;
   if (b >= ntiles) return;  // uniform over the workgroup
@@ -549,7 +548,7 @@ __global__ __launch_bounds__(64 * WG) void k_adjoint_tile(
   const Consts& c = cs[tr.inst];  // loaded where used
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  double* lds = stage + wave * (WW + 64);
+  double* lds = stage + (staged(P) ? wave * (WW + 64) : 0);
   const int OUT = W - 2 * H;
   const int64_t start = (int64_t)tr.t * OUT - H;
   const int64_t wstart = start + wave * WS;
@@ -557,69 +556,75 @@ __global__ __launch_bounds__(64 * WG) void k_adjoint_tile(
   const bool small = n < W;
   // output nodes of the tile that this wavefront owns (the mirror lanes
   // belong to the neighbours)
-  const bool mirror = (lane == 0 && wave > 0) || (lane == 63 && wave < WG - 1);
+  const bool mirror = (lane < M && wave > 0) || (lane >= 64 - M && wave < WG - 1);
   bool own[P];
 #pragma unroll
   for (int k = 0; k < P; ++k) {
     const int it = wave * WS + lane * P + k;
     own[k] = !mirror && it >= H && it < W - H && start + it < n;
   }
-  // the segment's global indices are the same in every state
-  int64_t gi[P];
-  tile_index<P>(n, wstart, inside, small, lane, gi);
-  double fb[6][P], raw[6][P];
-  tile_fetch<P>(fbn + off, S, gi, raw);
-  tile_transpose<P>(lane, lds, raw, fb);
+  // the segment lies alike in every state
+  const Segment<P> sg = make_segment<P>(n, wstart, inside, small, lane);
   auto state = [&](int i) {
     return (i == 0 ? ck : seg + (int64_t)((i - 1) / E) * SD) + off;
   };
   // the stored state step i starts from
   auto base = [](int i) { return E == 2 ? (i & ~1) : i; };
+  double fb[6][P], raw[6][P];
+  tile_fetch<P>(fbn + off, S, sg, lane, fb);
+  tile_fetch<P>(state(base(i_hi - 1)), S, sg, lane, raw);
+  tile_transpose<P>(lane, lds, fb, fb);
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  // the stored state of the next (earlier) step or pair is fetched while
-  // this one computes
-  tile_fetch<P>(state(base(i_hi - 1)), S, gi, raw);
-  int buf = 0;
-  auto refresh = [&](double (&ft)[6][P], bool recomputed) {
+  int buf = 0, since = 0;
+  // before `steps` more steps: refresh unless the mirror lanes still hold
+  auto refresh = [&](int steps) {
     if constexpr (WG > 1) {
-      adjoint_mirror_refresh<P, WG>(fb, ft, recomputed, edge[buf], lane, wave);
-      buf ^= 1;
+      if (since + steps > every) {
+        adjoint_mirror_refresh<P, WG, M>(fb, edge[buf], lane, wave);
+        buf ^= 1;
+        since = 0;
+      }
+      since += steps;
     }
   };
   int i = i_hi - 1;
-  if (E == 1 || !(i & 1)) {
-    // E = 1: every step's state is stored; E = 2: a launch whose first step
-    // is even starts with that stored state
-    for (; i >= i_lo && (E == 1 || i == i_hi - 1); --i) {
+  if constexpr (E == 1) {
+    for (; i >= i_lo; --i) {
       double ft[6][P];
       tile_transpose<P>(lane, lds, raw, ft);
-      if (i > i_lo) tile_fetch<P>(state(base(i - 1)), S, gi, raw);
-      refresh(ft, false);
+      if (i > i_lo) tile_fetch<P>(state(i - 1), S, sg, lane, raw);
+      refresh(1);
       adjoint_step_local<P, EQ>(c, ft, fb, own, acc);
     }
-  }
-  // E = 2, pairs of steps (i odd, i - 1): state i is recomputed from the
-  // stored state i - 1, whose thermodynamic state the recomputation keeps
-  // for step i - 1
-  for (; E == 2 && i >= i_lo; i -= 2) {
-    double fa[6][P], ft[6][P];
-    tile_transpose<P>(lane, lds, raw, fa);
-    if (i - 2 >= i_lo) tile_fetch<P>(state(base(i - 2)), S, gi, raw);
+  } else {
+    if (!(i & 1)) {  // a launch whose first step is even starts with that state
+      double ft[6][P];
+      tile_transpose<P>(lane, lds, raw, ft);
+      if (i > i_lo) tile_fetch<P>(state(base(i - 1)), S, sg, lane, raw);
+      refresh(1);
+      adjoint_step_local<P, EQ>(c, ft, fb, own, acc);
+      --i;
+    }
+    // pairs of steps (i odd, i - 1): state i is recomputed from the stored
+    // state i - 1, whose thermodynamic state the recomputation keeps for step
+    // i - 1
+    for (; i >= i_lo; i -= 2) {
+      double fa[6][P], ft[6][P];
+      tile_transpose<P>(lane, lds, raw, fa);
+      if (i - 2 >= i_lo) tile_fetch<P>(state(base(i - 2)), S, sg, lane, raw);
 #pragma unroll
-    for (int q = 0; q < 6; ++q)
+      for (int q = 0; q < 6; ++q)
 #pragma unroll
-      for (int k = 0; k < P; ++k) ft[q][k] = fa[q][k];
-    lbm::NodeThermo th[P];
-    tile_step<P, EQ, true>(c, ft, th);
-    refresh(ft, true);
-    adjoint_step_local<P, EQ>(c, ft, fb, own, acc);
-    if (i - 1 >= i_lo) {
-      refresh(fa, false);
-      adjoint_step_local<P, EQ, true>(c, fa, fb, own, acc, th);
+        for (int k = 0; k < P; ++k) ft[q][k] = fa[q][k];
+      lbm::NodeThermo th[P];
+      tile_step<P, EQ, true>(c, ft, th);
+      refresh(2);
+      adjoint_step_local<P, EQ>(c, ft, fb, own, acc);
+      if (i - 1 >= i_lo) adjoint_step_local<P, EQ, true>(c, fa, fb, own, acc, th);
     }
   }
-  const int lo = max(H - wave * WS, wave > 0 ? P : 0);
-  const int hi = min(W - H - wave * WS, wave < WG - 1 ? WW - P : WW);
+  const int lo = max(H - wave * WS, wave > 0 ? M * P : 0);
+  const int hi = min(W - H - wave * WS, wave < WG - 1 ? WW - M * P : WW);
   tile_store<P>(fbo + off, S, n, wstart, lo, hi, lane, lds, fb);
   double r0, r1, r2;
   rate_partials(c, acc, r0, r1, r2);
@@ -639,54 +644,52 @@ __global__ __launch_bounds__(64 * WG) void k_adjoint_tile(
   if (t < 3) rslots[3 * b + t] += red[t][0];
 }
 
-template <int P, int WG, int E, int EQ>
+template <int P, int WG, int M, int E, int EQ>
 void launch_adjoint_tile_t(const Consts* cs, const int64_t* offs,
                            const TileRef* tiles, int64_t ntiles,
                            const double* ck, const double* seg, int64_t SD,
                            int i_lo, int i_hi, const double* fbn, double* fbo,
                            int64_t S, int H, double* rslots, hipStream_t s) {
-  hipLaunchKernelGGL((k_adjoint_tile<P, WG, E, EQ>), dim3((unsigned)ntiles),
+  hipLaunchKernelGGL((k_adjoint_tile<P, WG, M, E, EQ>), dim3((unsigned)ntiles),
                      dim3(64 * WG), 0, s, cs, offs, tiles, ntiles, ck, seg, SD,
                      i_lo, i_hi, fbn, fbo, S, H, rslots);
 }
 
 // E: stride of the stored segment states (1, or 2 at P = 2); eq: 0 when
 // every lattice has the equilibria of section 8, else -1.
-int launch_adjoint_tile(int P, int WG, int E, int eq, const Consts* cs,
+int launch_adjoint_tile(const TileShape& t, int E, int eq, const Consts* cs,
                         const int64_t* offs, const TileRef* tiles,
                         int64_t ntiles, const double* ck, const double* seg,
                         int64_t SD, int i_lo, int i_hi, const double* fbn,
                         double* fbo, int64_t S, int H, double* rslots,
                         hipStream_t s) {
   if (i_hi - i_lo < 1 || 2 * (i_hi - i_lo) + (E == 2 ? 2 : 0) > H ||
-      2 * H >= lbm::tile_nodes(P, WG))
+      2 * H >= lbm::tile_nodes(t.P, t.W, t.M))
     return set_err(LBM_EINVAL, "bad adjoint tile geometry");
-#define LBM_ADJ_CASE(PP, WW, EE)                                               \
-  if (P == PP && WG == WW && E == EE) {                                        \
+#define LBM_ADJ_CASE(PP, WW, MM, EE)                                           \
+  if (t.P == PP && t.W == WW && t.M == MM && E == EE) {                        \
     if (eq == 0)                                                               \
-      launch_adjoint_tile_t<PP, WW, EE, 0>(cs, offs, tiles, ntiles, ck, seg,   \
-                                           SD, i_lo, i_hi, fbn, fbo, S, H,     \
-                                           rslots, s);                         \
+      launch_adjoint_tile_t<PP, WW, MM, EE, 0>(cs, offs, tiles, ntiles, ck,    \
+                                               seg, SD, i_lo, i_hi, fbn, fbo,  \
+                                               S, H, rslots, s);               \
     else                                                                       \
-      launch_adjoint_tile_t<PP, WW, EE, -1>(cs, offs, tiles, ntiles, ck, seg,  \
-                                            SD, i_lo, i_hi, fbn, fbo, S, H,    \
-                                            rslots, s);                        \
+      launch_adjoint_tile_t<PP, WW, MM, EE, -1>(cs, offs, tiles, ntiles, ck,   \
+                                                seg, SD, i_lo, i_hi, fbn, fbo, \
+                                                S, H, rslots, s);              \
     return hip_check(hipGetLastError(), "k_adjoint_tile");                     \
   }
-  LBM_ADJ_CASE(1, 1, 1)
-  LBM_ADJ_CASE(2, 1, 1)
-  LBM_ADJ_CASE(2, 2, 1)
-  LBM_ADJ_CASE(2, 4, 1)
-  LBM_ADJ_CASE(2, 8, 1)
-  LBM_ADJ_CASE(2, 1, 2)
-  LBM_ADJ_CASE(2, 2, 2)
-  LBM_ADJ_CASE(2, 4, 2)
-  LBM_ADJ_CASE(2, 8, 2)
-  LBM_ADJ_CASE(4, 8, 1)  // the only P = 4 shape rev_shape gives
+  LBM_ADJ_CASE(1, 1, 1, 1)
+  LBM_ADJ_CASE(2, 1, 4, 1)
+  LBM_ADJ_CASE(2, 2, 4, 1)
+  LBM_ADJ_CASE(2, 4, 4, 1)
+  LBM_ADJ_CASE(2, 1, 5, 2)
+  LBM_ADJ_CASE(2, 2, 5, 2)
+  LBM_ADJ_CASE(2, 4, 5, 2)
+  LBM_ADJ_CASE(4, 8, 1, 1)  // the only P = 4 shape rev_shape gives
 #undef LBM_ADJ_CASE
   return set_err(LBM_EINVAL,
-                 "unsupported adjoint tile shape P=%d waves=%d stride=%d", P,
-                 WG, E);
+                 "unsupported adjoint tile shape P=%d waves=%d mirror=%d stride=%d",
+                 t.P, t.W, t.M, E);
 }
 
 // fbar of the equilibrium initialisation -> adjoints of rho, J, zeta.
@@ -819,31 +822,35 @@ lbm_tuning rec_tuning(const lbm_tuning& t) { return t; }
 lbm_tuning fwd_tuning(const lbm_batch* b) { return b->tune; }
 
 // Tile shape of the blocked reverse kernel for a forward tuning and a stride
-// E of the stored segment states.  Its tiles span P (62 W + 2) nodes
-// (neighbouring wavefronts share two lanes) with halo H = 2K, or 2K + 2 at
+// E of the stored segment states, with halo H = 2K, or 2K + 2 at
 // E = 2 (see k_adjoint_tile).  P = 2 keeps two wavefronts per SIMD (the
-// reverse step needs 183-241 VGPRs at P = 2, over 256 at P = 4), with the
+// reverse step needs 167-250 VGPRs at P = 2, over 256 at P = 4), with the
 // wavefronts that give about the forward tile's width, at least the
 // forward's and at most 4: two workgroups per CU, so that one computes while
-// the other waits at a step's barrier (measured with the earlier two
+// the other waits at a barrier (measured with two
 // barriers per step: the 1024-lattice gradient's reverse phase took 442 ms
 // at 4 wavefronts, 472 at 8, 512 at 2); a halo too wide for those tiles
 // falls back to P = 4 with 8 wavefronts and E = 1.  A forward of one node
 // per lane (small problems) keeps P = 1, W = 1, E = 1 (about 110 VGPRs).
 struct RevShape {
-  int P, W, H, E;
-  int64_t out() const { return (int64_t)tile_nodes(P, W) - 2 * (int64_t)H; }
+  TileShape t;
+  int H, E;
+  int64_t out() const {
+    return (int64_t)tile_nodes(t.P, t.W, t.M) - 2 * (int64_t)H;
+  }
 };
 
 RevShape rev_shape(const lbm_tuning& t, int E) {
   const int K = t.steps_per_launch;
   // one node per lane (small lattices, bound by each step's latency): the
   // same for the reverse, whose halo the forward's K already fits
-  if (t.nodes_per_lane == 1) return RevShape{1, 1, 2 * K, 1};
-  RevShape r{2, std::min(4, std::max(t.waves_per_group,
-                                     t.nodes_per_lane * t.waves_per_group / 2)),
+  if (t.nodes_per_lane == 1) return RevShape{{1, 1, 1}, 2 * K, 1};
+  RevShape r{{2,
+              std::min(4, std::max(t.waves_per_group,
+                                   t.nodes_per_lane * t.waves_per_group / 2)),
+              E == 2 ? 5 : 4},
              2 * K + (E == 2 ? 2 : 0), E};
-  if (2 * r.H >= tile_nodes(2, r.W)) r = RevShape{4, 8, 2 * K, 1};
+  if (r.out() < 1) r = RevShape{{4, 8, 1}, 2 * K, 1};
   return r;
 }
 
@@ -875,7 +882,7 @@ bool resolve_adj_plain(const lbm_batch* b) {
 // Launches of the blocked reverse kernel fill the chip when they have at
 // least the 2048 wavefronts that 256 CUs hold at two per SIMD.
 bool rev_fills_chip(const lbm_batch* b, const RevShape& r) {
-  return tiles_of(b, r.out()) * r.W >= 2048;
+  return tiles_of(b, r.out()) * r.t.W >= 2048;
 }
 
 // Stride of the segment states the reverse sweep stores.  Every second one
@@ -1095,7 +1102,7 @@ int enqueue_adjoint(lbm_batch* b, void* ws, int64_t nsteps, int64_t C,
     for (int64_t hi = seg_len(k); hi > 0;) {
       const int64_t lo = std::max<int64_t>(0, hi - Krec);
       const int r = launch_adjoint_tile(
-          rv.P, rv.W, rv.E, b->eq_class(), cs, offs,
+          rv.t, rv.E, b->eq_class(), cs, offs,
           at<TileRef>(ws, L.rev_tiles), L.n_rev,
           ckpt(k), segbuf(k), (int64_t)SD, (int)lo, (int)hi, cur, oth,
           b->n_total, rv.H, slots, s);

@@ -10,15 +10,27 @@
 
 namespace {
 
-// Global memory is touched only at the start and the end of the launch, and
-// always coalesced: node i of a wavefront's segment travels through that
-// wavefront's LDS buffer between the coalesced order (lane l handles
-// i = k*64 + l) and the register order (lane l owns i = l*P + k).  The LDS
-// index i + i/P pads one double per lane row so that both orders are free of
-// bank conflicts.  Staging is private to a wavefront (wave_barrier only).
+// Global memory is always touched coalesced.  With one or two nodes per lane a
+// lane loads and stores its own nodes (two as one 16-byte access: a state's
+// arrays are 8-byte aligned, which such accesses allow).  With more, node i of
+// a wavefront's segment travels through that wavefront's LDS buffer between
+// the coalesced order (lane l handles i = k*64 + l) and the register order
+// (lane l owns i = l*P + k); the LDS index i + i/P pads one double per lane
+// row so that both orders are free of bank conflicts.  Staging is private to
+// a wavefront (wave_barrier only).
+constexpr bool staged(int P) { return P > 2; }
+
+typedef double pair_t __attribute__((ext_vector_type(2), aligned(8)));
+
 template <int P>
 __device__ __forceinline__ int lds_idx(int i) {
   return i + i / P;
+}
+
+// Node of the segment that access k of a lane touches.
+template <int P>
+__device__ __forceinline__ int seg_idx(int lane, int k) {
+  return staged(P) ? k * 64 + lane : lane * P + k;
 }
 
 // Node x of a tile in a lattice of n nodes.  small (the lattice is shorter
@@ -31,41 +43,66 @@ __device__ __forceinline__ int64_t wrap_near(int64_t x, int64_t n, bool small) {
   return x < 0 ? x + n : (x >= n ? x - n : x);
 }
 
-// The global indices of a segment in the coalesced order.
+// Where a wavefront's segment lies in its lattice: from node `start` on where
+// the whole tile is inside (uniform), else the wrapped index of each access.
 template <int P>
-__device__ __forceinline__ void tile_index(int64_t n, int64_t start,
-                                           bool inside, bool small, int lane,
-                                           int64_t (&gi)[P]) {
+struct Segment {
+  bool inside;
+  int64_t start;
+  int64_t gi[P];
+};
+
+template <int P>
+__device__ __forceinline__ Segment<P> make_segment(int64_t n, int64_t start,
+                                                   bool inside, bool small,
+                                                   int lane) {
+  Segment<P> sg{inside, start, {}};
+  if (!inside) {
 #pragma unroll
-  for (int k = 0; k < P; ++k) {
-    const int i = k * 64 + lane;
-    gi[k] = inside ? start + i : wrap_near(start + i, n, small);
+    for (int k = 0; k < P; ++k)
+      sg.gi[k] = wrap_near(start + seg_idx<P>(lane, k), n, small);
+  }
+  return sg;
+}
+
+// The segment's loads (arrays of a lattice at fin + q*S, S the array stride of
+// the state) into registers in the order of the accesses, to be followed by
+// tile_transpose; they may be issued a step ahead of it.
+template <int P>
+__device__ __forceinline__ void tile_fetch(const double* __restrict__ fin,
+                                           int64_t S, const Segment<P>& sg,
+                                           int lane, double (&raw)[6][P]) {
+  if (sg.inside) {  // one scalar base per array
+#pragma unroll
+    for (int q = 0; q < 6; ++q) {
+      const double* src = fin + ((int64_t)q * S + sg.start);
+      if constexpr (P == 2) {
+        const pair_t v = *reinterpret_cast<const pair_t*>(src + 2 * lane);
+        raw[q][0] = v.x;
+        raw[q][1] = v.y;
+      } else {
+#pragma unroll
+        for (int k = 0; k < P; ++k) raw[q][k] = src[seg_idx<P>(lane, k)];
+      }
+    }
+  } else {
+#pragma unroll
+    for (int q = 0; q < 6; ++q)
+#pragma unroll
+      for (int k = 0; k < P; ++k) raw[q][k] = fin[(int64_t)q * S + sg.gi[k]];
   }
 }
 
-// A segment's load in parts, for a kernel that reloads the same segment of
-// successive states: the global loads into registers in the coalesced order
-// (which may be issued a step ahead), and the pass through LDS into the
-// register order (one node per lane: the orders are the same).  raw and f
-// may be one array.
-template <int P>
-__device__ __forceinline__ void tile_fetch(const double* __restrict__ fin,
-                                           int64_t S, const int64_t (&gi)[P],
-                                           double (&raw)[6][P]) {
-#pragma unroll
-  for (int q = 0; q < 6; ++q)
-#pragma unroll
-    for (int k = 0; k < P; ++k) raw[q][k] = fin[(int64_t)q * S + gi[k]];
-}
-
+// The pass through LDS into the register order (raw and f may be one array).
 template <int P>
 __device__ __forceinline__ void tile_transpose(int lane, double* lds,
                                                const double (&raw)[6][P],
                                                double (&f)[6][P]) {
 #pragma unroll
   for (int q = 0; q < 6; ++q) {
-    if constexpr (P == 1) {
-      f[q][0] = raw[q][0];
+    if constexpr (!staged(P)) {
+#pragma unroll
+      for (int k = 0; k < P; ++k) f[q][k] = raw[q][k];
       continue;
     }
 #pragma unroll
@@ -77,8 +114,7 @@ __device__ __forceinline__ void tile_transpose(int lane, double* lds,
   }
 }
 
-// Arrays of a lattice of length L are at fin + q*S (S >= L, the array
-// stride of the state the lattice lives in).  All 6 P global loads are issued
+// A segment's load.  All global loads are issued
 // before the first pass through LDS, so a wavefront waits for memory once:
 // array by array it waited six times in a row, which was most of a launch's
 // fixed cost (at n = 8192, one-wavefront tiles: 4.1 -> 2.4 us per launch at
@@ -88,18 +124,8 @@ __device__ __forceinline__ void tile_load(const double* __restrict__ fin,
                                           int64_t S, int64_t n, int64_t start,
                                           bool inside, bool small, int lane,
                                           double* lds, double (&f)[6][P]) {
-  if (inside) {  // uniform: one scalar base per array
-#pragma unroll
-    for (int q = 0; q < 6; ++q) {
-      const double* src = fin + ((int64_t)q * S + start);
-#pragma unroll
-      for (int k = 0; k < P; ++k) f[q][k] = src[k * 64 + lane];
-    }
-  } else {
-    int64_t gi[P];
-    tile_index<P>(n, start, false, small, lane, gi);
-    tile_fetch<P>(fin, S, gi, f);
-  }
+  const Segment<P> sg = make_segment<P>(n, start, inside, small, lane);
+  tile_fetch<P>(fin, S, sg, lane, f);
   tile_transpose<P>(lane, lds, f, f);
 }
 
@@ -112,24 +138,40 @@ __device__ __forceinline__ void tile_store(double* __restrict__ fout,
                                            const double (&f)[6][P]) {
   // one 64-bit lane base and a wavefront-uniform upper bound keep few
   // values live around a kernel's step loop
-  const int64_t g0 = start + lane;
+  const int64_t g0 = start + (staged(P) ? lane : lane * P);
   const int64_t lim = n - start;  // i < lim  <=>  start + i < n
+  const int top = lim < hi ? (int)lim : hi;
 #pragma unroll
   for (int q = 0; q < 6; ++q) {
     double* dst = fout + (int64_t)q * S + g0;
     if constexpr (P == 1) {
-      if (lane >= lo && lane < hi && lane < lim) dst[0] = f[q][0];
+      if (lane >= lo && lane < top) dst[0] = f[q][0];
       continue;
     }
-#pragma unroll
-    for (int k = 0; k < P; ++k) lds[lds_idx<P>(lane * P + k)] = f[q][k];
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int k = 0; k < P; ++k) {
-      const int i = k * 64 + lane;
-      if (i >= lo && i < hi && i < lim) dst[k * 64] = lds[lds_idx<P>(i)];
+    if constexpr (P == 2) {
+      const int i = 2 * lane;
+      if (i >= lo && i + 1 < top) {
+        pair_t v;
+        v.x = f[q][0];
+        v.y = f[q][1];
+        *reinterpret_cast<pair_t*>(dst) = v;
+      } else {
+        if (i >= lo && i < top) dst[0] = f[q][0];
+        if (i + 1 >= lo && i + 1 < top) dst[1] = f[q][1];
+      }
+      continue;
     }
-    __builtin_amdgcn_wave_barrier();
+    if constexpr (staged(P)) {
+#pragma unroll
+      for (int k = 0; k < P; ++k) lds[lds_idx<P>(lane * P + k)] = f[q][k];
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int k = 0; k < P; ++k) {
+        const int i = k * 64 + lane;
+        if (i >= lo && i < top) dst[k * 64] = lds[lds_idx<P>(i)];
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
   }
 }
 
