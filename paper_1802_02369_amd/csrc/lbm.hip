@@ -383,21 +383,6 @@ __device__ __forceinline__ void mirror_refresh(double (&f)[6][P],
   }
 }
 
-// Active wavefronts of a tile that starts at lattice index `start` (halo H)
-// in a lattice of n nodes: the fewest of the WG whose span
-// P((64 - 2M) nw + 2M) still covers the nodes the tile stores plus both halos.
-// Only a lattice's last tile, or a lattice shorter than one tile, needs fewer
-// than WG.
-template <int P, int WG, int M>
-__device__ __forceinline__ int active_waves(int64_t n, int64_t start, int H) {
-  constexpr int WS = (64 - 2 * M) * P;
-  const int64_t store = n - (start + H);  // nodes from the tile's first output
-  const int64_t need = store + 2 * H - 2 * M * P;  // beyond the mirror lanes
-  if (need >= (int64_t)WS * WG) return WG;
-  const int nw = ((int)need + WS - 1) / WS;
-  return nw < 1 ? 1 : nw;
-}
-
 // Tile t of a lattice of n nodes (array stride S) starting at lattice index
 // `start` = t*OUT - H, OUT = tile_nodes - 2H: load, K <= H/2 steps, store of
 // the interior [H, span - H) (one step has radius 2, so K steps need
@@ -438,11 +423,18 @@ __device__ __forceinline__ void tile_run(const Consts& c,
   const int lo = max(H - wave * WS, wave > 0 ? M * P : 0);
   const int hi = min(W - H - wave * WS, wave < nw - 1 ? WW - M * P : WW);
   int since = 0, buf = 0;
+  // the next state to store and the steps up to it: counted, since dividing
+  // by `every` in each step took longer (n = 8192, P = 1, 34 steps:
+  // 18.1 -> 16.5 us)
+  int wait = every_step ? every - first % every : 0;
+  double* dst = every_step ? fout + (int64_t)(first / every) * state_stride : fout;
   for (int step = 0; step < K; ++step) {
     tile_step<P, EQ>(c, f);
-    if (every_step && (first + step + 1) % every == 0)
-      tile_store<P>(fout + (int64_t)((first + step) / every) * state_stride, S,
-                    n, wstart, lo, hi, lane, lds, f);
+    if (every_step && --wait == 0) {
+      tile_store<P>(dst, S, n, wstart, lo, hi, lane, lds, f);
+      dst += state_stride;
+      wait = every;
+    }
     if (WG > 1 && ++since == M * P / 2 && step + 1 < K) {
       mirror_refresh<P, WG, M>(f, edge[buf], lane, wave, nw);
       buf ^= 1;
@@ -1233,27 +1225,33 @@ int launch_moments(const Consts& c, const double* f, double* m, int64_t n,
   return hip_check(hipGetLastError(), "k_moments");
 }
 
-template <int P, int WG, int M>
+// SEGMENTS: the shape also stores checkpoint segments (state_stride > 0)
+template <int P, int WG, int M, bool SEGMENTS>
 static void launch_batch_t(const Consts* cs, const int64_t* offs,
                            const TileRef* tiles, int64_t ntiles,
                            const double* fin, double* fout, int64_t S, int H,
                            int K, int64_t state_stride, int first, int every,
                            int eq, hipStream_t s) {
   const dim3 grid((unsigned)ntiles), block(64 * WG);
-  if (eq == 0 && state_stride == 0)
+  if constexpr (SEGMENTS) {
+    if (state_stride != 0) {
+      if (eq == 0)
+        hipLaunchKernelGGL((k_batch_tile<P, WG, M, 0, true>), grid, block, 0, s,
+                           cs, offs, tiles, fin, fout, S, H, K, ntiles,
+                           state_stride, first, every);
+      else
+        hipLaunchKernelGGL((k_batch_tile<P, WG, M, -1, true>), grid, block, 0, s,
+                           cs, offs, tiles, fin, fout, S, H, K, ntiles,
+                           state_stride, first, every);
+      return;
+    }
+  }
+  if (eq == 0)
     hipLaunchKernelGGL((k_batch_tile<P, WG, M, 0, false>), grid, block, 0, s, cs,
                        offs, tiles, fin, fout, S, H, K, ntiles, state_stride, first,
                        every);
-  else if (eq == 0)
-    hipLaunchKernelGGL((k_batch_tile<P, WG, M, 0, true>), grid, block, 0, s, cs,
-                       offs, tiles, fin, fout, S, H, K, ntiles, state_stride, first,
-                       every);
-  else if (state_stride == 0)
-    hipLaunchKernelGGL((k_batch_tile<P, WG, M, -1, false>), grid, block, 0, s, cs,
-                       offs, tiles, fin, fout, S, H, K, ntiles, state_stride, first,
-                       every);
   else
-    hipLaunchKernelGGL((k_batch_tile<P, WG, M, -1, true>), grid, block, 0, s, cs,
+    hipLaunchKernelGGL((k_batch_tile<P, WG, M, -1, false>), grid, block, 0, s, cs,
                        offs, tiles, fin, fout, S, H, K, ntiles, state_stride, first,
                        every);
 }
@@ -1270,24 +1268,19 @@ int launch_batch_tile(const Consts* cs, const int64_t* offs,
     return set_err(LBM_EINVAL, "bad segment state numbering");
 #define LBM_BATCH_CASE(PP, WW, MM)                                            \
   if (t.P == PP && t.W == WW && t.M == MM) {                                  \
-    launch_batch_t<PP, WW, MM>(cs, offs, tiles, ntiles, fin, fout, S, H, K,   \
-                               state_stride, first, every, eq, s);            \
+    launch_batch_t<PP, WW, MM, true>(cs, offs, tiles, ntiles, fin, fout, S, H, \
+                                     K, state_stride, first, every, eq, s);   \
     return hip_check(hipGetLastError(), "k_batch_tile");                      \
   }
   LBM_TILE_SHAPES(LBM_BATCH_CASE)
 #undef LBM_BATCH_CASE
-  // the wide shapes of plan_batch, which stores no checkpoint segments
+  // of the wide shapes, only those of the recompute store segments
 #define LBM_BATCH_CASE(PP, WW, MM)                                            \
-  if (t.P == PP && t.W == WW && t.M == MM && state_stride == 0) {             \
-    const dim3 grid((unsigned)ntiles), block(64 * WW);                        \
-    if (eq == 0)                                                              \
-      hipLaunchKernelGGL((k_batch_tile<PP, WW, MM, 0, false>), grid, block,   \
-                         0, s, cs, offs, tiles, fin, fout, S, H, K, ntiles,   \
-                         state_stride, first, every);                         \
-    else                                                                      \
-      hipLaunchKernelGGL((k_batch_tile<PP, WW, MM, -1, false>), grid, block,  \
-                         0, s, cs, offs, tiles, fin, fout, S, H, K, ntiles,   \
-                         state_stride, first, every);                         \
+  if (t.P == PP && t.W == WW && t.M == MM &&                                  \
+      (state_stride == 0 || (PP <= 2 && WW <= 8))) {                          \
+    launch_batch_t<PP, WW, MM, (PP <= 2 && WW <= 8)>(                         \
+        cs, offs, tiles, ntiles, fin, fout, S, H, K, state_stride, first,     \
+        every, eq, s);                                                        \
     return hip_check(hipGetLastError(), "k_batch_tile");                      \
   }
   LBM_WIDE_SHAPES(LBM_BATCH_CASE)

@@ -479,9 +479,9 @@ __device__ __forceinline__ void rate_partials(const Consts& c,
 // publish fbar in `edge` (one buffer of a double-buffered pair, as in the
 // forward kernels), then the mirror lanes take those of the neighbouring
 // wavefronts.
-template <int P, int WG, int M>
+template <int P, int M>
 __device__ __forceinline__ void adjoint_mirror_refresh(
-    double (&fb)[6][P], double (*edge)[2][6 * P * M], int lane, int wave) {
+    double (&fb)[6][P], double (*edge)[2][6 * P * M], int lane, int wave, int nw) {
   const bool hi = lane >= 32;  // the right half of the wavefront
   const int pub = hi ? lane - (64 - 2 * M) : lane - M;
   if (pub >= 0 && pub < M) {
@@ -492,7 +492,7 @@ __device__ __forceinline__ void adjoint_mirror_refresh(
       for (int k = 0; k < P; ++k) d[(q * P + k) * M] = fb[q][k];
   }
   __syncthreads();
-  const bool left = lane < M && wave > 0, right = lane >= 64 - M && wave < WG - 1;
+  const bool left = lane < M && wave > 0, right = lane >= 64 - M && wave < nw - 1;
   if (left || right) {
     const double* e = left ? edge[wave - 1][1] + lane
                            : edge[wave + 1][0] + (lane - (64 - M));
@@ -533,13 +533,12 @@ __global__ __launch_bounds__(64 * WG) void k_adjoint_tile(
   static_assert(WG == 1 || (M * P >= 2 * E && 2 * M <= 32), "mirror lanes");
   constexpr int WW = 64 * P;                  // nodes of one wavefront
   constexpr int WS = (64 - 2 * M) * P;        // wavefront stride in the tile
-  constexpr int W = lbm::tile_nodes(P, WG, M);
   // steps between refreshes of the mirror lanes (E = 2: whole pairs, at least
   // one with a refresh between its steps when a pair does not fit)
   constexpr int every = E == 1 ? M * P / 2 : (M * P / 2 - 1);
   __shared__ double stage[staged(P) ? WG * (WW + 64) : 1];
   __shared__ double edge[2][WG][2][6 * P * M];
-  __shared__ double red[3][64 * WG];
+  __shared__ double red[3][WG];
   const int64_t b = blockIdx.x;
   if (b >= ntiles) return;  // uniform over the workgroup
   const TileRef tr = tiles[b];
@@ -549,14 +548,16 @@ __global__ __launch_bounds__(64 * WG) void k_adjoint_tile(
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   double* lds = stage + (staged(P) ? wave * (WW + 64) : 0);
-  const int OUT = W - 2 * H;
-  const int64_t start = (int64_t)tr.t * OUT - H;
+  const int64_t start = (int64_t)tr.t * (lbm::tile_nodes(P, WG, M) - 2 * H) - H;
+  const int nw = active_waves<P, WG, M>(n, start, H);
+  if (wave >= nw) return;  // uniform over the wavefront
+  const int W = lbm::tile_nodes(P, nw, M);
   const int64_t wstart = start + wave * WS;
   const bool inside = start >= 0 && start + W <= n;
   const bool small = n < W;
   // output nodes of the tile that this wavefront owns (the mirror lanes
   // belong to the neighbours)
-  const bool mirror = (lane < M && wave > 0) || (lane >= 64 - M && wave < WG - 1);
+  const bool mirror = (lane < M && wave > 0) || (lane >= 64 - M && wave < nw - 1);
   bool own[P];
 #pragma unroll
   for (int k = 0; k < P; ++k) {
@@ -580,7 +581,7 @@ __global__ __launch_bounds__(64 * WG) void k_adjoint_tile(
   auto refresh = [&](int steps) {
     if constexpr (WG > 1) {
       if (since + steps > every) {
-        adjoint_mirror_refresh<P, WG, M>(fb, edge[buf], lane, wave);
+        adjoint_mirror_refresh<P, M>(fb, edge[buf], lane, wave, nw);
         buf ^= 1;
         since = 0;
       }
@@ -624,24 +625,25 @@ __global__ __launch_bounds__(64 * WG) void k_adjoint_tile(
     }
   }
   const int lo = max(H - wave * WS, wave > 0 ? M * P : 0);
-  const int hi = min(W - H - wave * WS, wave < WG - 1 ? WW - M * P : WW);
+  const int hi = min(W - H - wave * WS, wave < nw - 1 ? WW - M * P : WW);
   tile_store<P>(fbo + off, S, n, wstart, lo, hi, lane, lds, fb);
   double r0, r1, r2;
   rate_partials(c, acc, r0, r1, r2);
-  const int t = threadIdx.x;
-  red[0][t] = r0;
-  red[1][t] = r1;
-  red[2][t] = r2;
-  __syncthreads();
-  for (int m = 32 * WG; m > 0; m >>= 1) {
-    if (t < m) {
-      red[0][t] += red[0][t + m];
-      red[1][t] += red[1][t + m];
-      red[2][t] += red[2][t + m];
-    }
-    __syncthreads();
+  r0 = wave_sum(r0);
+  r1 = wave_sum(r1);
+  r2 = wave_sum(r2);
+  if (lane == 0) {
+    red[0][wave] = r0;
+    red[1][wave] = r1;
+    red[2][wave] = r2;
   }
-  if (t < 3) rslots[3 * b + t] += red[t][0];
+  __syncthreads();
+  const int t = threadIdx.x;
+  if (t < 3) {
+    double a = red[t][0];
+    for (int w = 1; w < nw; ++w) a += red[t][w];
+    rslots[3 * b + t] += a;
+  }
 }
 
 template <int P, int WG, int M, int E, int EQ>
@@ -679,6 +681,8 @@ int launch_adjoint_tile(const TileShape& t, int E, int eq, const Consts* cs,
     return hip_check(hipGetLastError(), "k_adjoint_tile");                     \
   }
   LBM_ADJ_CASE(1, 1, 1, 1)
+  LBM_ADJ_CASE(1, 4, 8, 1)
+  LBM_ADJ_CASE(1, 8, 8, 1)
   LBM_ADJ_CASE(2, 1, 4, 1)
   LBM_ADJ_CASE(2, 2, 4, 1)
   LBM_ADJ_CASE(2, 4, 4, 1)
@@ -815,12 +819,6 @@ struct AdjLayout {
       rslots, scratch, pp, ckpt, seg, total;
 };
 
-// The recompute runs with the forward tile shape.
-lbm_tuning rec_tuning(const lbm_tuning& t) { return t; }
-
-// Tile shape of the checkpointed forward run.
-lbm_tuning fwd_tuning(const lbm_batch* b) { return b->tune; }
-
 // Tile shape of the blocked reverse kernel for a forward tuning and a stride
 // E of the stored segment states, with halo H = 2K, or 2K + 2 at
 // E = 2 (see k_adjoint_tile).  P = 2 keeps two wavefronts per SIMD (the
@@ -834,7 +832,7 @@ lbm_tuning fwd_tuning(const lbm_batch* b) { return b->tune; }
 // per lane (small problems) keeps P = 1, W = 1, E = 1 (about 110 VGPRs).
 struct RevShape {
   TileShape t;
-  int H, E;
+  int K, H, E;
   int64_t out() const {
     return (int64_t)tile_nodes(t.P, t.W, t.M) - 2 * (int64_t)H;
   }
@@ -844,13 +842,13 @@ RevShape rev_shape(const lbm_tuning& t, int E) {
   const int K = t.steps_per_launch;
   // one node per lane (small lattices, bound by each step's latency): the
   // same for the reverse, whose halo the forward's K already fits
-  if (t.nodes_per_lane == 1) return RevShape{{1, 1, 1}, 2 * K, 1};
+  if (t.nodes_per_lane == 1) return RevShape{{1, 1, 1}, K, 2 * K, 1};
   RevShape r{{2,
               std::min(4, std::max(t.waves_per_group,
                                    t.nodes_per_lane * t.waves_per_group / 2)),
               E == 2 ? 5 : 4},
-             2 * K + (E == 2 ? 2 : 0), E};
-  if (r.out() < 1) r = RevShape{{4, 8, 1}, 2 * K, 1};
+             K, 2 * K + (E == 2 ? 2 : 0), E};
+  if (r.out() < 1) r = RevShape{{4, 8, 1}, K, 2 * K, 1};
   return r;
 }
 
@@ -900,32 +898,89 @@ int resolve_every(const lbm_batch* b, bool plain) {
   return rev_fills_chip(b, r) ? 2 : 1;
 }
 
-// The reverse sweep's settings: one-step kernel or the blocked one with its
-// tile shape and state stride, and whether the sweep overlaps the recompute
-// of one checkpoint segment with the reverse steps of the next (two buffers
-// of segment states): with the blocked kernel when its launches leave most
-// of the chip idle, as on small lattices bound by launch latency.  A launch
-// that fills the chip gains nothing from a second stream (measured on the
-// 1024-lattice gradient) and the second buffer would cost its states again.
+// The library's own shapes of a sweep with segments of C steps whose stored
+// states have stride E.  The reverse kernel takes 0.3 us per step and 0.085
+// per node of a lane and wavefront of a tile, one or two tiles on a compute
+// unit side by side, and 6 us per launch: one node per lane while there is a
+// compute unit for every tile, two once there is not, and launches that split
+// the segment evenly.  The recompute runs as long launches on the like shape,
+// (2, 4, 1) where it stores every second state.  Per step of the
+// whole reverse sweep, on the shapes of the default tunings and here: 1.88 and
+// 1.42 us at n = 8192 (segments of 100), 2.81 and 1.94 at 30000 (50), 4.57 and
+// 3.15 at 100003 (40), 17.9 and 16.4 at 1 M (50), 88 and 72 for 512 lattices
+// of 2048 .. 16384 nodes (16).  One stream does: beside these launches a
+// second one for the recompute gained nothing at 8192 nodes and lost 3 to
+// 15 % elsewhere.
+AdjShapes own_shapes(const lbm_batch* b, int64_t C, int E) {
+  struct Shape {
+    TileShape t;
+    int E;
+  };
+  static const Shape shapes[] = {
+      {{1, 4, 8}, 1}, {{1, 8, 8}, 1}, {{2, 4, 4}, 1}, {{2, 4, 5}, 2}};
+  AdjShapes a{plan_tiles(b->offsets, C), {}, {}};
+  double least = INFINITY;
+  for (const Shape& sh : shapes) {
+    if (sh.E != E) continue;
+    const int64_t nodes = tile_nodes(sh.t.P, sh.t.W, sh.t.M) - 4 * (E - 1);
+    const int64_t top = (nodes - kPlanMinOut) / 4;
+    for (int64_t j = (C + top - 1) / top, K = 0;; ++j) {
+      K = (C + j - 1) / j;
+      double g = (double)tiles_of(b, nodes - 4 * K) / 256.0;
+      if (g < 2) g = std::ceil(g);
+      const double us =
+          (6.0 + 96.0 * (double)b->n_total / 5e6) * (double)j +
+          (double)C * (0.3 + 0.085 * sh.t.P * sh.t.W * g);
+      if (us < least) {
+        least = us;
+        a.rev = StepPlan{sh.t, std::max((int)K, E), 0};
+      }
+      if (K <= 8) break;
+    }
+  }
+  a.rec = a.rev;
+  if (a.rev.t.P > 1) a.rec.t = E == 2 ? TileShape{2, 4, 1} : TileShape{2, 8, 4};
+  return a;
+}
+
+// The sweep's settings: one-step kernel or the blocked one with its tile
+// shape and state stride, the shapes of the checkpointed forward and the
+// recompute, and whether the sweep overlaps the recompute of one checkpoint
+// segment with the reverse steps of the next (two buffers of segment states):
+// on the shapes of a tuning, with the blocked kernel when its launches leave
+// most of the chip idle, as on small lattices bound by launch latency.  A
+// launch that fills the chip gains nothing from a second stream (measured on
+// the 1024-lattice gradient) and the second buffer would cost its states
+// again.
 struct AdjPlan {
   bool plain, pipelined;
   RevShape rev;
+  StepPlan fwd, rec;  // the checkpointed forward and the recompute
 };
 
-AdjPlan adj_plan(const lbm_batch* b, bool plain, int every) {
-  AdjPlan p{plain, false, rev_shape(b->tune, plain ? 1 : every)};
+AdjPlan adj_plan(const lbm_batch* b, bool plain, int every, bool own, int64_t C) {
+  const int E = plain ? 1 : every;
+  if (own) {
+    const AdjShapes a = b->adj_own_ckpt == C && b->adj_own_every == E
+                            ? b->adj_own
+                            : own_shapes(b, C, E);
+    const RevShape rev{a.rev.t, a.rev.K, 2 * a.rev.K + (E == 2 ? 2 : 0), E};
+    return AdjPlan{plain, false, rev, a.fwd, a.rec};
+  }
+  const StepPlan tuned{shape_of(b->tune), b->tune.steps_per_launch, 0};
+  AdjPlan p{plain, false, rev_shape(b->tune, E), tuned, tuned};
   p.pipelined = !plain && p.rev.out() >= 1 && !rev_fills_chip(b, p.rev);
   return p;
 }
 
-// The plan of the current settings (workspace queries) and the one that
-// lbm_batch_forward_ckpt resolved (the reverse sweep and its checks).
-AdjPlan current_plan(const lbm_batch* b) {
-  const bool plain = resolve_adj_plain(b);
-  return adj_plan(b, plain, resolve_every(b, plain));
+// The plan that lbm_batch_forward_ckpt resolved (the reverse sweep and its
+// checks).
+AdjPlan resolved_plan(const lbm_batch* b, int64_t C) {
+  return adj_plan(b, b->adj_plain, b->adj_every, b->adj_auto, C);
 }
-AdjPlan resolved_plan(const lbm_batch* b) {
-  return adj_plan(b, b->adj_plain, b->adj_every);
+
+int64_t plan_out(const StepPlan& p) {
+  return tile_nodes(p.t.P, p.t.W, p.t.M) - 4 * (int64_t)p.K;
 }
 
 // Workspace layout.  The segment states come last: the other offsets do not
@@ -933,8 +988,8 @@ AdjPlan resolved_plan(const lbm_batch* b) {
 AdjLayout adj_layout(const lbm_batch* b, int64_t nsteps, int64_t C,
                      const AdjPlan& P) {
   AdjLayout L{};
-  L.n_fwd = b->count_tiles(fwd_tuning(b));
-  L.n_rec = b->count_tiles(rec_tuning(b->tune));
+  L.n_fwd = tiles_of(b, plan_out(P.fwd));
+  L.n_rec = tiles_of(b, plan_out(P.rec));
   L.n_rev = tiles_of(b, P.rev.out());
   L.n_adj = adj_tile_count(b);
   L.n_ck = nsteps > 0 ? (nsteps + C - 1) / C : 1;
@@ -990,46 +1045,41 @@ std::vector<TileRef> tile_table(const lbm_batch* b, int64_t out) {
   return v;
 }
 
-// Launches `steps` forward steps on f with ping-pong through pp (an even
-// number of launches when steps >= 2; otherwise one launch and a copy).
-int fwd_steps(lbm_batch* b, const Consts* cs, const int64_t* offs,
-              const TileRef* tiles, int64_t ntiles, double* f, double* pp,
-              int64_t steps, hipStream_t s) {
-  double* a = f;
-  double* w = pp;
-  int64_t launches = 0;
-  const lbm_tuning t = fwd_tuning(b);
-  const int H = 2 * t.steps_per_launch;
-  for (int k : split_steps(steps, t.steps_per_launch)) {
-    int rc = launch_batch_tile(cs, offs, tiles, ntiles, a, w, b->n_total,
-                               shape_of(t), H, k, b->eq_class(), s);
-    if (rc) return rc;
-    std::swap(a, w);
-    ++launches;
-  }
-  if (launches & 1)
-    return hip_check(hipMemcpyAsync(f, pp, sizeof(double) * 6 * b->n_total,
-                                    hipMemcpyDeviceToDevice, s),
-                     "hipMemcpyAsync");
-  return LBM_OK;
-}
-
 // The checkpointed forward on stream s: checkpoint k is the state at step
-// k * C, then the segment's launches.
+// k * C.  A segment's launches go from its checkpoint through f and pp in turn
+// into the next checkpoint, the last segment's into f: no state is copied but
+// the first.
 int enqueue_forward_ckpt(lbm_batch* b, void* ws, double* f, int64_t nsteps,
-                         int64_t C, const AdjLayout& L, hipStream_t s) {
-  const size_t SB = sizeof(double) * 6 * b->n_total;
+                         int64_t C, const AdjPlan& plan, const AdjLayout& L,
+                         hipStream_t s) {
+  const size_t SD = 6 * (size_t)b->n_total;
   const Consts* cs = at<Consts>(ws, L.consts);
   const int64_t* offs = at<int64_t>(ws, L.offs);
-  int rc = LBM_OK;
+  const TileRef* tiles = at<TileRef>(ws, L.fwd_tiles);
+  double* ck = at<double>(ws, L.ckpt);
+  double* pp = at<double>(ws, L.pp);
+  int rc = hip_check(hipMemcpyAsync(ck, f, sizeof(double) * SD,
+                                    hipMemcpyDeviceToDevice, s),
+                     "hipMemcpyAsync");
   for (int64_t k = 0; k < L.n_ck && !rc; ++k) {
-    rc = hip_check(hipMemcpyAsync(at<char>(ws, L.ckpt) + SB * k, f, SB,
-                                  hipMemcpyDeviceToDevice, s),
-                   "hipMemcpyAsync");
     const int64_t len = std::min(C, nsteps - k * C);
-    if (!rc && len > 0)
-      rc = fwd_steps(b, cs, offs, at<TileRef>(ws, L.fwd_tiles), L.n_fwd, f,
-                     at<double>(ws, L.pp), len, s);
+    if (len < 1) break;
+    const int64_t launches = (len + plan.fwd.K - 1) / plan.fwd.K;
+    const double* from = ck + SD * k;
+    int64_t done = 0;
+    for (int64_t i = 0; i < launches && !rc; ++i) {
+      // the steps of launch i, and its destination: with i launches to go,
+      // pp before the last one so that f is free for the result
+      const int64_t to = (i + 1) * len / launches;
+      double* dst = i + 1 < launches   ? ((launches - i) & 1 ? f : pp)
+                    : k + 1 < L.n_ck ? ck + SD * (k + 1)
+                                     : f;
+      rc = launch_batch_tile(cs, offs, tiles, L.n_fwd, from, dst, b->n_total,
+                             plan.fwd.t, 2 * plan.fwd.K, (int)(to - done),
+                             b->eq_class(), s);
+      done = to;
+      from = dst;
+    }
   }
   return rc;
 }
@@ -1043,7 +1093,7 @@ int check_adj(const lbm_batch* b, const void* ws, size_t ws_bytes,
     return set_err(LBM_EINVAL,
                    "no checkpoints for this workspace, nsteps and ckpt_every: "
                    "call lbm_batch_forward_ckpt first");
-  if (ws_bytes < adj_layout(b, nsteps, C, resolved_plan(b)).total)
+  if (ws_bytes < adj_layout(b, nsteps, C, resolved_plan(b, C)).total)
     return set_err(LBM_EWORKSPACE, "adjoint workspace too small");
   return LBM_OK;
 }
@@ -1051,7 +1101,7 @@ int check_adj(const lbm_batch* b, const void* ws, size_t ws_bytes,
 // The reverse sweep: recompute each checkpoint segment, then adjoint steps.
 int enqueue_adjoint(lbm_batch* b, void* ws, int64_t nsteps, int64_t C,
                     double* fbar, double* rbar, hipStream_t s) {
-  const AdjPlan plan = resolved_plan(b);
+  const AdjPlan plan = resolved_plan(b, C);
   const AdjLayout L = adj_layout(b, nsteps, C, plan);
   const Consts* cs = at<Consts>(ws, L.consts);
   const int64_t* offs = at<int64_t>(ws, L.offs);
@@ -1064,8 +1114,7 @@ int enqueue_adjoint(lbm_batch* b, void* ws, int64_t nsteps, int64_t C,
   if (rc) return rc;
   double* cur = fbar;
   double* oth = at<double>(ws, L.pp);
-  const lbm_tuning rt = rec_tuning(b->tune);
-  const int Krec = b->tune.steps_per_launch;
+  const int Krec = plan.rec.K;
   // stride of the stored segment states
   const int E = plan.plain ? 1 : plan.rev.E;
   auto seg_len = [&](int64_t k) { return std::min(C, nsteps - k * C); };
@@ -1089,7 +1138,7 @@ int enqueue_adjoint(lbm_batch* b, void* ws, int64_t nsteps, int64_t C,
       const int kk = (int)std::min<int64_t>(Kst, len - 1 - i0);
       const int r = launch_batch_tile(cs, offs, at<TileRef>(ws, L.rec_tiles),
                                       L.n_rec, state(k, i0), segbuf(k),
-                                      b->n_total, shape_of(rt), 2 * Krec, kk,
+                                      b->n_total, plan.rec.t, 2 * Krec, kk,
                                       b->eq_class(), st, (int64_t)SD, (int)i0,
                                       E);
       if (r) return r;
@@ -1097,10 +1146,10 @@ int enqueue_adjoint(lbm_batch* b, void* ws, int64_t nsteps, int64_t C,
     return LBM_OK;
   };
   const RevShape rv = plan.rev;
-  // the blocked reverse steps of segment k on s, up to Krec per launch
+  // the blocked reverse steps of segment k on s, up to rv.K per launch
   auto reverse = [&](int64_t k) -> int {
     for (int64_t hi = seg_len(k); hi > 0;) {
-      const int64_t lo = std::max<int64_t>(0, hi - Krec);
+      const int64_t lo = std::max<int64_t>(0, hi - rv.K);
       const int r = launch_adjoint_tile(
           rv.t, rv.E, b->eq_class(), cs, offs,
           at<TileRef>(ws, L.rev_tiles), L.n_rev,
@@ -1186,6 +1235,7 @@ lbm_batch* single_batch(lbm_handle* h) {
   const int64_t offs[2] = {0, h->n};
   if (lbm_batch_init(&h->one, 1, offs, &h->p, h->stream) != LBM_OK) return nullptr;
   if (h->tune.kernel == LBM_KERNEL_BLOCKED) lbm_batch_set_tuning(h->one, &h->tune);
+  h->one->plan_auto = h->plan_auto;
   return h->one;
 }
 
@@ -1196,6 +1246,7 @@ lbm_batch* synced_batch(lbm_handle* h) {
   if (!b) return nullptr;
   if (h->tune.kernel == LBM_KERNEL_BLOCKED && !same_tuning(b->tune, h->tune))
     lbm_batch_set_tuning(b, &h->tune);
+  b->plan_auto = h->plan_auto;
   b->adj_kernel = h->adj_kernel;
   b->rec_stride = h->rec_stride;
   return b;
@@ -1217,8 +1268,16 @@ extern "C" {
 size_t lbm_batch_adjoint_workspace_bytes(const lbm_batch* b, int64_t nsteps,
                                          int64_t ckpt_every) {
   if (!b || nsteps < 0 || ckpt_every < 1) return 0;
-  return adj_layout(b, nsteps, ckpt_every,
-                    current_plan(b)).total;
+  // enough for the library's own shapes and for those of the tuning, so that
+  // setting the tuning in force changes nothing about the workspace
+  const bool plain = resolve_adj_plain(b);
+  const int every = resolve_every(b, plain);
+  size_t most = 0;
+  for (const bool own : {false, b->plan_auto})
+    most = std::max(most, adj_layout(b, nsteps, ckpt_every,
+                                     adj_plan(b, plain, every, own, ckpt_every))
+                              .total);
+  return most;
 }
 
 int lbm_batch_forward_ckpt(lbm_batch* b, double* f, void* ws, size_t ws_bytes,
@@ -1230,7 +1289,15 @@ int lbm_batch_forward_ckpt(lbm_batch* b, double* f, void* ws, size_t ws_bytes,
   // its tiles can hold the forward halo, else the one-step kernel
   b->adj_plain = resolve_adj_plain(b);
   b->adj_every = resolve_every(b, b->adj_plain);
-  const AdjPlan plan = resolved_plan(b);
+  b->adj_auto = b->plan_auto;
+  if (b->adj_auto) {
+    const int E = b->adj_plain ? 1 : b->adj_every;
+    if (b->adj_own_ckpt != ckpt_every || b->adj_own_every != E)
+      b->adj_own = own_shapes(b, ckpt_every, E);
+    b->adj_own_ckpt = ckpt_every;
+    b->adj_own_every = E;
+  }
+  const AdjPlan plan = resolved_plan(b, ckpt_every);
   const AdjLayout L = adj_layout(b, nsteps, ckpt_every, plan);
   if (ws_bytes < L.total)
     return set_err(LBM_EWORKSPACE, "adjoint workspace of %zu bytes, need %zu",
@@ -1268,15 +1335,14 @@ int lbm_batch_forward_ckpt(lbm_batch* b, double* f, void* ws, size_t ws_bytes,
                     b->adj_ckpt == ckpt_every &&
                     same_tuning(b->adj_tune, b->tune) &&
                     b->adj_plain_up == b->adj_plain &&
-                    b->adj_every_up == b->adj_every;
+                    b->adj_every_up == b->adj_every &&
+                    b->adj_auto_up == b->adj_auto;
   if (!same) {
-    // tables of this workspace layout: forward and recompute tiles (the
-    // forward tile shape), tiles of the blocked and of the one-step reverse
-    // kernels, and each lattice's first tile in the two reverse tables
-    const lbm_tuning ft = fwd_tuning(b);
-    const auto fwd = tile_table(b, tile_width(ft) - 4 * ft.steps_per_launch);
-    const auto rec = tile_table(
-        b, tile_width(rec_tuning(b->tune)) - 4 * b->tune.steps_per_launch);
+    // tables of this workspace layout: forward and recompute tiles, tiles of
+    // the blocked and of the one-step reverse kernels, and each lattice's
+    // first tile in the two reverse tables
+    const auto fwd = tile_table(b, plan_out(plan.fwd));
+    const auto rec = tile_table(b, plan_out(plan.rec));
     const auto rev = tile_table(b, plan.rev.out());
     const auto adj = tile_table(b, kAdjOut);
     auto firsts = [&](const std::vector<TileRef>& tab) {
@@ -1310,8 +1376,9 @@ int lbm_batch_forward_ckpt(lbm_batch* b, double* f, void* ws, size_t ws_bytes,
     b->adj_tune = b->tune;
     b->adj_plain_up = b->adj_plain;
     b->adj_every_up = b->adj_every;
+    b->adj_auto_up = b->adj_auto;
   }
-  return enqueue_forward_ckpt(b, ws, f, nsteps, ckpt_every, L, s);
+  return enqueue_forward_ckpt(b, ws, f, nsteps, ckpt_every, plan, L, s);
 }
 
 int lbm_batch_adjoint(lbm_batch* b, void* ws, size_t ws_bytes, int64_t nsteps,
@@ -1357,9 +1424,9 @@ int lbm_batch_adjoint(lbm_batch* b, void* ws, size_t ws_bytes, int64_t nsteps,
 int lbm_batch_loss(lbm_batch* b, const double* f, const double* target,
                    void* ws, size_t ws_bytes, double* loss, double* fbar) {
   if (!b || !f || !ws || !loss || !fbar) return set_err(LBM_EINVAL, "NULL argument");
-  if (b->adj_ws != ws || ws_bytes < adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b)).total)
+  if (b->adj_ws != ws || ws_bytes < adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b, b->adj_ckpt)).total)
     return set_err(LBM_EINVAL, "call lbm_batch_forward_ckpt with this workspace first");
-  const AdjLayout L = adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b));
+  const AdjLayout L = adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b, b->adj_ckpt));
   // the tiles' sums take the rate slots, which a reverse sweep clears first
   double* parts = at<double>(ws, L.rslots);
   hipLaunchKernelGGL(k_loss, dim3((unsigned)L.n_adj), dim3(256), 0, b->stream,
@@ -1381,9 +1448,9 @@ int lbm_batch_equilibrium_adjoint(lbm_batch* b, const double* rho,
                                   size_t ws_bytes) {
   if (!b || !rho || !J || !zeta || !fbar || !rho_bar || !J_bar || !zeta_bar || !ws)
     return set_err(LBM_EINVAL, "NULL argument");
-  if (b->adj_ws != ws || ws_bytes < adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b)).total)
+  if (b->adj_ws != ws || ws_bytes < adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b, b->adj_ckpt)).total)
     return set_err(LBM_EINVAL, "call lbm_batch_forward_ckpt with this workspace first");
-  const AdjLayout L = adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b));
+  const AdjLayout L = adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b, b->adj_ckpt));
   hipLaunchKernelGGL(k_equilibrium_adjoint, node_grid(b), dim3(256), 0, b->stream,
                      at<Consts>(ws, L.consts), at<int64_t>(ws, L.offs), b->n_inst,
                      rho, J, zeta, fbar, rho_bar, J_bar, zeta_bar, b->n_total);
@@ -1393,9 +1460,9 @@ int lbm_batch_equilibrium_adjoint(lbm_batch* b, const double* rho,
 int lbm_batch_moments_adjoint(lbm_batch* b, const double* mbar, double* fbar,
                               void* ws, size_t ws_bytes) {
   if (!b || !mbar || !fbar || !ws) return set_err(LBM_EINVAL, "NULL argument");
-  if (b->adj_ws != ws || ws_bytes < adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b)).total)
+  if (b->adj_ws != ws || ws_bytes < adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b, b->adj_ckpt)).total)
     return set_err(LBM_EINVAL, "call lbm_batch_forward_ckpt with this workspace first");
-  const AdjLayout L = adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b));
+  const AdjLayout L = adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b, b->adj_ckpt));
   hipLaunchKernelGGL(k_moments_adjoint, node_grid(b), dim3(256), 0, b->stream,
                      at<Consts>(ws, L.consts), at<int64_t>(ws, L.offs), b->n_inst,
                      mbar, fbar, b->n_total);
@@ -1459,7 +1526,7 @@ int lbm_adjoint(lbm_handle* h, void* ws, size_t ws_bytes, int64_t nsteps,
   if (!h || !rbar) return set_err(LBM_EINVAL, "NULL argument");
   lbm_batch* b = single_batch(h);
   if (!b) return LBM_EINVAL;
-  const AdjLayout L = adj_layout(b, nsteps, ckpt_every, resolved_plan(b));
+  const AdjLayout L = adj_layout(b, nsteps, ckpt_every, resolved_plan(b, ckpt_every));
   double* dev = at<double>(ws, L.scratch);
   int rc = lbm_batch_adjoint(b, ws, ws_bytes, nsteps, ckpt_every, fbar, dev,
                              use_graph);
@@ -1477,7 +1544,7 @@ int lbm_loss(lbm_handle* h, const double* f, const double* target, void* ws,
   lbm_batch* b = single_batch(h);
   if (!b) return LBM_EINVAL;
   if (b->adj_ws != ws) return set_err(LBM_EINVAL, "call lbm_forward_ckpt first");
-  const AdjLayout L = adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b));
+  const AdjLayout L = adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b, b->adj_ckpt));
   double* dev = at<double>(ws, L.scratch);
   int rc = lbm_batch_loss(b, f, target, ws, ws_bytes, dev, fbar);
   if (!rc)

@@ -163,26 +163,17 @@ StepPlan plan_steps(int64_t n, int64_t nsteps) {
   return best;
 }
 
-// The plan of a batch, by the model of plan_steps over the lattices' lengths
-// (in bins).  Resident lattices at P nodes per lane take 0.06 + node P m per
-// step, m their wavefronts per SIMD of the longest lattice or, a third more
-// for uneven compute units, on average: no halo and no launches, but each is
-// bound to one compute unit, while tiles spread a lattice over several.  Where
-// both run they share the chip's SIMDs and the times add up (1.39: the
-// launches of the two streams do not overlap perfectly).  Large batches keep
-// four or eight nodes per lane, batches that leave the chip room take one or
-// two, or tiles alone: 64 lattices of 128 .. 2048 nodes ran 5.0 us per step
-// packed by twelve wavefronts of eight nodes per lane (a tenth of the chip),
-// 0.6 on (1, 8) tiles; 965 lattices of 247 .. 1108 nodes 5.2, 2.7 resident at
-// two nodes per lane; 4096 of 512 .. 16384 60 either way.  The constants
-// minimise the regret over sweeps of every choice on sixteen batches of 2e4 to
-// 2e7 nodes: 3 % on average, at most 8 %.
-BatchPlan plan_batch(const std::vector<int64_t>& offsets, bool resident) {
+namespace {
+
+// The model of plan_steps over the lattices of a batch, by their lengths in
+// bins of 32 nodes, at most 64 of them (neighbours merge).
+struct BatchModel {
   struct Bin {
     int64_t len, count;
   };
   std::vector<Bin> bins;
-  {
+
+  explicit BatchModel(const std::vector<int64_t>& offsets) {
     std::vector<int64_t> lens;
     for (size_t i = 0; i + 1 < offsets.size(); ++i)
       lens.push_back((offsets[i + 1] - offsets[i] + 31) / 32 * 32);
@@ -191,7 +182,6 @@ BatchPlan plan_batch(const std::vector<int64_t>& offsets, bool resident) {
       if (bins.empty() || bins.back().len != l) bins.push_back(Bin{l, 0});
       ++bins.back().count;
     }
-    // at most 64 bins: neighbours merge
     while (bins.size() > 64) {
       std::vector<Bin> half;
       for (size_t i = 0; i < bins.size(); i += 2) {
@@ -202,8 +192,10 @@ BatchPlan plan_batch(const std::vector<int64_t>& offsets, bool resident) {
       bins.swap(half);
     }
   }
-  // tiles of one candidate over the lattices longer than `above` nodes
-  auto tiles_us = [&](const TileCost& c, int K, int64_t above) {
+
+  // microseconds per step on tiles of one candidate over the lattices longer
+  // than `above` nodes; K steps per launch, `launches` of them per step
+  double tiles_us(const TileCost& c, int K, int64_t above, double launches) const {
     const int64_t nodes = tile_nodes(c.t.P, c.t.W, c.t.M), out = nodes - 4 * K;
     double tiles = 0, waves = 0, total = 0;
     for (const Bin& b : bins) {
@@ -225,14 +217,34 @@ BatchPlan plan_batch(const std::vector<int64_t>& offsets, bool resident) {
         std::min(1.0, std::max(1.3 * waves / (tiles * c.t.W), 1.0 / g));
     const double step = full * (c.base + used * (c.step(c.per_cu) - c.base)) +
                         (rest > 0 ? c.base + used * (c.step(rest) - c.base) : 0.0);
-    return step +
-           (0.75 * c.fixed + 48.0 * (tiles * (double)nodes + total) / 11e6) / (double)K;
-  };
+    return step + (0.75 * c.fixed +
+                   48.0 * (tiles * (double)nodes + total) / 11e6) * launches;
+  }
+};
+
+}  // namespace
+
+// The plan of a batch, by the model of plan_steps over the lattices' lengths
+// (in bins).  Resident lattices at P nodes per lane take 0.06 + node P m per
+// step, m their wavefronts per SIMD of the longest lattice or, a third more
+// for uneven compute units, on average: no halo and no launches, but each is
+// bound to one compute unit, while tiles spread a lattice over several.  Where
+// both run they share the chip's SIMDs and the times add up (1.39: the
+// launches of the two streams do not overlap perfectly).  Large batches keep
+// four or eight nodes per lane, batches that leave the chip room take one or
+// two, or tiles alone: 64 lattices of 128 .. 2048 nodes ran 5.0 us per step
+// packed by twelve wavefronts of eight nodes per lane (a tenth of the chip),
+// 0.6 on (1, 8) tiles; 965 lattices of 247 .. 1108 nodes 5.2, 2.7 resident at
+// two nodes per lane; 4096 of 512 .. 16384 60 either way.  The constants
+// minimise the regret over sweeps of every choice on sixteen batches of 2e4 to
+// 2e7 nodes: 3 % on average, at most 8 %.
+BatchPlan plan_batch(const std::vector<int64_t>& offsets, bool resident) {
+  const BatchModel model(offsets);
   BatchPlan best;
   double least = INFINITY;
   auto consider = [&](int P, int waves, int64_t above, double res_us,
                       const TileCost& c, int K) {
-    double us = tiles_us(c, K, above);
+    double us = model.tiles_us(c, K, above, 1.0 / K);
     us = us == 0 ? res_us : P == 0 ? us : us + 1.39 * (res_us - 0.1);
     if (us < least) {
       least = us;
@@ -248,7 +260,7 @@ BatchPlan plan_batch(const std::vector<int64_t>& offsets, bool resident) {
       if (P == 0 ? waves != 4 : waves > resident_max_waves(P)) continue;
       double n_waves = 0, longest = 0;
       const int64_t above = P == 0 ? 0 : waves * resident_span(P);
-      for (const Bin& b : bins) {
+      for (const BatchModel::Bin& b : model.bins) {
         if (b.len > above || b.len < kResidentMin) continue;
         const double nw = (double)resident_waves(b.len, P);
         n_waves += nw * (double)b.count;
@@ -273,6 +285,28 @@ BatchPlan plan_batch(const std::vector<int64_t>& offsets, bool resident) {
       }
     }
   }
+  return best;
+}
+
+// The same over tiles alone, for runs of `steps` steps in even launches (the
+// segments of a checkpointed sweep).  4.8e6 nodes in 512 lattices, segments of
+// 16: 25.8 us per step on (2, 4, 1) tiles, 21.5 on (4, 4, 2); one lattice of
+// 8192, segments of 100: 0.48 on one-wavefront tiles, 0.36 on (1, 4, 8).
+StepPlan plan_tiles(const std::vector<int64_t>& offsets, int64_t steps) {
+  const BatchModel model(offsets);
+  StepPlan best{{8, 4, 1}, 16, 0};
+  double least = INFINITY;
+  for (const TileCost& c : kTileCosts)
+    for (int64_t j = 1, K = 0; j == 1 || K > 8; ++j) {
+      const int64_t top = (tile_nodes(c.t.P, c.t.W, c.t.M) - kPlanMinOut) / 4;
+      j = std::max(j, (steps + top - 1) / top);
+      K = (steps + j - 1) / j;
+      const double us = model.tiles_us(c, (int)K, 0, (double)j / (double)steps);
+      if (us < least) {
+        least = us;
+        best = StepPlan{c.t, (int)K, 0};
+      }
+    }
   return best;
 }
 

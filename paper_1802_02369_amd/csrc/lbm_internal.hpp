@@ -161,6 +161,13 @@ struct BatchPlan;
 // The plan of a batch with these offsets (see BatchPlan), with resident
 // lattices or on tiles alone.
 BatchPlan plan_batch(const std::vector<int64_t>& offsets, bool resident);
+// Shape and steps per launch of runs of `steps` >= 1 steps on tiles.
+StepPlan plan_tiles(const std::vector<int64_t>& offsets, int64_t steps);
+// Tile shapes and steps per launch of a checkpointed sweep: forward, recompute
+// and reverse.
+struct AdjShapes {
+  StepPlan fwd, rec, rev;
+};
 // Fewest nodes a tile of a batch's plan stores (bounds the table's size).
 constexpr int64_t kPlanMinOut = 48;
 
@@ -337,6 +344,14 @@ struct lbm_batch {
   // launch (else K per launch)
   bool adj_plain = false;
   bool adj_plain_up = false;  // the value the uploaded tables were built for
+  // plan_auto when lbm_batch_forward_ckpt resolved the plan, and for the
+  // uploaded tables
+  bool adj_auto = false, adj_auto_up = false;
+  // the shapes of the library's own plan that lbm_batch_forward_ckpt made,
+  // for adj_own_ckpt steps per segment and state stride adj_own_every
+  lbm::AdjShapes adj_own{};
+  int64_t adj_own_ckpt = 0;
+  int32_t adj_own_every = 0;
   // requested stride of the segment states the reverse sweep stores (0:
   // automatic), what lbm_batch_forward_ckpt resolved it to, and the value
   // the uploaded tables were built for

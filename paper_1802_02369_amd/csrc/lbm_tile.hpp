@@ -1,6 +1,6 @@
 // Register-tile helpers shared by the forward and reverse tile kernels:
-// coalesced loads and stores of a wavefront's segment through LDS, and the
-// per-step boundary record exchanged between the wavefronts of a tile.
+// coalesced loads and stores of a wavefront's segment, the time step of its
+// nodes, and the wavefronts a tile needs.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -256,9 +256,19 @@ __device__ __forceinline__ void tile_step(const lbm::Consts& c, double (&f)[6][P
   f[5][P - 1] = gmR;
 }
 
-// Values exchanged between neighbouring wavefronts of a workgroup each step.
-struct Boundary {
-  double v[8];
-};
+// Active wavefronts of a tile that starts at lattice index `start` (halo H)
+// in a lattice of n nodes: the fewest of the WG whose span
+// P((64 - 2M) nw + 2M) still covers the nodes the tile stores plus both halos.
+// Only a lattice's last tile, or a lattice shorter than one tile, needs fewer
+// than WG.
+template <int P, int WG, int M>
+__device__ __forceinline__ int active_waves(int64_t n, int64_t start, int H) {
+  constexpr int WS = (64 - 2 * M) * P;
+  const int64_t store = n - (start + H);  // nodes from the tile's first output
+  const int64_t need = store + 2 * H - 2 * M * P;  // beyond the mirror lanes
+  if (need >= (int64_t)WS * WG) return WG;
+  const int nw = ((int)need + WS - 1) / WS;
+  return nw < 1 ? 1 : nw;
+}
 
 }  // namespace
