@@ -445,19 +445,22 @@ __device__ __forceinline__ void tile_run(const Consts& c,
 }
 
 // Wavefronts per SIMD the tile kernels are compiled for (the register
-// budget: 512 / n VGPRs each).  Section-8 kernels at P = 8 hold 168 VGPRs
+// budget: 512 / n VGPRs each).  Kernels of one kind of equilibria at P = 8 hold 168 VGPRs
 // for three (the few values that spill are touched only around the step
 // loop, which measured 297 -> 312 GLUPS at N = 2^24 against two); with 8
 // wavefronts per workgroup a CU gains no third one, so those stay at two.
 // The kernels that select the equilibria per lattice, or store the states
-// of a reverse sweep, need more registers at P >= 4 and take one.  P <= 2
+// of a reverse sweep, need more registers at P >= 4 and take one: a launch
+// whose lattices share linear or fluid equilibria has its own (150 VGPRs at
+// P = 8; n = 500 in one workgroup 0.45 -> 0.35 us per step, 3e5 1.56 -> 1.37,
+// 8e6 33.8 -> 31.1).  P <= 2
 // needs few registers: four.
-constexpr int tile_waves_per_simd(int P, int WG, bool sec8_plain) {
-  return P <= 2 ? 4 : WG > 8 ? 3 : !sec8_plain ? 1 : P == 8 && WG <= 4 ? 3 : 2;
+constexpr int tile_waves_per_simd(int P, int WG, bool one_eq_plain) {
+  return P <= 2 ? 4 : WG > 8 ? 3 : !one_eq_plain ? 1 : P == 8 && WG <= 4 ? 3 : 2;
 }
 
 template <int P, int WG, int M, int EQ>
-__global__ __launch_bounds__(64 * WG, tile_waves_per_simd(P, WG, EQ == 0)) void k_step_tile(
+__global__ __launch_bounds__(64 * WG, tile_waves_per_simd(P, WG, EQ >= 0)) void k_step_tile(
     Consts c, const double* __restrict__ fin, double* __restrict__ fout,
     int64_t n, int K, int64_t ntiles) {
   const int64_t tile = blockIdx.x;
@@ -473,7 +476,7 @@ __global__ __launch_bounds__(64 * WG, tile_waves_per_simd(P, WG, EQ == 0)) void 
 // EVERY: store the states of a checkpoint segment that the reverse sweep
 // loads (see tile_run: first, every).
 template <int P, int WG, int M, int EQ, bool EVERY>
-__global__ __launch_bounds__(64 * WG, tile_waves_per_simd(P, WG, EQ == 0 && !EVERY)) void k_batch_tile(
+__global__ __launch_bounds__(64 * WG, tile_waves_per_simd(P, WG, EQ >= 0 && !EVERY)) void k_batch_tile(
     const Consts* __restrict__ cs, const int64_t* __restrict__ offs,
     const lbm::TileRef* __restrict__ tiles, const double* __restrict__ fin,
     double* __restrict__ fout, int64_t S, int H, int K, int64_t ntiles,
@@ -1060,12 +1063,16 @@ template <int P, int WG, int M>
 static void launch_tile_t(const Consts& c, const double* fin, double* fout,
                           int64_t n, int K, hipStream_t s) {
   const int64_t ntiles = cdiv(n, tile_nodes(P, WG, M) - 4 * K);
+  const dim3 grid((unsigned)ntiles), block(64 * WG);
   if (c.eq_kind == 0)
-    hipLaunchKernelGGL((k_step_tile<P, WG, M, 0>), dim3((unsigned)ntiles),
-                       dim3(64 * WG), 0, s, c, fin, fout, n, K, ntiles);
+    hipLaunchKernelGGL((k_step_tile<P, WG, M, 0>), grid, block, 0, s, c, fin, fout,
+                       n, K, ntiles);
+  else if (c.eq_kind == 2)
+    hipLaunchKernelGGL((k_step_tile<P, WG, M, 2>), grid, block, 0, s, c, fin, fout,
+                       n, K, ntiles);
   else
-    hipLaunchKernelGGL((k_step_tile<P, WG, M, -1>), dim3((unsigned)ntiles),
-                       dim3(64 * WG), 0, s, c, fin, fout, n, K, ntiles);
+    hipLaunchKernelGGL((k_step_tile<P, WG, M, 1>), grid, block, 0, s, c, fin, fout,
+                       n, K, ntiles);
 }
 
 // The tile shapes (P, wavefronts, mirror lanes) of tuning records, and the
@@ -1175,9 +1182,12 @@ int launch_step_resident(const Consts& c, double* f, int64_t n, int64_t T,
 #define LBM_RES_CASE(PP)                                                      \
   if (P == PP && c.eq_kind == 0)                                              \
     hipLaunchKernelGGL((k_step_resident<PP, 0>), grid, block,                 \
-                       resident_lds(PP, (int)W), s, c, f, (int)n, T);              \
+                       resident_lds(PP, (int)W), s, c, f, (int)n, T);         \
+  else if (P == PP && c.eq_kind == 2)                                         \
+    hipLaunchKernelGGL((k_step_resident<PP, 2>), grid, block,                 \
+                       resident_lds(PP, (int)W), s, c, f, (int)n, T);         \
   else if (P == PP)                                                           \
-    hipLaunchKernelGGL((k_step_resident<PP, -1>), grid, block,                \
+    hipLaunchKernelGGL((k_step_resident<PP, 1>), grid, block,                 \
                        resident_lds(PP, (int)W), s, c, f, (int)n, T);
   LBM_RES_CASE(1)
   LBM_RES_CASE(2)
@@ -1246,14 +1256,19 @@ static void launch_batch_t(const Consts* cs, const int64_t* offs,
       return;
     }
   }
+#define LBM_EQ_LAUNCH(EE)                                                     \
+  hipLaunchKernelGGL((k_batch_tile<P, WG, M, EE, false>), grid, block, 0, s,  \
+                     cs, offs, tiles, fin, fout, S, H, K, ntiles,             \
+                     state_stride, first, every)
   if (eq == 0)
-    hipLaunchKernelGGL((k_batch_tile<P, WG, M, 0, false>), grid, block, 0, s, cs,
-                       offs, tiles, fin, fout, S, H, K, ntiles, state_stride, first,
-                       every);
+    LBM_EQ_LAUNCH(0);
+  else if (eq == 1)
+    LBM_EQ_LAUNCH(1);
+  else if (eq == 2)
+    LBM_EQ_LAUNCH(2);
   else
-    hipLaunchKernelGGL((k_batch_tile<P, WG, M, -1, false>), grid, block, 0, s, cs,
-                       offs, tiles, fin, fout, S, H, K, ntiles, state_stride, first,
-                       every);
+    LBM_EQ_LAUNCH(-1);
+#undef LBM_EQ_LAUNCH
 }
 
 int launch_batch_tile(const Consts* cs, const int64_t* offs,

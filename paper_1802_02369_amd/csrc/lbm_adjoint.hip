@@ -1076,7 +1076,7 @@ int enqueue_forward_ckpt(lbm_batch* b, void* ws, double* f, int64_t nsteps,
                                      : f;
       rc = launch_batch_tile(cs, offs, tiles, L.n_fwd, from, dst, b->n_total,
                              plan.fwd.t, 2 * plan.fwd.K, (int)(to - done),
-                             b->eq_class(), s);
+                             b->tile_eq, s);
       done = to;
       from = dst;
     }

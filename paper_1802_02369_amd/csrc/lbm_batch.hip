@@ -114,7 +114,7 @@ int enqueue_tiles(lbm_batch* b, const Layout& L, void* ws, double* f,
   int64_t done = 0, launches = 0;
   for (int k : split_steps(nsteps, K)) {
     int rc = launch_batch_tile(cs, offs, tiles, ntiles, a, w, b->n_total, t, H,
-                               k, b->eq_class(), s);
+                               k, b->tile_eq, s);
     done += k;
     if (!rc && check)
       rc = launch_batch_check(cs, offs, tiles, ntiles, w, b->n_total, out,
@@ -609,6 +609,12 @@ int lbm_batch_init(lbm_batch** b, int64_t n_inst, const int64_t* offsets,
                           [](const lbm_params& q) { return q.eq_kind == 0; })
                   ? 0
                   : -1;
+  x->tile_eq = std::all_of(params, params + n_inst,
+                           [&](const lbm_params& q) {
+                             return q.eq_kind == params[0].eq_kind;
+                           })
+                   ? params[0].eq_kind
+                   : -1;
   x->consts.resize(n_inst);
   for (int64_t i = 0; i < n_inst; ++i) {
     int rc = make_consts(&params[i], &x->consts[i]);

@@ -264,9 +264,10 @@ struct NodeThermo {
 
 // Steps (ii)-(vi) at one node, in place on the six populations: moments,
 // equilibria, relaxation, back to populations.  Returns uh, Th and the two
-// factors the source needs: rw = rh / Th and w = 1 / Th.  EQ = 0 compiles
-// the equilibria of section 8 only (every lattice of the launch has
-// eq_kind 0); EQ = -1 selects them per lattice from c.eq_kind.  SAVE: also
+// factors the source needs: rw = rh / Th and w = 1 / Th.  EQ = 0, 1 or 2
+// compiles those equilibria only (every lattice of the launch has that
+// eq_kind); EQ = -1 selects them per lattice from c.eq_kind, whose branches
+// at every node keep a lane's nodes from sharing registers.  SAVE: also
 // writes the node's thermodynamic state into *save.
 //
 // (v) relaxation (eq. relaxation-d1q3q3) and (vi) f* = M^-1 m*, combined: only
@@ -303,12 +304,12 @@ __device__ __forceinline__ void collide_local(const Consts& c, double& f0,
   double sh, Y, lr, ir;
   thermo_scaled(c, rh, Jh, zh, u, sh, Y, T, lr, ir);
   double d, dp, dx;
-  if (EQ == 0 || c.eq_kind == 0) {
+  if (EQ == 0 || (EQ < 0 && c.eq_kind == 0)) {
     const double y = fma(u, u, c.hP * T);
     d = fma(rh, y, -sf);
     dp = fma(zh, u, gm - gp);
     dx = fma(rh, fma(y, sh, c.tgy * Y), -sg);
-  } else if (c.eq_kind == 2) {
+  } else if (EQ == 2 || (EQ < 0 && c.eq_kind == 2)) {
     d = fma(rh, fma(u, u, c.hP * exp2_fin(c.gm1 * lr)), -sf);
     dp = gm - gp;
     dx = fma(2.0, g0, -sg) * (1.0 / 3.0);

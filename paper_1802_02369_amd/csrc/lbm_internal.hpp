@@ -99,9 +99,9 @@ int launch_moments(const Consts& c, const double* f, double* m, int64_t n,
 
 // state_stride > 0: fin is state `first` of a checkpoint segment, and of
 // the states first+1 .. first+K the launch reaches, state i is stored into
-// fout + ((i-1)/every)*state_stride when i is a multiple of `every`.  eq = 0
-// when every lattice of the table has the equilibria of section 8
-// (eq_kind 0), else -1.
+// fout + ((i-1)/every)*state_stride when i is a multiple of `every`.  eq:
+// the eq_kind of every lattice of the table, or -1 when they differ (segments
+// are stored by kernels for eq_kind 0 or for any).
 int launch_batch_tile(const Consts* cs, const int64_t* offs,
                       const TileRef* tiles, int64_t ntiles, const double* fin,
                       double* fout, int64_t S, const TileShape& t, int H, int K,
@@ -368,6 +368,9 @@ struct lbm_batch {
   // (set by lbm_batch_init; the constants do not change afterwards)
   int32_t eq_cls = 0;
   int eq_class() const { return eq_cls; }
+  // eq_kind of every lattice, -1 if they differ: the equilibria the launches
+  // that store no checkpoint segments are compiled for
+  int32_t tile_eq = 0;
 
   // whether lattice i may run resident with the current mode: only in
   // batches of section-8 lattices (the kernel that selects the equilibria
