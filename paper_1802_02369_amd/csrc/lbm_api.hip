@@ -437,13 +437,13 @@ int step_run(lbm_handle* h, double* f, double* ws, int64_t nsteps) {
     // with LBM_CHECK_FINITE the launches are the tuning's, so that the steps a
     // failure is reported after do not depend on the plan
     const bool planned = h->plan_auto && !check;
-    if (planned && h->plan_nsteps != nsteps) {
-      h->plan = plan_steps(n, nsteps);
+    StepPlan plan{shape_of(h->tune), h->tune.steps_per_launch, 0};
+    if (planned) {
+      std::lock_guard<std::mutex> lock(h->plan_lock);
+      if (h->plan_nsteps != nsteps) h->plan = plan_steps(n, nsteps);
       h->plan_nsteps = nsteps;
+      plan = h->plan;
     }
-    const StepPlan plan =
-        planned ? h->plan
-                : StepPlan{shape_of(h->tune), h->tune.steps_per_launch, 0};
     if (plan.resident) {
       for (int64_t t = 0; t < nsteps && !rc; t += kResidentMaxSteps)
         rc = launch_step_resident(h->c, a, n,
@@ -615,6 +615,7 @@ int lbm_init(lbm_handle** h, int64_t n, const lbm_params* p, void* stream) {
 void lbm_destroy(lbm_handle* h) {
   if (!h) return;
   lbm_batch_destroy(h->one);
+  if (h->diag_sums) (void)hipHostFree(h->diag_sums);
   delete h;
 }
 
@@ -719,15 +720,20 @@ int lbm_diagnostics(lbm_handle* h, const double* f, void* ws, size_t ws_bytes,
   if (!h || !f || !ws || !out) return set_err(LBM_EINVAL, "NULL argument");
   if (ws_bytes < lbm_workspace_bytes(h, LBM_WS_STEP))
     return set_err(LBM_EWORKSPACE, "workspace too small");
-  double* scratch = (double*)ws + 6 * h->n;
-  int rc = launch_diagnostics(h->c, f, h->n, scratch, h->stream);
-  if (rc) return rc;
-  rc = hip_check(hipMemcpyAsync(out, scratch, 8 * sizeof(double),
-                                hipMemcpyDeviceToHost, h->stream),
-                 "hipMemcpyAsync");
-  if (rc) return rc;
-  rc = hip_check(hipStreamSynchronize(h->stream), "hipStreamSynchronize");
-  if (rc) return rc;
+  int rc = LBM_OK;
+  {
+    std::lock_guard<std::mutex> lock(h->diag_lock);
+    if (!h->diag_sums &&
+        (rc = hip_check(hipHostMalloc((void**)&h->diag_sums, diag_sums_bytes(),
+                                      hipHostMallocDefault),
+                        "hipHostMalloc")))
+      return rc;
+    if ((rc = launch_diagnostics(h->c, f, h->n, h->diag_sums, h->stream)))
+      return rc;
+    rc = hip_check(hipStreamSynchronize(h->stream), "hipStreamSynchronize");
+    if (rc) return rc;
+    combine_diagnostics(h->diag_sums, h->n, out);
+  }
   if (out[6] > 0 || out[7] > 0)
     return set_err(LBM_ENONFINITE,
                    "state holds %g non-finite values and %g nodes with rho<=0 "

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <string>
+#include <mutex>
 #include <vector>
 #include <map>
 
@@ -92,8 +93,13 @@ int launch_step_plain(const Consts& c, const double* fin, double* fout,
                       double* halo, int64_t n, hipStream_t s);
 int launch_step_tile(const Consts& c, const double* fin, double* fout,
                      int64_t n, const TileShape& t, int K, hipStream_t s);
+// The diagnostics of f: the sums of diag_blocks(n) blocks, 8 values each, to
+// `sums` (host memory the device can write, diag_sums_bytes), and their
+// combination once the launch has ended.
+size_t diag_sums_bytes();
 int launch_diagnostics(const Consts& c, const double* f, int64_t n,
-                       double* scratch, hipStream_t s);
+                       double* sums, hipStream_t s);
+void combine_diagnostics(const double* sums, int64_t n, double out[8]);
 int launch_moments(const Consts& c, const double* f, double* m, int64_t n,
                    hipStream_t s);
 
@@ -266,10 +272,15 @@ struct lbm_handle {
   bool tune_default = true;  // tune is the default for n and the equilibria
   // steps run on the library's own plan (plan_steps): until lbm_set_tuning,
   // or when lbm_autotune measured nothing faster; the last plan and the step
-  // count it was made for
+  // count it was made for, under plan_lock (threads may share a handle)
   bool plan_auto = true;
+  std::mutex plan_lock;
   lbm::StepPlan plan{};
   int64_t plan_nsteps = -1;
+  // pinned host memory the diagnostics' block sums go to, from the first call
+  // on, used by one call at a time
+  std::mutex diag_lock;
+  double* diag_sums = nullptr;
   int32_t adj_kernel = LBM_KERNEL_AUTO;  // reverse-sweep kernel
   int32_t rec_stride = 0;  // stride of the stored segment states (0: auto)
   lbm_batch* one = nullptr;  // batch of this one lattice, for the adjoint
