@@ -260,6 +260,7 @@ __device__ __forceinline__ void thermo_scaled(const Consts& c, double rh,
 // step computes it (kept by the reverse sweep for a state it recomputes).
 struct NodeThermo {
   double uh, sh, Y, Th, lr, ir, w;
+  double du, dT;  // uh and Th of the right neighbour less the left one's
 };
 
 // Steps (ii)-(vi) at one node, in place on the six populations: moments,
@@ -329,7 +330,7 @@ __device__ __forceinline__ void collide_local(const Consts& c, double& f0,
   gm = fma(-c.sp_2, dp, fma(c.sx_2, dx, gm));
   w = recip(T);
   rw = rh * w;
-  if constexpr (SAVE) *save = NodeThermo{u, sh, Y, T, lr, ir, w};
+  if constexpr (SAVE) *save = NodeThermo{u, sh, Y, T, lr, ir, w, 0.0, 0.0};
 }
 
 // uh and Th of a node (the halo nodes of the one-step kernel), rounded as in

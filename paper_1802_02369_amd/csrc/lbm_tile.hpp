@@ -189,9 +189,13 @@ __device__ __forceinline__ void tile_step(const lbm::Consts& c, double (&f)[6][P
     double u, T, rw, w;
     lbm::collide_local<EQ, SAVE>(c, f[0][0], f[1][0], f[2][0], f[3][0], f[4][0],
                                  f[5][0], u, T, rw, w, th);
-    lbm::add_source(c, rw, w, lbm::from_left(u), lbm::from_right(u),
-                    lbm::from_left(T), lbm::from_right(T), f[3][0], f[4][0],
-                    f[5][0]);
+    const double ul = lbm::from_left(u), ur = lbm::from_right(u);
+    const double Tl = lbm::from_left(T), Tr = lbm::from_right(T);
+    lbm::add_source(c, rw, w, ul, ur, Tl, Tr, f[3][0], f[4][0], f[5][0]);
+    if constexpr (SAVE) {
+      th->du = ur - ul;
+      th->dT = Tr - Tl;
+    }
     f[1][0] = lbm::from_left(f[1][0]);
     f[4][0] = lbm::from_left(f[4][0]);
     f[2][0] = lbm::from_right(f[2][0]);
@@ -228,6 +232,10 @@ __device__ __forceinline__ void tile_step(const lbm::Consts& c, double (&f)[6][P
       Tr = TR;
     }
     lbm::add_source(c, rwm, wm, ul, ur, Tl, Tr, f[3][k], f[4][k], f[5][k]);
+    if constexpr (SAVE) {
+      th[k].du = ur - ul;
+      th[k].dT = Tr - Tl;
+    }
     ul = um;
     Tl = Tm;
     um = ur;
