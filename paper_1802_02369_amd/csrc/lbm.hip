@@ -330,120 +330,6 @@ __global__ __launch_bounds__(256) void k_save_halo(const double* __restrict__ f,
   for (int q = 0; q < 6; ++q) halo[i * 6 + q] = f[q * n + j];
 }
 
-// K time steps of one register-resident tile per workgroup (see the file
-// header).  The workgroup has WG wavefronts of 64 lanes, lane l of wavefront
-// w holding the P consecutive nodes starting at tile index
-// P ((64 - 2M) w + l).  Neighbouring wavefronts overlap by 2M lanes: the first
-// M lanes of wavefront w > 0 mirror lanes 64-2M .. 63-M of w-1, the last M
-// lanes of w < WG-1 mirror lanes M .. 2M-1 of w+1.  A tile thus spans
-// tile_nodes = P((64 - 2M) WG + 2M) nodes; tile t stores nodes
-// [t*OUT, t*OUT + OUT) with OUT = tile_nodes - 4K and loads
-// [t*OUT - 2K, t*OUT + OUT + 2K) (periodic).
-//
-// Every step runs within the wavefront (lane neighbours through DPP).  The
-// outermost lanes have no neighbour there; as one step has radius 2, the
-// error this leaves at the mirror lanes' outer end moves two nodes inwards per
-// step and reaches the wavefront's own lanes after MP/2 steps.  So every MP/2
-// steps the wavefronts copy their edge lanes into the neighbours' mirror
-// lanes through LDS (one workgroup barrier per copy, double-buffered); each
-// wavefront stores only its own lanes.  The error at the tile's two outer
-// ends is what the halo of 2K nodes absorbs.  A copy costs about 0.3 us of
-// latency.  With M = 1 a P = 2 tile pays it at every step (n = 8192, 4
-// wavefronts, K = 40: 0.80 us per step, 0.54 with M = 4), so the wide shapes
-// of plan_steps take 8/P mirror lanes: a copy every four steps at every P.
-// One node per lane needs them to have several wavefronts at all.
-//
-// Refresh of the mirror lanes: the M lanes next to them on each side publish
-// their populations in `edge` (one buffer of the double-buffered pair: a
-// buffer is written again only after the next refresh's barrier, which every
-// reader of its previous contents has passed), then the mirror lanes take
-// those of the neighbouring wavefronts.
-template <int P, int WG, int M>
-__device__ __forceinline__ void mirror_refresh(double (&f)[6][P],
-                                               double (*edge)[2][6 * P * M],
-                                               int lane, int wave, int nw) {
-  const bool hi = lane >= 32;  // the right half of the wavefront
-  const int pub = hi ? lane - (64 - 2 * M) : lane - M;
-  if (pub >= 0 && pub < M) {
-    double* d = edge[wave][hi] + pub;
-#pragma unroll
-    for (int q = 0; q < 6; ++q)
-#pragma unroll
-      for (int k = 0; k < P; ++k) d[(q * P + k) * M] = f[q][k];
-  }
-  __syncthreads();
-  const bool left = lane < M && wave > 0, right = lane >= 64 - M && wave < nw - 1;
-  if (left || right) {
-    const double* e = left ? edge[wave - 1][1] + lane
-                           : edge[wave + 1][0] + (lane - (64 - M));
-#pragma unroll
-    for (int q = 0; q < 6; ++q)
-#pragma unroll
-      for (int k = 0; k < P; ++k) f[q][k] = e[(q * P + k) * M];
-  }
-}
-
-// Tile t of a lattice of n nodes (array stride S) starting at lattice index
-// `start` = t*OUT - H, OUT = tile_nodes - 2H: load, K <= H/2 steps, store of
-// the interior [H, span - H) (one step has radius 2, so K steps need
-// H >= 2K).  Only the first nw wavefronts work (active_waves); the
-// others end at once, which a workgroup barrier allows (it waits for the
-// wavefronts that have not ended), and leave their SIMDs to other
-// workgroups.  With every_step (the recompute of a checkpoint segment for a
-// reverse sweep), the state after step s = 1..K is state i = first + s of
-// the segment, and the interior of those states whose i is a multiple of
-// `every` is stored, state i into fout + ((i-1)/every)*state_stride.
-template <int P, int WG, int M, int EQ>
-__device__ __forceinline__ void tile_run(const Consts& c,
-                                         const double* __restrict__ fin,
-                                         double* __restrict__ fout, int64_t S,
-                                         int64_t n, int64_t start, int H,
-                                         int K, bool every_step = false,
-                                         int64_t state_stride = 0,
-                                         int first = 0, int every = 1) {
-  // mirror lanes must hold at least one step's two wrong nodes
-  static_assert(WG == 1 || (M * P >= 2 && 2 * M <= 32), "mirror lanes");
-  constexpr int WW = 64 * P;              // nodes of one wavefront
-  constexpr int WS = (64 - 2 * M) * P;    // wavefront stride in the tile
-  __shared__ double stage[staged(P) ? WG * (WW + 64) : 1];
-  __shared__ double edge[2][WG][2][6 * P * M];
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int nw = active_waves<P, WG, M>(n, start, H);
-  if (wave >= nw) return;  // uniform over the wavefront
-  const int W = lbm::tile_nodes(P, nw, M);
-  double* lds = stage + (staged(P) ? wave * (WW + 64) : 0);
-  const int64_t wstart = start + wave * WS;
-  const bool inside = start >= 0 && start + W <= n;
-  const bool small = n < W;
-  double f[6][P];
-  tile_load<P>(fin, S, n, wstart, inside, small, lane, lds, f);
-  // the tile's valid indices [H, W - H), in this wavefront's numbering and
-  // restricted to its own lanes (the mirror lanes belong to the neighbours)
-  const int lo = max(H - wave * WS, wave > 0 ? M * P : 0);
-  const int hi = min(W - H - wave * WS, wave < nw - 1 ? WW - M * P : WW);
-  int since = 0, buf = 0;
-  // the next state to store and the steps up to it: counted, since dividing
-  // by `every` in each step took longer (n = 8192, P = 1, 34 steps:
-  // 18.1 -> 16.5 us)
-  int wait = every_step ? every - first % every : 0;
-  double* dst = every_step ? fout + (int64_t)(first / every) * state_stride : fout;
-  for (int step = 0; step < K; ++step) {
-    tile_step<P, EQ>(c, f);
-    if (every_step && --wait == 0) {
-      tile_store<P>(dst, S, n, wstart, lo, hi, lane, lds, f);
-      dst += state_stride;
-      wait = every;
-    }
-    if (WG > 1 && ++since == M * P / 2 && step + 1 < K) {
-      mirror_refresh<P, WG, M>(f, edge[buf], lane, wave, nw);
-      buf ^= 1;
-      since = 0;
-    }
-  }
-  if (!every_step) tile_store<P>(fout, S, n, wstart, lo, hi, lane, lds, f);
-}
-
 // Wavefronts per SIMD the tile kernels are compiled for (the register
 // budget: 512 / n VGPRs each).  Kernels of one kind of equilibria at P = 8 hold 168 VGPRs
 // for three (the few values that spill are touched only around the step

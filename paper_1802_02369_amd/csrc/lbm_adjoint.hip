@@ -537,9 +537,9 @@ __device__ __forceinline__ void adjoint_mirror_refresh(
 //
 // The stored states are fetched a step (E = 1) or a pair (E = 2) ahead.
 template <int P, int WG, int M, int E, int EQ>
-__global__ __launch_bounds__(64 * WG, E == 2 && EQ == 0 ? 2 : 1) void k_adjoint_tile(
+__device__ __forceinline__ void adjoint_tile(
     const Consts* __restrict__ cs, const int64_t* __restrict__ offs,
-    const TileRef* __restrict__ tiles, int64_t ntiles,
+    const TileRef* __restrict__ tiles, int64_t b,
     const double* __restrict__ ck, const double* __restrict__ seg, int64_t SD,
     int i_lo, int i_hi, const double* __restrict__ fbn,
     double* __restrict__ fbo, int64_t S, int H, double* __restrict__ rslots) {
@@ -552,8 +552,6 @@ __global__ __launch_bounds__(64 * WG, E == 2 && EQ == 0 ? 2 : 1) void k_adjoint_
   __shared__ double stage[staged(P) ? WG * (WW + 64) : 1];
   __shared__ double edge[2][WG][2][6 * P * M];
   __shared__ double red[3][WG];
-  const int64_t b = blockIdx.x;
-  if (b >= ntiles) return;  // uniform over the workgroup
   const TileRef tr = tiles[b];
   const int64_t off = offs[tr.inst];
   const int64_t n = offs[tr.inst + 1] - off;
@@ -660,6 +658,58 @@ __global__ __launch_bounds__(64 * WG, E == 2 && EQ == 0 ? 2 : 1) void k_adjoint_
 }
 
 template <int P, int WG, int M, int E, int EQ>
+__global__ __launch_bounds__(64 * WG, E == 2 && EQ == 0 ? 2 : 1) void k_adjoint_tile(
+    const Consts* __restrict__ cs, const int64_t* __restrict__ offs,
+    const TileRef* __restrict__ tiles, int64_t ntiles,
+    const double* __restrict__ ck, const double* __restrict__ seg, int64_t SD,
+    int i_lo, int i_hi, const double* __restrict__ fbn,
+    double* __restrict__ fbo, int64_t S, int H, double* __restrict__ rslots) {
+  if (blockIdx.x >= ntiles) return;  // uniform over the workgroup
+  adjoint_tile<P, WG, M, E, EQ>(cs, offs, tiles, blockIdx.x, ck, seg, SD, i_lo,
+                                i_hi, fbn, fbo, S, H, rslots);
+}
+
+// A launch of reverse steps of one segment and a launch of the recompute of
+// the segment before it, side by side in one grid, on tiles of one node per
+// lane: workgroups below n_rev reverse, the others recompute.  Either is bound
+// by the latency of its steps and leaves most of the chip idle, and on two
+// streams the events between them cost what the overlap gained.  (n = 8192,
+// segments of 100 steps, 1000 steps: 1250 us one after the other, 1190 on two
+// streams, 780 so.)
+struct RecLaunch {  // see k_batch_tile: K states from state `first` on
+  const TileRef* tiles;
+  int64_t ntiles;
+  const double* in;
+  double* out;
+  int H, K, first;
+};
+
+template <int WG, int EQ>
+__global__ __launch_bounds__(64 * WG) void k_sweep_tile(
+    const Consts* __restrict__ cs, const int64_t* __restrict__ offs,
+    const TileRef* __restrict__ tiles, int64_t n_rev,
+    const double* __restrict__ ck, const double* __restrict__ seg, int64_t SD,
+    int i_lo, int i_hi, const double* __restrict__ fbn,
+    double* __restrict__ fbo, int64_t S, int H, double* __restrict__ rslots,
+    RecLaunch rec) {
+  if (blockIdx.x < n_rev) {
+    adjoint_tile<1, WG, 8, 1, EQ>(cs, offs, tiles, blockIdx.x, ck, seg, SD, i_lo,
+                                  i_hi, fbn, fbo, S, H, rslots);
+    return;
+  }
+  const int64_t b = blockIdx.x - n_rev;
+  if (b >= rec.ntiles) return;  // uniform over the workgroup
+  const TileRef tr = rec.tiles[b];
+  const int64_t off = offs[tr.inst];
+  const int64_t n = offs[tr.inst + 1] - off;
+  const Consts c = cs[tr.inst];
+  const int OUT = lbm::tile_nodes(1, WG, 8) - 2 * rec.H;
+  tile_run<1, WG, 8, EQ>(c, rec.in + off, rec.out + off, S, n,
+                         (int64_t)tr.t * OUT - rec.H, rec.H, rec.K, true, SD,
+                         rec.first, 1);
+}
+
+template <int P, int WG, int M, int E, int EQ>
 void launch_adjoint_tile_t(const Consts* cs, const int64_t* offs,
                            const TileRef* tiles, int64_t ntiles,
                            const double* ck, const double* seg, int64_t SD,
@@ -707,6 +757,32 @@ int launch_adjoint_tile(const TileShape& t, int E, int eq, const Consts* cs,
   return set_err(LBM_EINVAL,
                  "unsupported adjoint tile shape P=%d waves=%d mirror=%d stride=%d",
                  t.P, t.W, t.M, E);
+}
+
+int launch_sweep_tile(const TileShape& t, int eq, const Consts* cs,
+                      const int64_t* offs, const TileRef* tiles, int64_t n_rev,
+                      const double* ck, const double* seg, int64_t SD, int i_lo,
+                      int i_hi, const double* fbn, double* fbo, int64_t S, int H,
+                      double* rslots, const RecLaunch& rec, hipStream_t s) {
+  const int64_t nodes = lbm::tile_nodes(t.P, t.W, t.M);
+  if (i_hi - i_lo < 1 || 2 * (i_hi - i_lo) > H || 2 * H >= nodes || rec.K < 1 ||
+      2 * rec.K > rec.H || 2 * rec.H >= nodes || rec.first < 0)
+    return set_err(LBM_EINVAL, "bad sweep tile geometry");
+#define LBM_SWEEP_CASE(WW, EE)                                                 \
+  if (t.P == 1 && t.W == WW && t.M == 8 && (eq == 0) == (EE == 0)) {           \
+    hipLaunchKernelGGL((k_sweep_tile<WW, EE>),                                 \
+                       dim3((unsigned)(n_rev + rec.ntiles)), dim3(64 * WW), 0, \
+                       s, cs, offs, tiles, n_rev, ck, seg, SD, i_lo, i_hi,     \
+                       fbn, fbo, S, H, rslots, rec);                           \
+    return hip_check(hipGetLastError(), "k_sweep_tile");                       \
+  }
+  LBM_SWEEP_CASE(4, 0)
+  LBM_SWEEP_CASE(4, -1)
+  LBM_SWEEP_CASE(8, 0)
+  LBM_SWEEP_CASE(8, -1)
+#undef LBM_SWEEP_CASE
+  return set_err(LBM_EINVAL, "unsupported sweep tile shape P=%d waves=%d mirror=%d",
+                 t.P, t.W, t.M);
 }
 
 // fbar of the equilibrium initialisation -> adjoints of rho, J, zeta.
@@ -914,16 +990,16 @@ int resolve_every(const lbm_batch* b, bool plain) {
 // The library's own shapes of a sweep with segments of C steps whose stored
 // states have stride E.  The reverse kernel takes 0.3 us per step and 0.085
 // per node of a lane and wavefront of a tile, one or two tiles on a compute
-// unit side by side, and 6 us per launch: one node per lane while there is a
-// compute unit for every tile, two once there is not, and launches that split
-// the segment evenly.  The recompute runs as long launches on the like shape,
-// (2, 4, 1) where it stores every second state.  Per step of the
-// whole reverse sweep, on the shapes of the default tunings and here: 1.88 and
-// 1.42 us at n = 8192 (segments of 100), 2.81 and 1.94 at 30000 (50), 4.57 and
-// 3.15 at 100003 (40), 17.9 and 16.4 at 1 M (50), 88 and 72 for 512 lattices
-// of 2048 .. 16384 nodes (16).  One stream does: beside these launches a
-// second one for the recompute gained nothing at 8192 nodes and lost 3 to
-// 15 % elsewhere.
+// unit side by side, 6 us per launch, and 96 bytes per node at 5 TB/s: one
+// node per lane while there is a compute unit for every tile, two once there
+// is not, and launches that split the segment evenly.  The recompute runs as
+// long launches on the like shape, (2, 4, 1) where it stores every second
+// state.  At one node per lane its launches join the reverse ones
+// (k_sweep_tile); of the others each step's recompute counts 0.2 us more.  Per
+// step of the whole reverse sweep, on the shapes of the default tunings and
+// here: 1.88 and 0.78 us at n = 8192 (segments of 100), 2.81 and 1.35 at 30000
+// (50), 4.57 and 3.0 at 100003 (40), 17.9 and 16.4 at 1 M (50), 88 and 72 for
+// 512 lattices of 2048 .. 16384 nodes (16).
 AdjShapes own_shapes(const lbm_batch* b, int64_t C, int E) {
   struct Shape {
     TileShape t;
@@ -943,7 +1019,8 @@ AdjShapes own_shapes(const lbm_batch* b, int64_t C, int E) {
       if (g < 2) g = std::ceil(g);
       const double us =
           (6.0 + 96.0 * (double)b->n_total / 5e6) * (double)j +
-          (double)C * (0.3 + 0.085 * sh.t.P * sh.t.W * g);
+          (double)C * (0.3 + 0.085 * sh.t.P * sh.t.W * g +
+                       (sh.E == 1 && sh.t.P > 1 ? 0.2 : 0.0));
       if (us < least) {
         least = us;
         a.rev = StepPlan{sh.t, std::max((int)K, E), 0};
@@ -965,8 +1042,11 @@ AdjShapes own_shapes(const lbm_batch* b, int64_t C, int E) {
 // launch that fills the chip gains nothing from a second stream (measured on
 // the 1024-lattice gradient) and the second buffer would cost its states
 // again.
+// The library's own shapes of one node per lane run both in the same launches
+// instead (joined; k_sweep_tile), unless that took a second buffer where the
+// tuning's shapes take one.
 struct AdjPlan {
-  bool plain, pipelined;
+  bool plain, pipelined, joined;
   RevShape rev;
   StepPlan fwd, rec;  // the checkpointed forward and the recompute
 };
@@ -978,10 +1058,12 @@ AdjPlan adj_plan(const lbm_batch* b, bool plain, int every, bool own, int64_t C)
                             ? b->adj_own
                             : own_shapes(b, C, E);
     const RevShape rev{a.rev.t, a.rev.K, 2 * a.rev.K + (E == 2 ? 2 : 0), E};
-    return AdjPlan{plain, false, rev, a.fwd, a.rec};
+    const bool joined = !plain && rev.t.P == 1 &&
+                        !rev_fills_chip(b, rev_shape(b->tune, E));
+    return AdjPlan{plain, false, joined, rev, a.fwd, a.rec};
   }
   const StepPlan tuned{shape_of(b->tune), b->tune.steps_per_launch, 0};
-  AdjPlan p{plain, false, rev_shape(b->tune, E), tuned, tuned};
+  AdjPlan p{plain, false, false, rev_shape(b->tune, E), tuned, tuned};
   p.pipelined = !plain && p.rev.out() >= 1 && !rev_fills_chip(b, p.rev);
   return p;
 }
@@ -1037,7 +1119,7 @@ AdjLayout adj_layout(const lbm_batch* b, int64_t nsteps, int64_t C,
   L.ckpt = o;
   o = align256(o + state * (size_t)L.n_ck);
   L.seg = o;
-  L.seg_bufs = P.pipelined ? 2 : 1;
+  L.seg_bufs = P.pipelined || P.joined ? 2 : 1;
   o = align256(o + state * (size_t)L.n_seg * L.seg_bufs);
   L.total = o;
   return L;
@@ -1145,29 +1227,33 @@ int enqueue_adjoint(lbm_batch* b, void* ws, int64_t nsteps, int64_t C,
   const int Kst = E == 2 ? Krec & ~1 : Krec;
   if (Kst < 1)  // resolve_every gives E = 2 only for K >= 2
     return set_err(LBM_EINVAL, "recompute stride %d with K = %d", E, Krec);
+  auto recompute_launch = [&](int64_t k, int64_t i0, int kk, hipStream_t st) {
+    return launch_batch_tile(cs, offs, at<TileRef>(ws, L.rec_tiles), L.n_rec,
+                             state(k, i0), segbuf(k), b->n_total, plan.rec.t,
+                             2 * Krec, kk, b->eq_class(), st, (int64_t)SD,
+                             (int)i0, E);
+  };
   auto recompute = [&](int64_t k, hipStream_t st) -> int {
     const int64_t len = seg_len(k);
     for (int64_t i0 = 0; i0 + 1 < len; i0 += Kst) {
-      const int kk = (int)std::min<int64_t>(Kst, len - 1 - i0);
-      const int r = launch_batch_tile(cs, offs, at<TileRef>(ws, L.rec_tiles),
-                                      L.n_rec, state(k, i0), segbuf(k),
-                                      b->n_total, plan.rec.t, 2 * Krec, kk,
-                                      b->eq_class(), st, (int64_t)SD, (int)i0,
-                                      E);
+      const int r = recompute_launch(
+          k, i0, (int)std::min<int64_t>(Kst, len - 1 - i0), st);
       if (r) return r;
     }
     return LBM_OK;
   };
   const RevShape rv = plan.rev;
   // the blocked reverse steps of segment k on s, up to rv.K per launch
+  auto reverse_launch = [&](int64_t k, int64_t lo, int64_t hi) {
+    return launch_adjoint_tile(rv.t, rv.E, b->eq_class(), cs, offs,
+                               at<TileRef>(ws, L.rev_tiles), L.n_rev, ckpt(k),
+                               segbuf(k), (int64_t)SD, (int)lo, (int)hi, cur, oth,
+                               b->n_total, rv.H, slots, s);
+  };
   auto reverse = [&](int64_t k) -> int {
     for (int64_t hi = seg_len(k); hi > 0;) {
       const int64_t lo = std::max<int64_t>(0, hi - rv.K);
-      const int r = launch_adjoint_tile(
-          rv.t, rv.E, b->eq_class(), cs, offs,
-          at<TileRef>(ws, L.rev_tiles), L.n_rev,
-          ckpt(k), segbuf(k), (int64_t)SD, (int)lo, (int)hi, cur, oth,
-          b->n_total, rv.H, slots, s);
+      const int r = reverse_launch(k, lo, hi);
       if (r) return r;
       std::swap(cur, oth);
       hi = lo;
@@ -1187,7 +1273,35 @@ int enqueue_adjoint(lbm_batch* b, void* ws, int64_t nsteps, int64_t C,
         std::swap(cur, oth);
       }
     }
-  } else if (L.seg_bufs == 1) {
+  } else if (plan.joined) {
+    // each launch of segment k's reverse steps beside one of the recompute of
+    // segment k-1, whose buffer reverse(k+1) was the last to read
+    if ((rc = recompute(L.n_ck - 1, s))) return rc;
+    for (int64_t k = L.n_ck - 1; k >= 0; --k) {
+      const int64_t len = k > 0 ? seg_len(k - 1) : 0;
+      int64_t hi = seg_len(k), i0 = 0;
+      while (hi > 0 || i0 + 1 < len) {
+        const int64_t lo = std::max<int64_t>(0, hi - rv.K);
+        const int kk = (int)std::min<int64_t>(Kst, len - 1 - i0);
+        if (hi > 0 && kk > 0)
+          rc = launch_sweep_tile(
+              rv.t, b->eq_class(), cs, offs, at<TileRef>(ws, L.rev_tiles),
+              L.n_rev, ckpt(k), segbuf(k), (int64_t)SD, (int)lo, (int)hi, cur,
+              oth, b->n_total, rv.H, slots,
+              RecLaunch{at<TileRef>(ws, L.rec_tiles), L.n_rec, state(k - 1, i0),
+                        segbuf(k - 1), 2 * Krec, kk, (int)i0},
+              s);
+        else if (hi > 0)
+          rc = reverse_launch(k, lo, hi);
+        else
+          rc = recompute_launch(k - 1, i0, kk, s);
+        if (rc) return rc;
+        if (hi > 0) std::swap(cur, oth);
+        hi = lo;
+        i0 += Kst;
+      }
+    }
+  } else if (!plan.pipelined) {
     for (int64_t k = L.n_ck - 1; k >= 0; --k) {
       if ((rc = recompute(k, s))) return rc;
       if ((rc = reverse(k))) return rc;
@@ -1325,7 +1439,7 @@ int lbm_batch_forward_ckpt(lbm_batch* b, double* f, void* ws, size_t ws_bytes,
                    "for this shape) cannot hold a halo of 2K = %d nodes; use "
                    "the one-step adjoint kernel or a smaller K",
                    2 * b->tune.steps_per_launch);
-  if (L.seg_bufs == 2) {
+  if (plan.pipelined) {
     // the pipelined reverse sweep's side stream (default priority) and
     // events, created once, outside any capture
     if (!b->rstream) {

@@ -90,3 +90,36 @@ def test_setting_the_tuning_in_force_keeps_the_workspace():
     b.forward_ckpt(f, 40, 10, ws)
     _, fbar = b.loss(f, None, ws)
     b.adjoint(ws, 40, 10, fbar)
+
+
+@pytest.mark.parametrize("lens, nsteps, ckpt", [
+    # a last segment shorter and longer than a launch, of one step, one
+    # segment alone; two and eight wavefronts' shapes
+    ([300, 65], 31, 10), ([300, 65], 30, 10), ([300, 65], 9, 20),
+    ([2000], 120, 119), ([2000], 301, 150), ([45001], 26, 25), ([45001], 60, 25),
+])
+def test_joined_launches_repeat_and_capture(lens, nsteps, ckpt):
+    """Recompute and reverse in the same launches: a second sweep, a captured
+    one and its replay give the bits of the first."""
+    tuned = dict(nodes_per_lane=2, steps_per_launch=4, waves_per_group=2)
+    f0, fb0, r0 = _sweep(lens, nsteps, ckpt, 1, 0, tuned)
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    f1, fb1, r1 = _sweep(lens, nsteps, ckpt, 1, 0, None)
+    assert torch.equal(f0, f1) and torch.equal(fb0, fb1)
+    assert np.abs(r0 - r1).max() <= 1e-9 * np.abs(r0).max()
+    b = lbm.Batch(off, [lbm.Params(s_e=1.3 + 0.01 * i) for i in range(len(lens))])
+    b.set_recompute_stride(1)
+    g = torch.Generator().manual_seed(11)
+    n = int(off[-1])
+    rho = (1 + 0.01 * torch.rand(n, generator=g, dtype=torch.float64)).cuda()
+    J = (0.01 * torch.rand(n, generator=g, dtype=torch.float64)).cuda()
+    ws = b.adjoint_workspace(nsteps, ckpt)
+    f = b.equilibrium(rho, J, torch.zeros_like(rho))
+    b.forward_ckpt(f, nsteps, ckpt, ws)
+    _, seed = b.loss(f, None, ws)
+    fbar = seed.clone()
+    for _ in range(4):
+        fbar.copy_(seed)
+        rates = b.adjoint(ws, nsteps, ckpt, fbar, use_graph=True).cpu().numpy()
+        assert torch.equal(fbar, fb1)
+        assert np.array_equal(rates, r1)
