@@ -291,8 +291,9 @@ LBM_API int lbm_forward_ckpt(lbm_handle* h, double* f, void* ws, size_t ws_bytes
                              int64_t nsteps, int64_t ckpt_every);
 /* Reverse sweep (synchronising for rbar).  fbar (device, 6*n): on entry
  * dL/df(T), on return dL/df(0).  rbar (host, 3): dL/d(s_e, s_psi, s_eps).
- * use_graph = 1 captures the launch sequence into a hipGraph on first use
- * (re-captured when ws, nsteps, ckpt_every, fbar or the tuning change). */
+ * use_graph = 1 captures the launch sequence into a hipGraph when the same
+ * arguments come a second time and replays it from then on (the first call
+ * with another ws, nsteps, ckpt_every, fbar or tuning enqueues it directly). */
 LBM_API int lbm_adjoint(lbm_handle* h, void* ws, size_t ws_bytes, int64_t nsteps,
                         int64_t ckpt_every, double* fbar, double rbar[3],
                         int use_graph);
@@ -421,8 +422,9 @@ LBM_API int lbm_batch_set_equilibrium(lbm_batch* b, const double* rho, const dou
                                       size_t ws_bytes);
 /* Advances every lattice of the batch state f (device, 6*n_total doubles) by
  * nsteps time steps, in place.  With use_graph = 1 the launches are captured
- * once into a hipGraph (re-captured when f, ws, nsteps or the tuning change)
- * and replayed with one hipGraphLaunch on the stream.  Lattices with
+ * into a hipGraph when the same arguments come a second time (the first call
+ * with another f, ws, nsteps or tuning enqueues them directly) and replayed
+ * with one hipGraphLaunch on the stream from then on.  Lattices with
  * LBM_CHECK_FINITE in their flags are checked after every launch (the
  * checks and the reset of the failure record are kernels inside the graph);
  * if any has them, the call synchronises and returns LBM_ENONFINITE when one

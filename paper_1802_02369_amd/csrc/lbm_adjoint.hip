@@ -1517,8 +1517,16 @@ int lbm_batch_adjoint(lbm_batch* b, void* ws, size_t ws_bytes, int64_t nsteps,
   if (overlaps(fbar, sizeof(double) * 6 * b->n_total, ws, ws_bytes))
     return set_err(LBM_EINVAL, "fbar overlaps the workspace");
   if (!use_graph) return enqueue_adjoint(b, ws, nsteps, ckpt_every, fbar, rbar, b->stream);
-  if (!(b->adj_exec && b->ag_fbar == fbar && b->ag_rbar == rbar)) {
+  // captured when the same arguments come a second time (see lbm_batch_run)
+  if (b->ag_fbar != fbar || b->ag_rbar != rbar) {
     drop_adjoint_graph(b);
+    rc = enqueue_adjoint(b, ws, nsteps, ckpt_every, fbar, rbar, b->stream);
+    if (rc) return rc;
+    b->ag_fbar = fbar;
+    b->ag_rbar = rbar;
+    return LBM_OK;
+  }
+  if (!b->adj_exec) {
     if (!b->cap &&
         (rc = hip_check(hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking),
                         "hipStreamCreate")))
@@ -1542,8 +1550,6 @@ int lbm_batch_adjoint(lbm_batch* b, void* ws, size_t ws_bytes, int64_t nsteps,
       b->adj_exec = nullptr;
       return rc;
     }
-    b->ag_fbar = fbar;
-    b->ag_rbar = rbar;
   }
   return hip_check(hipGraphLaunch(b->adj_exec, b->stream), "hipGraphLaunch");
 }

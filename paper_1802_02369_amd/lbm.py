@@ -41,6 +41,11 @@ class CParams(ctypes.Structure):
         ("flags", ctypes.c_int32), ("reserved", ctypes.c_int32)]
 
 
+# the same record in a numpy array
+PARAMS_DTYPE = [(k, "f8" if t is ctypes.c_double else "i4")
+                for k, t in CParams._fields_]
+
+
 class CTuning(ctypes.Structure):
     _fields_ = [("kernel", ctypes.c_int32), ("nodes_per_lane", ctypes.c_int32),
                 ("steps_per_launch", ctypes.c_int32),
@@ -383,13 +388,26 @@ class Batch:
     Params per lattice.  States are float64 tensors (6, n_total)."""
 
     def __init__(self, offsets, params, stream=None):
+        params = list(params)
+        self._open(offsets, (CParams * len(params))(*[p.c() for p in params]),
+                   stream)
+        self.params = params
+
+    @classmethod
+    def _from_records(cls, offsets, records, stream=None):
+        """A batch of parameter records (numpy, PARAMS_DTYPE) without a Params
+        object per lattice."""
+        b = cls.__new__(cls)
+        b._open(offsets, (CParams * len(records)).from_buffer(records), stream)
+        b.params = None
+        return b
+
+    def _open(self, offsets, arr, stream):
         import numpy as np
         self.offsets = np.ascontiguousarray(np.asarray(offsets, dtype=np.int64))
         self.n_inst = len(self.offsets) - 1
-        self.params = list(params)
-        if len(self.params) != self.n_inst:
+        if len(arr) != self.n_inst:
             raise ValueError("need one Params per lattice")
-        arr = (CParams * self.n_inst)(*[p.c() for p in self.params])
         self._h = _vp()
         check(lib().lbm_batch_init(
             ctypes.byref(self._h), self.n_inst,

@@ -1,0 +1,33 @@
+"""Parameter records of a batch, made for all lattices at once, are those of a
+Params object and the library's coupled rates per lattice, byte for byte."""
+import ctypes
+
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_1802_02369_amd import autograd, lbm  # noqa: E402
+
+
+@pytest.mark.parametrize("n", [1, 2, 1000])
+@pytest.mark.parametrize("consts", [None, dict(gamma=1.67, prandtl=0.7, c0=0.4,
+                                               lam=1.3, source_on=0)])
+def test_records_match_params(n, consts):
+    c = autograd._consts(consts)
+    g = torch.Generator().manual_seed(n)
+    s_e = 0.05 + 1.9 * torch.rand(n, generator=g, dtype=torch.float64)
+    s_eps = 0.5 + torch.rand(n, generator=g, dtype=torch.float64)
+    records, dpsi = autograd._records(s_e, s_eps, c)
+    assert records.itemsize == ctypes.sizeof(lbm.CParams)
+    for i in range(n):
+        s_psi, _, d = lbm.coupled_rates(float(s_e[i]), c["gamma"], c["prandtl"])
+        p = lbm.Params(s_e=float(s_e[i]), s_psi=s_psi, s_eps=float(s_eps[i]), **c)
+        assert records[i].tobytes() == bytes(p.c())
+        assert dpsi[i] == d
+
+
+@pytest.mark.parametrize("bad", [0.0, 2.0, -1.0, float("nan"), float("inf")])
+def test_records_refuse_what_the_library_refuses(bad):
+    s_e = torch.tensor([1.5, bad, 1.2], dtype=torch.float64)
+    with pytest.raises(lbm.LBMError, match="s_e must lie in"):
+        autograd._records(s_e, torch.ones(3), autograd._consts(None))
