@@ -1013,7 +1013,8 @@ AdjShapes own_shapes(const lbm_batch* b, int64_t C, int E) {
     if (sh.E != E) continue;
     const int64_t nodes = tile_nodes(sh.t.P, sh.t.W, sh.t.M) - 4 * (E - 1);
     const int64_t top = (nodes - kPlanMinOut) / 4;
-    for (int64_t j = (C + top - 1) / top, K = 0;; ++j) {
+    for (int64_t K = std::min(top, C); K > 0; K = next_split(K)) {
+      const int64_t j = (C + K - 1) / K;
       K = (C + j - 1) / j;
       double g = (double)tiles_of(b, nodes - 4 * K) / 256.0;
       if (g < 2) g = std::ceil(g);
@@ -1025,7 +1026,6 @@ AdjShapes own_shapes(const lbm_batch* b, int64_t C, int E) {
         least = us;
         a.rev = StepPlan{sh.t, std::max((int)K, E), 0};
       }
-      if (K <= 8) break;
     }
   }
   a.rec = a.rev;
@@ -1051,10 +1051,15 @@ struct AdjPlan {
   StepPlan fwd, rec;  // the checkpointed forward and the recompute
 };
 
+// Steps of a sweep's longest segment (at least one).
+int64_t segment_steps(int64_t nsteps, int64_t C) {
+  return std::max<int64_t>(1, std::min(nsteps, C));
+}
+
 AdjPlan adj_plan(const lbm_batch* b, bool plain, int every, bool own, int64_t C) {
   const int E = plain ? 1 : every;
   if (own) {
-    const AdjShapes a = b->adj_own_ckpt == C && b->adj_own_every == E
+    const AdjShapes a = b->adj_own_seg == C && b->adj_own_every == E
                             ? b->adj_own
                             : own_shapes(b, C, E);
     const RevShape rev{a.rev.t, a.rev.K, 2 * a.rev.K + (E == 2 ? 2 : 0), E};
@@ -1070,8 +1075,9 @@ AdjPlan adj_plan(const lbm_batch* b, bool plain, int every, bool own, int64_t C)
 
 // The plan that lbm_batch_forward_ckpt resolved (the reverse sweep and its
 // checks).
-AdjPlan resolved_plan(const lbm_batch* b, int64_t C) {
-  return adj_plan(b, b->adj_plain, b->adj_every, b->adj_auto, C);
+AdjPlan resolved_plan(const lbm_batch* b, int64_t nsteps, int64_t C) {
+  return adj_plan(b, b->adj_plain, b->adj_every, b->adj_auto,
+                  segment_steps(nsteps, C));
 }
 
 int64_t plan_out(const StepPlan& p) {
@@ -1188,7 +1194,7 @@ int check_adj(const lbm_batch* b, const void* ws, size_t ws_bytes,
     return set_err(LBM_EINVAL,
                    "no checkpoints for this workspace, nsteps and ckpt_every: "
                    "call lbm_batch_forward_ckpt first");
-  if (ws_bytes < adj_layout(b, nsteps, C, resolved_plan(b, C)).total)
+  if (ws_bytes < adj_layout(b, nsteps, C, resolved_plan(b, nsteps, C)).total)
     return set_err(LBM_EWORKSPACE, "adjoint workspace too small");
   return LBM_OK;
 }
@@ -1196,7 +1202,7 @@ int check_adj(const lbm_batch* b, const void* ws, size_t ws_bytes,
 // The reverse sweep: recompute each checkpoint segment, then adjoint steps.
 int enqueue_adjoint(lbm_batch* b, void* ws, int64_t nsteps, int64_t C,
                     double* fbar, double* rbar, hipStream_t s) {
-  const AdjPlan plan = resolved_plan(b, C);
+  const AdjPlan plan = resolved_plan(b, nsteps, C);
   const AdjLayout L = adj_layout(b, nsteps, C, plan);
   const Consts* cs = at<Consts>(ws, L.consts);
   const int64_t* offs = at<int64_t>(ws, L.offs);
@@ -1402,7 +1408,8 @@ size_t lbm_batch_adjoint_workspace_bytes(const lbm_batch* b, int64_t nsteps,
   size_t most = 0;
   for (const bool own : {false, b->plan_auto})
     most = std::max(most, adj_layout(b, nsteps, ckpt_every,
-                                     adj_plan(b, plain, every, own, ckpt_every))
+                                     adj_plan(b, plain, every, own,
+                                              segment_steps(nsteps, ckpt_every)))
                               .total);
   return most;
 }
@@ -1419,12 +1426,13 @@ int lbm_batch_forward_ckpt(lbm_batch* b, double* f, void* ws, size_t ws_bytes,
   b->adj_auto = b->plan_auto;
   if (b->adj_auto) {
     const int E = b->adj_plain ? 1 : b->adj_every;
-    if (b->adj_own_ckpt != ckpt_every || b->adj_own_every != E)
-      b->adj_own = own_shapes(b, ckpt_every, E);
-    b->adj_own_ckpt = ckpt_every;
+    const int64_t seg = segment_steps(nsteps, ckpt_every);
+    if (b->adj_own_seg != seg || b->adj_own_every != E)
+      b->adj_own = own_shapes(b, seg, E);
+    b->adj_own_seg = seg;
     b->adj_own_every = E;
   }
-  const AdjPlan plan = resolved_plan(b, ckpt_every);
+  const AdjPlan plan = resolved_plan(b, nsteps, ckpt_every);
   const AdjLayout L = adj_layout(b, nsteps, ckpt_every, plan);
   if (ws_bytes < L.total)
     return set_err(LBM_EWORKSPACE, "adjoint workspace of %zu bytes, need %zu",
@@ -1557,9 +1565,9 @@ int lbm_batch_adjoint(lbm_batch* b, void* ws, size_t ws_bytes, int64_t nsteps,
 int lbm_batch_loss(lbm_batch* b, const double* f, const double* target,
                    void* ws, size_t ws_bytes, double* loss, double* fbar) {
   if (!b || !f || !ws || !loss || !fbar) return set_err(LBM_EINVAL, "NULL argument");
-  if (b->adj_ws != ws || ws_bytes < adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b, b->adj_ckpt)).total)
+  if (b->adj_ws != ws || ws_bytes < adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b, b->adj_nsteps, b->adj_ckpt)).total)
     return set_err(LBM_EINVAL, "call lbm_batch_forward_ckpt with this workspace first");
-  const AdjLayout L = adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b, b->adj_ckpt));
+  const AdjLayout L = adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b, b->adj_nsteps, b->adj_ckpt));
   // the tiles' sums take the rate slots, which a reverse sweep clears first
   double* parts = at<double>(ws, L.rslots);
   hipLaunchKernelGGL(k_loss, dim3((unsigned)L.n_adj), dim3(256), 0, b->stream,
@@ -1581,9 +1589,9 @@ int lbm_batch_equilibrium_adjoint(lbm_batch* b, const double* rho,
                                   size_t ws_bytes) {
   if (!b || !rho || !J || !zeta || !fbar || !rho_bar || !J_bar || !zeta_bar || !ws)
     return set_err(LBM_EINVAL, "NULL argument");
-  if (b->adj_ws != ws || ws_bytes < adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b, b->adj_ckpt)).total)
+  if (b->adj_ws != ws || ws_bytes < adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b, b->adj_nsteps, b->adj_ckpt)).total)
     return set_err(LBM_EINVAL, "call lbm_batch_forward_ckpt with this workspace first");
-  const AdjLayout L = adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b, b->adj_ckpt));
+  const AdjLayout L = adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b, b->adj_nsteps, b->adj_ckpt));
   hipLaunchKernelGGL(k_equilibrium_adjoint, node_grid(b), dim3(256), 0, b->stream,
                      at<Consts>(ws, L.consts), at<int64_t>(ws, L.offs), b->n_inst,
                      rho, J, zeta, fbar, rho_bar, J_bar, zeta_bar, b->n_total);
@@ -1593,9 +1601,9 @@ int lbm_batch_equilibrium_adjoint(lbm_batch* b, const double* rho,
 int lbm_batch_moments_adjoint(lbm_batch* b, const double* mbar, double* fbar,
                               void* ws, size_t ws_bytes) {
   if (!b || !mbar || !fbar || !ws) return set_err(LBM_EINVAL, "NULL argument");
-  if (b->adj_ws != ws || ws_bytes < adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b, b->adj_ckpt)).total)
+  if (b->adj_ws != ws || ws_bytes < adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b, b->adj_nsteps, b->adj_ckpt)).total)
     return set_err(LBM_EINVAL, "call lbm_batch_forward_ckpt with this workspace first");
-  const AdjLayout L = adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b, b->adj_ckpt));
+  const AdjLayout L = adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b, b->adj_nsteps, b->adj_ckpt));
   hipLaunchKernelGGL(k_moments_adjoint, node_grid(b), dim3(256), 0, b->stream,
                      at<Consts>(ws, L.consts), at<int64_t>(ws, L.offs), b->n_inst,
                      mbar, fbar, b->n_total);
@@ -1659,7 +1667,7 @@ int lbm_adjoint(lbm_handle* h, void* ws, size_t ws_bytes, int64_t nsteps,
   if (!h || !rbar) return set_err(LBM_EINVAL, "NULL argument");
   lbm_batch* b = single_batch(h);
   if (!b) return LBM_EINVAL;
-  const AdjLayout L = adj_layout(b, nsteps, ckpt_every, resolved_plan(b, ckpt_every));
+  const AdjLayout L = adj_layout(b, nsteps, ckpt_every, resolved_plan(b, nsteps, ckpt_every));
   double* dev = at<double>(ws, L.scratch);
   int rc = lbm_batch_adjoint(b, ws, ws_bytes, nsteps, ckpt_every, fbar, dev,
                              use_graph);
@@ -1677,7 +1685,7 @@ int lbm_loss(lbm_handle* h, const double* f, const double* target, void* ws,
   lbm_batch* b = single_batch(h);
   if (!b) return LBM_EINVAL;
   if (b->adj_ws != ws) return set_err(LBM_EINVAL, "call lbm_forward_ckpt first");
-  const AdjLayout L = adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b, b->adj_ckpt));
+  const AdjLayout L = adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b, b->adj_nsteps, b->adj_ckpt));
   double* dev = at<double>(ws, L.scratch);
   int rc = lbm_batch_loss(b, f, target, ws, ws_bytes, dev, fbar);
   if (!rc)

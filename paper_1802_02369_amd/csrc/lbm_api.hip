@@ -296,10 +296,11 @@ StepPlan plan_tiles(const std::vector<int64_t>& offsets, int64_t steps) {
   const BatchModel model(offsets);
   StepPlan best{{8, 4, 1}, 16, 0};
   double least = INFINITY;
-  for (const TileCost& c : kTileCosts)
-    for (int64_t j = 1, K = 0; j == 1 || K > 8; ++j) {
-      const int64_t top = (tile_nodes(c.t.P, c.t.W, c.t.M) - kPlanMinOut) / 4;
-      j = std::max(j, (steps + top - 1) / top);
+  for (const TileCost& c : kTileCosts) {
+    const int64_t top = (tile_nodes(c.t.P, c.t.W, c.t.M) - kPlanMinOut) / 4;
+    for (int64_t K = std::min<int64_t>({top, steps, 128}); K > 0;
+         K = next_split(K)) {
+      const int64_t j = (steps + K - 1) / K;
       K = (steps + j - 1) / j;
       const double us = model.tiles_us(c, (int)K, 0, (double)j / (double)steps);
       if (us < least) {
@@ -307,6 +308,7 @@ StepPlan plan_tiles(const std::vector<int64_t>& offsets, int64_t steps) {
         best = StepPlan{c.t, (int)K, 0};
       }
     }
+  }
   return best;
 }
 
@@ -725,7 +727,7 @@ int lbm_diagnostics(lbm_handle* h, const double* f, void* ws, size_t ws_bytes,
     std::lock_guard<std::mutex> lock(h->diag_lock);
     if (!h->diag_sums &&
         (rc = hip_check(hipHostMalloc((void**)&h->diag_sums, diag_sums_bytes(),
-                                      hipHostMallocDefault),
+                                      hipHostMallocPortable),
                         "hipHostMalloc")))
       return rc;
     if ((rc = launch_diagnostics(h->c, f, h->n, h->diag_sums, h->stream)))

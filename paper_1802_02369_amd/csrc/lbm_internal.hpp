@@ -3,8 +3,9 @@
 
 #include <hip/hip_runtime.h>
 
-#include <string>
+#include <algorithm>
 #include <mutex>
+#include <string>
 #include <vector>
 #include <map>
 
@@ -169,6 +170,11 @@ struct BatchPlan;
 BatchPlan plan_batch(const std::vector<int64_t>& offsets, bool resident);
 // Shape and steps per launch of runs of `steps` >= 1 steps on tiles.
 StepPlan plan_tiles(const std::vector<int64_t>& offsets, int64_t steps);
+// The next shorter launch length to consider, 0 at the end (8 steps, or less
+// where no more were asked for): a few dozen however long the run.
+inline int64_t next_split(int64_t K) {
+  return K <= 8 ? 0 : K - std::max<int64_t>(1, K / 12);
+}
 // Tile shapes and steps per launch of a checkpointed sweep: forward, recompute
 // and reverse.
 struct AdjShapes {
@@ -359,9 +365,9 @@ struct lbm_batch {
   // uploaded tables
   bool adj_auto = false, adj_auto_up = false;
   // the shapes of the library's own plan that lbm_batch_forward_ckpt made,
-  // for adj_own_ckpt steps per segment and state stride adj_own_every
+  // for segments of adj_own_seg steps and state stride adj_own_every
   lbm::AdjShapes adj_own{};
-  int64_t adj_own_ckpt = 0;
+  int64_t adj_own_seg = 0;
   int32_t adj_own_every = 0;
   // requested stride of the segment states the reverse sweep stores (0:
   // automatic), what lbm_batch_forward_ckpt resolved it to, and the value
