@@ -630,17 +630,11 @@ def bench_adjoint(torch, lbm, workloads, stream, counter_run=False):
     # A lattice this small leaves the chip mostly idle: each step is a chain
     # of dependent arithmetic per lane, so the time per step, not the issue
     # rate, bounds it.
-    t = lat.get_tuning()
-    span = t["nodes_per_lane"] * (62 * t["waves_per_group"] + 2) \
-        if t["nodes_per_lane"] > 1 else 64
-    tiles = -(-n // (span - 4 * t["steps_per_launch"]))
     roof = leg_roofline("adjoint", g * 1e9, GRAD_BYTES_PER_NODE_STEP,
                         "forward node-step", bytes_basis=GRAD_BYTES_BASIS)
     roof["latency"] = {
         "us_per_time_step": ms * 1e3 / steps,
-        "forward_alone_us_per_time_step": n / (fwd["default"] * 1e9) * 1e6,
-        "forward_wavefronts_per_launch": tiles * t["waves_per_group"],
-        "chip_wavefronts_at_two_per_simd": 2048}
+        "forward_alone_us_per_time_step": n / (fwd["default"] * 1e9) * 1e6}
     return {"value": g, "unit": "G forward node-steps/s (whole gradient)",
             "n_nodes": n, "time_steps": steps, "ckpt_every": ck,
             "ms_per_gradient": ms, "workspace_gb": aws.numel() * 8 / 1e9,
@@ -890,7 +884,7 @@ def main():
     Fv = c["valu_instr"] / c["computed_units"] if c else None
     traffic = ((c["fetch_bytes"] + c["write_bytes"]) / c["launches"]
                if c and c.get("fetch_bytes") and c.get("write_bytes") else None)
-    kname = f"k_step_tile<{P}, {Wg}, 0>"
+    kname = f"k_step_tile<{P}, {Wg}, 1, 0>"
     # algorithmic FP64 instructions per launch: per node-update figure times
     # the node-updates one launch delivers (halo recomputation is overhead)
     per_launch_s = n * T / L / (launch_ms * 1e-3) / 1e12
