@@ -277,11 +277,12 @@ LBM_API int lbm_autotune(lbm_handle* h, double* f, void* ws, size_t ws_bytes,
  * stride (0 on bad arguments): ceil(nsteps/ckpt_every) checkpoints, the
  * stored recomputed states (m = min(ckpt_every, nsteps) - 1 of them, or
  * floor(m/2) at stride 2, see lbm_set_recompute_stride), one more state and
- * tables.  The recomputed states are held twice when the reverse sweep is
- * pipelined: with the blocked reverse kernel on problems whose reverse
- * launches hold fewer than 2048 wavefronts (small lattices), the recompute
- * of one checkpoint segment runs on a second stream beside the reverse
- * steps of the next. */
+ * tables.  The recomputed states are held twice with the blocked reverse
+ * kernel on problems whose reverse launches hold fewer than 2048 wavefronts
+ * (small lattices): there the recompute of one checkpoint segment runs beside
+ * the reverse steps of the next, in the same launches, or on a second stream
+ * once a tuning is set.  Until then the sweep picks its own tile shapes; the
+ * size is enough for those and for the tuning's. */
 LBM_API size_t lbm_adjoint_workspace_bytes(lbm_handle* h, int64_t nsteps,
                                            int64_t ckpt_every);
 /* Advances f (device, 6*n) by nsteps steps in place like lbm_step, keeping
