@@ -1191,6 +1191,19 @@ int launch_batch_tile(const Consts* cs, const int64_t* offs,
   }
   LBM_WIDE_SHAPES(LBM_BATCH_CASE)
 #undef LBM_BATCH_CASE
+  // the recompute of k_sweep_tile's shape of two nodes per lane
+  if (t.P == 2 && t.W == 4 && t.M == 4 && state_stride != 0) {
+    const dim3 grid((unsigned)ntiles), block(256);
+    if (eq == 0)
+      hipLaunchKernelGGL((k_batch_tile<2, 4, 4, 0, true>), grid, block, 0, s, cs,
+                         offs, tiles, fin, fout, S, H, K, ntiles, state_stride,
+                         first, every);
+    else
+      hipLaunchKernelGGL((k_batch_tile<2, 4, 4, -1, true>), grid, block, 0, s, cs,
+                         offs, tiles, fin, fout, S, H, K, ntiles, state_stride,
+                         first, every);
+    return hip_check(hipGetLastError(), "k_batch_tile");
+  }
   return set_err(LBM_EINVAL, "unsupported tile shape P=%d waves=%d mirror=%d",
                  t.P, t.W, t.M);
 }

@@ -670,8 +670,7 @@ __global__ __launch_bounds__(64 * WG, E == 2 && EQ == 0 ? 2 : 1) void k_adjoint_
 }
 
 // A launch of reverse steps of one segment and a launch of the recompute of
-// the segment before it, side by side in one grid, on tiles of one node per
-// lane: workgroups below n_rev reverse, the others recompute.  Either is bound
+// the segment before it, side by side in one grid: workgroups below n_rev reverse, the others recompute.  Either is bound
 // by the latency of its steps and leaves most of the chip idle, and on two
 // streams the events between them cost what the overlap gained.  (n = 8192,
 // segments of 100 steps, 1000 steps: 1250 us one after the other, 1190 on two
@@ -684,7 +683,7 @@ struct RecLaunch {  // see k_batch_tile: K states from state `first` on
   int H, K, first;
 };
 
-template <int WG, int EQ>
+template <int P, int WG, int M, int EQ>
 __global__ __launch_bounds__(64 * WG) void k_sweep_tile(
     const Consts* __restrict__ cs, const int64_t* __restrict__ offs,
     const TileRef* __restrict__ tiles, int64_t n_rev,
@@ -693,7 +692,7 @@ __global__ __launch_bounds__(64 * WG) void k_sweep_tile(
     double* __restrict__ fbo, int64_t S, int H, double* __restrict__ rslots,
     RecLaunch rec) {
   if (blockIdx.x < n_rev) {
-    adjoint_tile<1, WG, 8, 1, EQ>(cs, offs, tiles, blockIdx.x, ck, seg, SD, i_lo,
+    adjoint_tile<P, WG, M, 1, EQ>(cs, offs, tiles, blockIdx.x, ck, seg, SD, i_lo,
                                   i_hi, fbn, fbo, S, H, rslots);
     return;
   }
@@ -703,8 +702,8 @@ __global__ __launch_bounds__(64 * WG) void k_sweep_tile(
   const int64_t off = offs[tr.inst];
   const int64_t n = offs[tr.inst + 1] - off;
   const Consts c = cs[tr.inst];
-  const int OUT = lbm::tile_nodes(1, WG, 8) - 2 * rec.H;
-  tile_run<1, WG, 8, EQ>(c, rec.in + off, rec.out + off, S, n,
+  const int OUT = lbm::tile_nodes(P, WG, M) - 2 * rec.H;
+  tile_run<P, WG, M, EQ>(c, rec.in + off, rec.out + off, S, n,
                          (int64_t)tr.t * OUT - rec.H, rec.H, rec.K, true, SD,
                          rec.first, 1);
 }
@@ -768,18 +767,20 @@ int launch_sweep_tile(const TileShape& t, int eq, const Consts* cs,
   if (i_hi - i_lo < 1 || 2 * (i_hi - i_lo) > H || 2 * H >= nodes || rec.K < 1 ||
       2 * rec.K > rec.H || 2 * rec.H >= nodes || rec.first < 0)
     return set_err(LBM_EINVAL, "bad sweep tile geometry");
-#define LBM_SWEEP_CASE(WW, EE)                                                 \
-  if (t.P == 1 && t.W == WW && t.M == 8 && (eq == 0) == (EE == 0)) {           \
-    hipLaunchKernelGGL((k_sweep_tile<WW, EE>),                                 \
+#define LBM_SWEEP_CASE(PP, WW, MM, EE)                                         \
+  if (t.P == PP && t.W == WW && t.M == MM && (eq == 0) == (EE == 0)) {         \
+    hipLaunchKernelGGL((k_sweep_tile<PP, WW, MM, EE>),                         \
                        dim3((unsigned)(n_rev + rec.ntiles)), dim3(64 * WW), 0, \
                        s, cs, offs, tiles, n_rev, ck, seg, SD, i_lo, i_hi,     \
                        fbn, fbo, S, H, rslots, rec);                           \
     return hip_check(hipGetLastError(), "k_sweep_tile");                       \
   }
-  LBM_SWEEP_CASE(4, 0)
-  LBM_SWEEP_CASE(4, -1)
-  LBM_SWEEP_CASE(8, 0)
-  LBM_SWEEP_CASE(8, -1)
+  LBM_SWEEP_CASE(1, 4, 8, 0)
+  LBM_SWEEP_CASE(1, 4, 8, -1)
+  LBM_SWEEP_CASE(1, 8, 8, 0)
+  LBM_SWEEP_CASE(1, 8, 8, -1)
+  LBM_SWEEP_CASE(2, 4, 4, 0)
+  LBM_SWEEP_CASE(2, 4, 4, -1)
 #undef LBM_SWEEP_CASE
   return set_err(LBM_EINVAL, "unsupported sweep tile shape P=%d waves=%d mirror=%d",
                  t.P, t.W, t.M);
@@ -987,18 +988,27 @@ int resolve_every(const lbm_batch* b, bool plain) {
   return rev_fills_chip(b, r) ? 2 : 1;
 }
 
+// Whether reverse launches of this shape (E = 1) take the recompute beside
+// them (k_sweep_tile): at one node per lane always; at two, which hold 169
+// VGPRs, while both parts' tiles find a place on the chip at once (100003 nodes
+// on 253 tiles: 2.79 -> 2.42 us per step; 180000 on 446: 3.77 -> 4.24).
+bool sweeps_joined(const lbm_batch* b, const StepPlan& rev) {
+  return rev.t.P == 1 ||
+         tiles_of(b, tile_nodes(rev.t.P, rev.t.W, rev.t.M) - 4 * rev.K) <= 256;
+}
+
 // The library's own shapes of a sweep with segments of C steps whose stored
 // states have stride E.  The reverse kernel takes 0.3 us per step and 0.085
 // per node of a lane and wavefront of a tile, one or two tiles on a compute
 // unit side by side, 6 us per launch, and 96 bytes per node at 5 TB/s: one
 // node per lane while there is a compute unit for every tile, two once there
 // is not, and launches that split the segment evenly.  The recompute runs as
-// long launches on the like shape, (2, 4, 1) where it stores every second
-// state.  At one node per lane its launches join the reverse ones
-// (k_sweep_tile); of the others each step's recompute counts 0.2 us more.  Per
+// long launches on the same shape where they join the reverse ones
+// (sweeps_joined), else on (2, 8, 4), which counts 0.2 us per step more, and on
+// (2, 4, 1) where it stores every second state.  Per
 // step of the whole reverse sweep, on the shapes of the default tunings and
 // here: 1.88 and 0.78 us at n = 8192 (segments of 100), 2.81 and 1.35 at 30000
-// (50), 4.57 and 3.0 at 100003 (40), 17.9 and 16.4 at 1 M (50), 88 and 72 for
+// (50), 4.57 and 2.4 at 100003 (40), 17.9 and 16.4 at 1 M (50), 88 and 72 for
 // 512 lattices of 2048 .. 16384 nodes (16).
 AdjShapes own_shapes(const lbm_batch* b, int64_t C, int E) {
   struct Shape {
@@ -1017,11 +1027,12 @@ AdjShapes own_shapes(const lbm_batch* b, int64_t C, int E) {
       const int64_t j = (C + K - 1) / K;
       K = (C + j - 1) / j;
       double g = (double)tiles_of(b, nodes - 4 * K) / 256.0;
-      if (g < 2) g = std::ceil(g);
+      const bool side = sh.E == 1 && (sh.t.P == 1 || g <= 1);
+      if (g < 3) g = std::ceil(g);
       const double us =
           (6.0 + 96.0 * (double)b->n_total / 5e6) * (double)j +
           (double)C * (0.3 + 0.085 * sh.t.P * sh.t.W * g +
-                       (sh.E == 1 && sh.t.P > 1 ? 0.2 : 0.0));
+                       (sh.E == 1 && !side ? 0.2 : 0.0));
       if (us < least) {
         least = us;
         a.rev = StepPlan{sh.t, std::max((int)K, E), 0};
@@ -1029,7 +1040,10 @@ AdjShapes own_shapes(const lbm_batch* b, int64_t C, int E) {
     }
   }
   a.rec = a.rev;
-  if (a.rev.t.P > 1) a.rec.t = E == 2 ? TileShape{2, 4, 1} : TileShape{2, 8, 4};
+  if (E == 2)
+    a.rec.t = TileShape{2, 4, 1};
+  else if (!sweeps_joined(b, a.rev))
+    a.rec.t = TileShape{2, 8, 4};
   return a;
 }
 
@@ -1042,8 +1056,8 @@ AdjShapes own_shapes(const lbm_batch* b, int64_t C, int E) {
 // launch that fills the chip gains nothing from a second stream (measured on
 // the 1024-lattice gradient) and the second buffer would cost its states
 // again.
-// The library's own shapes of one node per lane run both in the same launches
-// instead (joined; k_sweep_tile), unless that took a second buffer where the
+// The library's own shapes run both in the same launches instead where that is
+// faster (joined; sweeps_joined), unless that took a second buffer where the
 // tuning's shapes take one.
 struct AdjPlan {
   bool plain, pipelined, joined;
@@ -1063,7 +1077,7 @@ AdjPlan adj_plan(const lbm_batch* b, bool plain, int every, bool own, int64_t C)
                             ? b->adj_own
                             : own_shapes(b, C, E);
     const RevShape rev{a.rev.t, a.rev.K, 2 * a.rev.K + (E == 2 ? 2 : 0), E};
-    const bool joined = !plain && rev.t.P == 1 &&
+    const bool joined = !plain && E == 1 && sweeps_joined(b, a.rev) &&
                         !rev_fills_chip(b, rev_shape(b->tune, E));
     return AdjPlan{plain, false, joined, rev, a.fwd, a.rec};
   }

@@ -97,6 +97,8 @@ def test_setting_the_tuning_in_force_keeps_the_workspace():
     # segment alone; two and eight wavefronts' shapes
     ([300, 65], 31, 10), ([300, 65], 30, 10), ([300, 65], 9, 20),
     ([2000], 120, 119), ([2000], 301, 150), ([45001], 26, 25), ([45001], 60, 25),
+    # two nodes per lane, joined and not
+    ([100003], 5, 2), ([95001], 35, 17), ([180001], 31, 15),
 ])
 def test_joined_launches_repeat_and_capture(lens, nsteps, ckpt):
     """Recompute and reverse in the same launches: a second sweep, a captured
