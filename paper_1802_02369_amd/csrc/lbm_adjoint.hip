@@ -1070,7 +1070,8 @@ int64_t segment_steps(int64_t nsteps, int64_t C) {
   return std::max<int64_t>(1, std::min(nsteps, C));
 }
 
-AdjPlan adj_plan(const lbm_batch* b, bool plain, int every, bool own, int64_t C) {
+AdjPlan adj_plan(const lbm_batch* b, const lbm_tuning& t, bool plain, int every,
+                 bool own, int64_t C) {
   const int E = plain ? 1 : every;
   if (own) {
     const AdjShapes a = b->adj_own_seg == C && b->adj_own_every == E
@@ -1078,20 +1079,20 @@ AdjPlan adj_plan(const lbm_batch* b, bool plain, int every, bool own, int64_t C)
                             : own_shapes(b, C, E);
     const RevShape rev{a.rev.t, a.rev.K, 2 * a.rev.K + (E == 2 ? 2 : 0), E};
     const bool joined = !plain && E == 1 && sweeps_joined(b, a.rev) &&
-                        !rev_fills_chip(b, rev_shape(b->tune, E));
+                        !rev_fills_chip(b, rev_shape(t, E));
     return AdjPlan{plain, false, joined, rev, a.fwd, a.rec};
   }
-  const StepPlan tuned{shape_of(b->tune), b->tune.steps_per_launch, 0};
-  AdjPlan p{plain, false, false, rev_shape(b->tune, E), tuned, tuned};
+  const StepPlan tuned{shape_of(t), t.steps_per_launch, 0};
+  AdjPlan p{plain, false, false, rev_shape(t, E), tuned, tuned};
   p.pipelined = !plain && p.rev.out() >= 1 && !rev_fills_chip(b, p.rev);
   return p;
 }
 
-// The plan that lbm_batch_forward_ckpt resolved (the reverse sweep and its
-// checks).
-AdjPlan resolved_plan(const lbm_batch* b, int64_t nsteps, int64_t C) {
-  return adj_plan(b, b->adj_plain, b->adj_every, b->adj_auto,
-                  segment_steps(nsteps, C));
+// The plan of the uploaded tables, for the calls after a forward: whatever
+// settings or refused forwards came since, the tables are where it puts them.
+AdjPlan uploaded_plan(const lbm_batch* b, int64_t nsteps, int64_t C) {
+  return adj_plan(b, b->adj_tune, b->adj_plain_up, b->adj_every_up,
+                  b->adj_auto_up, segment_steps(nsteps, C));
 }
 
 int64_t plan_out(const StepPlan& p) {
@@ -1208,7 +1209,7 @@ int check_adj(const lbm_batch* b, const void* ws, size_t ws_bytes,
     return set_err(LBM_EINVAL,
                    "no checkpoints for this workspace, nsteps and ckpt_every: "
                    "call lbm_batch_forward_ckpt first");
-  if (ws_bytes < adj_layout(b, nsteps, C, resolved_plan(b, nsteps, C)).total)
+  if (ws_bytes < adj_layout(b, nsteps, C, uploaded_plan(b, nsteps, C)).total)
     return set_err(LBM_EWORKSPACE, "adjoint workspace too small");
   return LBM_OK;
 }
@@ -1216,7 +1217,7 @@ int check_adj(const lbm_batch* b, const void* ws, size_t ws_bytes,
 // The reverse sweep: recompute each checkpoint segment, then adjoint steps.
 int enqueue_adjoint(lbm_batch* b, void* ws, int64_t nsteps, int64_t C,
                     double* fbar, double* rbar, hipStream_t s) {
-  const AdjPlan plan = resolved_plan(b, nsteps, C);
+  const AdjPlan plan = uploaded_plan(b, nsteps, C);
   const AdjLayout L = adj_layout(b, nsteps, C, plan);
   const Consts* cs = at<Consts>(ws, L.consts);
   const int64_t* offs = at<int64_t>(ws, L.offs);
@@ -1280,7 +1281,7 @@ int enqueue_adjoint(lbm_batch* b, void* ws, int64_t nsteps, int64_t C,
     }
     return LBM_OK;
   };
-  if (b->adj_plain) {
+  if (plan.plain) {
     for (int64_t k = L.n_ck - 1; k >= 0; --k) {
       if ((rc = recompute(k, s))) return rc;
       for (int64_t i = seg_len(k) - 1; i >= 0; --i) {
@@ -1367,7 +1368,7 @@ int enqueue_adjoint(lbm_batch* b, void* ws, int64_t nsteps, int64_t C,
                       "hipMemcpyAsync")))
     return rc;
   hipLaunchKernelGGL((k_tile_sum<3>), dim3((unsigned)b->n_inst), dim3(256), 0, s,
-                     at<int64_t>(ws, b->adj_plain ? L.adj_first : L.rev_first),
+                     at<int64_t>(ws, plan.plain ? L.adj_first : L.rev_first),
                      (const double*)slots, rbar);
   return hip_check(hipGetLastError(), "k_tile_sum");
 }
@@ -1422,7 +1423,7 @@ size_t lbm_batch_adjoint_workspace_bytes(const lbm_batch* b, int64_t nsteps,
   size_t most = 0;
   for (const bool own : {false, b->plan_auto})
     most = std::max(most, adj_layout(b, nsteps, ckpt_every,
-                                     adj_plan(b, plain, every, own,
+                                     adj_plan(b, b->tune, plain, every, own,
                                               segment_steps(nsteps, ckpt_every)))
                               .total);
   return most;
@@ -1437,16 +1438,10 @@ int lbm_batch_forward_ckpt(lbm_batch* b, double* f, void* ws, size_t ws_bytes,
   // its tiles can hold the forward halo, else the one-step kernel
   b->adj_plain = resolve_adj_plain(b);
   b->adj_every = resolve_every(b, b->adj_plain);
-  b->adj_auto = b->plan_auto;
-  if (b->adj_auto) {
-    const int E = b->adj_plain ? 1 : b->adj_every;
-    const int64_t seg = segment_steps(nsteps, ckpt_every);
-    if (b->adj_own_seg != seg || b->adj_own_every != E)
-      b->adj_own = own_shapes(b, seg, E);
-    b->adj_own_seg = seg;
-    b->adj_own_every = E;
-  }
-  const AdjPlan plan = resolved_plan(b, nsteps, ckpt_every);
+  const bool own = b->plan_auto;
+  const int64_t seg = segment_steps(nsteps, ckpt_every);
+  const AdjPlan plan =
+      adj_plan(b, b->tune, b->adj_plain, b->adj_every, own, seg);
   const AdjLayout L = adj_layout(b, nsteps, ckpt_every, plan);
   if (ws_bytes < L.total)
     return set_err(LBM_EWORKSPACE, "adjoint workspace of %zu bytes, need %zu",
@@ -1485,7 +1480,7 @@ int lbm_batch_forward_ckpt(lbm_batch* b, double* f, void* ws, size_t ws_bytes,
                     same_tuning(b->adj_tune, b->tune) &&
                     b->adj_plain_up == b->adj_plain &&
                     b->adj_every_up == b->adj_every &&
-                    b->adj_auto_up == b->adj_auto;
+                    b->adj_auto_up == own;
   if (!same) {
     // tables of this workspace layout: forward and recompute tiles, tiles of
     // the blocked and of the one-step reverse kernels, and each lattice's
@@ -1525,7 +1520,13 @@ int lbm_batch_forward_ckpt(lbm_batch* b, double* f, void* ws, size_t ws_bytes,
     b->adj_tune = b->tune;
     b->adj_plain_up = b->adj_plain;
     b->adj_every_up = b->adj_every;
-    b->adj_auto_up = b->adj_auto;
+    b->adj_auto_up = own;
+    if (own) {
+      b->adj_own = AdjShapes{plan.fwd, plan.rec,
+                             StepPlan{plan.rev.t, plan.rev.K, 0}};
+      b->adj_own_seg = seg;
+      b->adj_own_every = b->adj_plain ? 1 : b->adj_every;
+    }
   }
   return enqueue_forward_ckpt(b, ws, f, nsteps, ckpt_every, plan, L, s);
 }
@@ -1579,9 +1580,9 @@ int lbm_batch_adjoint(lbm_batch* b, void* ws, size_t ws_bytes, int64_t nsteps,
 int lbm_batch_loss(lbm_batch* b, const double* f, const double* target,
                    void* ws, size_t ws_bytes, double* loss, double* fbar) {
   if (!b || !f || !ws || !loss || !fbar) return set_err(LBM_EINVAL, "NULL argument");
-  if (b->adj_ws != ws || ws_bytes < adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b, b->adj_nsteps, b->adj_ckpt)).total)
+  if (b->adj_ws != ws || ws_bytes < adj_layout(b, b->adj_nsteps, b->adj_ckpt, uploaded_plan(b, b->adj_nsteps, b->adj_ckpt)).total)
     return set_err(LBM_EINVAL, "call lbm_batch_forward_ckpt with this workspace first");
-  const AdjLayout L = adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b, b->adj_nsteps, b->adj_ckpt));
+  const AdjLayout L = adj_layout(b, b->adj_nsteps, b->adj_ckpt, uploaded_plan(b, b->adj_nsteps, b->adj_ckpt));
   // the tiles' sums take the rate slots, which a reverse sweep clears first
   double* parts = at<double>(ws, L.rslots);
   hipLaunchKernelGGL(k_loss, dim3((unsigned)L.n_adj), dim3(256), 0, b->stream,
@@ -1603,9 +1604,9 @@ int lbm_batch_equilibrium_adjoint(lbm_batch* b, const double* rho,
                                   size_t ws_bytes) {
   if (!b || !rho || !J || !zeta || !fbar || !rho_bar || !J_bar || !zeta_bar || !ws)
     return set_err(LBM_EINVAL, "NULL argument");
-  if (b->adj_ws != ws || ws_bytes < adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b, b->adj_nsteps, b->adj_ckpt)).total)
+  if (b->adj_ws != ws || ws_bytes < adj_layout(b, b->adj_nsteps, b->adj_ckpt, uploaded_plan(b, b->adj_nsteps, b->adj_ckpt)).total)
     return set_err(LBM_EINVAL, "call lbm_batch_forward_ckpt with this workspace first");
-  const AdjLayout L = adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b, b->adj_nsteps, b->adj_ckpt));
+  const AdjLayout L = adj_layout(b, b->adj_nsteps, b->adj_ckpt, uploaded_plan(b, b->adj_nsteps, b->adj_ckpt));
   hipLaunchKernelGGL(k_equilibrium_adjoint, node_grid(b), dim3(256), 0, b->stream,
                      at<Consts>(ws, L.consts), at<int64_t>(ws, L.offs), b->n_inst,
                      rho, J, zeta, fbar, rho_bar, J_bar, zeta_bar, b->n_total);
@@ -1615,9 +1616,9 @@ int lbm_batch_equilibrium_adjoint(lbm_batch* b, const double* rho,
 int lbm_batch_moments_adjoint(lbm_batch* b, const double* mbar, double* fbar,
                               void* ws, size_t ws_bytes) {
   if (!b || !mbar || !fbar || !ws) return set_err(LBM_EINVAL, "NULL argument");
-  if (b->adj_ws != ws || ws_bytes < adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b, b->adj_nsteps, b->adj_ckpt)).total)
+  if (b->adj_ws != ws || ws_bytes < adj_layout(b, b->adj_nsteps, b->adj_ckpt, uploaded_plan(b, b->adj_nsteps, b->adj_ckpt)).total)
     return set_err(LBM_EINVAL, "call lbm_batch_forward_ckpt with this workspace first");
-  const AdjLayout L = adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b, b->adj_nsteps, b->adj_ckpt));
+  const AdjLayout L = adj_layout(b, b->adj_nsteps, b->adj_ckpt, uploaded_plan(b, b->adj_nsteps, b->adj_ckpt));
   hipLaunchKernelGGL(k_moments_adjoint, node_grid(b), dim3(256), 0, b->stream,
                      at<Consts>(ws, L.consts), at<int64_t>(ws, L.offs), b->n_inst,
                      mbar, fbar, b->n_total);
@@ -1681,7 +1682,7 @@ int lbm_adjoint(lbm_handle* h, void* ws, size_t ws_bytes, int64_t nsteps,
   if (!h || !rbar) return set_err(LBM_EINVAL, "NULL argument");
   lbm_batch* b = single_batch(h);
   if (!b) return LBM_EINVAL;
-  const AdjLayout L = adj_layout(b, nsteps, ckpt_every, resolved_plan(b, nsteps, ckpt_every));
+  const AdjLayout L = adj_layout(b, nsteps, ckpt_every, uploaded_plan(b, nsteps, ckpt_every));
   double* dev = at<double>(ws, L.scratch);
   int rc = lbm_batch_adjoint(b, ws, ws_bytes, nsteps, ckpt_every, fbar, dev,
                              use_graph);
@@ -1699,7 +1700,7 @@ int lbm_loss(lbm_handle* h, const double* f, const double* target, void* ws,
   lbm_batch* b = single_batch(h);
   if (!b) return LBM_EINVAL;
   if (b->adj_ws != ws) return set_err(LBM_EINVAL, "call lbm_forward_ckpt first");
-  const AdjLayout L = adj_layout(b, b->adj_nsteps, b->adj_ckpt, resolved_plan(b, b->adj_nsteps, b->adj_ckpt));
+  const AdjLayout L = adj_layout(b, b->adj_nsteps, b->adj_ckpt, uploaded_plan(b, b->adj_nsteps, b->adj_ckpt));
   double* dev = at<double>(ws, L.scratch);
   int rc = lbm_batch_loss(b, f, target, ws, ws_bytes, dev, fbar);
   if (!rc)

@@ -361,11 +361,9 @@ struct lbm_batch {
   // launch (else K per launch)
   bool adj_plain = false;
   bool adj_plain_up = false;  // the value the uploaded tables were built for
-  // plan_auto when lbm_batch_forward_ckpt resolved the plan, and for the
-  // uploaded tables
-  bool adj_auto = false, adj_auto_up = false;
-  // the shapes of the library's own plan that lbm_batch_forward_ckpt made,
-  // for segments of adj_own_seg steps and state stride adj_own_every
+  bool adj_auto_up = false;  // plan_auto when the tables were uploaded
+  // the shapes of the library's own plan in the uploaded tables, for segments
+  // of adj_own_seg steps and state stride adj_own_every
   lbm::AdjShapes adj_own{};
   int64_t adj_own_seg = 0;
   int32_t adj_own_every = 0;

@@ -1,0 +1,122 @@
+"""What the library launches, seen through a recorded HIP runtime (no GPU)."""
+import ctypes
+import shutil
+
+import numpy as np
+import pytest
+
+from launch_util import Memory, run_recorded
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+
+
+def recorded(tmp_path, function, *args):
+    run_recorded(tmp_path, "test_launches_host", function, *args)
+
+
+class Null:
+    cuda_stream = 0
+
+
+def make_batch(lens, kinds=(0,)):
+    from paper_1802_02369_amd import lbm
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    return lbm.Batch(off, [lbm.Params(s_e=1.3, eq_kind=k, source_on=int(k < 2),
+                                      s_psi=1.3)
+                           for k in np.resize(kinds, len(lens))], stream=Null())
+
+
+# ------------------------------------ a refused forward leaves the sweep --
+
+def set_tuning(L, h, shape=None):
+    """The tuning (P, K, wavefronts), or the one in force."""
+    from paper_1802_02369_amd import lbm
+    t = lbm.CTuning()
+    assert L.lbm_batch_get_tuning(h, ctypes.byref(t)) == 0
+    if shape:
+        t.nodes_per_lane, t.steps_per_launch, t.waves_per_group = shape
+    assert L.lbm_batch_set_tuning(h, ctypes.byref(t)) == 0
+
+
+def sweep_calls(rec, tuned, between):
+    """Return codes of the calls that use a checkpointed forward's tables, and
+    the calls they made, pointers as buffer and offset; `between` runs after
+    the forward."""
+    from paper_1802_02369_amd import lbm
+    L = lbm.lib()
+    b = make_batch([3000, 20000, 770])
+    h, n, T, C = b._h, 23770, 20, 7
+    if tuned:
+        set_tuning(L, h, tuned)
+    ws = Memory(L.lbm_batch_adjoint_workspace_bytes(h, T, C))
+    f, fbar, aux = Memory(48 * n), Memory(48 * n), Memory(48 * n)
+    assert L.lbm_batch_forward_ckpt(h, f.ptr, ws.ptr, ws.nbytes, T, C) == 0
+    between(L, h, f, ws, T, C)
+    rec.clear()
+    codes = [
+        L.lbm_batch_loss(h, f.ptr, None, ws.ptr, ws.nbytes, aux.ptr, fbar.ptr),
+        L.lbm_batch_moments_adjoint(h, aux.ptr, fbar.ptr, ws.ptr, ws.nbytes),
+        L.lbm_batch_equilibrium_adjoint(h, aux.ptr, aux.ptr, aux.ptr, fbar.ptr,
+                                        aux.ptr, aux.ptr, aux.ptr, ws.ptr,
+                                        ws.nbytes),
+        L.lbm_batch_adjoint(h, ws.ptr, ws.nbytes, T, C, fbar.ptr, aux.ptr, 0)]
+    buffers = {"ws": ws, "f": f, "fbar": fbar, "aux": aux}
+
+    def name(word):
+        if not word.startswith("0x"):
+            return word
+        p = int(word, 16)
+        return next((f"{k}+{p - m.ptr}" for k, m in buffers.items()
+                     if m.ptr <= p < m.ptr + m.nbytes), "host")
+    return codes, [" ".join(map(name, x.split())) for x in rec.log()]
+
+
+def too_small(L, h, f, ws, T, C):
+    set_tuning(L, h)
+    assert L.lbm_batch_forward_ckpt(h, f.ptr, ws.ptr, 64, T, C) == -3
+
+
+def overlapping(L, h, f, ws, T, C):
+    set_tuning(L, h)
+    assert L.lbm_batch_forward_ckpt(h, ws.ptr + 64, ws.ptr, ws.nbytes, T, C) == -1
+
+
+def misaligned(L, h, f, ws, T, C):
+    set_tuning(L, h)
+    assert L.lbm_batch_forward_ckpt(h, f.ptr + 4, ws.ptr, ws.nbytes, T, C) == -1
+
+
+def other_steps(L, h, f, ws, T, C):
+    assert L.lbm_batch_forward_ckpt(h, f.ptr, ws.ptr, 64, 3 * T, C + 2) == -3
+
+
+def other_stride(L, h, f, ws, T, C):
+    assert L.lbm_batch_set_recompute_stride(h, 2) == 0
+    assert L.lbm_batch_forward_ckpt(h, f.ptr, ws.ptr, 64, T, C) == -3
+
+
+def other_shape(L, h, f, ws, T, C):
+    set_tuning(L, h, (4, 16, 2))
+
+
+def refused_forward(rec, how, tuned, sweeps):
+    want, plain = sweep_calls(rec, tuned, lambda *a: None)
+    assert want == [0] * 4
+    got, calls = sweep_calls(rec, tuned, globals()[how])
+    assert got == [0, 0, 0, 0 if sweeps else -1], got
+    if not sweeps:
+        plain = plain[:len(calls)]
+    assert calls == plain, [x for x in zip(calls, plain) if x[0] != x[1]][:3]
+
+
+@pytest.mark.parametrize("how, tuned, sweeps", [
+    ("too_small", None, True), ("overlapping", None, True),
+    ("misaligned", None, True), ("other_steps", None, True),
+    # settings the sweep was not resolved for: the reverse sweep is refused
+    # until the next forward_ckpt, the other calls take the tables there are
+    ("other_stride", (2, 8, 1), False), ("other_shape", (2, 8, 1), False)])
+def test_refused_forward_leaves_the_sweep(tmp_path, how, tuned, sweeps):
+    """A forward_ckpt that is refused, also after the tuning in force was set,
+    changes nothing about the sweep of the forward before it: the launches are
+    the same, on the same tables of the workspace."""
+    recorded(tmp_path, "refused_forward", how, tuned, sweeps)
