@@ -1682,9 +1682,11 @@ int lbm_adjoint(lbm_handle* h, void* ws, size_t ws_bytes, int64_t nsteps,
   if (!h || !rbar) return set_err(LBM_EINVAL, "NULL argument");
   lbm_batch* b = single_batch(h);
   if (!b) return LBM_EINVAL;
+  int rc = check_adj(b, ws, ws_bytes, nsteps, ckpt_every);
+  if (rc) return rc;
   const AdjLayout L = adj_layout(b, nsteps, ckpt_every, uploaded_plan(b, nsteps, ckpt_every));
   double* dev = at<double>(ws, L.scratch);
-  int rc = lbm_batch_adjoint(b, ws, ws_bytes, nsteps, ckpt_every, fbar, dev,
+  rc = lbm_batch_adjoint(b, ws, ws_bytes, nsteps, ckpt_every, fbar, dev,
                              use_graph);
   if (!rc)
     rc = hip_check(hipMemcpyAsync(rbar, dev, 3 * sizeof(double),

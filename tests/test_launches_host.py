@@ -120,3 +120,26 @@ def test_refused_forward_leaves_the_sweep(tmp_path, how, tuned, sweeps):
     changes nothing about the sweep of the forward before it: the launches are
     the same, on the same tables of the workspace."""
     recorded(tmp_path, "refused_forward", how, tuned, sweeps)
+
+
+# --------------------------------------- arguments no forward was run with --
+
+def adjoint_of_no_forward(rec, ckpt, after):
+    from paper_1802_02369_amd import lbm
+    L = lbm.lib()
+    lat = lbm.Lattice(100, stream=Null())
+    ws, f, fbar = Memory(1 << 20), Memory(4800), Memory(4800)
+    if after:
+        assert L.lbm_forward_ckpt(lat._h, f.ptr, ws.ptr, ws.nbytes, 9, 3) == 0
+    rec.clear()
+    rates = (ctypes.c_double * 3)()
+    assert L.lbm_adjoint(lat._h, ws.ptr, ws.nbytes, 9, ckpt, fbar.ptr, rates, 0) == -1
+    assert rec.log() == []
+
+
+@pytest.mark.parametrize("ckpt", [0, -1, 4])
+@pytest.mark.parametrize("after", [False, True])
+def test_adjoint_refuses_other_checkpoints(tmp_path, ckpt, after):
+    """lbm_adjoint with a ckpt_every that no forward was run with, 0 among
+    them, is refused before it does anything."""
+    recorded(tmp_path, "adjoint_of_no_forward", ckpt, after)
