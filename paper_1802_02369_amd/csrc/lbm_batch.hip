@@ -609,12 +609,6 @@ int lbm_batch_init(lbm_batch** b, int64_t n_inst, const int64_t* offsets,
                           [](const lbm_params& q) { return q.eq_kind == 0; })
                   ? 0
                   : -1;
-  x->tile_eq = std::all_of(params, params + n_inst,
-                           [&](const lbm_params& q) {
-                             return q.eq_kind == params[0].eq_kind;
-                           })
-                   ? params[0].eq_kind
-                   : -1;
   x->consts.resize(n_inst);
   for (int64_t i = 0; i < n_inst; ++i) {
     int rc = make_consts(&params[i], &x->consts[i]);
@@ -623,7 +617,9 @@ int lbm_batch_init(lbm_batch** b, int64_t n_inst, const int64_t* offsets,
       return set_err(rc, "lattice %lld: %s", (long long)i, g_err.c_str());
     }
   }
+  x->tile_eq = x->consts[0].eq_kind;
   for (int64_t i = 0; i < n_inst; ++i) {
+    if (x->consts[i].eq_kind != x->tile_eq) x->tile_eq = -1;
     x->plan_tiles += (offsets[i + 1] - offsets[i] + kPlanMinOut - 1) / kPlanMinOut;
     if (params[i].flags & LBM_CHECK_FINITE) x->any_check = true;
   }

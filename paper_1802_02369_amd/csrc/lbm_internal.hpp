@@ -383,8 +383,9 @@ struct lbm_batch {
   // (set by lbm_batch_init; the constants do not change afterwards)
   int32_t eq_cls = 0;
   int eq_class() const { return eq_cls; }
-  // eq_kind of every lattice, -1 if they differ: the equilibria the launches
-  // that store no checkpoint segments are compiled for
+  // Consts::eq_kind of every lattice (the thermal scheme's are linear), -1 if
+  // they differ: the equilibria the launches that store no checkpoint segments
+  // are compiled for
   int32_t tile_eq = 0;
 
   // whether lattice i may run resident with the current mode: only in

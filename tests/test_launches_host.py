@@ -21,7 +21,7 @@ class Null:
 def make_batch(lens, kinds=(0,)):
     from paper_1802_02369_amd import lbm
     off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
-    return lbm.Batch(off, [lbm.Params(s_e=1.3, eq_kind=k, source_on=int(k < 2),
+    return lbm.Batch(off, [lbm.Params(s_e=1.3, eq_kind=int(k), source_on=int(k < 2),
                                       s_psi=1.3)
                            for k in np.resize(kinds, len(lens))], stream=Null())
 
@@ -143,3 +143,37 @@ def test_adjoint_refuses_other_checkpoints(tmp_path, ckpt, after):
     """lbm_adjoint with a ckpt_every that no forward was run with, 0 among
     them, is refused before it does anything."""
     recorded(tmp_path, "adjoint_of_no_forward", ckpt, after)
+
+
+# ------------------------------------------------- kernels of one kind --
+
+def kinds_of_kernels(rec, kinds, want):
+    from paper_1802_02369_amd import lbm
+    L = lbm.lib()
+    b = make_batch([3000, 700, 90, 41], kinds)
+    h, n = b._h, 3831
+    f = Memory(48 * n)
+    for tuned in (None, (4, 16, 4)):
+        if tuned:
+            set_tuning(L, h, tuned)
+        ws = Memory(L.lbm_batch_workspace_bytes(h, 0))
+        assert L.lbm_batch_prepare(h, ws.ptr, ws.nbytes) == 0
+        rec.clear()
+        assert L.lbm_batch_run(h, f.ptr, ws.ptr, ws.nbytes, 40, 0) == 0
+        aws = Memory(L.lbm_batch_adjoint_workspace_bytes(h, 10, 5))
+        assert L.lbm_batch_forward_ckpt(h, f.ptr, aws.ptr, aws.nbytes, 10, 5) == 0
+        # k_batch_tile<P, W, M, EQ, false>
+        eq = {x.split("k_batch_tileI")[1].split("EEE")[0].split("E")[3]
+              for x in rec.launches("k_batch_tile")}
+        assert eq == {want}, eq
+
+
+@pytest.mark.parametrize("kinds, want", [
+    ((0,), "Li0"), ((1,), "Li1"), ((2,), "Li2"),
+    # the thermal scheme's equilibria are linear
+    ((3,), "Li1"), ((1, 3), "Li1"),
+    ((0, 1), "Lin1"), ((2, 3), "Lin1")])
+def test_kernels_of_one_kind_of_equilibria(tmp_path, kinds, want):
+    """Batches whose lattices have equilibria of one form run the kernels
+    compiled for it, others the one that selects them per lattice."""
+    recorded(tmp_path, "kinds_of_kernels", kinds, want)
