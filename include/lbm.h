@@ -257,7 +257,9 @@ LBM_API int lbm_diagnostics(lbm_handle* h, const double* f, void* ws, size_t ws_
  * <equilibrium class>/<kernel generation>" to the chosen shape; a hit skips
  * the timing, a miss adds the entry.  The
  * chosen shape becomes the handle's tuning and is returned in *out (may be
- * NULL). */
+ * NULL).  The library's own choice (see lbm_set_tuning) takes part as the
+ * default tuning: where it is the fastest, the entry says so, the handle goes
+ * on choosing by itself, and *out is the default tuning of its n. */
 LBM_API int lbm_autotune(lbm_handle* h, double* f, void* ws, size_t ws_bytes,
                          int64_t probe_steps, const char* cache_path, lbm_tuning* out);
 

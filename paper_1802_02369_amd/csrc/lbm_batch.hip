@@ -236,10 +236,12 @@ void drop_graph(lbm_batch* b) {
 
 // --------------------------------------------------------- tuning cache --
 
-// A tuning-cache entry: the shape and, for batches, optional shape groups
-// with their measured time per computed node-update.
+// A tuning-cache entry: the shape, whether it stands for the library's own
+// plan, and, for batches, optional shape groups with their measured time per
+// computed node-update.
 struct CacheEntry {
   lbm_tuning t{};
+  bool plan = false;
   std::vector<lbm_tuning> gshape;
   std::vector<double> gcost;
   int resident = -1;  // batch entries: the resident mode the search kept
@@ -275,6 +277,11 @@ std::map<std::string, CacheEntry> read_cache(const char* path) {
                     &t.kernel, &t.nodes_per_lane, &t.steps_per_launch,
                     &t.waves_per_group) == 4 &&
         check_tuning(&t) == LBM_OK) {
+      // optional "plan": 1
+      const size_t pp = body.find("\"plan\"");
+      int pl = 0;
+      e.plan = pp != std::string::npos &&
+               std::sscanf(body.c_str() + pp, "\"plan\" : %d", &pl) == 1 && pl == 1;
       // optional "groups": [[P, K, W, seconds per node-update], ...]
       const size_t gp = body.find("\"groups\"");
       size_t q = gp == std::string::npos ? gp : body.find('[', gp);
@@ -318,12 +325,13 @@ std::map<std::string, CacheEntry> read_cache(const char* path) {
 namespace lbm {
 
 bool tune_cache_get(const char* path, const std::string& key, lbm_tuning* t,
-                    std::vector<lbm_tuning>* gshape, std::vector<double>* gcost,
+                    bool* plan, std::vector<lbm_tuning>* gshape, std::vector<double>* gcost,
                     int* resident) {
   auto m = read_cache(path);
   auto it = m.find(key);
   if (it == m.end()) return false;
   *t = it->second.t;
+  *plan = it->second.plan;
   if (gshape) *gshape = it->second.gshape;
   if (gcost) *gcost = it->second.gcost;
   if (resident && it->second.resident >= 0) *resident = it->second.resident;
@@ -331,12 +339,14 @@ bool tune_cache_get(const char* path, const std::string& key, lbm_tuning* t,
 }
 
 void tune_cache_put(const char* path, const std::string& key,
-                    const lbm_tuning& t, const std::vector<lbm_tuning>* gshape,
+                    const lbm_tuning& t, bool plan,
+                    const std::vector<lbm_tuning>* gshape,
                     const std::vector<double>* gcost, int resident) {
   if (!path) return;
   auto m = read_cache(path);
   CacheEntry e;
   e.t = t;
+  e.plan = plan;
   if (gshape && gcost) {
     e.gshape = *gshape;
     e.gcost = *gcost;
@@ -353,6 +363,7 @@ void tune_cache_put(const char* path, const std::string& key,
     std::fprintf(fp, "  \"%s\": {\"kernel\": %d, \"P\": %d, \"K\": %d, \"W\": %d",
                  kv.first.c_str(), x.t.kernel, x.t.nodes_per_lane,
                  x.t.steps_per_launch, x.t.waves_per_group);
+    if (x.plan) std::fprintf(fp, ", \"plan\": 1");
     if (!x.gshape.empty()) {
       std::fprintf(fp, ", \"groups\": [");
       for (size_t g = 0; g < x.gshape.size(); ++g)
@@ -466,7 +477,7 @@ int apply_groups(lbm_batch* b, const std::vector<lbm_tuning>& gshape,
 
 // Generation of the tile kernels, the last component of every tuning-cache
 // key: entries measured on kernels of another generation are not reused.
-constexpr const char* kKernelGeneration = "/k7";
+constexpr const char* kKernelGeneration = "/k8";
 
 // Times `run(t)` for each candidate on the state f, restoring f from
 // `backup` before each run and at the end; returns the fastest, and every
@@ -548,7 +559,11 @@ int lbm_autotune(lbm_handle* h, double* f, void* ws, size_t ws_bytes,
       (h->p.eq_kind == 0 ? "/eq8" : "/eqsel") + kKernelGeneration;
   lbm_tuning best{};
   const lbm_tuning d = default_tuning(h->n, h->n, h->p.eq_kind == 0 ? 0 : -1);
-  if (!tune_cache_get(cache_path, key, &best)) {
+  bool plan = false;
+  if (tune_cache_get(cache_path, key, &best, &plan)) {
+    // the plan that won may have been measured at a size with another default
+    if (plan) best = d;
+  } else {
     std::vector<lbm_tuning> cands = tuning_candidates();
     cands.push_back(lbm_tuning{LBM_KERNEL_PLAIN, 0, 1, 1});
     // the default tuning stands for the library's own plan (plan_steps) here
@@ -575,11 +590,12 @@ int lbm_autotune(lbm_handle* h, double* f, void* ws, size_t ws_bytes,
       h->plan_auto = prev_auto;
       return rc;
     }
-    tune_cache_put(cache_path, key, best);
+    plan = same_tuning(best, d);
+    tune_cache_put(cache_path, key, best, plan);
   }
   h->tune = best;
   h->tune_default = false;
-  h->plan_auto = same_tuning(best, d);
+  h->plan_auto = plan;
   if (out) *out = best;
   return LBM_OK;
 }
@@ -1038,7 +1054,10 @@ int lbm_batch_autotune(lbm_batch* b, double* f, void* ws, size_t ws_bytes,
   std::vector<lbm_tuning> gshape;
   std::vector<double> gcost;
   int resident = b->resident_mode;
-  if (!tune_cache_get(cache_path, key, &best, &gshape, &gcost, &resident)) {
+  bool plan = false;
+  if (tune_cache_get(cache_path, key, &best, &plan, &gshape, &gcost, &resident)) {
+    if (plan) best = d;  // as in lbm_autotune
+  } else {
     double* backup = at<double>(ws, layout(b, tune_tiles(b), true).backup);
     const size_t sbytes = sizeof(double) * 6 * (size_t)b->n_total;
     // a failed search leaves the tuning, the groups and the mode as they were
@@ -1199,10 +1218,12 @@ int lbm_batch_autotune(lbm_batch* b, double* f, void* ws, size_t ws_bytes,
         resident = 1;
       }
     }
-    tune_cache_put(cache_path, key, best, &gshape, &gcost, resident);
+    plan = same_tuning(best, d);
+    tune_cache_put(cache_path, key, best, plan, &gshape, &gcost, resident);
   }
   b->resident_mode = resident;
-  use(best);
+  b->tune = best;
+  b->plan_auto = plan;
   int rc = gshape.empty() ? lbm_batch_set_groups(b, 0, nullptr, nullptr)
                           : apply_groups(b, gshape, gcost);
   if (!rc) rc = lbm_batch_prepare(b, ws, ws_bytes);

@@ -188,16 +188,18 @@ std::vector<lbm_tuning> tuning_candidates();
 
 bool overlaps(const void* a, size_t na, const void* b, size_t nb);
 
-// Tuning cache: "<arch>/<kind>/<class>" -> shape, in a small JSON file.
-// Batch entries may carry shape groups with their measured time per computed
-// node-update (gshape, gcost; absent groups read back empty) and the
-// resident mode (-1: none stored, *resident left as it is).
+// Tuning cache: "<arch>/<kind>/<class>" -> shape, in a small JSON file, with
+// *plan when the library's own plan was the fastest (the shape is then the
+// default tuning of the size it was measured at, which may not be that of
+// another size of the class).  Batch entries may carry shape groups with their
+// measured time per computed node-update (gshape, gcost; absent groups read
+// back empty) and the resident mode (-1: none stored, *resident left as it is).
 bool tune_cache_get(const char* path, const std::string& key, lbm_tuning* t,
-                    std::vector<lbm_tuning>* gshape = nullptr,
+                    bool* plan, std::vector<lbm_tuning>* gshape = nullptr,
                     std::vector<double>* gcost = nullptr,
                     int* resident = nullptr);
 void tune_cache_put(const char* path, const std::string& key,
-                    const lbm_tuning& t,
+                    const lbm_tuning& t, bool plan,
                     const std::vector<lbm_tuning>* gshape = nullptr,
                     const std::vector<double>* gcost = nullptr,
                     int resident = -1);

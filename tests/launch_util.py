@@ -1,10 +1,14 @@
 """Runs a function of a test file in a process whose HIP runtime is
 hip_recorder.cpp (no GPU): the library's host side is real, its kernels are
 written down instead of run."""
+import atexit
 import ctypes
+import functools
 import os
+import shutil
 import subprocess
 import sys
+import tempfile
 
 import numpy as np
 
@@ -12,14 +16,21 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 
 
-def run_recorded(tmp_path, module, function, *args):
-    """Calls module.function(recorder, *args) in the recorded process; the
-    child's assertions end it with a failure."""
-    so = os.path.join(str(tmp_path), "hip_recorder.so")
+@functools.lru_cache(None)
+def build():
+    tmp = tempfile.mkdtemp()
+    atexit.register(shutil.rmtree, tmp)
+    so = os.path.join(tmp, "hip_recorder.so")
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC",
                     os.path.join(HERE, "hip_recorder.cpp"), "-o", so], check=True)
+    return so
+
+
+def run_recorded(module, function, *args):
+    """Calls module.function(recorder, *args) in the recorded process; the
+    child's assertions end it with a failure."""
     code = (f"import sys; sys.path[:0] = [{ROOT!r}, {HERE!r}]\n"
-            f"from launch_util import Recorder\nr = Recorder({so!r})\n"
+            f"from launch_util import Recorder\nr = Recorder({build()!r})\n"
             f"import {module} as m\nm.{function}(r, *{args!r})\n")
     r = subprocess.run([sys.executable, "-c", code], capture_output=True,
                        text=True, timeout=300)

@@ -10,8 +10,8 @@ from launch_util import Memory, run_recorded
 pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
 
 
-def recorded(tmp_path, function, *args):
-    run_recorded(tmp_path, "test_launches_host", function, *args)
+def recorded(function, *args):
+    run_recorded("test_launches_host", function, *args)
 
 
 class Null:
@@ -115,11 +115,11 @@ def refused_forward(rec, how, tuned, sweeps):
     # settings the sweep was not resolved for: the reverse sweep is refused
     # until the next forward_ckpt, the other calls take the tables there are
     ("other_stride", (2, 8, 1), False), ("other_shape", (2, 8, 1), False)])
-def test_refused_forward_leaves_the_sweep(tmp_path, how, tuned, sweeps):
+def test_refused_forward_leaves_the_sweep(how, tuned, sweeps):
     """A forward_ckpt that is refused, also after the tuning in force was set,
     changes nothing about the sweep of the forward before it: the launches are
     the same, on the same tables of the workspace."""
-    recorded(tmp_path, "refused_forward", how, tuned, sweeps)
+    recorded("refused_forward", how, tuned, sweeps)
 
 
 # --------------------------------------- arguments no forward was run with --
@@ -139,10 +139,10 @@ def adjoint_of_no_forward(rec, ckpt, after):
 
 @pytest.mark.parametrize("ckpt", [0, -1, 4])
 @pytest.mark.parametrize("after", [False, True])
-def test_adjoint_refuses_other_checkpoints(tmp_path, ckpt, after):
+def test_adjoint_refuses_other_checkpoints(ckpt, after):
     """lbm_adjoint with a ckpt_every that no forward was run with, 0 among
     them, is refused before it does anything."""
-    recorded(tmp_path, "adjoint_of_no_forward", ckpt, after)
+    recorded("adjoint_of_no_forward", ckpt, after)
 
 
 # ------------------------------------------------- kernels of one kind --
@@ -173,7 +173,80 @@ def kinds_of_kernels(rec, kinds, want):
     # the thermal scheme's equilibria are linear
     ((3,), "Li1"), ((1, 3), "Li1"),
     ((0, 1), "Lin1"), ((2, 3), "Lin1")])
-def test_kernels_of_one_kind_of_equilibria(tmp_path, kinds, want):
+def test_kernels_of_one_kind_of_equilibria(kinds, want):
     """Batches whose lattices have equilibria of one form run the kernels
     compiled for it, others the one that selects them per lattice."""
-    recorded(tmp_path, "kinds_of_kernels", kinds, want)
+    recorded("kinds_of_kernels", kinds, want)
+
+
+# ------------------------------------------------------ the tuning cache --
+
+def run_of(rec, n, batch, cache=None, tuned=None, steps=50):
+    """The tile launches of `steps` steps of one lattice of n nodes (as a batch
+    of one with resident lattices off, or alone) after an autotune with the
+    cache, with a tuning, or with neither."""
+    from paper_1802_02369_amd import lbm
+    L = lbm.lib()
+    if batch:
+        b, pre = make_batch([n]), "lbm_batch_"
+        assert L.lbm_batch_set_resident(b._h, 0) == 0
+    else:
+        b, pre = lbm.Lattice(n, stream=Null()), "lbm_"
+    call = lambda name, *a: getattr(L, pre + name)(b._h, *a)
+    f = Memory(48 * n)
+    if cache:
+        ws = Memory(call("workspace_bytes", lbm.WS_TUNE))
+        assert call("autotune", f.ptr, ws.ptr, ws.nbytes, 32, cache.encode(),
+                    None) == 0
+    if tuned:
+        t = lbm.CTuning(lbm.KERNEL_BLOCKED, *tuned)
+        assert call("set_tuning", ctypes.byref(t)) == 0
+    ws = Memory(call("workspace_bytes", lbm.WS_STEP))
+    if batch:
+        assert call("prepare", ws.ptr, ws.nbytes) == 0
+    rec.clear()
+    if batch:
+        assert call("run", f.ptr, ws.ptr, ws.nbytes, steps, 0) == 0
+    else:
+        assert call("step", f.ptr, ws.ptr, ws.nbytes, steps) == 0
+    return [tuple(x.split()[1:4]) for x in rec.log() if x.startswith("launch")]
+
+
+def cached_plan(rec, tmp, batch):
+    import json
+    cache = tmp + "/tune.json"
+    rec.prefer("ELi8ELi0E")  # eight mirror lanes: only the plan has them
+    small = run_of(rec, 16000, batch, cache)
+    assert small == run_of(rec, 16000, batch)
+    assert len(json.load(open(cache))) == 1
+    # the same class of sizes, another default tuning: the plan, not that of
+    # the default of 16000 nodes
+    large = run_of(rec, 17000, batch, cache)
+    assert len(json.load(open(cache))) == 1
+    assert large == run_of(rec, 17000, batch)
+    assert large != run_of(rec, 17000, batch, tuned=(1, 13, 1))
+
+
+def cached_shape(rec, tmp, batch):
+    import json
+    cache = tmp + "/tune.json"
+    kernel = "k_batch_tile" if batch else "k_step_tile"
+    run_of(rec, 1500000, batch, cache)
+    (key, entry), = json.load(open(cache)).items()
+    # a set shape won there; it is the default tuning of the larger size
+    with open(cache, "w") as fp:
+        json.dump({key: {"kernel": entry["kernel"], "P": 8, "K": 40, "W": 4,
+                         **({"resident": 0} if batch else {})}}, fp)
+    got = run_of(rec, 2500000, batch, cache)
+    assert len(json.load(open(cache))) == 1
+    assert got == run_of(rec, 2500000, batch, tuned=(8, 40, 4))
+    assert got != run_of(rec, 2500000, batch)
+    assert all(kernel in x[0] for x in got)
+
+
+@pytest.mark.parametrize("batch", [False, True])
+@pytest.mark.parametrize("what", ["cached_plan", "cached_shape"])
+def test_tuning_cache_across_defaults(tmp_path, what, batch):
+    """An entry of the tuning cache means the same at every size of its class:
+    the library's own plan, or a shape."""
+    recorded(what, str(tmp_path), batch)
