@@ -1417,11 +1417,12 @@ size_t lbm_batch_adjoint_workspace_bytes(const lbm_batch* b, int64_t nsteps,
                                          int64_t ckpt_every) {
   if (!b || nsteps < 0 || ckpt_every < 1) return 0;
   // enough for the library's own shapes and for those of the tuning, so that
-  // setting the tuning in force changes nothing about the workspace
+  // going from one to the other (set_tuning, an autotuner that finds the
+  // library's own plan the fastest) changes nothing about the workspace
   const bool plain = resolve_adj_plain(b);
   const int every = resolve_every(b, plain);
   size_t most = 0;
-  for (const bool own : {false, b->plan_auto})
+  for (const bool own : {false, true})
     most = std::max(most, adj_layout(b, nsteps, ckpt_every,
                                      adj_plan(b, b->tune, plain, every, own,
                                               segment_steps(nsteps, ckpt_every)))

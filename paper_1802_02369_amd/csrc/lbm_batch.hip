@@ -761,7 +761,15 @@ int64_t lbm_batch_resident_lattices(const lbm_batch* b) {
 
 size_t lbm_batch_workspace_bytes(const lbm_batch* b, int kind) {
   if (!b) return 0;
-  if (kind == LBM_WS_STEP) return layout(b, b->run_tiles(), false).total;
+  // enough for the groups or shape in force, for the library's own plan and
+  // for the tuning, so that going from one to another (set_tuning, an autotuner
+  // that finds the plan the fastest, no groups) takes no new workspace; the
+  // plan's table is 1/6 of a byte per node
+  if (kind == LBM_WS_STEP)
+    return layout(b, std::max({b->run_tiles(), b->plan_tiles,
+                               b->count_tiles(b->tune)}),
+                  false)
+        .total;
   if (kind == LBM_WS_TUNE) return layout(b, tune_tiles(b), true).total;
   return 0;
 }
