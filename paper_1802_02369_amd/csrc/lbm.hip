@@ -697,8 +697,9 @@ __host__ __device__ inline void diag_combine(double* a, const double* b) {
   a[7] += b[7];
 }
 
-// Block partials of the diagnostics, fixed tree order (deterministic).  They
-// go straight to pinned host memory, at most 64 KB, and the host combines
+// Block partials of the diagnostics, fixed tree order (deterministic).  From a
+// handle's second call on they go straight to pinned host memory, at most
+// 64 KB, and the host combines
 // them once the launch has ended: a second launch for that and a copy of its
 // eight values took 19 us of the 42 us that 25 steps of n = 30011 and their
 // diagnostics took.
@@ -731,6 +732,25 @@ __global__ __launch_bounds__(kDiagBlock) void k_diag_partial(
     __syncthreads();
   }
   if (threadIdx.x < 8) partial[blockIdx.x * 8 + threadIdx.x] = s[0][threadIdx.x];
+}
+
+// The combination of the block partials, as combine_diagnostics on the host.
+__global__ __launch_bounds__(kDiagBlock) void k_diag_final(
+    const double* __restrict__ partial, int nblocks, double* __restrict__ out) {
+  __shared__ double s[kDiagBlock][8];
+  const int t = threadIdx.x;
+  const int rows = nblocks < kDiagBlock ? nblocks : kDiagBlock;
+  if (t < rows) {
+    for (int k = 0; k < 8; ++k) s[t][k] = partial[8 * t + k];
+    for (int b = t + kDiagBlock; b < nblocks; b += kDiagBlock)
+      diag_combine(s[t], partial + 8 * b);
+  }
+  __syncthreads();
+  for (int w = kDiagBlock / 2; w > 0; w >>= 1) {
+    if (t < w && t + w < rows) diag_combine(s[t], s[t + w]);
+    __syncthreads();
+  }
+  if (t < 8) out[t] = s[0][t];
 }
 
 // Per-lattice diagnostics of a batch, one workgroup per lattice, fixed tree
@@ -976,9 +996,9 @@ int launch_step_tile(const Consts& c, const double* fin, double* fout,
                  t.P, t.W, t.M);
 }
 
-// The workspace behind the states: room of this size, so that workspaces sized
-// once stay valid, with the failure record of LBM_CHECK_FINITE (4 doubles) at
-// its end.
+// The workspace behind the states: of a handle's first diagnostics (8 final
+// values, 8 per block), then the failure record of LBM_CHECK_FINITE (4
+// doubles).
 size_t diag_ws_doubles() { return (size_t)kDiagMaxBlocks * 8 + 8 + 4; }
 size_t check_record_double() { return (size_t)kDiagMaxBlocks * 8 + 8; }
 
@@ -1096,7 +1116,9 @@ static int diag_blocks(int64_t n) {
   return (int)std::min<int64_t>(kDiagMaxBlocks, cdiv(n, kDiagBlock));
 }
 
-size_t diag_sums_bytes() { return sizeof(double) * 8 * kDiagMaxBlocks; }
+size_t diag_sums_bytes(int64_t n) {
+  return sizeof(double) * 8 * (size_t)diag_blocks(n);
+}
 
 int launch_diagnostics(const Consts& c, const double* f, int64_t n,
                        double* sums, hipStream_t s) {
@@ -1105,7 +1127,13 @@ int launch_diagnostics(const Consts& c, const double* f, int64_t n,
   return hip_check(hipGetLastError(), "k_diag_partial");
 }
 
-// In the order of a workgroup's tree, so that the result depends on n alone.
+int launch_combine(const double* sums, int64_t n, double* out, hipStream_t s) {
+  hipLaunchKernelGGL(k_diag_final, dim3(1), dim3(kDiagBlock), 0, s, sums,
+                     diag_blocks(n), out);
+  return hip_check(hipGetLastError(), "k_diag_final");
+}
+
+// In the order of k_diag_final, so that the result depends on n alone.
 void combine_diagnostics(const double* sums, int64_t n, double out[8]) {
   const int nb = diag_blocks(n), rows = std::min(nb, kDiagBlock);
   double s[kDiagBlock][8];

@@ -250,3 +250,32 @@ def test_tuning_cache_across_defaults(tmp_path, what, batch):
     """An entry of the tuning cache means the same at every size of its class:
     the library's own plan, or a shape."""
     recorded(what, str(tmp_path), batch)
+
+
+# ------------------------------------------------ host memory of diagnostics --
+
+def diagnostics_memory(rec, n):
+    from paper_1802_02369_amd import lbm
+    L = lbm.lib()
+    out = (ctypes.c_double * 8)()
+    lat = lbm.Lattice(n, stream=Null())
+    f = Memory(48 * n)
+    ws = Memory(L.lbm_workspace_bytes(lat._h, lbm.WS_STEP))
+    pinned = []
+    for _ in range(4):
+        rec.clear()
+        assert L.lbm_diagnostics(lat._h, f.ptr, ws.ptr, ws.nbytes, out) == 0
+        pinned.append([int(x.split()[1]) for x in rec.log()
+                       if x.startswith("host_malloc")])
+    blocks = min(1024, -(-n // 256))
+    assert pinned == [[], [64 * blocks], [], []], pinned
+    rec.clear()
+    del lat
+    assert rec.log() == ["host_free"]
+
+
+@pytest.mark.parametrize("n", [3, 256, 257, 1000003])
+def test_diagnostics_take_pinned_memory_at_the_second_call(n):
+    """A lattice that is read once takes no pinned memory; one that is read
+    again takes what its sums need, once."""
+    recorded("diagnostics_memory", n)
