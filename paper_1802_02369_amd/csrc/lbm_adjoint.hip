@@ -1017,7 +1017,7 @@ AdjShapes own_shapes(const lbm_batch* b, int64_t C, int E) {
   };
   static const Shape shapes[] = {
       {{1, 4, 8}, 1}, {{1, 8, 8}, 1}, {{2, 4, 4}, 1}, {{2, 4, 5}, 2}};
-  AdjShapes a{plan_tiles(b->offsets, C), {}, {}};
+  AdjShapes a{plan_tiles(b->offsets, C, b->tile_eq < 0), {}, {}};
   double least = INFINITY;
   for (const Shape& sh : shapes) {
     if (sh.E != E) continue;

@@ -108,12 +108,26 @@ struct TileCost {
   }
 };
 
-const TileCost kTileCosts[] = {
+const std::vector<TileCost> kTileCosts = {
     {{1, 4, 8}, 8, 0.098, 0.155, 3.2},  {{1, 8, 8}, 4, 0.098, 0.155, 3.2},
     {{1, 12, 8}, 2, 0.098, 0.155, 3.2}, {{2, 8, 4}, 4, 0.115, 0.153, 3.6},
     {{2, 12, 4}, 2, 0.115, 0.153, 3.6}, {{4, 4, 2}, 4, 0.21, 0.150, 4.4},
     {{4, 8, 2}, 2, 0.21, 0.150, 4.4},   {{4, 12, 2}, 1, 0.21, 0.150, 4.4},
     {{8, 4, 1}, 3, 0.375, 0.147, 6.2}};
+
+// The shapes for batches of mixed kinds of equilibria.  The kernel that selects
+// them per lattice holds 256 registers at eight nodes per lane, two wavefronts
+// per SIMD where the kernels of one kind have three, and the wider workgroups
+// of four nodes per lane leave the chip unevenly filled.  Microseconds per step
+// with lattices of two kinds on (8, 4, 1) and (4, 4, 1), either at its best
+// launch length: 512 of 1024 .. 8192 nodes 9.4 and 8.5, 4096 of 512 .. 16384
+// 74.1 and 67.8, 100 of 1e5 36.0 and 35.8, two of 2^23 56.6 and 57.5 (the costs
+// of the kernels of one kind chose (8, 4, 1) for all four).
+const std::vector<TileCost> kMixedTileCosts = {
+    {{1, 4, 8}, 8, 0.098, 0.155, 3.2},  {{1, 8, 8}, 4, 0.098, 0.155, 3.2},
+    {{1, 12, 8}, 2, 0.098, 0.155, 3.2}, {{2, 8, 4}, 4, 0.115, 0.153, 3.6},
+    {{2, 12, 4}, 2, 0.115, 0.153, 3.6}, {{4, 4, 1}, 3, 0.21, 0.150, 4.4},
+    {{8, 4, 1}, 2, 0.375, 0.155, 6.2}};
 
 }  // namespace
 
@@ -238,7 +252,8 @@ struct BatchModel {
 // two nodes per lane; 4096 of 512 .. 16384 60 either way.  The constants
 // minimise the regret over sweeps of every choice on sixteen batches of 2e4 to
 // 2e7 nodes: 3 % on average, at most 8 %.
-BatchPlan plan_batch(const std::vector<int64_t>& offsets, bool resident) {
+BatchPlan plan_batch(const std::vector<int64_t>& offsets, bool resident,
+                     bool mixed) {
   const BatchModel model(offsets);
   BatchPlan best;
   double least = INFINITY;
@@ -273,7 +288,7 @@ BatchPlan plan_batch(const std::vector<int64_t>& offsets, bool resident) {
       if (P == 8) m = std::max(m, std::min(3.0, n_waves / 4.0));
       const double res_us =
           P == 0 ? 0.0 : (P == 8 ? 0.375 + 0.184 * P * m : 0.06 + 0.163 * P * m);
-      for (const TileCost& c : kTileCosts) {
+      for (const TileCost& c : mixed ? kMixedTileCosts : kTileCosts) {
         // beside resident lattices, the shapes of four or eight wavefronts
         // with at least two nodes per lane that proved even-tempered there
         const bool mixes = (c.t.P == 2 && c.t.W == 8) || (c.t.P == 4 && c.t.W == 4) ||
@@ -292,11 +307,12 @@ BatchPlan plan_batch(const std::vector<int64_t>& offsets, bool resident) {
 // segments of a checkpointed sweep).  4.8e6 nodes in 512 lattices, segments of
 // 16: 25.8 us per step on (2, 4, 1) tiles, 21.5 on (4, 4, 2); one lattice of
 // 8192, segments of 100: 0.48 on one-wavefront tiles, 0.36 on (1, 4, 8).
-StepPlan plan_tiles(const std::vector<int64_t>& offsets, int64_t steps) {
+StepPlan plan_tiles(const std::vector<int64_t>& offsets, int64_t steps,
+                    bool mixed) {
   const BatchModel model(offsets);
   StepPlan best{{8, 4, 1}, 16, 0};
   double least = INFINITY;
-  for (const TileCost& c : kTileCosts) {
+  for (const TileCost& c : mixed ? kMixedTileCosts : kTileCosts) {
     const int64_t top = (tile_nodes(c.t.P, c.t.W, c.t.M) - kPlanMinOut) / 4;
     for (int64_t K = std::min<int64_t>({top, steps, 128}); K > 0;
          K = next_split(K)) {

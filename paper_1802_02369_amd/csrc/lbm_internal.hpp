@@ -168,10 +168,12 @@ struct StepPlan {
 StepPlan plan_steps(int64_t n, int64_t nsteps);
 struct BatchPlan;
 // The plan of a batch with these offsets (see BatchPlan), with resident
-// lattices or on tiles alone.
-BatchPlan plan_batch(const std::vector<int64_t>& offsets, bool resident);
+// lattices or on tiles alone; mixed: the equilibria are selected per lattice.
+BatchPlan plan_batch(const std::vector<int64_t>& offsets, bool resident,
+                     bool mixed);
 // Shape and steps per launch of runs of `steps` >= 1 steps on tiles.
-StepPlan plan_tiles(const std::vector<int64_t>& offsets, int64_t steps);
+StepPlan plan_tiles(const std::vector<int64_t>& offsets, int64_t steps,
+                    bool mixed);
 // The next shorter launch length to consider, 0 at the end (8 steps, or less
 // where no more were asked for): a few dozen however long the run.
 inline int64_t next_split(int64_t K) {
@@ -410,7 +412,7 @@ struct lbm_batch {
   int plan_mode() const { return eq_cls == 0 ? resident_mode : 0; }
   void make_plan() {
     const int m = plan_mode();
-    if (!plan_made[m]) plans[m] = lbm::plan_batch(offsets, m == 1);
+    if (!plan_made[m]) plans[m] = lbm::plan_batch(offsets, m == 1, tile_eq < 0);
     plan_made[m] = true;
   }
   const lbm::BatchPlan& plan() const { return plans[plan_mode()]; }

@@ -279,3 +279,45 @@ def test_diagnostics_take_pinned_memory_at_the_second_call(n):
     """A lattice that is read once takes no pinned memory; one that is read
     again takes what its sums need, once."""
     recorded("diagnostics_memory", n)
+
+
+# -------------------------------------------------- plans of mixed batches --
+
+def mixed_plan(rec, lens, eight):
+    from paper_1802_02369_amd import lbm
+    L = lbm.lib()
+    n = sum(lens)
+    shapes = {}
+    for kinds in ((0, 1), (0,), (1, 3)):
+        b = make_batch(lens, kinds)
+        assert L.lbm_batch_set_resident(b._h, 0) == 0
+        f = Memory(48 * n)
+        ws = Memory(L.lbm_batch_workspace_bytes(b._h, lbm.WS_STEP))
+        assert L.lbm_batch_prepare(b._h, ws.ptr, ws.nbytes) == 0
+        aws = Memory(L.lbm_batch_adjoint_workspace_bytes(b._h, 4, 4))
+        rec.clear()
+        assert L.lbm_batch_run(b._h, f.ptr, ws.ptr, ws.nbytes, 40, 0) == 0
+        assert L.lbm_batch_forward_ckpt(b._h, f.ptr, aws.ptr, aws.nbytes, 4, 4) == 0
+        names = {x.split("k_batch_tileI")[1].split("EEE")[0]
+                 for x in rec.launches("k_batch_tile")}
+        shapes[kinds] = {tuple(int(v[2:]) for v in x.split("E")[:3]) for x in names}
+    # nodes per lane, wavefronts, mirror lanes
+    wide = {(4, 4, 2), (4, 8, 2), (4, 12, 2)}
+    assert not shapes[(0, 1)] & wide, shapes
+    assert all((8, 4, 1) in shapes[k] for k in eight), shapes
+    assert all((8, 4, 1) not in shapes[k] for k in shapes if k not in eight), shapes
+    # one form of equilibria: the plan does not depend on which
+    assert shapes[(0,)] == shapes[(1, 3)], shapes
+
+
+@pytest.mark.parametrize("lens, eight", [
+    ([700, 90, 41], []), ([2000] * 40, []), ([4096] * 400, []),
+    ([int(1024 * 8 ** (i / 511)) for i in range(512)], []),
+    ([int(512 * 32 ** (i / 1023)) for i in range(1024)], [(0,), (1, 3)]),
+    # long lattices: eight nodes per lane by their small halo on either
+    ([1 << 22] * 2, [(0, 1), (0,), (1, 3)])])
+def test_plans_of_mixed_batches(lens, eight):
+    """The plan of a batch whose kernels select the equilibria per lattice has
+    the shapes that suit those kernels; eight: the kinds that run at eight nodes
+    per lane."""
+    recorded("mixed_plan", lens, eight)
