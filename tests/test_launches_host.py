@@ -312,8 +312,8 @@ def mixed_plan(rec, lens, eight):
 
 @pytest.mark.parametrize("lens, eight", [
     ([700, 90, 41], []), ([2000] * 40, []), ([4096] * 400, []),
-    ([int(1024 * 8 ** (i / 511)) for i in range(512)], []),
-    ([int(512 * 32 ** (i / 1023)) for i in range(1024)], [(0,), (1, 3)]),
+    ([int(1024 * 8 ** (i / 511)) for i in range(512)], [(0,), (1, 3)]),
+    ([int(512 * 32 ** (i / 1023)) for i in range(1024)], []),
     # long lattices: eight nodes per lane by their small halo on either
     ([1 << 22] * 2, [(0, 1), (0,), (1, 3)])])
 def test_plans_of_mixed_batches(lens, eight):
