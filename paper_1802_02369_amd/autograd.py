@@ -81,19 +81,22 @@ def _records(s_e, s_eps, c):
     coupling of lbm_coupled_rates in the same operations, for all at once: a
     Params object and a library call per lattice took 1.1 ms for 512 of them
     before the first launch."""
-    se = s_e.detach().cpu().to(torch.float64).numpy()
+    if s_e.is_complex() or s_eps.is_complex():
+        raise TypeError("BatchLBMFunction: rates must be real")
+    se, seps = (r.detach().cpu().to(torch.float64).numpy() for r in (s_e, s_eps))
+    gamma, prandtl = float(c["gamma"]), float(c["prandtl"])
     for bad in se[~((se > 0.0) & (se < 2.0))][:1].tolist():
-        lbm.coupled_rates(bad, c["gamma"], c["prandtl"])  # raises
+        lbm.coupled_rates(bad, gamma, prandtl)  # raises
     if len(se):
-        lbm.coupled_rates(float(se[0]), c["gamma"], c["prandtl"])
-    fixed = lbm.Params(s_psi=1.0, **c).c()
+        lbm.coupled_rates(float(se[0]), gamma, prandtl)
+    fixed = lbm.Params(s_e=1.0, s_psi=1.0, s_eps=1.0, **c).c()
     records = np.zeros(len(se), dtype=lbm.PARAMS_DTYPE)
     for name in records.dtype.names:
         records[name] = getattr(fixed, name)
-    k = 1.5 * c["gamma"] / c["prandtl"]
+    k = 1.5 * gamma / prandtl
     records["s_e"] = se
     records["s_psi"] = 1.0 / (k * (1.0 / se - 0.5) + 0.5)
-    records["s_eps"] = s_eps.detach().cpu().to(torch.float64).numpy()
+    records["s_eps"] = seps
     ratio = records["s_psi"] / se
     return records, k * ratio * ratio
 

@@ -31,3 +31,31 @@ def test_records_refuse_what_the_library_refuses(bad):
     s_e = torch.tensor([1.5, bad, 1.2], dtype=torch.float64)
     with pytest.raises(lbm.LBMError, match="s_e must lie in"):
         autograd._records(s_e, torch.ones(3), autograd._consts(None))
+
+
+@pytest.mark.parametrize("name", ["s_e", "s_psi", "s_eps"])
+def test_records_refuse_rates_among_the_constants(name):
+    """The rates have arguments of their own: a constant of their name is
+    refused, as lbm.Params refuses it beside them."""
+    c = autograd._consts({name: 1.2})
+    with pytest.raises(TypeError, match="multiple values"):
+        autograd._records(torch.tensor([1.5]), torch.tensor([1.5]), c)
+
+
+@pytest.mark.parametrize("which", [0, 1])
+def test_records_refuse_complex_rates(which):
+    rates = [torch.tensor([1.5]), torch.tensor([1.5])]
+    rates[which] = rates[which].to(torch.complex128)
+    with pytest.raises(TypeError):
+        autograd._records(*rates, autograd._consts(None))
+
+
+def test_records_take_constants_as_tensors():
+    """A constant may be anything lbm.Params takes, a tensor of one element
+    among them, with its value as it is."""
+    c = autograd._consts({"gamma": torch.tensor(1.375, dtype=torch.float32)})
+    s_e = torch.tensor([1.1, 1.7], dtype=torch.float64)
+    records, dpsi = autograd._records(s_e, torch.ones(2), c)
+    for i in range(2):
+        s_psi, _, d = lbm.coupled_rates(float(s_e[i]), 1.375, 1.0)
+        assert records["s_psi"][i] == s_psi and dpsi[i] == d
