@@ -543,11 +543,12 @@ __device__ __forceinline__ void adjoint_tile(
     const double* __restrict__ ck, const double* __restrict__ seg, int64_t SD,
     int i_lo, int i_hi, const double* __restrict__ fbn,
     double* __restrict__ fbo, int64_t S, int H, double* __restrict__ rslots) {
-  static_assert(WG == 1 || (M * P >= 2 * E && 2 * M <= 32), "mirror lanes");
+  // a step takes two mirror nodes, a pair (E = 2) four and two
+  static_assert(WG == 1 || (M * P >= (E == 2 ? 6 : 2) && 2 * M <= 32),
+                "mirror lanes");
   constexpr int WW = 64 * P;                  // nodes of one wavefront
   constexpr int WS = (64 - 2 * M) * P;        // wavefront stride in the tile
-  // steps between refreshes of the mirror lanes (E = 2: whole pairs, at least
-  // one with a refresh between its steps when a pair does not fit)
+  // steps between refreshes of the mirror lanes
   constexpr int every = E == 1 ? M * P / 2 : (M * P / 2 - 1);
   __shared__ double stage[staged(P) ? WG * (WW + 64) : 1];
   __shared__ double edge[2][WG][2][6 * P * M];
