@@ -321,3 +321,49 @@ def test_plans_of_mixed_batches(lens, eight):
     the shapes that suit those kernels; eight: the kinds that run at eight nodes
     per lane."""
     recorded("mixed_plan", lens, eight)
+
+
+# ------------------------------------------------------------------ graphs --
+
+def captures(rec, tuned):
+    """What a call does: "direct", "capture" (and launch) or "replay"."""
+    from paper_1802_02369_amd import lbm
+    L = lbm.lib()
+    b = make_batch([3000, 700, 90, 41])
+    h, n = b._h, 3831
+    if tuned:
+        set_tuning(L, h, tuned)
+    f, g, r = Memory(48 * n), Memory(48 * n), Memory(96)
+    ws = Memory(L.lbm_batch_workspace_bytes(h, lbm.WS_STEP))
+    aws = Memory(L.lbm_batch_adjoint_workspace_bytes(h, 20, 7))
+    assert L.lbm_batch_prepare(h, ws.ptr, ws.nbytes) == 0
+    assert L.lbm_batch_forward_ckpt(h, f.ptr, aws.ptr, aws.nbytes, 20, 7) == 0
+
+    def did(call):
+        rec.clear()
+        assert call() == 0
+        log = [x.split()[0] for x in rec.log()]
+        if "capture" in log:
+            assert log[0] == "capture" and log.count("graph") == 1
+            assert log[-1] == "graph" and "launch" in log
+            return "capture"
+        if "graph" in log:
+            assert log == ["graph"]
+            return "replay"
+        return "direct"
+
+    run = lambda m, k: did(lambda: L.lbm_batch_run(h, m.ptr, ws.ptr, ws.nbytes, k, 1))
+    sweep = lambda m: did(lambda: L.lbm_batch_adjoint(
+        h, aws.ptr, aws.nbytes, 20, 7, m.ptr, r.ptr, 1))
+    assert [run(f, 20) for _ in range(4)] == ["direct", "capture", "replay", "replay"]
+    assert [run(f, 21), run(f, 20), run(g, 20)] == ["direct"] * 3
+    assert [run(g, 20), run(g, 20)] == ["capture", "replay"]
+    assert [sweep(f) for _ in range(4)] == ["direct", "capture", "replay", "replay"]
+    assert [sweep(g), sweep(f), sweep(f)] == ["direct", "direct", "capture"]
+
+
+@pytest.mark.parametrize("tuned", [None, (2, 8, 2), (2, 8, 4)])
+def test_second_call_alike_is_captured(tuned):
+    """A run or reverse sweep whose arguments come a second time in a row is
+    captured, later ones are replayed, and others enqueue directly."""
+    recorded("captures", tuned)
