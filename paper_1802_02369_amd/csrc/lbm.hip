@@ -8,9 +8,9 @@
 //   k_step_tile    K time steps per launch.  Each 64-lane wavefront holds
 //                  64*P consecutive nodes (P per lane, contiguous) in VGPRs
 //                  for all K steps; neighbour values move between lanes with
-//                  DPP wave shifts, and the wavefronts of a workgroup overlap
-//                  by two lanes that are refreshed through LDS every P/2
-//                  steps.  A step has radius 2 (the source reads u, T at
+//                  DPP wave shifts, and neighbouring wavefronts of a
+//                  workgroup share 2M lanes that are refreshed through LDS
+//                  every MP/2 steps.  A step has radius 2 (the source reads u, T at
 //                  j+-1 of the node whose populations stream to j+-1), so a
 //                  tile loads 2K halo nodes on each side and stores its
 //                  interior.
@@ -331,16 +331,15 @@ __global__ __launch_bounds__(256) void k_save_halo(const double* __restrict__ f,
 }
 
 // Wavefronts per SIMD the tile kernels are compiled for (the register
-// budget: 512 / n VGPRs each).  Kernels of one kind of equilibria at P = 8 hold 168 VGPRs
-// for three (the few values that spill are touched only around the step
-// loop, which measured 297 -> 312 GLUPS at N = 2^24 against two); with 8
-// wavefronts per workgroup a CU gains no third one, so those stay at two.
-// The kernels that select the equilibria per lattice, or store the states
-// of a reverse sweep, need more registers at P >= 4 and take one: a launch
-// whose lattices share linear or fluid equilibria has its own (150 VGPRs at
+// budget: 512 / n VGPRs each).  Kernels of one kind of equilibria are held to
+// three at P = 8 (they hold 150 VGPRs and spill nothing; three measured 297 ->
+// 312 GLUPS at N = 2^24 against two); with 8 wavefronts per workgroup a CU
+// gains no third one, so those stay at two.  The kernels that select the
+// equilibria per lattice (226 VGPRs at P = 8, 127 at P = 4), or store the
+// states of a reverse sweep, are not held to a budget at P >= 4: a launch whose
+// lattices share linear or fluid equilibria has its own (150 and 151 VGPRs at
 // P = 8; n = 500 in one workgroup 0.45 -> 0.35 us per step, 3e5 1.56 -> 1.37,
-// 8e6 33.8 -> 31.1).  P <= 2
-// needs few registers: four.
+// 8e6 33.8 -> 31.1).  P <= 2 needs few registers: four.
 constexpr int tile_waves_per_simd(int P, int WG, bool one_eq_plain) {
   return P <= 2 ? 4 : WG > 8 ? 3 : !one_eq_plain ? 1 : P == 8 && WG <= 4 ? 3 : 2;
 }
@@ -940,7 +939,7 @@ static void launch_plain_t(const Consts& c, const double* fin, double* fout,
 // doubles per block.
 int launch_step_plain(const Consts& c, const double* fin, double* fout,
                       double* halo, int64_t n, hipStream_t s) {
-  if (n >= 256 * (int64_t)kPlainBlock) {
+  if (n >= kComputeUnits * kPlainBlock) {
     if (c.eq_kind == 0)
       launch_plain_t<kPlainBlock, 0>(c, fin, fout, halo, n, s);
     else

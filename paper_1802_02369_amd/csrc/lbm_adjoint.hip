@@ -913,14 +913,14 @@ struct AdjLayout {
 // Tile shape of the blocked reverse kernel for a forward tuning and a stride
 // E of the stored segment states, with halo H = 2K, or 2K + 2 at
 // E = 2 (see k_adjoint_tile).  P = 2 keeps two wavefronts per SIMD (the
-// reverse step needs 167-250 VGPRs at P = 2, over 256 at P = 4), with the
+// reverse step holds 159-256 VGPRs at P = 2, over 256 at P = 4), with the
 // wavefronts that give about the forward tile's width, at least the
 // forward's and at most 4: two workgroups per CU, so that one computes while
 // the other waits at a barrier (measured with two
 // barriers per step: the 1024-lattice gradient's reverse phase took 442 ms
 // at 4 wavefronts, 472 at 8, 512 at 2); a halo too wide for those tiles
 // falls back to P = 4 with 8 wavefronts and E = 1.  A forward of one node
-// per lane (small problems) keeps P = 1, W = 1, E = 1 (about 110 VGPRs).
+// per lane (small problems) keeps P = 1, W = 1, E = 1 (93 VGPRs).
 struct RevShape {
   TileShape t;
   int K, H, E;
@@ -969,9 +969,9 @@ bool resolve_adj_plain(const lbm_batch* b) {
 }
 
 // Launches of the blocked reverse kernel fill the chip when they have at
-// least the 2048 wavefronts that 256 CUs hold at two per SIMD.
+// least the wavefronts that the compute units hold at two per SIMD.
 bool rev_fills_chip(const lbm_batch* b, const RevShape& r) {
-  return tiles_of(b, r.out()) * r.t.W >= 2048;
+  return tiles_of(b, r.out()) * r.t.W >= 8 * kComputeUnits;
 }
 
 // Stride of the segment states the reverse sweep stores.  Every second one
@@ -995,7 +995,8 @@ int resolve_every(const lbm_batch* b, bool plain) {
 // on 253 tiles: 2.79 -> 2.42 us per step; 180000 on 446: 3.77 -> 4.24).
 bool sweeps_joined(const lbm_batch* b, const StepPlan& rev) {
   return rev.t.P == 1 ||
-         tiles_of(b, tile_nodes(rev.t.P, rev.t.W, rev.t.M) - 4 * rev.K) <= 256;
+         tiles_of(b, tile_nodes(rev.t.P, rev.t.W, rev.t.M) - 4 * rev.K) <=
+             kComputeUnits;
 }
 
 // The library's own shapes of a sweep with segments of C steps whose stored
@@ -1027,7 +1028,7 @@ AdjShapes own_shapes(const lbm_batch* b, int64_t C, int E) {
     for (int64_t K = std::min(top, C); K > 0; K = next_split(K)) {
       const int64_t j = (C + K - 1) / K;
       K = (C + j - 1) / j;
-      double g = (double)tiles_of(b, nodes - 4 * K) / 256.0;
+      double g = (double)tiles_of(b, nodes - 4 * K) / (double)kComputeUnits;
       const bool side = sh.E == 1 && (sh.t.P == 1 || g <= 1);
       if (g < 3) g = std::ceil(g);
       const double us =

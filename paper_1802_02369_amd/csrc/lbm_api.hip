@@ -57,9 +57,10 @@ std::vector<lbm_tuning> tuning_candidates() {
 
 lbm_tuning default_tuning(int64_t len, int64_t total, int eq) {
   // tile shapes from the widest down, with the K that measured best for
-  // each.  The kernels that select the equilibria per lattice (eq != 0)
-  // need over 256 VGPRs at P = 8, i.e. one wavefront per SIMD, so they
-  // start at P = 4.
+  // each.  Batches of mixed kinds (eq != 0) run the kernel that selects the
+  // equilibria per lattice: 226 VGPRs at P = 8, two wavefronts per SIMD, so
+  // they start at P = 4 (kMixedTileCosts has both measured); so do lattices of
+  // one other kind, whose kernels hold 151.
   // Small problems are bound by the latency of each step's chain of
   // arithmetic, not by throughput: their one-wavefront tiles take K = 16
   // (fewer launches) rather than the width's best, and at most 16384 nodes
@@ -116,7 +117,7 @@ const std::vector<TileCost> kTileCosts = {
     {{8, 4, 1}, 3, 0.375, 0.147, 6.2}};
 
 // The shapes for batches of mixed kinds of equilibria.  The kernel that selects
-// them per lattice holds 256 registers at eight nodes per lane, two wavefronts
+// them per lattice holds 226 registers at eight nodes per lane, two wavefronts
 // per SIMD where the kernels of one kind have three, and the wider workgroups
 // of four nodes per lane leave the chip unevenly filled.  Microseconds per step
 // with lattices of two kinds on (8, 4, 1) and (4, 4, 1), either at its best
@@ -156,7 +157,7 @@ StepPlan plan_steps(int64_t n, int64_t nsteps) {
       const StepSplit sp = split_steps(nsteps, (int)std::min(K, top));
       const int64_t k = sp.base + (sp.extra ? 1 : 0);
       const int64_t out = nodes - 4 * k;
-      const int64_t tiles = (n + out - 1) / out, g = (tiles + 255) / 256;
+      const int64_t tiles = (n + out - 1) / out, g = (tiles + kComputeUnits - 1) / kComputeUnits;
       const double us =
           (double)sp.count *
           (c.fixed + 48.0 * ((double)tiles * (double)nodes + (double)n) / 11e6 +
@@ -171,7 +172,7 @@ StepPlan plan_steps(int64_t n, int64_t nsteps) {
     // the longest launches whose tiles fit g per compute unit, and some
     // lengths for the many rounds of large lattices
     for (int64_t g = 1; g <= 4 * c.per_cu; ++g)
-      consider((nodes - (n + 256 * g - 1) / (256 * g)) / 4);
+      consider((nodes - (n + kComputeUnits * g - 1) / (kComputeUnits * g)) / 4);
     for (int64_t K : {16, 24, 32, 40}) consider(K);
   }
   return best;
@@ -224,7 +225,7 @@ struct BatchModel {
       total += (double)(b.len * b.count);
     }
     if (tiles == 0) return 0.0;
-    const double g = std::ceil(tiles / 256.0);
+    const double g = std::ceil(tiles / (double)kComputeUnits);
     const double full = std::floor(g / c.per_cu), rest = g - full * c.per_cu;
     // workgroups that need fewer wavefronts than W leave their SIMDs free
     const double used =
@@ -284,7 +285,8 @@ BatchPlan plan_batch(const std::vector<int64_t>& offsets, bool resident,
       if (P > 0 && n_waves == 0) continue;
       // wavefronts per SIMD: of the longest lattice, or on average; the
       // workgroups of eight nodes per lane are filled before new ones open
-      double m = std::max(std::ceil(longest / 4.0), n_waves / 1024.0 * 1.33);
+      double m = std::max(std::ceil(longest / 4.0),
+                          n_waves / (4.0 * kComputeUnits) * 1.33);
       if (P == 8) m = std::max(m, std::min(3.0, n_waves / 4.0));
       const double res_us =
           P == 0 ? 0.0 : (P == 8 ? 0.375 + 0.184 * P * m : 0.06 + 0.163 * P * m);

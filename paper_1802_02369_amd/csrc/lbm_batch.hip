@@ -827,8 +827,9 @@ int lbm_batch_prepare(lbm_batch* b, void* ws, size_t ws_bytes) {
       for (int64_t i : order) total += waves(i);
       res_wg = std::max<int>(4, waves(order[0]));
       const size_t least =
-          std::min<size_t>(order.size(), 256 * (size_t)((total + 256 * res_wg - 1) /
-                                                        (256 * res_wg)));
+          std::min<size_t>(order.size(),
+                           kComputeUnits * ((total + kComputeUnits * res_wg - 1) /
+                                            (kComputeUnits * res_wg)));
       std::multimap<int32_t, size_t> by_use;  // wavefronts used -> workgroup
       for (size_t g = 0; g < least; ++g) by_use.emplace(0, g);
       bins.resize(least);

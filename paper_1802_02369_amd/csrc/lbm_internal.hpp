@@ -19,6 +19,9 @@ int set_err(int code, const char* fmt, ...);
 int hip_check(hipError_t e, const char* what);
 int make_consts(const lbm_params* p, Consts* c);
 
+// Compute units of the chip: what the plans fill and round up to.
+constexpr int64_t kComputeUnits = 256;
+
 // A register tile's shape: P nodes per lane, W wavefronts, M mirror lanes on
 // each side of a wavefront (see tile_run).
 struct TileShape {
@@ -55,9 +58,9 @@ int read_check_record(const unsigned long long* rec, hipStream_t s,
 
 // Resident lattices of a batch (k_batch_resident): P nodes per lane,
 // workgroups of kResidentWaves wavefronts, lattices of 2P to
-// 62 P kResidentWaves nodes.  Twelve wavefronts at three per SIMD (168
-// VGPRs) measured 278 GLUPS on the 4096-lattice batch (lengths 512 ..
-// 16384) against 272 for eight at two per SIMD and 265 on tiles alone.
+// 62 P kResidentWaves nodes.  Twelve wavefronts at three per SIMD (165 of the
+// 168 VGPRs that leaves) measured 278 GLUPS on the 4096-lattice batch (lengths
+// 512 .. 16384) against 272 for eight at two per SIMD and 265 on tiles alone.
 constexpr int kResP = 8;
 constexpr int kResidentWaves = 12;
 constexpr int64_t kResidentMin = 2 * kResP;
@@ -77,8 +80,9 @@ int launch_batch_resident(const Consts* cs, const int64_t* offs,
 // Nodes a wavefront owns in a resident lattice of P nodes per lane (8/P
 // mirror lanes on each side).
 constexpr int64_t resident_span(int P) { return 64 * P - 16; }
-// Most wavefronts of a resident workgroup: at P = 4 twelve, whose LDS (58 KB)
-// is what 16 take at P = 2.
+// Most wavefronts of a resident workgroup: at P = 4 twelve, as their LDS (58 KB
+// with the staging, which P <= 2 does without: 36 KB for 16) stays below the
+// 64 KB that a launch may ask for.
 constexpr int resident_max_waves(int P) { return P == 8 || P == 4 ? 12 : 16; }
 // All T steps of one lattice of n nodes in place in one workgroup.
 int launch_step_resident(const Consts& c, double* f, int64_t n, int64_t T,

@@ -279,7 +279,8 @@ __device__ __forceinline__ int active_waves(int64_t n, int64_t start, int H) {
   return nw < 1 ? 1 : nw;
 }
 
-// K time steps of one register-resident tile per workgroup .  The workgroup has WG wavefronts of 64 lanes, lane l of wavefront
+// K time steps of one register-resident tile per workgroup.  The workgroup has
+// WG wavefronts of 64 lanes, lane l of wavefront
 // w holding the P consecutive nodes starting at tile index
 // P ((64 - 2M) w + l).  Neighbouring wavefronts overlap by 2M lanes: the first
 // M lanes of wavefront w > 0 mirror lanes 64-2M .. 63-M of w-1, the last M
