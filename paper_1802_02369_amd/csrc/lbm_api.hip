@@ -744,14 +744,16 @@ int lbm_diagnostics(lbm_handle* h, const double* f, void* ws, size_t ws_bytes,
   // them.  Taking that memory and giving it back costs more than it saves once
   // (create, one call, destroy at n = 8192: 48 us, 35 where a second kernel
   // combines the sums in the workspace and its eight values are copied; every
-  // later call 16 and 28), so the first call does the latter.
+  // later call 16 and 28), so the first call does the latter, and so does every
+  // call while pinned memory cannot be had.
   std::lock_guard<std::mutex> lock(h->diag_lock);
   int rc = LBM_OK;
   if (!h->diag_sums && h->diag_called &&
-      (rc = hip_check(hipHostMalloc((void**)&h->diag_sums, diag_sums_bytes(h->n),
-                                    hipHostMallocPortable),
-                      "hipHostMalloc")))
-    return rc;
+      hipHostMalloc((void**)&h->diag_sums, diag_sums_bytes(h->n),
+                    hipHostMallocPortable) != hipSuccess) {
+    (void)hipGetLastError();
+    h->diag_sums = nullptr;
+  }
   double* scratch = (double*)ws + 6 * h->n;
   double* sums = h->diag_sums ? h->diag_sums : scratch + 8;
   if ((rc = launch_diagnostics(h->c, f, h->n, sums, h->stream))) return rc;

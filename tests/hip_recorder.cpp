@@ -18,6 +18,7 @@
 #include <cstring>
 #include <map>
 #include <string>
+#include <utility>
 
 namespace {
 struct Dim3 {
@@ -25,11 +26,13 @@ struct Dim3 {
 };
 std::map<const void*, std::string> kernels;
 std::string text, preferred;
+bool refuse_host_memory;
 // time: a launch of a kernel whose name holds `preferred` takes 1 ms, others 1 s
 double clock_ms = 0;
 Dim3 call_grid, call_block;
 size_t call_shared;
 void* call_stream;
+int last_error;
 
 void note(const char* fmt, ...) {
   char line[1024];
@@ -46,6 +49,7 @@ extern "C" {
 const char* rec_log() { return text.c_str(); }
 void rec_clear() { text.clear(); }
 void rec_prefer(const char* name) { preferred = name; }
+void rec_refuse_host_memory(int on) { refuse_host_memory = on != 0; }
 
 void** __hipRegisterFatBinary(const void*) {
   static void* handle;
@@ -92,6 +96,7 @@ int hipMemcpyAsync(void* dst, const void* src, size_t bytes, int, void* stream) 
 }
 int hipHostMalloc(void** p, size_t bytes, unsigned) {
   note("host_malloc %zu\n", bytes);
+  if (refuse_host_memory) return last_error = 2;  // out of memory
   *p = std::calloc(1, bytes);
   return 0;
 }
@@ -128,7 +133,7 @@ int hipGraphDestroy(void* g) { return delete static_cast<char*>(g), 0; }
 int hipGraphExecDestroy(void* e) { return delete static_cast<char*>(e), 0; }
 int hipGraphLaunch(void*, void*) { return note("graph\n"), 0; }
 
-int hipGetLastError() { return 0; }
+int hipGetLastError() { return std::exchange(last_error, 0); }
 const char* hipGetErrorString(int) { return "error"; }
 int hipGetDevice(int* d) { return *d = 0, 0; }
 int hipGetDevicePropertiesR0600(void*, int) { return 999; }  // unknown

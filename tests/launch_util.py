@@ -51,6 +51,10 @@ class Recorder:
         """Launches of kernels named so take a thousandth of the time."""
         self._l.rec_prefer(kernel.encode())
 
+    def refuse_host_memory(self, on: bool):
+        """hipHostMalloc fails from now on, or works again."""
+        self._l.rec_refuse_host_memory(int(on))
+
     def log(self):
         return self._l.rec_log().decode().splitlines()
 

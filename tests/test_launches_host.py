@@ -274,6 +274,33 @@ def diagnostics_memory(rec, n):
     assert rec.log() == ["host_free"]
 
 
+def diagnostics_without_pinned(rec):
+    from paper_1802_02369_amd import lbm
+    L = lbm.lib()
+    out = (ctypes.c_double * 8)()
+    lat = lbm.Lattice(1000, stream=Null())
+    f = Memory(48 * 1000)
+    ws = Memory(L.lbm_workspace_bytes(lat._h, lbm.WS_STEP))
+    call = lambda: L.lbm_diagnostics(lat._h, f.ptr, ws.ptr, ws.nbytes, out)
+    assert call() == 0
+    rec.refuse_host_memory(True)
+    for _ in range(2):
+        rec.clear()
+        assert call() == 0
+        assert [x.split("k_diag")[1][:6] for x in rec.launches()] == ["_parti", "_final"]
+    rec.refuse_host_memory(False)
+    assert call() == 0
+    rec.clear()
+    assert call() == 0
+    assert len(rec.launches()) == 1
+
+
+def test_diagnostics_go_on_without_pinned_memory():
+    """Where pinned memory cannot be had, the sums are combined in the
+    workspace as in a first call."""
+    recorded("diagnostics_without_pinned")
+
+
 @pytest.mark.parametrize("n", [3, 256, 257, 1000003])
 def test_diagnostics_take_pinned_memory_at_the_second_call(n):
     """A lattice that is read once takes no pinned memory; one that is read
