@@ -95,7 +95,7 @@ lbm_tuning default_tuning(int64_t len, int64_t total, int eq) {
 // default tuning at K = 16 1.09; 4e5 nodes 1.50 against 2.73, 1e6 nodes 3.55
 // against 3.88, 8192 nodes 0.35 against 0.51).  The constants are fits to
 // sweeps of every shape over K at twelve sizes from 160 to 2^24 nodes, where
-// the modelled choice is within 1 % of the fastest measured one.  From some
+// the modelled choice is within 1.1 % of the fastest measured one.  From some
 // millions of nodes on the widest tile wins by its small halo.
 namespace {
 
@@ -252,7 +252,8 @@ struct BatchModel {
 // 0.6 on (1, 8) tiles; 965 lattices of 247 .. 1108 nodes 5.2, 2.7 resident at
 // two nodes per lane; 4096 of 512 .. 16384 60 either way.  The constants
 // minimise the regret over sweeps of every choice on sixteen batches of 2e4 to
-// 2e7 nodes: 3 % on average, at most 8 %.
+// 2e7 nodes: 3 % on average, at most 10 % (mixed kinds, eighteen batches: 1 %,
+// at most 5 %).
 BatchPlan plan_batch(const std::vector<int64_t>& offsets, bool resident,
                      bool mixed) {
   const BatchModel model(offsets);
