@@ -243,9 +243,10 @@ LBM_API int lbm_moments(lbm_handle* h, const double* f, double* m);
  * sum zeta, sum rho E, min rho, min T, count of non-finite entries of f,
  * count of nodes with rho <= 0 or T <= 0; rho E = p/(gamma-1) + J^2/(2 rho)
  * (section 5).  Returns LBM_ENONFINITE when either count is non-zero
- * (out is still filled).  From its second call on a handle keeps pinned host
- * memory for this (at most 64 KB), which lbm_destroy frees; that may wait for
- * the device. */
+ * (out is still filled).  The library keeps pinned host memory for this: 64 KB
+ * for each call under way at once, at most eight of them while there are
+ * handles (calls beyond that copy), one once lbm_destroy has destroyed the last
+ * (freeing the others may wait for the device). */
 LBM_API int lbm_diagnostics(lbm_handle* h, const double* f, void* ws, size_t ws_bytes,
                             double out[8]);
 

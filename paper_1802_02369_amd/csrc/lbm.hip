@@ -696,9 +696,8 @@ __host__ __device__ inline void diag_combine(double* a, const double* b) {
   a[7] += b[7];
 }
 
-// Block partials of the diagnostics, fixed tree order (deterministic).  From a
-// handle's second call on they go straight to pinned host memory, at most
-// 64 KB, and the host combines
+// Block partials of the diagnostics, fixed tree order (deterministic).  They
+// go straight to pinned host memory, at most 64 KB, and the host combines
 // them once the launch has ended: a second launch for that and a copy of its
 // eight values took 19 us of the 42 us that 25 steps of n = 30011 and their
 // diagnostics took.
@@ -995,8 +994,8 @@ int launch_step_tile(const Consts& c, const double* fin, double* fout,
                  t.P, t.W, t.M);
 }
 
-// The workspace behind the states: of a handle's first diagnostics (8 final
-// values, 8 per block), then the failure record of LBM_CHECK_FINITE (4
+// The workspace behind the states: of diagnostics without pinned memory (8
+// final values, 8 per block), then the failure record of LBM_CHECK_FINITE (4
 // doubles).
 size_t diag_ws_doubles() { return (size_t)kDiagMaxBlocks * 8 + 8 + 4; }
 size_t check_record_double() { return (size_t)kDiagMaxBlocks * 8 + 8; }
@@ -1115,9 +1114,7 @@ static int diag_blocks(int64_t n) {
   return (int)std::min<int64_t>(kDiagMaxBlocks, cdiv(n, kDiagBlock));
 }
 
-size_t diag_sums_bytes(int64_t n) {
-  return sizeof(double) * 8 * (size_t)diag_blocks(n);
-}
+size_t diag_sums_bytes() { return sizeof(double) * 8 * kDiagMaxBlocks; }
 
 int launch_diagnostics(const Consts& c, const double* f, int64_t n,
                        double* sums, hipStream_t s) {

@@ -2,6 +2,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <complex>
 #include <cstdint>
@@ -538,6 +539,63 @@ int noalloc_scratch(double** out) {
 
 }  // namespace
 
+namespace {
+
+// Pinned host memory for the block sums of lbm_diagnostics: one buffer for each
+// call under way, kept between calls.  A handle that had its own took and gave
+// it back at a cost a program that reads a lattice once does not earn back
+// (create, one call, destroy at n = 8192: 48 us, 34 before pinned memory was
+// used, 23 so), and a free waits for the device.  At most kMost buffers of 64 KB
+// while there are handles, one once the last handle is gone; calls beyond them
+// do without (take gives nullptr).
+class PinnedSums {
+ public:
+  PinnedSums() { idle_.reserve(kMost); }
+  double* take() {
+    {
+      std::lock_guard<std::mutex> lock(m_);
+      if (!idle_.empty()) {
+        double* p = idle_.back();
+        idle_.pop_back();
+        return p;
+      }
+      if (count_ == kMost) return nullptr;
+      ++count_;
+    }
+    double* p = nullptr;
+    if (hipHostMalloc((void**)&p, diag_sums_bytes(), hipHostMallocPortable) ==
+        hipSuccess)
+      return p;
+    (void)hipGetLastError();
+    std::lock_guard<std::mutex> lock(m_);
+    --count_;
+    return nullptr;
+  }
+  void give(double* p) {
+    std::lock_guard<std::mutex> lock(m_);
+    idle_.push_back(p);
+  }
+  void trim() {
+    std::lock_guard<std::mutex> lock(m_);
+    while (idle_.size() > 1) {
+      (void)hipHostFree(idle_.back());
+      idle_.pop_back();
+      --count_;
+    }
+  }
+
+ private:
+  static constexpr int kMost = 8;
+  std::mutex m_;
+  std::vector<double*> idle_;
+  int count_ = 0;
+};
+
+PinnedSums pinned_sums;
+std::atomic<int64_t> live_handles{0};
+
+}  // namespace
+
 extern "C" {
 
 const char* lbm_last_error(void) { return g_err.c_str(); }
@@ -629,6 +687,7 @@ int lbm_init(lbm_handle** h, int64_t n, const lbm_params* p, void* stream) {
   x->stream = (hipStream_t)stream;
   x->tune = default_tuning(n, n, p->eq_kind == 0 ? 0 : -1);
   x->tune_default = true;
+  ++live_handles;
   *h = x;
   return LBM_OK;
 }
@@ -636,8 +695,8 @@ int lbm_init(lbm_handle** h, int64_t n, const lbm_params* p, void* stream) {
 void lbm_destroy(lbm_handle* h) {
   if (!h) return;
   lbm_batch_destroy(h->one);
-  if (h->diag_sums) (void)hipHostFree(h->diag_sums);
   delete h;
+  if (--live_handles == 0) pinned_sums.trim();
 }
 
 int lbm_set_stream(lbm_handle* h, void* stream) {
@@ -741,34 +800,22 @@ int lbm_diagnostics(lbm_handle* h, const double* f, void* ws, size_t ws_bytes,
   if (!h || !f || !ws || !out) return set_err(LBM_EINVAL, "NULL argument");
   if (ws_bytes < lbm_workspace_bytes(h, LBM_WS_STEP))
     return set_err(LBM_EWORKSPACE, "workspace too small");
-  // The block sums go to pinned memory of the handle, where the host combines
-  // them.  Taking that memory and giving it back costs more than it saves once
-  // (create, one call, destroy at n = 8192: 48 us, 35 where a second kernel
-  // combines the sums in the workspace and its eight values are copied; every
-  // later call 16 and 28), so the first call does the latter, and so does every
-  // call while pinned memory cannot be had.
-  std::lock_guard<std::mutex> lock(h->diag_lock);
-  int rc = LBM_OK;
-  if (!h->diag_sums && h->diag_called &&
-      hipHostMalloc((void**)&h->diag_sums, diag_sums_bytes(h->n),
-                    hipHostMallocPortable) != hipSuccess) {
-    (void)hipGetLastError();
-    h->diag_sums = nullptr;
-  }
+  // The block sums go to pinned memory, where the host combines them; where
+  // none is to be had, a second kernel combines them in the workspace and its
+  // eight values are copied (n = 8192: 16 and 28 us per call).
   double* scratch = (double*)ws + 6 * h->n;
-  double* sums = h->diag_sums ? h->diag_sums : scratch + 8;
-  if ((rc = launch_diagnostics(h->c, f, h->n, sums, h->stream))) return rc;
-  if (!h->diag_sums) {
-    if ((rc = launch_combine(sums, h->n, scratch, h->stream))) return rc;
+  double* pinned = pinned_sums.take();
+  int rc = launch_diagnostics(h->c, f, h->n, pinned ? pinned : scratch + 8,
+                              h->stream);
+  if (!rc && !pinned) rc = launch_combine(scratch + 8, h->n, scratch, h->stream);
+  if (!rc && !pinned)
     rc = hip_check(hipMemcpyAsync(out, scratch, 8 * sizeof(double),
                                   hipMemcpyDeviceToHost, h->stream),
                    "hipMemcpyAsync");
-    if (rc) return rc;
-  }
-  if ((rc = hip_check(hipStreamSynchronize(h->stream), "hipStreamSynchronize")))
-    return rc;
-  if (h->diag_sums) combine_diagnostics(h->diag_sums, h->n, out);
-  h->diag_called = true;
+  if (!rc) rc = hip_check(hipStreamSynchronize(h->stream), "hipStreamSynchronize");
+  if (!rc && pinned) combine_diagnostics(pinned, h->n, out);
+  if (pinned) pinned_sums.give(pinned);
+  if (rc) return rc;
   if (out[6] > 0 || out[7] > 0)
     return set_err(LBM_ENONFINITE,
                    "state holds %g non-finite values and %g nodes with rho<=0 "

@@ -99,10 +99,10 @@ int launch_step_plain(const Consts& c, const double* fin, double* fout,
 int launch_step_tile(const Consts& c, const double* fin, double* fout,
                      int64_t n, const TileShape& t, int K, hipStream_t s);
 // The diagnostics of f: the sums of diag_blocks(n) blocks, 8 values each, to
-// `sums` (device memory, or host memory the device can write; diag_sums_bytes),
-// and their combination, by a second launch or on the host once the launch has
-// ended, in the same order.
-size_t diag_sums_bytes(int64_t n);
+// `sums` (device memory, or host memory the device can write; at most
+// diag_sums_bytes), and their combination, by a second launch or on the host
+// once the launch has ended, in the same order.
+size_t diag_sums_bytes();
 int launch_diagnostics(const Consts& c, const double* f, int64_t n,
                        double* sums, hipStream_t s);
 int launch_combine(const double* sums, int64_t n, double* out, hipStream_t s);
@@ -293,11 +293,6 @@ struct lbm_handle {
   std::mutex plan_lock;
   lbm::StepPlan plan{};
   int64_t plan_nsteps = -1;
-  // pinned host memory the diagnostics' block sums go to, from the second call
-  // on, used by one call at a time
-  std::mutex diag_lock;
-  double* diag_sums = nullptr;
-  bool diag_called = false;
   int32_t adj_kernel = LBM_KERNEL_AUTO;  // reverse-sweep kernel
   int32_t rec_stride = 0;  // stride of the stored segment states (0: auto)
   lbm_batch* one = nullptr;  // batch of this one lattice, for the adjoint

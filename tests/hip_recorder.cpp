@@ -10,6 +10,8 @@
 //     take pointers there)
 //   copy <destination> <source> <bytes> <stream>
 //   capture, graph, host_malloc <bytes>, host_free
+#include <chrono>
+#include <condition_variable>
 #include <cstdarg>
 #include <cstddef>
 #include <cstdint>
@@ -17,6 +19,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <mutex>
 #include <string>
 #include <utility>
 
@@ -26,15 +29,19 @@ struct Dim3 {
 };
 std::map<const void*, std::string> kernels;
 std::string text, preferred;
-bool refuse_host_memory;
+bool refuse_host_memory, holding;
+int waiting;
+std::mutex text_lock;
+std::condition_variable changed;
 // time: a launch of a kernel whose name holds `preferred` takes 1 ms, others 1 s
 double clock_ms = 0;
-Dim3 call_grid, call_block;
-size_t call_shared;
-void* call_stream;
-int last_error;
+thread_local Dim3 call_grid, call_block;
+thread_local size_t call_shared;
+thread_local void* call_stream;
+thread_local int last_error;
 
 void note(const char* fmt, ...) {
+  std::lock_guard<std::mutex> lock(text_lock);
   char line[1024];
   va_list a;
   va_start(a, fmt);
@@ -49,6 +56,18 @@ extern "C" {
 const char* rec_log() { return text.c_str(); }
 void rec_clear() { text.clear(); }
 void rec_prefer(const char* name) { preferred = name; }
+void rec_hold(int on) {
+  std::lock_guard<std::mutex> lock(text_lock);
+  holding = on != 0;
+  changed.notify_all();
+}
+int rec_wait_for(int calls) {
+  std::unique_lock<std::mutex> lock(text_lock);
+  return changed.wait_for(lock, std::chrono::seconds(60),
+                          [&] { return waiting >= calls; })
+             ? 0
+             : 1;
+}
 void rec_refuse_host_memory(int on) { refuse_host_memory = on != 0; }
 
 void** __hipRegisterFatBinary(const void*) {
@@ -122,7 +141,14 @@ int hipEventElapsedTime(float* ms, void* a, void* b) {
 
 int hipStreamCreateWithFlags(void** s, unsigned) { return *s = new char(0), 0; }
 int hipStreamDestroy(void* s) { return delete static_cast<char*>(s), 0; }
-int hipStreamSynchronize(void*) { return 0; }
+int hipStreamSynchronize(void*) {
+  std::unique_lock<std::mutex> lock(text_lock);
+  ++waiting;
+  changed.notify_all();
+  changed.wait(lock, [] { return !holding; });
+  --waiting;
+  return 0;
+}
 int hipStreamWaitEvent(void*, void*, unsigned) { return 0; }
 int hipStreamBeginCapture(void*, int) { return note("capture\n"), 0; }
 int hipStreamEndCapture(void*, void** g) { return *g = new char(0), 0; }

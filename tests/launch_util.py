@@ -55,6 +55,14 @@ class Recorder:
         """hipHostMalloc fails from now on, or works again."""
         self._l.rec_refuse_host_memory(int(on))
 
+    def hold(self, on: bool):
+        """Synchronising a stream waits while on."""
+        self._l.rec_hold(int(on))
+
+    def wait_for(self, calls: int):
+        """Waits until so many calls synchronise a stream."""
+        assert self._l.rec_wait_for(calls) == 0
+
     def log(self):
         return self._l.rec_log().decode().splitlines()
 

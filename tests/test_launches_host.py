@@ -254,58 +254,96 @@ def test_tuning_cache_across_defaults(tmp_path, what, batch):
 
 # ------------------------------------------------ host memory of diagnostics --
 
-def diagnostics_memory(rec, n):
+def diagnose(rec, lat, n):
+    """What one call of lbm_diagnostics asks for: host memory, launches."""
     from paper_1802_02369_amd import lbm
     L = lbm.lib()
     out = (ctypes.c_double * 8)()
-    lat = lbm.Lattice(n, stream=Null())
     f = Memory(48 * n)
     ws = Memory(L.lbm_workspace_bytes(lat._h, lbm.WS_STEP))
-    pinned = []
-    for _ in range(4):
-        rec.clear()
-        assert L.lbm_diagnostics(lat._h, f.ptr, ws.ptr, ws.nbytes, out) == 0
-        pinned.append([int(x.split()[1]) for x in rec.log()
-                       if x.startswith("host_malloc")])
-    blocks = min(1024, -(-n // 256))
-    assert pinned == [[], [64 * blocks], [], []], pinned
     rec.clear()
+    assert L.lbm_diagnostics(lat._h, f.ptr, ws.ptr, ws.nbytes, out) == 0
+    names = [x.split("k_diag_")[1][:5] for x in rec.launches()]
+    return [x for x in rec.log() if x.startswith("host")], names
+
+
+def diagnostics_memory(rec):
+    from paper_1802_02369_amd import lbm
+    lats = {n: lbm.Lattice(n, stream=Null()) for n in (3, 257, 100003)}
+    first = True
+    for _ in range(3):
+        for n, lat in lats.items():
+            got = diagnose(rec, lat, n)
+            assert got == (["host_malloc 65536"] if first else [], ["parti"]), got
+            first = False
+    # handles that come and go one by one, and the last one
+    rec.clear()
+    for n in (3, 1000):
+        lat = lbm.Lattice(n, stream=Null())
+        assert diagnose(rec, lat, n) == ([], ["parti"])
     del lat
-    assert rec.log() == ["host_free"]
+    rec.clear()
+    lats.clear()
+    assert rec.log() == []
+
+
+def test_diagnostics_share_pinned_memory():
+    """Calls one after another share one buffer of pinned memory, whatever
+    their handles; making and destroying handles takes and frees none."""
+    recorded("diagnostics_memory")
 
 
 def diagnostics_without_pinned(rec):
     from paper_1802_02369_amd import lbm
-    L = lbm.lib()
-    out = (ctypes.c_double * 8)()
     lat = lbm.Lattice(1000, stream=Null())
-    f = Memory(48 * 1000)
-    ws = Memory(L.lbm_workspace_bytes(lat._h, lbm.WS_STEP))
-    call = lambda: L.lbm_diagnostics(lat._h, f.ptr, ws.ptr, ws.nbytes, out)
-    assert call() == 0
     rec.refuse_host_memory(True)
-    for _ in range(2):
-        rec.clear()
-        assert call() == 0
-        assert [x.split("k_diag")[1][:6] for x in rec.launches()] == ["_parti", "_final"]
+    for _ in range(20):
+        assert diagnose(rec, lat, 1000) == (["host_malloc 65536"], ["parti", "final"])
     rec.refuse_host_memory(False)
-    assert call() == 0
-    rec.clear()
-    assert call() == 0
-    assert len(rec.launches()) == 1
+    assert diagnose(rec, lat, 1000) == (["host_malloc 65536"], ["parti"])
+    assert diagnose(rec, lat, 1000) == ([], ["parti"])
 
 
 def test_diagnostics_go_on_without_pinned_memory():
     """Where pinned memory cannot be had, the sums are combined in the
-    workspace as in a first call."""
+    workspace."""
     recorded("diagnostics_without_pinned")
 
 
-@pytest.mark.parametrize("n", [3, 256, 257, 1000003])
-def test_diagnostics_take_pinned_memory_at_the_second_call(n):
-    """A lattice that is read once takes no pinned memory; one that is read
-    again takes what its sums need, once."""
-    recorded("diagnostics_memory", n)
+def diagnostics_at_once(rec):
+    import threading
+    from paper_1802_02369_amd import lbm
+    L = lbm.lib()
+    lats = [lbm.Lattice(500, stream=Null()) for _ in range(12)]
+    rec.hold(True)  # every call waits until all have come
+    codes = []
+
+    def call(lat):
+        out = (ctypes.c_double * 8)()
+        f, ws = Memory(48 * 500), Memory(L.lbm_workspace_bytes(lat._h, lbm.WS_STEP))
+        codes.append(L.lbm_diagnostics(lat._h, f.ptr, ws.ptr, ws.nbytes, out))
+
+    rec.clear()
+    threads = [threading.Thread(target=call, args=(lat,)) for lat in lats]
+    for t in threads:
+        t.start()
+    rec.wait_for(12)
+    rec.hold(False)
+    for t in threads:
+        t.join()
+    assert codes == [0] * 12
+    log = [x.split()[0] for x in rec.log()]
+    assert log.count("host_malloc") == 8 and log.count("launch") == 12 + 4
+    rec.clear()
+    del threads
+    lats.clear()
+    assert rec.log() == ["host_free"] * 7
+
+
+def test_diagnostics_at_once_are_bounded():
+    """Twelve calls at once: eight buffers, the others do without; all but one
+    go back with the last handle."""
+    recorded("diagnostics_at_once")
 
 
 # -------------------------------------------------- plans of mixed batches --
