@@ -416,6 +416,9 @@ LBM_API int lbm_batch_set_resident(lbm_batch* b, int mode);
 LBM_API int64_t lbm_batch_resident_lattices(const lbm_batch* b);
 /* Total nodes n_total of the batch (0 on a bad handle). */
 LBM_API int64_t lbm_batch_total_nodes(const lbm_batch* b);
+/* Bytes of the workspace of that kind (0 on bad arguments), enough for the
+ * library's own choice of shapes, for the tuning and for the shape groups in
+ * force; another tuning or other groups may need more. */
 LBM_API size_t lbm_batch_workspace_bytes(const lbm_batch* b, int kind);
 /* Uploads the per-lattice constants, offsets and the tile table of the
  * current tuning into ws (synchronising).  Required before the calls below
